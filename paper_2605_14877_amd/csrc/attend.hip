@@ -3,14 +3,14 @@
 //
 // For head (b,h) the keys are the head's run of retained rows in the arena
 // followed by the t_k rows of the current scale; queries are the t_k rows of
-// the current scale.  Both kernels walk this virtual key sequence in tiles,
-// keep running row maxima and row sums in fp32 (online softmax) and normalise
-// once at the end.
+// the current scale.  The kernel walks this virtual key sequence in tiles, keeps
+// running row maxima and row sums in fp32 (online softmax) and normalises once at
+// the end.  This file holds the bf16 kernel and the launcher; fp32: attend_f32.hip.
 #include <atomic>
 #include <cstdlib>
 #include <type_traits>
 
-#include "copy_rows.h"
+#include "attend_params.h"
 #include "device_util.h"
 #include "kernels.h"
 #include "tile_lds.h"
@@ -18,27 +18,6 @@
 namespace heatkv {
 
 namespace {
-
-struct AttendParams {
-  int H, batch, t_k;
-  long long arena_tokens;
-  const HeadWork* work;
-  // uniform_len >= 0: every head of the layer holds a run of that many rows, head h's run starts at row
-  // uniform_row0 + h * uniform_len, and (batch row, head) pairs are taken in index order: a workgroup then knows
-  // all its addresses from its id and the kernel arguments, and its first fetches do not wait for a table read.
-  int uniform_len, uniform_row0;
-  const void *q, *k_cur, *v_cur, *k_arena, *v_arena;
-  void* out;
-  float sm_scale;
-  int n_qtiles;
-  // Workgroups with blockIdx.x >= attend_blocks run the fused cache update (copy descriptor, batch entry).
-  // They sit at the end of the grid on purpose: there they fill the slots that the last attention workgroups
-  // leave one by one.  Spread through the grid instead, their memory traffic lengthened the latency of the
-  // attention workgroups' tile fetches and the launch became up to 1.4x slower.
-  int attend_blocks;
-  int ndesc;
-  CopyParams copy;
-};
 
 // ---------------------------------------------------------------------------
 // bf16, d = 128 or 64: matrix-core kernel (the description takes d = 128: rows of 256 bytes).
@@ -614,113 +593,6 @@ __global__ __launch_bounds__(256 * KS * QS, (KS == 1 && QS == 1) ? 2 : 1) void a
   }
 }
 
-// ---------------------------------------------------------------------------
-// fp32 (any supported d): plain vector-ALU kernel, 16 queries per workgroup,
-// 16 lanes per query, key tiles of 32 rows in LDS.
-// ---------------------------------------------------------------------------
-constexpr int FQ = 16;  // queries per workgroup
-constexpr int FN = 32;  // keys per tile
-
-template <int D>
-__global__ __launch_bounds__(256) void attend_f32_kernel(AttendParams p) {
-  __shared__ float Qs[FQ][D + 1];
-  __shared__ float Ks[FN][D + 1];
-  __shared__ float Vs[FN][D];
-  __shared__ float Ps[FQ][FN];
-
-  if (static_cast<int>(blockIdx.x) >= p.attend_blocks) {  // fused append: a plain row copy
-    const int j = blockIdx.x - p.attend_blocks;
-    copy_rows_block(p.copy, j % p.ndesc, j / p.ndesc);
-    return;
-  }
-  const int tid = threadIdx.x, r = tid >> 4, g = tid & 15;
-  int id = blockIdx.x;
-  const int qt = id % p.n_qtiles;
-  id /= p.n_qtiles;
-  const int b = id % p.batch;
-  const HeadWork hw = p.work[id / p.batch];
-  const int h = hw.head;
-
-  const int t_k = p.t_k;
-  const int n_prior = hw.run_len;
-  const int n_total = n_prior + t_k;
-  const long long cur_off = (static_cast<long long>(b) * p.H + h) * t_k * D;
-  const long long run_off = (static_cast<long long>(b) * p.arena_tokens + hw.run_row) * D;
-  const float* k_prior = static_cast<const float*>(p.k_arena) + run_off;
-  const float* v_prior = static_cast<const float*>(p.v_arena) + run_off;
-  const float* k_cur = static_cast<const float*>(p.k_cur) + cur_off;
-  const float* v_cur = static_cast<const float*>(p.v_cur) + cur_off;
-  const float* q = static_cast<const float*>(p.q) + cur_off;
-
-  for (int e = tid; e < FQ * D; e += 256) {
-    const int rr = e / D, dd = e % D;
-    const int row = qt * FQ + rr;
-    Qs[rr][dd] = row < t_k ? q[static_cast<long long>(row) * D + dd] : 0.f;
-  }
-
-  constexpr int DPL = D / 16;  // output dims per lane
-  float o[DPL];
-#pragma unroll
-  for (int e = 0; e < DPL; ++e) o[e] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;
-
-  const int n_tiles = (n_total + FN - 1) / FN;
-  for (int tile = 0; tile < n_tiles; ++tile) {
-    __syncthreads();
-    for (int e = tid; e < FN * D; e += 256) {
-      const int rr = e / D, dd = e % D;
-      const int gk = tile * FN + rr;
-      float kv = 0.f, vv = 0.f;
-      if (gk < n_total) {
-        const long long off = (gk < n_prior ? static_cast<long long>(gk) : static_cast<long long>(gk - n_prior)) * D + dd;
-        kv = (gk < n_prior ? k_prior : k_cur)[off];
-        vv = (gk < n_prior ? v_prior : v_cur)[off];
-      }
-      Ks[rr][dd] = kv;
-      Vs[rr][dd] = vv;
-    }
-    __syncthreads();
-
-    float s[2];
-#pragma unroll
-    for (int jj = 0; jj < 2; ++jj) {
-      const int j = g + 16 * jj;
-      float acc = 0.f;
-#pragma unroll 8
-      for (int dd = 0; dd < D; ++dd) acc = fmaf(Qs[r][dd], Ks[j][dd], acc);
-      s[jj] = tile * FN + j < n_total ? acc * p.sm_scale : -INFINITY;
-    }
-    float mx = fmaxf(s[0], s[1]);
-#pragma unroll
-    for (int off = 8; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 16));
-    const float m_new = fmaxf(m_run, mx);
-    const float alpha = expf(m_run - m_new);
-    const float p0 = expf(s[0] - m_new), p1 = expf(s[1] - m_new);
-    float rowsum = p0 + p1;
-#pragma unroll
-    for (int off = 8; off >= 1; off >>= 1) rowsum += __shfl_xor(rowsum, off, 16);
-    l_run = l_run * alpha + rowsum;
-    m_run = m_new;
-    Ps[r][g] = p0;
-    Ps[r][g + 16] = p1;
-    __syncthreads();
-#pragma unroll
-    for (int e = 0; e < DPL; ++e) {
-      float acc = o[e] * alpha;
-      for (int j = 0; j < FN; ++j) acc = fmaf(Ps[r][j], Vs[j][g + 16 * e], acc);
-      o[e] = acc;
-    }
-  }
-
-  const int row = qt * FQ + r;
-  if (row < t_k) {
-    float* op = static_cast<float*>(p.out) + cur_off + static_cast<long long>(row) * D;
-    const float inv = 1.f / l_run;
-#pragma unroll
-    for (int e = 0; e < DPL; ++e) op[g + 16 * e] = o[e] * inv;
-  }
-}
-
 }  // namespace
 
 size_t attend_workspace_bytes(int, int, int, int, int, int) { return 0; }
@@ -831,15 +703,7 @@ hipError_t launch_attend(const AttendArgs& a, hipStream_t stream) {
     }
   } else {
     if (a.kv_fp8) return hipErrorInvalidValue;
-    p.n_qtiles = (a.t_k + FQ - 1) / FQ;
-    p.attend_blocks = int(unsigned(p.n_qtiles) * a.H * a.batch);
-    const dim3 grid(unsigned(p.attend_blocks) + copy_blocks);
-    if (a.d == 64)
-      hipLaunchKernelGGL(attend_f32_kernel<64>, grid, dim3(256), 0, stream, p);
-    else if (a.d == 128)
-      hipLaunchKernelGGL(attend_f32_kernel<128>, grid, dim3(256), 0, stream, p);
-    else
-      return hipErrorInvalidValue;
+    return launch_attend_f32(p, a.d, copy_blocks, stream);
   }
   return hipGetLastError();
 }

@@ -1,0 +1,189 @@
+// Next-scale attention over the ragged per-head KV cache, fp32 (attend.hip describes the path).
+//
+// Matrix-core kernel in full fp32.  A workgroup takes 16 queries; its four wavefronts split the keys (tiles of 16,
+// dealt round robin, current scale first, then the head's retained run), each with a running reference, row sums and
+// accumulators of its own, and are merged through LDS at the end.  fp32 problems are small (reference outputs,
+// checks): a launch rarely has more than a few hundred query tiles, so the split over keys is what fills the chip.
+//
+// S^T = K Q^T leaves lane (n, g) with keys 4 g .. 4 g + 3 of query n, which is the B operand of O^T += V^T P^T as it
+// stands: MFMA step r of a tile takes the keys 4 g + r.  V^T is the A operand; row n of accumulator block 4 j + i
+// stands for column 64 j + 4 n + i, so that 16 lanes read 64 consecutive floats of a V row, 16 bytes each.
+//
+// K and V go from memory into registers: V of the tile is fetched under the score MFMAs, K of the wavefront's next
+// tile under the P V MFMAs.
+//
+// Bound: the matrix pipe where a launch fills the chip (128 pairs x 400 queries x 800 keys, d = 128: 221 us = 95 TFLOP/s
+// of the 151 a large fp32 matrix product reaches here; d = 64, 784 x 1384: 344 us = 103), the distribution of a few
+// workgroups per compute unit below that (16 pairs, 625 + 500 keys: 77 us = 75 TFLOP/s).  The vector-ALU kernel that this
+// one replaced fed its FMAs from LDS and reached 7 TFLOP/s (the same 625-query layer of a pruned image: 334 -> 67 us).
+// Eight wavefronts per workgroup, or 32 queries per workgroup (half the loads per MFMA): 0-15 % slower at every size,
+// the first for the longer merge, the second for the coarser distribution and one wavefront less per SIMD.  Key
+// tiles through LDS by global_load_lds (half the L1 accesses): within 4 % either way.
+#include "attend_params.h"
+#include "device_util.h"
+#include "f32_mfma.h"
+#include "kernels.h"
+
+namespace heatkv {
+
+namespace {
+
+constexpr int NW = 4;  // wavefronts of a workgroup
+
+template <int D>
+__global__ __launch_bounds__(64 * NW) void attend_f32_kernel(AttendParams p) {
+  constexpr int T = f32m::TILE;
+  constexpr int NB = D / 16;    // accumulator blocks of 16 columns
+  constexpr int PITCH = D + 4;  // floats per row of a parked output tile
+  __shared__ __attribute__((aligned(16))) float park[NW][T][PITCH];
+  __shared__ float part_m[NW][T], part_l[NW][T];
+
+  if (static_cast<int>(blockIdx.x) >= p.attend_blocks) {  // fused append: a plain row copy
+    const int j = blockIdx.x - p.attend_blocks;
+    copy_rows_block(p.copy, j % p.ndesc, j / p.ndesc);
+    return;
+  }
+  const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // All query tiles of a (batch row, head) pair get ids on one XCD (id % 8): they read the same keys.  Pairs come by
+  // decreasing run length and are dealt back and forth.
+  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+  const int turn = slot / p.n_qtiles;
+  const int pair = turn * 8 + ((turn & 1) ? 7 - xcd : xcd);
+  if (pair >= p.H * p.batch) return;
+  const int qt = slot % p.n_qtiles;
+  const int b = pair % p.batch;
+  int h, n_prior, run_row;
+  if (p.uniform_len >= 0) {
+    h = pair / p.batch;
+    n_prior = p.uniform_len;
+    run_row = p.uniform_row0 + h * p.uniform_len;
+  } else {
+    const HeadWork hw = p.work[pair / p.batch];
+    h = hw.head;
+    n_prior = hw.run_len;
+    run_row = hw.run_row;
+  }
+  const int t_k = p.t_k;
+  const long long cur_off = (static_cast<long long>(b) * p.H + h) * t_k * D;
+  const long long run_off = (static_cast<long long>(b) * p.arena_tokens + run_row) * D;
+  const float* k_cur = static_cast<const float*>(p.k_cur) + cur_off;
+  const float* v_cur = static_cast<const float*>(p.v_cur) + cur_off;
+  const float* k_prior = static_cast<const float*>(p.k_arena) + run_off;
+  const float* v_prior = static_cast<const float*>(p.v_arena) + run_off;
+  const long long q_off = cur_off + static_cast<long long>(qt) * T * D;
+  const int q_rows = min(t_k - qt * T, T);
+
+  const int tiles_cur = (t_k + T - 1) / T;
+  const int tiles_all = tiles_cur + (n_prior + T - 1) / T;
+  struct Tile {
+    bool prior;
+    long long first;  // element offset of its first row in the segment
+    int rows;         // valid rows, 1..16
+  };
+  auto tile_of = [&](int it) {
+    const bool prior = it >= tiles_cur;
+    const int local = prior ? it - tiles_cur : it;
+    return Tile{prior, static_cast<long long>(local) * (T * D), min((prior ? n_prior : t_k) - local * T, T)};
+  };
+
+  f32m::Rows<D> q, k;
+  auto load_k = [&](int it) {
+    const Tile t = tile_of(it);
+    k.load((t.prior ? k_prior : k_cur) + t.first, t.rows, lane);
+  };
+  q.load(static_cast<const float*>(p.q) + q_off, q_rows, lane);
+  if (wave < tiles_all) load_k(wave);
+
+  f32x4 o[NB];
+#pragma unroll
+  for (int i = 0; i < NB; ++i) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // Scores in base-2 exponents.  The reference m of a query is common to its four lanes and only raised when a score
+  // exceeds it by more than 8: probabilities stay at most 2^8 and the accumulators are rescaled a few times per row.
+  const float c = p.sm_scale * kLog2e;
+  float m = -INFINITY, l = 0.f;
+
+  for (int it = wave; it < tiles_all; it += NW) {
+    const Tile t = tile_of(it);
+    const float* vb = (t.prior ? v_prior : v_cur) + t.first + 4 * n;
+    f32x4 v[4][NB / 4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int j = 0; j < NB / 4; ++j)
+        v[r][j] = *reinterpret_cast<const f32x4*>(vb + min(4 * g + r, t.rows - 1) * D + 64 * j);
+    f32x4 s = f32m::scores<D>(k, q);
+    load_k(it + NW < tiles_all ? it + NW : it);  // the last step reloads its own tile: no branch around the prefetch
+    s *= c;
+    if (t.rows < T) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (4 * g + r >= t.rows) s[r] = -INFINITY;
+    }
+    const float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
+    if (__any(mx > m + 8.f)) {
+      const float m_new = fmaxf(m, f32m::max_groups(mx));
+      const float alpha = fast_exp2(m - m_new);
+      m = m_new;
+      l *= alpha;
+#pragma unroll
+      for (int i = 0; i < NB; ++i) o[i] *= alpha;
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) s[r] = fast_exp2(s[r] - m);
+    l += (s[0] + s[1]) + (s[2] + s[3]);
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int i = 0; i < NB; ++i) o[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[r][i / 4][i % 4], s[r], o[i], 0, 0, 0);
+  }
+
+  // Merge: every wavefront brings its accumulators to the common reference and divides by the common row sum; the
+  // parked tiles are then added in wavefront order.  A wavefront without a tile has reference -inf: factor 0.
+  l = f32m::sum_groups(l);
+  if (g == 0) {
+    part_m[wave][n] = m;
+    part_l[wave][n] = l;
+  }
+  __syncthreads();
+  float m_all = part_m[0][n], l_all = 0.f;
+#pragma unroll
+  for (int w = 1; w < NW; ++w) m_all = fmaxf(m_all, part_m[w][n]);
+#pragma unroll
+  for (int w = 0; w < NW; ++w) l_all += part_l[w][n] * fast_exp2(part_m[w][n] - m_all);
+  const float f = fast_exp2(m - m_all) / l_all;
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+#pragma unroll
+    for (int j = 0; j < NB / 4; ++j) {  // lane (n, g) holds columns 64 j + 16 g + 4 r + i of query n
+      const f32x4 x = {o[4 * j][r], o[4 * j + 1][r], o[4 * j + 2][r], o[4 * j + 3][r]};
+      *reinterpret_cast<f32x4*>(&park[wave][n][64 * j + 16 * g + 4 * r]) = x * f;
+    }
+  __syncthreads();
+  float* out = static_cast<float*>(p.out) + q_off;
+  for (int e = tid; e < q_rows * (D / 4); e += 64 * NW) {
+    const int row = e / (D / 4), col = e % (D / 4) * 4;
+    f32x4 x = *reinterpret_cast<const f32x4*>(&park[0][row][col]);
+#pragma unroll
+    for (int w = 1; w < NW; ++w) x += *reinterpret_cast<const f32x4*>(&park[w][row][col]);
+    *reinterpret_cast<f32x4*>(out + row * D + col) = x;
+  }
+}
+
+}  // namespace
+
+hipError_t launch_attend_f32(AttendParams p, int d, unsigned copy_blocks, hipStream_t stream) {
+  p.n_qtiles = (p.t_k + f32m::TILE - 1) / f32m::TILE;
+  const unsigned pairs8 = (unsigned(p.H) * p.batch + 7) / 8 * 8;  // padded so that id % 8 is the XCD
+  p.attend_blocks = int(unsigned(p.n_qtiles) * pairs8);
+  const dim3 grid(unsigned(p.attend_blocks) + copy_blocks), block(64 * NW);
+  if (d == 64)
+    hipLaunchKernelGGL(attend_f32_kernel<64>, grid, block, 0, stream, p);
+  else if (d == 128)
+    hipLaunchKernelGGL(attend_f32_kernel<128>, grid, block, 0, stream, p);
+  else
+    return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
+}  // namespace heatkv

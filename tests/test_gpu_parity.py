@@ -689,3 +689,27 @@ def test_tile_stream_probe_copies_what_it_claims():
     with pytest.raises(hk.HeatKVError):
         hp.heatkv_probe_tile_stream(src, out, 0, steps)
 
+
+
+@pytest.mark.parametrize("d,H,sides,s,den,batch", [
+    # one query tile and one key tile exactly; one over and one under; wavefronts without any tile; runs of one row
+    (64, 3, ((1, 1), (4, 4), (1, 17), (3, 5), (8, 8)), 1, 1, 1),
+    # nine pairs (padding to eight leaves idle workgroups), ragged query and key tiles, more tiles than wavefronts
+    (128, 3, ((1, 1), (2, 3), (7, 9), (11, 12), (13, 19)), 2, 2, 3),
+])
+def test_fp32_attention_at_the_edges_of_its_tiles(d, H, sides, s, den, batch):
+    # 16-query, 16-key matrix-core tiles over four wavefronts; the fused call has the bits of the two separate ones.
+    t0 = hi.tokens_per_scale(sides)
+    K = len(t0)
+    sm = 1.0 / np.sqrt(d)
+    cfg = dict(L=1, H=H, d=d, dtype="f32", batch=batch, sides=sides)
+    B = H * hi.cumulative_tokens(t0)[-2] // den
+    w = hi.head_weights(17, 1, H, K)
+    beta0 = hi.expected_beta_from_weights(w, t0).astype(np.float32)
+    plan = hk.heatkv_build_schedule(hk.Shape(1, H, d, t0, batch, "f32"), beta0, B * 2 * d * 4, s)
+    ref = harness.oracle_schedule(beta0, 1, H, t0, s, B)
+    q, k, v = hi.make_qkv(17, 0, cfg, w=w)
+    outs = device_generation(plan, 0, *_dev(q, k, v), t0, sm, fused=True)
+    for a, b in zip(outs, device_generation(plan, 0, *_dev(q, k, v), t0, sm)):
+        assert torch.equal(a, b)
+    _check_all(outs, q, k, v, t0, ref["present"], 0, sm, TOL["f32"])
