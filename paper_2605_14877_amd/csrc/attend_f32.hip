@@ -9,16 +9,14 @@
 // stands: MFMA step r of a tile takes the keys 4 g + r.  V^T is the A operand; row n of accumulator block 4 j + i
 // stands for column 64 j + 4 n + i, so that 16 lanes read 64 consecutive floats of a V row, 16 bytes each.
 //
-// K and V go from memory into registers: V of the tile is fetched under the score MFMAs, K of the wavefront's next
-// tile under the P V MFMAs.
-//
-// Bound: the matrix pipe where a launch fills the chip (128 pairs x 400 queries x 800 keys, d = 128: 221 us = 95 TFLOP/s
-// of the 151 a large fp32 matrix product reaches here; d = 64, 784 x 1384: 344 us = 103), the distribution of a few
-// workgroups per compute unit below that (16 pairs, 625 + 500 keys: 77 us = 75 TFLOP/s).  The vector-ALU kernel that this
-// one replaced fed its FMAs from LDS and reached 7 TFLOP/s (the same 625-query layer of a pruned image: 334 -> 67 us).
-// Eight wavefronts per workgroup, or 32 queries per workgroup (half the loads per MFMA): 0-15 % slower at every size,
-// the first for the longer merge, the second for the coarser distribution and one wavefront less per SIMD.  Key
-// tiles through LDS by global_load_lds (half the L1 accesses): within 4 % either way.
+// Bound: the matrix pipe plus the vector instructions that do not overlap with it (f32_mfma.h) where a launch fills the
+// chip (128 pairs x 400 queries x 800 keys, d = 128: 200 us = 105 TFLOP/s of the 151 a large fp32 matrix product reaches
+// here; d = 64, 784 x 1384: 320 us = 111), the distribution of a few workgroups per compute unit below that (16 pairs,
+// 625 + 500 keys: 72 us = 80 TFLOP/s).  The vector-ALU kernel that this one replaced fed its FMAs from LDS and reached 7
+// TFLOP/s (the 625-query layer of a pruned image: 334 -> 58 us).  Keys straight into registers instead of through the
+// stage: 221 us with the compiler's 64-bit vector addresses, 208 us with scalar ones, on the first shape.  Eight
+// wavefronts per workgroup, or 32 queries per workgroup (half the loads per MFMA): 0-15 % slower at every size, the
+// first for the longer merge, the second for the coarser distribution and one wavefront less per SIMD.
 #include "attend_params.h"
 #include "device_util.h"
 #include "f32_mfma.h"
@@ -35,7 +33,9 @@ __global__ __launch_bounds__(64 * NW) void attend_f32_kernel(AttendParams p) {
   constexpr int T = f32m::TILE;
   constexpr int NB = D / 16;    // accumulator blocks of 16 columns
   constexpr int PITCH = D + 4;  // floats per row of a parked output tile
-  __shared__ __attribute__((aligned(16))) float park[NW][T][PITCH];
+  using Stage = f32m::KeyStage<D>;
+  static_assert(T * PITCH * 4 >= Stage::BYTES, "the parked output tiles take the place of the key stages");
+  __shared__ __attribute__((aligned(1024))) float park[NW][T][PITCH];
   __shared__ float part_m[NW][T], part_l[NW][T];
 
   if (static_cast<int>(blockIdx.x) >= p.attend_blocks) {  // fused append: a plain row copy
@@ -87,13 +87,15 @@ __global__ __launch_bounds__(64 * NW) void attend_f32_kernel(AttendParams p) {
     return Tile{prior, static_cast<long long>(local) * (T * D), min((prior ? n_prior : t_k) - local * T, T)};
   };
 
+  const char* stage = reinterpret_cast<const char*>(&park[0][0][0]) + wave * Stage::BYTES;
+  const Stage keys(stage, lane);
   f32m::Rows<D> q, k;
-  auto load_k = [&](int it) {
+  auto fetch = [&](int it) {
     const Tile t = tile_of(it);
-    k.load((t.prior ? k_prior : k_cur) + t.first, t.rows, lane);
+    keys.fill((t.prior ? k_prior : k_cur) + t.first, t.rows, lane);
   };
   q.load(static_cast<const float*>(p.q) + q_off, q_rows, lane);
-  if (wave < tiles_all) load_k(wave);
+  if (wave < tiles_all) fetch(wave);
 
   f32x4 o[NB];
 #pragma unroll
@@ -105,15 +107,19 @@ __global__ __launch_bounds__(64 * NW) void attend_f32_kernel(AttendParams p) {
 
   for (int it = wave; it < tiles_all; it += NW) {
     const Tile t = tile_of(it);
-    const float* vb = (t.prior ? v_prior : v_cur) + t.first + 4 * n;
-    f32x4 v[4][NB / 4];
+    const f32m::GlobalBytes vb = f32m::scalar_base((t.prior ? v_prior : v_cur) + t.first);
+    // K of the tile out of the stage, the copy of the next one into it, V: the waits for V then also cover that copy,
+    // which is older, and the next step starts without waiting.
+    Stage::take(k, stage, lane);
+    if (it + NW < tiles_all) fetch(it + NW);
+    f32x4 v[4][NB / 4];  // rows 4 g + r, columns 64 j + 4 n .. + 3
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
+    for (int r = 0; r < 4; ++r) {
+      const unsigned off = (min(4 * g + r, t.rows - 1) * D + 4 * n) * 4;
 #pragma unroll
-      for (int j = 0; j < NB / 4; ++j)
-        v[r][j] = *reinterpret_cast<const f32x4*>(vb + min(4 * g + r, t.rows - 1) * D + 64 * j);
+      for (int j = 0; j < NB / 4; ++j) v[r][j] = f32m::load16(vb, off + 256 * j);
+    }
     f32x4 s = f32m::scores<D>(k, q);
-    load_k(it + NW < tiles_all ? it + NW : it);  // the last step reloads its own tile: no branch around the prefetch
     s *= c;
     if (t.rows < T) {
 #pragma unroll
@@ -140,6 +146,7 @@ __global__ __launch_bounds__(64 * NW) void attend_f32_kernel(AttendParams p) {
 
   // Merge: every wavefront brings its accumulators to the common reference and divides by the common row sum; the
   // parked tiles are then added in wavefront order.  A wavefront without a tile has reference -inf: factor 0.
+  __syncthreads();  // every wavefront has taken its last tile
   l = f32m::sum_groups(l);
   if (g == 0) {
     part_m[wave][n] = m;

@@ -61,6 +61,10 @@ __device__ __forceinline__ void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0F70);
 }
 
+// The same for the LDS / scalar-memory counter: every LDS read issued so far has returned (vmcnt and expcnt at their
+// maxima: no wait on them).
+__device__ __forceinline__ void wait_lgkmcnt0() { __builtin_amdgcn_s_waitcnt(0xC07F); }
+
 __device__ __forceinline__ uint4 ldg16(const void* p) { return *reinterpret_cast<const uint4*>(p); }
 
 // A 64-bit LDS read that transposes 16-bit elements inside each group of 16

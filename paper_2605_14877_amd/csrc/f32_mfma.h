@@ -5,25 +5,90 @@
 //
 // Scores are formed transposed, S^T = K Q^T (A = 16 key rows, B = 16 query rows).  The order of the d products of a dot
 // product is free as long as both operands agree, so MFMA step 4 j + i takes element 16 j + 4 g + i of the rows: a
-// lane then loads its row in pieces of 16 bytes.  The operands go from memory straight into registers: the wavefronts
-// of a workgroup walk different keys, so there is nothing for them to share in LDS.
+// lane then takes its row in pieces of 16 bytes.
+//
+// Two things about this chip shape the kernels.  (1) fp32 matrix instructions do not overlap with vector-ALU
+// instructions, not even those of another wavefront (32 MFMAs 1.75 ms, 128 FMAs 1.10 ms, both side by side 2.85 ms; with
+// bf16 MFMAs 1.89, 1.13 and 1.94): every vector instruction of a tile step adds to its 1024 (scores, d = 128) or 2048
+// cycles, hence the care with addresses below.  (2) The vector L1 coalesces neighbouring lanes only, and in the operand
+// layout those are in different rows: a fetch of keys straight into it costs 64 accesses per instruction, 2048 cycles
+// of the L1 for the tiles of four wavefronts, twice their score MFMAs.  So a wavefront fetches its key tiles into an LDS
+// stage of its own with whole rows side by side, and takes the operand from there.
 #pragma once
 
 #include "device_util.h"
+#include "tile_lds.h"
 
 namespace heatkv {
 namespace f32m {
 
 constexpr int TILE = 16;  // keys, or queries, of an MFMA tile
 
+// A load is written as scalar base + 32-bit lane offset + immediate.  The base is hidden from the optimiser, which
+// otherwise folds the two into 64-bit vector arithmetic of its own for every load.
+typedef const __attribute__((address_space(1))) char* GlobalBytes;
+__device__ __forceinline__ GlobalBytes scalar_base(const float* p) {
+  GlobalBytes b = (GlobalBytes)p;
+  asm volatile("; scalar base" : "+s"(b));
+  return b;
+}
+__device__ __forceinline__ f32x4 load16(GlobalBytes base, unsigned off) {
+  return *(const __attribute__((address_space(1))) f32x4*)(base + off);
+}
+
 // 16 rows of D floats as an MFMA operand (A or B); rows past the `rows` valid ones repeat the last.
 template <int D>
 struct Rows {
   f32x4 v[D / 16];
-  __device__ __forceinline__ void load(const float* base, int rows, int lane) {
-    const float* p = base + min(lane & 15, rows - 1) * D + 4 * (lane >> 4);
+  __device__ __forceinline__ void load(const float* p, int rows, int lane) {
+    const GlobalBytes base = scalar_base(p);
+    const unsigned off = (min(lane & 15, rows - 1) * D + 4 * (lane >> 4)) * 4;
 #pragma unroll
-    for (int j = 0; j < D / 16; ++j) v[j] = *reinterpret_cast<const f32x4*>(p + 16 * j);
+    for (int j = 0; j < D / 16; ++j) v[j] = load16(base, off + 64 * j);
+  }
+};
+
+// A wavefront's LDS stage for one tile of 16 key rows.  Copies of 1 KB (tile_lds.h: copy_1k; the compiler does not see
+// them as LDS stores or count them); the 16-byte chunks of a row are XORed with the row number, so that the 16 lanes
+// that read the same chunk of 16 rows (rows start on the same bank) cover all 64 banks.
+template <int D>
+struct KeyStage {
+  static constexpr int BYTES = TILE * D * 4;
+  static constexpr int COPIES = BYTES / 1024;
+  static constexpr int CPR = D / 4;  // chunks per row
+  unsigned lds;                      // LDS byte address of the stage
+  int off[COPIES];                   // lane offsets of the copies of a full tile
+  __device__ __forceinline__ KeyStage(const char* stage, int lane) {
+    lds = __builtin_amdgcn_readfirstlane(
+        static_cast<unsigned>(reinterpret_cast<unsigned long long>((__attribute__((address_space(3))) const char*)stage)));
+#pragma unroll
+    for (int j = 0; j < COPIES; ++j) off[j] = offset(j, lane, TILE);
+  }
+  static __device__ __forceinline__ int offset(int j, int lane, int rows) {
+    const int row = (64 * j + lane) / CPR;
+    return min(row, rows - 1) * (4 * D) + (((lane & (CPR - 1)) ^ row) << 4);
+  }
+  // Starts the copy of rows base[0 .. rows); the stage must have been taken.
+  __device__ __forceinline__ void fill(const float* base, int rows, int lane) const {
+    const char* src = reinterpret_cast<const char*>(base);
+    if (rows == TILE) {
+#pragma unroll
+      for (int j = 0; j < COPIES; ++j) tile::copy_1k(lds + 1024 * j, off[j], src);
+    } else {
+#pragma unroll
+      for (int j = 0; j < COPIES; ++j) tile::copy_1k_ragged(lds + 1024 * j, offset(j, lane, rows), src);
+    }
+  }
+  // Waits for every load of the wavefront, takes the tile; on return the stage may be filled again.
+  static __device__ __forceinline__ void take(Rows<D>& k, const char* stage, int lane) {
+    wait_vmcnt<0>();
+    asm volatile("" ::: "memory");
+    const int n = lane & 15, g = lane >> 4;
+#pragma unroll
+    for (int j = 0; j < D / 16; ++j)
+      k.v[j] = *reinterpret_cast<const f32x4*>(stage + n * (D * 4) + (((4 * j + g) ^ n) << 4));
+    wait_lgkmcnt0();
+    __builtin_amdgcn_sched_barrier(0);
   }
 };
 

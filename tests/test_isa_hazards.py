@@ -14,7 +14,7 @@ import pytest
 
 from paper_2605_14877_amd import build as hb
 
-SOURCES_WITH_COPIES = ["attend.hip", "calibrate.hip", "probe.hip"]
+SOURCES_WITH_COPIES = ["attend.hip", "attend_f32.hip", "calibrate.hip", "probe.hip"]
 VALU_SGPR_WRITERS = ("v_readlane_b32", "v_readfirstlane_b32", "v_cmp", "v_add_co", "v_sub_co", "v_subrev_co",
                      "v_addc_co", "v_subb_co", "v_div_scale")
 
