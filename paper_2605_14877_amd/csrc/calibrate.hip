@@ -17,6 +17,7 @@
 #include <type_traits>
 
 #include "device_util.h"
+#include "f32_mfma.h"
 #include "kernels.h"
 #include "tile_lds.h"
 
@@ -30,7 +31,7 @@ constexpr int MAXK = HEATKV_MAX_SCALES;
 // once, unlike generation); their workgroups are laid out one scale after the other, largest scale first.
 struct ScaleJob {
   int k1;
-  int block_begin;  // first workgroup id of this scale (a multiple of 8 in the bf16 kernel)
+  int block_begin;  // first workgroup id of this scale (a multiple of 8)
   const void *q, *k_all;
   float* partial;  // [batch*H][n_qtiles][K]
   float* mass;     // [batch*H][K], may be null in the accumulating variant
@@ -46,6 +47,13 @@ struct CalibParams {
   float weight;
   int layer;
 };
+
+// The kernel arguments take more than a kilobyte, and which of them a workgroup needs follows from others: read one
+// after the other they are a chain of scalar-cache misses.  This asks for their lines together.
+__device__ __forceinline__ void touch_params(const CalibParams& p) {
+  asm volatile("; kernel arguments" ::"s"(p.n_scales), "s"(p.t[13]), "s"(p.t[29]), "s"(p.c[14]), "s"(p.job[0].k1),
+               "s"(p.job[1].block_begin), "s"(p.sm_scale));
+}
 
 // The scale a workgroup belongs to (workgroup-uniform, a handful of scalar compares).
 __device__ __forceinline__ int scale_of_block(const CalibParams& p, int block) {
@@ -277,86 +285,132 @@ __global__ __launch_bounds__(256, CSETS == 1 ? 3 : 2) void calibrate_bf16_kernel
 }
 
 // ---------------------------------------------------------------------------
-// fp32: vector-ALU kernel, 16 queries per workgroup, 16 lanes per query.
+// fp32: S^T = K Q^T on the fp32 matrix instructions (f32_mfma.h), 16 queries per workgroup.  The key tiles (16 rows,
+// block-major) are dealt round robin to the four wavefronts; a lane keeps the running maximum and the sum of the
+// block being walked for its own keys, the lane groups are combined when the wavefront leaves a block and the
+// wavefronts at the end, all in a fixed order.
+//
+// Bound: start-up below about 100 query rows (4.4 us of kernel for one tile), the matrix pipe with the step's vector
+// instructions and one or two workgroups per compute unit above (16 heads, 400 x 937, d = 128: 27.5 us = 56 TFLOP/s;
+// the vector-ALU kernel that this one replaced: 261 us).  Keys straight into registers instead of through the stage:
+// 34 us; sizes of blocks looked up in every step: 33 us; kernel arguments read one after the other: +0.8 us per launch.
 // ---------------------------------------------------------------------------
-constexpr int FQ = 16;
-constexpr int FN = 32;
+constexpr int FQ = f32m::TILE;
+constexpr int FW = 4;           // wavefronts of a workgroup
+constexpr float LOWEST = -3e38f;  // below any score; finite, so that differences of references are never NaN
 
 template <int D>
-__global__ __launch_bounds__(256) void calibrate_f32_kernel(CalibParams p) {
-  __shared__ float Qs[FQ][D + 1];
-  __shared__ float Ks[FN][D + 1];
-  __shared__ float blk_sum[MAXK][FQ];
-  __shared__ float blk_max[MAXK][FQ];
+__global__ __launch_bounds__(64 * FW) void calibrate_f32_kernel(CalibParams p) {
+  using Stage = f32m::KeyStage<D>;
+  __shared__ __attribute__((aligned(1024))) char stages[FW][Stage::BYTES];
+  __shared__ float blk_sum[MAXK][FW][FQ], blk_max[MAXK][FW][FQ];
+  __shared__ float fin_max[FW][FQ], row_inv[FQ];
 
-  const int tid = threadIdx.x, r = tid >> 4, g = tid & 15;
+  const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  touch_params(p);
   const ScaleJob& job = p.job[scale_of_block(p, blockIdx.x)];
   const int k1 = job.k1, t_k1 = p.t[k1];
   const int n_qtiles = (t_k1 + FQ - 1) / FQ;
-  const int id = blockIdx.x - job.block_begin;
-  const int qt = id % n_qtiles;
-  const int bh = id / n_qtiles;
+  const int block = blockIdx.x - job.block_begin;
+  const int xcd = block & 7, slot = block >> 3;  // all query tiles of a (batch row, head) on one XCD
+  const int bh = (slot / n_qtiles) * 8 + xcd;
+  if (bh >= p.batch * p.H) return;
+  const int qt = slot % n_qtiles;
+  const int q_rows = min(t_k1 - qt * FQ, FQ);
   const float* kbase = static_cast<const float*>(job.k_all) + static_cast<long long>(bh) * p.c[k1] * D;
-  const float* q = static_cast<const float*>(job.q) + static_cast<long long>(bh) * t_k1 * D;
 
-  for (int e = tid; e < FQ * D; e += 256) {
-    const int rr = e / D, dd = e % D;
-    const int row = qt * FQ + rr;
-    Qs[rr][dd] = row < t_k1 ? q[static_cast<long long>(row) * D + dd] : 0.f;
-  }
-  float m_run = -INFINITY;
-  for (int k2 = 0; k2 <= k1; ++k2) {
-    float cur = 0.f;
-    const int first = p.c[k2] - p.t[k2];
-    const int tiles_here = (p.t[k2] + FN - 1) / FN;
-    for (int tile = 0; tile < tiles_here; ++tile) {
-      const int left = p.t[k2] - tile * FN;
-      __syncthreads();
-      for (int e = tid; e < FN * D; e += 256) {
-        const int rr = e / D, dd = e % D;
-        Ks[rr][dd] = rr < left ? kbase[static_cast<long long>(first + tile * FN + rr) * D + dd] : 0.f;
+  const Stage keys(stages[wave], lane);
+  f32m::Rows<D> q, k;
+  q.load(static_cast<const float*>(job.q) + (static_cast<long long>(bh) * t_k1 + qt * FQ) * D, q_rows, lane);
+
+  // The wavefront's tile: number `tile` of block k2, which has rows_left rows from that tile on.  `first` is the tile's
+  // first key.  Sizes of blocks are read only when the walk enters one: a step that stays inside its block reads no
+  // tables.
+  int k2 = 0, first = 0, rows_left = 0;
+  auto enter = [&](int tile) {  // tile number counted from the start of block k2; carries it over to the block that has it
+    while (k2 <= k1) {
+      const int rows = p.t[k2], here = (rows + FQ - 1) / FQ;
+      if (tile < here) {
+        first = p.c[k2] - rows + tile * FQ;
+        rows_left = rows - tile * FQ;
+        return;
       }
-      __syncthreads();
-      float s[2];
-#pragma unroll
-      for (int jj = 0; jj < 2; ++jj) {
-        const int j = g + 16 * jj;
-        float acc = 0.f;
-#pragma unroll 8
-        for (int dd = 0; dd < D; ++dd) acc = fmaf(Qs[r][dd], Ks[j][dd], acc);
-        s[jj] = j < left ? acc * p.sm_scale : -INFINITY;
-      }
-      float mx = fmaxf(s[0], s[1]);
-#pragma unroll
-      for (int off = 8; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 16));
-      const float m_new = fmaxf(m_run, mx);
-      float rowsum = expf(s[0] - m_new) + expf(s[1] - m_new);
-#pragma unroll
-      for (int off = 8; off >= 1; off >>= 1) rowsum += __shfl_xor(rowsum, off, 16);
-      cur = cur * expf(m_run - m_new) + rowsum;
-      m_run = m_new;
+      tile -= here;
+      ++k2;
     }
+  };
+  auto fetch = [&] { keys.fill(kbase + static_cast<long long>(first) * D, min(rows_left, FQ), lane); };
+  for (int j = 0; j <= k1; ++j)  // blocks without a tile of this wavefront
     if (g == 0) {
-      blk_sum[k2][r] = cur;
-      blk_max[k2][r] = m_run;
+      blk_sum[j][wave][n] = 0.f;
+      blk_max[j][wave][n] = LOWEST;
+    }
+  enter(wave);
+  if (k2 <= k1) fetch();
+  const float c = p.sm_scale * kLog2e;
+  float m = LOWEST, cur = 0.f;
+  while (k2 <= k1) {
+    const int here = k2, rows = rows_left;
+    Stage::take(k, stages[wave], lane);
+    if (rows_left > FW * FQ) {
+      first += FW * FQ;
+      rows_left -= FW * FQ;
+    } else {
+      const int tiles_left = (rows_left + FQ - 1) / FQ;  // of this block, from the tile on: at most FW
+      ++k2;
+      enter(FW - tiles_left);
+    }
+    if (k2 <= k1) fetch();
+    f32x4 s = f32m::scores<D>(k, q);
+    s *= c;
+    if (rows < FQ) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (4 * g + r >= rows) s[r] = -INFINITY;
+    }
+    const float m_new = fmaxf(m, fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])));
+    cur *= fast_exp2(m - m_new);
+    m = m_new;
+    cur += (fast_exp2(s[0] - m) + fast_exp2(s[1] - m)) + (fast_exp2(s[2] - m) + fast_exp2(s[3] - m));
+    if (k2 != here) {  // the wavefront leaves the block
+      const float mb = f32m::max_groups(m);
+      const float sb = f32m::sum_groups(cur * fast_exp2(m - mb));
+      if (g == 0) {
+        blk_sum[here][wave][n] = sb;
+        blk_max[here][wave][n] = mb;
+      }
+      cur = 0.f;
+    }
+  }
+  m = f32m::max_groups(m);
+  if (g == 0) fin_max[wave][n] = m;
+  __syncthreads();
+
+  // Row masses relative to the final maximum, normalised; rows past t_k1 contribute nothing.
+  {
+    const int row = tid & (FQ - 1);
+    float mf = fin_max[0][row];
+#pragma unroll
+    for (int w = 1; w < FW; ++w) mf = fmaxf(mf, fin_max[w][row]);
+    for (int j = tid / FQ; j <= k1; j += 64 * FW / FQ) {
+      float v = 0.f;
+#pragma unroll
+      for (int w = 0; w < FW; ++w) v += blk_sum[j][w][row] * fast_exp2(blk_max[j][w][row] - mf);
+      blk_sum[j][0][row] = v;
     }
   }
   __syncthreads();
   if (tid < FQ) {
-    const float mf = blk_max[k1][tid];
     float l = 0.f;
-    for (int j = 0; j <= k1; ++j) {
-      const float w = blk_sum[j][tid] * expf(blk_max[j][tid] - mf);
-      blk_sum[j][tid] = w;
-      l += w;
-    }
-    const float inv = (qt * FQ + tid < t_k1) ? 1.f / l : 0.f;
-    for (int j = 0; j <= k1; ++j) blk_sum[j][tid] *= inv;
+    for (int j = 0; j <= k1; ++j) l += blk_sum[j][0][tid];
+    row_inv[tid] = tid < q_rows ? 1.f / l : 0.f;
   }
   __syncthreads();
   if (tid <= k1) {
     float v = 0.f;
-    for (int rr = 0; rr < FQ; ++rr) v += blk_sum[tid][rr];
+#pragma unroll
+    for (int rr = 0; rr < FQ; ++rr) v += blk_sum[tid][0][rr] * row_inv[rr];
     job.partial[(static_cast<long long>(bh) * n_qtiles + qt) * p.K + tid] = v;
   }
 }
@@ -456,25 +510,25 @@ hipError_t launch_calibrate(const CalibrateArgs& a, hipStream_t stream) {
   p.beta = a.beta;
   p.weight = a.weight;
   p.layer = a.layer;
-  const bool mfma = a.dtype == HEATKV_BF16;
+  const bool bf16 = a.dtype == HEATKV_BF16;
   // bf16: the instance with two query sets per wavefront if its workgroups fill their 512 slots at least once.
   // Both leave one partial per 128 query rows (qpt), bit for bit the same ones.
   const int qpt = queries_per_tile(a.dtype);
   int rows_per_block = qpt;
-  if (mfma) {
+  if (bf16) {
     unsigned long long wide_blocks = 0;
     for (int i = 0; i < a.n_scales; ++i)
       wide_blocks += (unsigned long long)((a.t[a.k1[i]] + 2 * CBM1 - 1) / (2 * CBM1)) * a.H * a.batch;
     if (wide_blocks >= 512) rows_per_block = 2 * CBM1;
   }
-  if (mfma && a.d != 128 && a.d != 64) return hipErrorInvalidValue;
-  if (!mfma && a.d != 64 && a.d != 128) return hipErrorInvalidValue;
+  if (bf16 && a.d != 128 && a.d != 64) return hipErrorInvalidValue;
+  if (!bf16 && a.d != 64 && a.d != 128) return hipErrorInvalidValue;
   // Largest scale first: its workgroups are the long ones, the short ones then fill the gaps they leave.
   int order[MAXK];
   for (int i = 0; i < a.n_scales; ++i) order[i] = i;
   std::stable_sort(order, order + a.n_scales, [&](int x, int y) { return a.t[a.k1[x]] > a.t[a.k1[y]]; });
-  // In the bf16 kernel the (batch row, head) pairs are padded to a multiple of 8 so that id % 8 is the XCD.
-  const unsigned pairs = mfma ? (unsigned(a.H) * a.batch + 7) / 8 * 8 : unsigned(a.H) * a.batch;
+  // The (batch row, head) pairs are padded to a multiple of 8 so that id % 8 is the XCD.
+  const unsigned pairs = (unsigned(a.H) * a.batch + 7) / 8 * 8;
   unsigned blocks = 0;
   size_t ws_off = 0;
   int k1_max = 0;
@@ -491,7 +545,7 @@ hipError_t launch_calibrate(const CalibrateArgs& a, hipStream_t stream) {
     ws_off += (calibrate_workspace_bytes(a.dtype, a.d, a.H, a.batch, a.K, a.t[job.k1]) + 255) / 256 * 256;
     k1_max = job.k1 > k1_max ? job.k1 : k1_max;
   }
-  if (mfma) {
+  if (bf16) {
     // Many scales need more than the default 64 KB of dynamic LDS for the parked block sums: raise the limit to
     // what the largest scale count can ask for, once per device.
     static std::atomic<unsigned long long> raised{0};  // one bit per device ordinal below 64

@@ -713,3 +713,33 @@ def test_fp32_attention_at_the_edges_of_its_tiles(d, H, sides, s, den, batch):
     for a, b in zip(outs, device_generation(plan, 0, *_dev(q, k, v), t0, sm)):
         assert torch.equal(a, b)
     _check_all(outs, q, k, v, t0, ref["present"], 0, sm, TOL["f32"])
+
+
+@pytest.mark.parametrize("d,H,sides", [
+    # blocks of one tile, of one tile and a row, of fewer tiles than wavefronts; the last block ends inside a tile
+    (64, 3, ((1, 1), (4, 4), (1, 17), (3, 5), (8, 9))),
+    # nine pairs (padding to eight leaves idle workgroups), a block of several rounds of the four wavefronts
+    (128, 3, ((1, 1), (2, 3), (7, 9), (1, 64), (13, 19))),
+])
+def test_fp32_calibration_at_the_edges_of_its_tiles(d, H, sides):
+    t0 = hi.tokens_per_scale(sides)
+    c = hi.cumulative_tokens(t0)
+    K, nb = len(t0), 3 if d == 128 else 1
+    sm = 1.0 / np.sqrt(d)
+    cfg = dict(L=1, H=H, d=d, dtype="f32", batch=nb, sides=sides)
+    q, k, _ = hi.make_qkv(23, 0, cfg, w=hi.head_weights(23, 1, H, K))
+    dq, dk = _dev(q, k)
+    shape = hk.Shape(1, H, d, t0, nb, "f32")
+    t1 = orc.one_based(t0)
+    for k1 in range(K):
+        mass = torch.empty(nb, H, K, device="cuda")
+        ws = torch.empty(hk.binding.calibrate_workspace_bytes(shape, k1), dtype=torch.uint8, device="cuda")
+        hk.heatkv_calibrate(shape, 0, k1, dq[:, :, c[k1] - t0[k1]:c[k1]].contiguous(), dk[:, :, :c[k1]].contiguous(), sm,
+                            mass, ws)
+        got = mass.cpu().double().numpy()
+        for b in range(nb):
+            for h in range(H):
+                want = orc.beta_row(q[b, h].double().numpy(), k[b, h].double().numpy(), t1, k1 + 1, sm)
+                # fp32 sums of t * c probabilities: far inside the 1e-4 that masses are held to
+                assert np.abs(got[b, h, :k1 + 1] - want[1:k1 + 2]).max() <= 1e-5, (k1, b, h)
+                assert not got[b, h, k1 + 1:].any()
