@@ -1,4 +1,8 @@
-"""ctypes binding of the C ABI declared in include/heatkv.h (same names, argument marshalling only)."""
+"""Binding of the C ABI declared in include/heatkv.h (same names, argument marshalling only).
+
+ctypes throughout.  The calls that a generation or calibration pass repeats go through the module _heatkv_call first
+(csrc/call_path.cpp: the same operand checks, the stream and the library call without the interpreter, 4 instead of 10 us
+a call); it declines whatever is not plainly in order, and the ctypes path below it reports what is wrong."""
 from __future__ import annotations
 
 import ctypes as C
@@ -29,6 +33,7 @@ class _CShape(C.Structure):
 
 _lib = None
 _torch = None
+_call = None
 
 
 def library_path():
@@ -113,6 +118,9 @@ def lib():
     L.heatkv_head_scores.argtypes = [sp, f32p, C.c_int, C.c_int, f64p]
     L.heatkv_rank_dispersion.restype = C.c_int
     L.heatkv_rank_dispersion.argtypes = [sp, f32p, C.c_int, C.c_int, C.c_int, f64p]
+    global _call
+    from . import _heatkv_call
+    _call = _heatkv_call
     _lib = L
     return L
 
@@ -135,6 +143,7 @@ class Shape:
         self.K = int(self.t.size)
         self.dtype = _DTYPES[dtype] if isinstance(dtype, str) else int(dtype)
         self.c_struct = _CShape(self.L, self.H, self.d, self.K, self.batch, self.dtype, _i32p(self.t))
+        self.address = C.addressof(self.c_struct)
 
     @property
     def ref(self):
@@ -213,6 +222,8 @@ class Plan:
         # what the per-scale tensors and the arenas must look like (checked by the wrappers on every call)
         self.scale_shapes = [(shape.batch, shape.H, int(t), shape.d) for t in shape.t]
         self.arena_bytes_cached = int(lib().heatkv_plan_arena_bytes(self.handle))
+        self.call_info = _call.plan_info(self.handle.value, shape.L, shape.H, shape.d, shape.batch, shape.dtype,
+                                         tuple(int(t) for t in shape.t), self.arena_bytes_cached)
 
     def __del__(self):
         if getattr(self, "handle", None) and _lib is not None:
@@ -312,7 +323,28 @@ def calibrate_workspace_bytes(shape, k1):
     return int(lib().heatkv_calibrate_workspace_bytes(shape.ref, k1))
 
 
+def _calibrate_call(shape, which, layer, k1, q, k_all, sm_scale, weight, beta, mass, ws, stream):
+    """True if the native path has made the call."""
+    if _call is None:
+        lib()
+    rc = _call.calibrate_call(shape.address, which, layer, k1, q, k_all, sm_scale, weight, beta, mass, ws, stream)
+    if rc is None:
+        return False
+    _check(rc)
+    return True
+
+
+def _scale_call(plan, which, layer, k, q, k_cur, v_cur, k_arena, v_arena, sm_scale, out, ws, stream):
+    rc = _call.scale_call(plan.call_info, which, layer, k, q, k_cur, v_cur, k_arena, v_arena, sm_scale, out, ws, stream)
+    if rc is None:
+        return False
+    _check(rc)
+    return True
+
+
 def heatkv_calibrate(shape, layer, k1, q, k_all, sm_scale, mass, ws, stream=None):
+    if _calibrate_call(shape, 0, layer, k1, q, k_all, sm_scale, 0.0, None, mass, ws, stream):
+        return
     _check_calibrate_operands(shape, k1, q, k_all, mass, None)
     _check_tensor(ws, "ws")
     ws_bytes = 0 if ws is None else ws.numel() * ws.element_size()
@@ -325,6 +357,8 @@ calibrate = heatkv_calibrate
 
 def heatkv_calibrate_static(shape, layer, k1, q, k_all, sm_scale, mass, stream=None):
     """heatkv_calibrate with the library's static workspace: no allocation, no workspace argument."""
+    if _calibrate_call(shape, 1, layer, k1, q, k_all, sm_scale, 0.0, None, mass, None, stream):
+        return
     _check_calibrate_operands(shape, k1, q, k_all, mass, None)
     _check(lib().heatkv_calibrate_static(shape.ref, layer, k1, _ptr(q), _ptr(k_all), float(sm_scale), _ptr(mass),
                                          _stream() if stream is None else stream))
@@ -337,6 +371,8 @@ def heatkv_accumulate_beta(shape, layer, k1, mass, weight, beta, stream=None):
 
 
 def heatkv_append_scale(plan, layer, k, k_new, v_new, k_arena, v_arena, stream=None):
+    if _scale_call(plan, 0, layer, k, None, k_new, v_new, k_arena, v_arena, 0.0, None, None, stream):
+        return
     _check_scale_operands(plan, layer, k, (("k_new", k_new), ("v_new", v_new)),
                           (("k_arena", k_arena), ("v_arena", v_arena)))
     _check(lib().heatkv_append_scale(plan.handle, layer, k, _ptr(k_new), _ptr(v_new), _ptr(k_arena), _ptr(v_arena),
@@ -344,6 +380,8 @@ def heatkv_append_scale(plan, layer, k, k_new, v_new, k_arena, v_arena, stream=N
 
 
 def heatkv_attend_scale(plan, layer, k, q, k_cur, v_cur, k_arena, v_arena, sm_scale, out, ws=None, stream=None):
+    if _scale_call(plan, 1, layer, k, q, k_cur, v_cur, k_arena, v_arena, sm_scale, out, ws, stream):
+        return
     _check_scale_operands(plan, layer, k, (("q", q), ("k_cur", k_cur), ("v_cur", v_cur), ("out", out)),
                           (("k_arena", k_arena), ("v_arena", v_arena)))
     _check_tensor(ws, "ws")
@@ -354,6 +392,8 @@ def heatkv_attend_scale(plan, layer, k, q, k_cur, v_cur, k_arena, v_arena, sm_sc
 
 
 def heatkv_attend_append_scale(plan, layer, k, q, k_cur, v_cur, k_arena, v_arena, sm_scale, out, ws=None, stream=None):
+    if _scale_call(plan, 2, layer, k, q, k_cur, v_cur, k_arena, v_arena, sm_scale, out, ws, stream):
+        return
     _check_scale_operands(plan, layer, k, (("q", q), ("k_cur", k_cur), ("v_cur", v_cur), ("out", out)),
                           (("k_arena", k_arena), ("v_arena", v_arena)))
     _check_tensor(ws, "ws")
@@ -364,6 +404,8 @@ def heatkv_attend_append_scale(plan, layer, k, q, k_cur, v_cur, k_arena, v_arena
 
 
 def heatkv_calibrate_accumulate(shape, layer, k1, q, k_all, sm_scale, weight, beta, mass, ws, stream=None):
+    if _calibrate_call(shape, 2, layer, k1, q, k_all, sm_scale, weight, beta, mass, ws, stream):
+        return
     _check_calibrate_operands(shape, k1, q, k_all, mass, beta)
     _check_tensor(ws, "ws")
     ws_bytes = 0 if ws is None else ws.numel() * ws.element_size()
@@ -381,6 +423,13 @@ def heatkv_calibrate_scales_accumulate(shape, layer, k1_list, q_list, k_all_list
                                        ws, stream=None):
     """Eq. 2 masses of several query scales and their dataset average in one launch (see include/heatkv.h).
     q_list / k_all_list: one tensor per entry of k1_list; mass_list: None or one tensor-or-None per entry."""
+    if _call is None:
+        lib()
+    rc = _call.calibrate_scales_call(shape.address, layer, k1_list, q_list, k_all_list, sm_scale, weight, beta, mass_list,
+                                     ws, stream)
+    if rc is not None:
+        _check(rc)
+        return
     n = len(k1_list)
     if len(q_list) != n or len(k_all_list) != n or (mass_list is not None and len(mass_list) != n):
         raise ValueError("k1_list, q_list, k_all_list and mass_list must have the same length")

@@ -1,10 +1,12 @@
 """Builds the two shared libraries for gfx950 with hipcc: libheatkv.so (HIP kernels + host planner + C ABI of
-include/heatkv.h) and libheatkv_probe.so (the measurement aids of include/heatkv_probe.h, for bench.py)."""
+include/heatkv.h) and libheatkv_probe.so (the measurement aids of include/heatkv_probe.h, for bench.py); then, with the
+host compiler, the Python module _heatkv_call (csrc/call_path.cpp) over the first."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -12,6 +14,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libheatkv.so")
 PROBE_LIB = os.path.join(HERE, "libheatkv_probe.so")
 LIBRARIES = {LIB: ["plan.cpp", "abi.cpp", "attend.hip", "attend_f32.hip", "append.hip", "calibrate.hip"], PROBE_LIB: ["probe.hip"]}
+CALL_MODULE = os.path.join(HERE, "_heatkv_call.so")
 SOURCES = [src for srcs in LIBRARIES.values() for src in srcs]
 
 # Packed-fp32 VALU forms are switched off for every device translation unit.
@@ -51,7 +54,25 @@ def build(verbose: bool = True) -> str:
         if verbose:
             print(" ".join(cmd), flush=True)
         subprocess.run(cmd, check=True)
+    build_call_module(verbose)
     return LIB
+
+
+def build_call_module(verbose: bool = True) -> str:
+    """Host code only, against the installed PyTorch; it finds libheatkv.so next to itself."""
+    import torch
+
+    t = os.path.dirname(torch.__file__)
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I", sysconfig.get_paths()["include"],
+           "-isystem", os.path.join(t, "include"), "-isystem", os.path.join(t, "include", "torch", "csrc", "api", "include"),
+           "-isystem", "/opt/rocm/include", "-I", os.path.join(ROOT, "include"), os.path.join(CSRC, "call_path.cpp"),
+           "-o", CALL_MODULE, "-L", os.path.join(t, "lib"), "-L", HERE, "-ltorch_python", "-ltorch", "-ltorch_cpu",
+           "-lc10", "-lc10_hip", "-l:libheatkv.so", "-Wl,-rpath,$ORIGIN"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    return CALL_MODULE
 
 
 if __name__ == "__main__":
