@@ -28,9 +28,9 @@ namespace {
 // on key order, and each segment is then one contiguous range, so a tile's
 // addresses are a wavefront-uniform base plus a fixed per-lane offset).
 //
-// Tiles go from HBM straight into LDS (global_load_lds, no registers, no LDS
-// store instructions), double-buffered with one barrier per tile.  A tile is
-// stored row-major, 256 bytes per row, unpadded; the 16-byte chunks of a row are
+// Tiles go from HBM straight into LDS (buffer_load .. lds, no registers, no LDS
+// store instructions), double-buffered with one barrier per tile; the descriptor's
+// range check takes care of ragged tiles.  A tile is stored row-major, 256 bytes per row, unpadded; the 16-byte chunks of a row are
 // XOR-swizzled with the row number (the lane that fills an LDS slot simply
 // fetches the matching global chunk), K tiles and V tiles each with the pattern
 // that keeps their read instruction free of bank conflicts (tile_lds.h holds the
@@ -94,6 +94,7 @@ __global__ __launch_bounds__(256 * KS * QS, (KS == 1 && QS == 1) ? 2 : 1) void a
   char* const raw_k = reinterpret_cast<char*>(lds) + 4 * TILE_BYTES;  // FP8 only: landing buffers, 8 KB each
   char* const raw_v = raw_k + tile::RAW8_BYTES;
 
+  touch_params(p);
   if (static_cast<int>(blockIdx.x) >= p.attend_blocks) {  // fused append: a plain row copy by 256 lanes
     const int j = blockIdx.x - p.attend_blocks;
     if ((KS == 1 && QS == 1) || threadIdx.x < 256) copy_rows_block(p.copy, j % p.ndesc, j / p.ndesc);
@@ -111,21 +112,23 @@ __global__ __launch_bounds__(256 * KS * QS, (KS == 1 && QS == 1) ? 2 : 1) void a
   // (batch row, head) pair read the same K/V, so they are given ids that land on one XCD; pairs are dealt
   // to XCDs in order of decreasing run length, alternating direction, which balances the work between XCDs.
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  const int turn = slot / p.n_qtiles;  // pairs are dealt to the XCDs back and forth (0..7, 7..0, 0..7, ...)
+  const int turn = fast_div(slot, p.n_qtiles, p.div_qtiles);  // pairs are dealt to the XCDs back and forth (0..7, 7..0, 0..7, ...)
   const int pair = turn * 8 + ((turn & 1) ? 7 - xcd : xcd);
   if (pair >= p.H * p.batch) return;
-  const int qt = slot % p.n_qtiles;
-  const int b = pair % p.batch;
+  const int qt = slot - turn * p.n_qtiles;
+  const int rank = fast_div(pair, p.batch, p.div_batch), b = pair - rank * p.batch;
   int h, n_prior, run_row;
   if (p.uniform_len >= 0) {
-    h = pair / p.batch;
+    h = rank;
     n_prior = p.uniform_len;
     run_row = p.uniform_row0 + h * p.uniform_len;
   } else {
-    const HeadWork hw = p.work[pair / p.batch];  // one 16-byte record: head, first row and length of its run
-    h = hw.head;
-    n_prior = hw.run_len;
-    run_row = hw.run_row;
+    // One 16-byte record: head, first row and length of its run.  Read as constant memory, i.e. by a scalar load: what
+    // follows from it (tile addresses, descriptors) is then known to be wavefront-uniform.
+    const auto* hw = (const __attribute__((address_space(4))) HeadWork*)(p.work) + rank;
+    h = hw->head;
+    n_prior = hw->run_len;
+    run_row = hw->run_row;
   }
 
   const int t_k = p.t_k;
@@ -157,8 +160,8 @@ __global__ __launch_bounds__(256 * KS * QS, (KS == 1 && QS == 1) ? 2 : 1) void a
   const int steps_all = (tiles_all + KS - 1) / KS;
   auto has_tile = [&](int j) { return KS == 1 || KS * j + g < tiles_all; };
 
-  // Loader and reader offsets of the shared tile format.  The copy HBM -> LDS is issued as raw global_load_lds
-  // instructions (tile::issue_full / issue_ragged): the compiler then does not see an LDS store it would have to
+  // Loader and reader offsets of the shared tile format.  The copy HBM -> LDS is issued as raw instructions
+  // (tile::copy_1k_checked): the compiler then does not see an LDS store it would have to
   // order against the tile reads of the other buffer (it would wait for the whole prefetch in the middle of the
   // math).  Ordering is explicit instead: s_waitcnt vmcnt(0) and the workgroup barrier at the top of every step.
   const int ld_off_k = tile::loader_off_k<ROW_BYTES>(lw, lane);
@@ -188,39 +191,77 @@ __global__ __launch_bounds__(256 * KS * QS, (KS == 1 && QS == 1) ? 2 : 1) void a
   // Step `it` computes the scores of tile it+1 (matrix cores) while it turns the scores of tile `it` into
   // probabilities (vector ALU) and accumulates P V for tile `it`.  K tiles are therefore fetched one tile
   // further ahead than V tiles: at the top of step `it` the copies K(it+1) and V(it) must have landed.
-  auto issue_k = [&](int j, int buf) {
+  // A tile past the walk's end (the one that a stream's last step lacks, or the one after the last) has no valid rows.
+  constexpr int CPT = TILE_BYTES / (1024 * NW);  // copies of a tile per wavefront
+  struct TileSpan {
+    bool prior;
+    int local, left;  // tile number inside its segment, rows from its first one to the segment's end
+  };
+  auto span_of = [&](int j) {
     const int it = KS * j + g;
     const bool prior = it >= tiles_cur;
     const int local = prior ? it - tiles_cur : it;
-    const int left = (prior ? n_prior : t_k) - local * BN;
-    if (FP8 && prior) {  // codes land in the K landing buffer; the step that needs the tile converts it
-      tile::issue_raw8<NW>(lds_base + 4 * TILE_BYTES, lw, lane, left, k_prior + static_cast<long long>(local) * PRIOR_TILE_BYTES);
-      return;
+    return TileSpan{prior, local, (prior ? n_prior : t_k) - local * BN};
+  };
+  auto source = [&](int j, const char* cur, const char* prior) {
+    const TileSpan t = span_of(j);
+    return tile::tile_descriptor<ROW_BYTES>((t.prior ? prior : cur) + static_cast<long long>(t.local) * TILE_BYTES, t.left);
+  };
+  // The same for the steady-state steps, one tile after the other: K and V of the walk's tile j, rows left from it on.
+  struct Walk {
+    const char *k, *v;
+    int it, left;
+  };
+  auto walk_at = [&](int j) {
+    const TileSpan t = span_of(j);
+    const long long off = static_cast<long long>(t.local) * TILE_BYTES;
+    return Walk{(t.prior ? k_prior : k_cur) + off, (t.prior ? v_prior : v_cur) + off, KS * j + g, t.left};
+  };
+  auto advance = [&](Walk& w) {
+    w.it += KS;
+    w.k += KS * TILE_BYTES;
+    w.v += KS * TILE_BYTES;
+    w.left -= KS * BN;
+    const int local = w.it - tiles_cur;
+    if (local >= 0 && local < KS) {  // into the retained run
+      w.k = k_prior + local * TILE_BYTES;
+      w.v = v_prior + local * TILE_BYTES;
+      w.left = n_prior - local * BN;
     }
-    const char* kb = (prior ? k_prior : k_cur) + static_cast<long long>(local) * TILE_BYTES;
-    const unsigned kd = lds_base + buf * (2 * TILE_BYTES);
-    // Two separate statements under a workgroup-uniform branch: the full-tile path has no per-lane arithmetic.
-    if (left >= BN)
-      tile::issue_full<ROW_BYTES, NW>(kd, lw, ld_off_k, kb);
-    else
-      tile::issue_ragged<false, ROW_BYTES, NW>(kd, lw, lane, left, kb);
+  };
+  // Copy i (0 .. CPT - 1) of a tile into K (V) stage `buf`.
+  auto copy_k = [&](const tile::Descriptor& src, int buf, int i) {
+    tile::copy_1k_checked(lds_base + buf * (2 * TILE_BYTES) + lw * 1024 + i * (1024 * NW), ld_off_k, src, i * (1024 * NW));
+  };
+  auto copy_v = [&](const tile::Descriptor& src, int buf, int i) {
+    tile::copy_1k_checked(lds_base + buf * (2 * TILE_BYTES) + TILE_BYTES + lw * 1024 + i * (1024 * NW), ld_off_v, src,
+                          i * (1024 * NW));
+  };
+  auto issue_k = [&](int j, int buf) {
+    if constexpr (FP8) {  // codes land in the K landing buffer; the step that needs the tile converts it
+      const TileSpan t = span_of(j);
+      if (t.prior) {
+        tile::issue_raw8<NW>(lds_base + 4 * TILE_BYTES, lw, lane, t.left,
+                             k_prior + static_cast<long long>(t.local) * PRIOR_TILE_BYTES);
+        return;
+      }
+    }
+    const tile::Descriptor src = source(j, k_cur, k_prior);
+#pragma unroll
+    for (int i = 0; i < CPT; ++i) copy_k(src, buf, i);
   };
   auto issue_v = [&](int j, int buf) {
-    const int it = KS * j + g;
-    const bool prior = it >= tiles_cur;
-    const int local = prior ? it - tiles_cur : it;
-    const int left = (prior ? n_prior : t_k) - local * BN;
-    if (FP8 && prior) {
-      tile::issue_raw8<NW>(lds_base + 4 * TILE_BYTES + tile::RAW8_BYTES, lw, lane, left,
-                           v_prior + static_cast<long long>(local) * PRIOR_TILE_BYTES);
-      return;
+    if constexpr (FP8) {
+      const TileSpan t = span_of(j);
+      if (t.prior) {
+        tile::issue_raw8<NW>(lds_base + 4 * TILE_BYTES + tile::RAW8_BYTES, lw, lane, t.left,
+                             v_prior + static_cast<long long>(t.local) * PRIOR_TILE_BYTES);
+        return;
+      }
     }
-    const char* vb = (prior ? v_prior : v_cur) + static_cast<long long>(local) * TILE_BYTES;
-    const unsigned vd = lds_base + buf * (2 * TILE_BYTES) + TILE_BYTES;
-    if (left >= BN)
-      tile::issue_full<ROW_BYTES, NW>(vd, lw, ld_off_v, vb);
-    else
-      tile::issue_ragged<true, ROW_BYTES, NW>(vd, lw, lane, left, vb);
+    const tile::Descriptor src = source(j, v_cur, v_prior);
+#pragma unroll
+    for (int i = 0; i < CPT; ++i) copy_v(src, buf, i);
   };
 
   // S^T = K Q^T for the 64 keys of the K tile in buffer `buf` x this wavefront's 32 queries.
@@ -263,12 +304,9 @@ __global__ __launch_bounds__(256 * KS * QS, (KS == 1 && QS == 1) ? 2 : 1) void a
       for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[cb][r]);
     return mx;
   };
-  // Masks the ragged tail of the stream's tile j (keys past the end of the scale or of the run get -inf);
-  // returns whether there was one.
-  auto mask_tail = [&](int j, f32x16 (&s)[2]) {
-    const int it = KS * j + g;
-    const bool prior = it >= tiles_cur;
-    const int left = (prior ? n_prior : t_k) - (prior ? it - tiles_cur : it) * BN;
+  // Masks the ragged tail of a tile with `left` rows from its first one on (keys past the end of the scale or of the run
+  // get -inf); returns whether there was one.
+  auto mask_tail = [&](int left, f32x16 (&s)[2]) {
     if (left >= BN) return false;  // workgroup-uniform and rare: kept a branch
     // Register r of block cb holds key 32 cb + 8 (r / 4) + r % 4 + 4 hl: compared as a compile-time constant
     // against one per-lane limit, formed here and hidden from the optimiser so that it is not turned back into
@@ -284,7 +322,7 @@ __global__ __launch_bounds__(256 * KS * QS, (KS == 1 && QS == 1) ? 2 : 1) void a
   };
   // Masks the tail of tile j and folds its row maxima into the running reference.
   auto settle = [&](int j, f32x16 (&s)[2]) {
-    mask_tail(j, s);
+    mask_tail(span_of(j).left, s);
     raise(lane_max(s));
   };
   // P^T = 2^(S^T c - m c) in bf16, 16 keys at a time, each chunk feeding O^T += V^T P^T at once.  The row
@@ -335,8 +373,15 @@ __global__ __launch_bounds__(256 * KS * QS, (KS == 1 && QS == 1) ? 2 : 1) void a
   //   A(g) and S(g+1), the row maxima of the new scores in those of A(3); the K operands of S(g+1) are read in the
   //   slots of S(g), the V operands of A(g+1) in those of A(g): every operand a whole phase before its MFMA (those
   //   of S(0) and A(0), which only exist after the barrier, in preload() and in the slots of S(0)).
+  // The step's tile copies go out one per slot, from the second slot on.  The path into LDS takes 64 bytes per clock
+  // and compute unit, 512 cycles for a K and a V tile; issued together behind the barrier (550 cycles of every step for a
+  // lone wavefront, 740 with two workgroups on the unit) they held back the step's arithmetic.  Spread out: t_k = 4096 of
+  // the serving shape 4211 -> 4052 us, 1600: 782 -> 751; two key streams at 1024 tokens (batch 2): 56.5 -> 50.6 us.
+  // Where they start (slot 0, 1, 2 or 4) and whether every slot or every second one has a copy makes no difference.
   // Returns this lane's maximum over the new scores (before any tail mask).
-  auto step_math = [&](const f32x16 (&s_in)[2], f32x16 (&s_out)[2], const bf16x8 (&k0)[2], auto kb1, auto vb0) {
+  auto step_math = [&](const f32x16 (&s_in)[2], f32x16 (&s_out)[2], const bf16x8 (&k0)[2], auto kb1, auto vb0,
+                       auto copies, const tile::Descriptor& k_src, const tile::Descriptor& v_src) {
+    constexpr int COPIES = decltype(copies)::value * CPT;  // 0: none, 1: the K tile's, 2: those of K and V
     constexpr int KPC = NK / 4;          // K-steps per phase S
     constexpr int NS = 2 * KPC;          // slots of a phase S
     constexpr int NA = NV;               // slots of a phase A
@@ -380,6 +425,17 @@ __global__ __launch_bounds__(256 * KS * QS, (KS == 1 && QS == 1) ? 2 : 1) void a
 #pragma unroll
     for (int cb = 0; cb < 2; ++cb) kop[0][cb] = k0[cb];
     float mx = -INFINITY;
+    int slot_no = 0;  // compile-time after unrolling
+    auto copy_slot = [&] {  // one of the step's tile copies
+      const int i = slot_no - 1;
+      if (i >= 0 && i < COPIES) {
+        if (i < CPT)
+          copy_k(k_src, decltype(vb0)::value, i);  // K(j+2): the stage that step j-1 read
+        else
+          copy_v(v_src, decltype(kb1)::value, i - CPT);  // V(j+1) likewise
+      }
+      ++slot_no;
+    };
     auto s_slot = [&](int gch, int i, int halves_chunk, int& half) {  // slot i of phase S(gch)
       const int ks = gch * KPC + (i >> 1), cb = i & 1;
       s_out[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kop[ks][cb], qreg[ks], s_out[cb], 0, 0, 0);
@@ -389,6 +445,7 @@ __global__ __launch_bounds__(256 * KS * QS, (KS == 1 && QS == 1) ? 2 : 1) void a
         load_v(0, i);
       }
       if (gch < 3) load_k(ks + KPC, cb);
+      copy_slot();
       const int n = gch == 0 ? HALVES / NS : HALVES / (NS + NA);
       for (int u = 0; u < n; ++u) p_half(halves_chunk, half++);
       fence();
@@ -405,6 +462,7 @@ __global__ __launch_bounds__(256 * KS * QS, (KS == 1 && QS == 1) ? 2 : 1) void a
         fence();
         if (gch < 3) {
           load_v(gch + 1, d);
+          copy_slot();
 #pragma unroll
           for (int u = 0; u < HALVES / (NS + NA); ++u) p_half(gch + 1, half++);
         } else {  // the new scores are complete: their maxima, 32 / NA registers per slot
@@ -421,8 +479,7 @@ __global__ __launch_bounds__(256 * KS * QS, (KS == 1 && QS == 1) ? 2 : 1) void a
     }
     return mx;
   };
-  // The K operands of a step's first two MFMAs: read right after the barrier, before the step's tile copies are
-  // issued, so that their LDS round trip passes under the scalar work of issuing.  Only those: right after a
+  // The K operands of a step's first two MFMAs: read right after the barrier.  Only those: right after a
   // barrier all wavefronts of the workgroup read at once, and what they ask for queues up in front of the first
   // MFMA; everything else is read from the slots of phase S(0) on.
   auto preload = [&](bf16x8 (&k0)[2], auto kb1) {
@@ -437,8 +494,19 @@ __global__ __launch_bounds__(256 * KS * QS, (KS == 1 && QS == 1) ? 2 : 1) void a
   const bool active = q_row0 < t_k;
   // Steady-state step j (j + 1 < steps_all): K of the stream's tile j+1 sits in K stage kb1, V of its tile j in
   // V stage vb0.  s_in holds the scores of tile j, s_out receives those of tile j+1: the two register sets swap
-  // roles from step to step instead of being copied.
-  auto pipe_step = [&](int j, auto kb1, auto vb0, f32x16 (&s_in)[2], f32x16 (&s_out)[2]) {
+  // roles from step to step instead of being copied.  With two streams the second may lack the last successor tile: it
+  // lands as zeros and is masked like any other ragged tile.  `copies` as for step_math.
+  Walk w = walk_at(1);
+  auto pipe_step = [&](int j, auto kb1, auto vb0, f32x16 (&s_in)[2], f32x16 (&s_out)[2], auto copies) {
+    constexpr int COPIES = decltype(copies)::value;
+    // w: tile j+1 on entry, tile j+2 on return
+    const int left1 = FP8 ? span_of(j + 1).left : w.left;
+    tile::Descriptor k_src{}, v_src{};
+    if constexpr (!FP8) {
+      if constexpr (COPIES > 1) v_src = tile::tile_descriptor<ROW_BYTES>(w.v, w.left);
+      advance(w);
+      k_src = tile::tile_descriptor<ROW_BYTES>(w.k, w.left);
+    }
     wait_vmcnt<0>();
     __syncthreads();
     if constexpr (FP8) {
@@ -450,22 +518,20 @@ __global__ __launch_bounds__(256 * KS * QS, (KS == 1 && QS == 1) ? 2 : 1) void a
       if (cv) tile::convert_raw8<true, 64 * NW>(raw_v, lds[decltype(vb0)::value][1], tid);
       if (ck || cv) __syncthreads();
     }
-    if constexpr (KS == 2) {  // two streams: the compiler's own order (a stream's last step may lack a successor tile)
-      if (j + 2 < steps_all && has_tile(j + 2)) issue_k(j + 2, decltype(vb0)::value);
-      if (has_tile(j + 1)) issue_v(j + 1, decltype(kb1)::value);
-      if (!active) return;
-      if (has_tile(j + 1)) scores(s_out, kb1);
-      accumulate(s_in, vb0);
-      if (has_tile(j + 1)) settle(j + 1, s_out);
-      return;
-    }
     bf16x8 k0[2];
     if (active) preload(k0, kb1);
-    if (j + 2 < steps_all) issue_k(j + 2, decltype(vb0)::value);  // K stage j & 1: read by step j-1
-    if (j > 0) issue_v(j + 1, decltype(kb1)::value);  // V stage (j+1) & 1 likewise; the prologue has already fetched V(1)
-    if (!active) return;
-    const float mx = step_math(s_in, s_out, k0, kb1, vb0);
-    raise(mask_tail(j + 1, s_out) ? lane_max(s_out) : mx);
+    if constexpr (FP8) {
+      if (j + 2 < steps_all) issue_k(j + 2, decltype(vb0)::value);
+      if (COPIES > 1) issue_v(j + 1, decltype(kb1)::value);
+      if (!active) return;
+    } else if (!active) {
+#pragma unroll
+      for (int i = 0; i < COPIES * CPT; ++i)
+        i < CPT ? copy_k(k_src, decltype(vb0)::value, i) : copy_v(v_src, decltype(kb1)::value, i - CPT);
+      return;
+    }
+    const float mx = step_math(s_in, s_out, k0, kb1, vb0, std::integral_constant<int, FP8 ? 0 : COPIES>{}, k_src, v_src);
+    raise(mask_tail(left1, s_out) ? lane_max(s_out) : mx);
   };
 
   // Prologue: all four tile stages are free, so K(0), V(0), K(1) and V(1) all go out at once: one memory round
@@ -473,7 +539,6 @@ __global__ __launch_bounds__(256 * KS * QS, (KS == 1 && QS == 1) ? 2 : 1) void a
   // Loads return in issue order, so waiting until only the copies younger than K(0) are outstanding means that
   // K(0) has landed (CPT copies per wavefront and bf16 tile, two per 8-bit tile); tile 0 is a current-scale tile,
   // whose address does not depend on the head's run.
-  constexpr int CPT = TILE_BYTES / (1024 * NW);
   if (KS == 1) {
     issue_k(0, 0);
     issue_v(0, 0);
@@ -487,10 +552,10 @@ __global__ __launch_bounds__(256 * KS * QS, (KS == 1 && QS == 1) ? 2 : 1) void a
     } else {
       wait_vmcnt<CPT>();
     }
-  } else {  // a stream may have no tile at all, or one: everything it has goes out, then a full wait
-    if (has_tile(0)) issue_k(0, 0);
-    if (steps_all > 1 && has_tile(1)) issue_k(1, 1);
-    if (has_tile(0)) issue_v(0, 0);
+  } else {
+    issue_k(0, 0);
+    issue_k(1, 1);
+    issue_v(0, 0);
     wait_vmcnt<0>();
   }
   __syncthreads();
@@ -502,14 +567,23 @@ __global__ __launch_bounds__(256 * KS * QS, (KS == 1 && QS == 1) ? 2 : 1) void a
   // above never waited for its query rows): otherwise it waits for them inside every step, and with them for the
   // tile copies that the step has just issued.  The first step starts with the same wait, so this one is free.
   wait_vmcnt<0>();
+  // Scores of even steps live in s_cur, of odd steps in s_nxt.  With one key stream the prologue has fetched V(1): the
+  // first step copies K(2) only.
+  using Zero = std::integral_constant<int, 0>;
+  using One = std::integral_constant<int, 1>;
+  using Both = std::integral_constant<int, 2>;
   int it = 0;
-  for (; it + 2 < steps_all; it += 2) {  // scores of even steps live in s_cur, of odd steps in s_nxt
-    pipe_step(it, std::integral_constant<int, 1>{}, std::integral_constant<int, 0>{}, s_cur, s_nxt);
-    pipe_step(it + 1, std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{}, s_nxt, s_cur);
-  }
-  if (it + 1 < steps_all) {
-    pipe_step(it, std::integral_constant<int, 1>{}, std::integral_constant<int, 0>{}, s_cur, s_nxt);
-    ++it;
+  if (steps_all > 1) {
+    pipe_step(0, One{}, Zero{}, s_cur, s_nxt, std::integral_constant<int, KS == 1 ? 1 : 2>{});
+    it = 1;
+    for (; it + 2 < steps_all; it += 2) {
+      pipe_step(it, Zero{}, One{}, s_nxt, s_cur, Both{});
+      pipe_step(it + 1, One{}, Zero{}, s_cur, s_nxt, Both{});
+    }
+    if (it + 1 < steps_all) {
+      pipe_step(it, Zero{}, One{}, s_nxt, s_cur, Both{});
+      ++it;
+    }
   }
   // Epilogue: the last tile has scores but no successor.
   wait_vmcnt<0>();
@@ -667,23 +741,27 @@ hipError_t launch_attend(const AttendArgs& a, hipStream_t stream) {
   if (a.dtype == HEATKV_BF16) {
     if (a.d != 128 && a.d != 64) return hipErrorInvalidValue;
     if (a.d == 64 && a.kv_fp8) return hipErrorInvalidValue;
-    p.n_qtiles = (a.t_k + BM - 1) / BM;
     const unsigned pairs8 = (unsigned(a.H) * a.batch + 7) / 8 * 8;  // padded so that id % 8 is the XCD
-    p.attend_blocks = int(unsigned(p.n_qtiles) * pairs8);
-    const dim3 grid(unsigned(p.attend_blocks) + copy_blocks);
     // Long walks on a full chip: 256 queries per workgroup share every K/V tile (d = 128, either cache format).
     const int wide = (a.t_k + 2 * BM - 1) / (2 * BM);
     const bool two_sets = a.d == 128 && a.t_k >= TWO_SET_MIN_TOKENS &&
                           unsigned(wide) * pairs8 >= unsigned(TWO_SET_MIN_BLOCKS) && (wide * 2 * BM - a.t_k) * 16 <= a.t_k;
     const unsigned wide_blocks = unsigned(wide) * pairs8;
+    auto set_split = [&](int n_qtiles) {
+      p.n_qtiles = n_qtiles;
+      p.attend_blocks = int(unsigned(n_qtiles) * pairs8);
+      p.div_qtiles = reciprocal(p.attend_blocks, n_qtiles);
+    };
+    set_split((a.t_k + BM - 1) / BM);
+    p.div_batch = reciprocal(pairs8, a.batch);
+    const dim3 grid(unsigned(p.attend_blocks) + copy_blocks);
     if (a.d == 64) {  // rows of 128 bytes: the single-stream instance
       hipLaunchKernelGGL((attend_bf16_kernel<1, false, 64>), grid, dim3(256), 0, stream, p);
     } else if (a.kv_fp8) {  // 8-bit cache rows: the single-stream instances with landing buffers
       const hipError_t e = allow_two_stream_lds();
       if (e != hipSuccess) return e;
       if (two_sets) {
-        p.n_qtiles = wide;
-        p.attend_blocks = int(wide_blocks);
+        set_split(wide);
         hipLaunchKernelGGL((attend_bf16_kernel<1, true, 128, 2>), dim3(wide_blocks + copy_blocks), dim3(512),
                            FP8_LDS_BYTES, stream, p);
       } else {
@@ -695,8 +773,7 @@ hipError_t launch_attend(const AttendArgs& a, hipStream_t stream) {
       if (e != hipSuccess) return e;
       hipLaunchKernelGGL((attend_bf16_kernel<2, false, 128>), grid, dim3(512), TWO_STREAM_LDS_BYTES, stream, p);
     } else if (two_sets) {
-      p.n_qtiles = wide;
-      p.attend_blocks = int(wide_blocks);
+      set_split(wide);
       hipLaunchKernelGGL((attend_bf16_kernel<1, false, 128, 2>), dim3(wide_blocks + copy_blocks), dim3(512), 0, stream, p);
     } else {
       hipLaunchKernelGGL((attend_bf16_kernel<1, false, 128>), grid, dim3(256), 0, stream, p);

@@ -38,6 +38,7 @@ __global__ __launch_bounds__(64 * NW) void attend_f32_kernel(AttendParams p) {
   __shared__ __attribute__((aligned(1024))) float park[NW][T][PITCH];
   __shared__ float part_m[NW][T], part_l[NW][T];
 
+  touch_params(p);
   if (static_cast<int>(blockIdx.x) >= p.attend_blocks) {  // fused append: a plain row copy
     const int j = blockIdx.x - p.attend_blocks;
     copy_rows_block(p.copy, j % p.ndesc, j / p.ndesc);
@@ -48,21 +49,21 @@ __global__ __launch_bounds__(64 * NW) void attend_f32_kernel(AttendParams p) {
   // All query tiles of a (batch row, head) pair get ids on one XCD (id % 8): they read the same keys.  Pairs come by
   // decreasing run length and are dealt back and forth.
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  const int turn = slot / p.n_qtiles;
+  const int turn = fast_div(slot, p.n_qtiles, p.div_qtiles);
   const int pair = turn * 8 + ((turn & 1) ? 7 - xcd : xcd);
   if (pair >= p.H * p.batch) return;
-  const int qt = slot % p.n_qtiles;
-  const int b = pair % p.batch;
+  const int qt = slot - turn * p.n_qtiles;
+  const int rank = fast_div(pair, p.batch, p.div_batch), b = pair - rank * p.batch;
   int h, n_prior, run_row;
   if (p.uniform_len >= 0) {
-    h = pair / p.batch;
+    h = rank;
     n_prior = p.uniform_len;
     run_row = p.uniform_row0 + h * p.uniform_len;
   } else {
-    const HeadWork hw = p.work[pair / p.batch];
-    h = hw.head;
-    n_prior = hw.run_len;
-    run_row = hw.run_row;
+    const auto* hw = (const __attribute__((address_space(4))) HeadWork*)(p.work) + rank;  // a scalar load
+    h = hw->head;
+    n_prior = hw->run_len;
+    run_row = hw->run_row;
   }
   const int t_k = p.t_k;
   const long long cur_off = (static_cast<long long>(b) * p.H + h) * t_k * D;
@@ -183,6 +184,8 @@ hipError_t launch_attend_f32(AttendParams p, int d, unsigned copy_blocks, hipStr
   p.n_qtiles = (p.t_k + f32m::TILE - 1) / f32m::TILE;
   const unsigned pairs8 = (unsigned(p.H) * p.batch + 7) / 8 * 8;  // padded so that id % 8 is the XCD
   p.attend_blocks = int(unsigned(p.n_qtiles) * pairs8);
+  p.div_qtiles = reciprocal(p.attend_blocks, p.n_qtiles);
+  p.div_batch = reciprocal(pairs8, p.batch);
   const dim3 grid(unsigned(p.attend_blocks) + copy_blocks), block(64 * NW);
   if (d == 64)
     hipLaunchKernelGGL(attend_f32_kernel<64>, grid, block, 0, stream, p);

@@ -111,26 +111,37 @@ __device__ __forceinline__ void issue_ragged(unsigned lds_tile, int wave, int la
   }
 }
 
+// Range-checked form of the copy: buffer_load .. lds with a descriptor that ends where the tile's valid rows end.  Lanes
+// past the end write zeros and touch no memory, so a ragged tile (or one that does not exist: no valid rows) takes the
+// same instructions as a full one, with no per-lane address arithmetic.  The check covers lane offset + soffset.
+typedef int Descriptor __attribute__((ext_vector_type(4)));
+template <int RB = ROW_BYTES>
+__device__ __forceinline__ Descriptor tile_descriptor(const char* src, int left) {
+  static_assert(RB == 256 || RB == 128, "row of 256 or 128 bytes");
+  // max(0, min(left, ROWS)) rows; as text, because the compiler takes the vector ALU's three-operand form for it.
+  int bytes;
+  asm("s_min_i32 %0, %1, 64\n\ts_max_i32 %0, %0, 0\n\ts_lshl_b32 %0, %0, %2" : "=s"(bytes) : "s"(left), "n"(RB == 256 ? 8 : 7) : "scc");
+  const unsigned long long a = reinterpret_cast<unsigned long long>(src);
+  return Descriptor{static_cast<int>(a), static_cast<int>((a >> 32) & 0xffff), bytes, 0x00020000};
+}
+// The leading s_nop is the wait state between the write of M0 and the copy (copy_1k has a move there).
+__device__ __forceinline__ void copy_1k_checked(unsigned lds_dst, int lane_off, const Descriptor& tile, int soffset) {
+  asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
+               :
+               : "v"(lane_off), "s"(tile), "s"(soffset), "{m0}"(lds_dst)
+               : "memory");
+}
+
 // 8-bit cache rows (FP8 E4M3 codes, 128 bytes per row): a 64-row tile is 8 KB and lands in LDS as it lies in
-// memory, 8 / NW KB per wavefront (NW wavefronts share a tile) in copies of 1 KB; `left` < 64: rows past the end
-// re-read the last valid row.
+// memory, 8 / NW KB per wavefront (NW wavefronts share a tile) in copies of 1 KB.
 constexpr int RAW8_ROW_BYTES = 128;
 constexpr int RAW8_BYTES = ROWS * RAW8_ROW_BYTES;
 template <int NW = 4>
 __device__ __forceinline__ void issue_raw8(unsigned lds_tile, int wave, int lane, int left, const char* src) {
-  constexpr int PER_WAVE = RAW8_BYTES / NW;  // bytes of the tile this wavefront copies
-  if (left >= ROWS) {
+  const Descriptor tile = tile_descriptor<RAW8_ROW_BYTES>(src, left);
 #pragma unroll
-    for (int j = 0; j < PER_WAVE / 1024; ++j)
-      copy_1k(lds_tile + wave * PER_WAVE + j * 1024, lane * 16, src + wave * PER_WAVE + j * 1024);
-  } else {
-#pragma unroll
-    for (int j = 0; j < PER_WAVE / 1024; ++j) {
-      const int row = (ROWS / NW) * wave + 8 * j + (lane >> 3);
-      const int rr = row < left ? row : left - 1;
-      copy_1k_ragged(lds_tile + wave * PER_WAVE + j * 1024, rr * RAW8_ROW_BYTES + (lane & 7) * 16, src);
-    }
-  }
+  for (int j = 0; j < RAW8_BYTES / (1024 * NW); ++j)
+    copy_1k_checked(lds_tile + (NW * j + wave) * 1024, wave * 1024 + lane * 16, tile, j * (1024 * NW));
 }
 // Turns a landed 8-bit tile (`raw`, LDS) into the bf16 tile format at `stage` (LDS): NT lanes, 1024 / NT groups of
 // eight codes each; every E4M3 value is a bf16 value, so the conversion is exact.  SWZ_V selects the V swizzle.

@@ -743,3 +743,11 @@ def test_fp32_calibration_at_the_edges_of_its_tiles(d, H, sides):
                 # fp32 sums of t * c probabilities: far inside the 1e-4 that masses are held to
                 assert np.abs(got[b, h, :k1 + 1] - want[1:k1 + 2]).max() <= 1e-5, (k1, b, h)
                 assert not got[b, h, k1 + 1:].any()
+
+
+@pytest.mark.parametrize("d,H,batch", [(128, 3, 1), (64, 5, 2)])
+def test_bf16_tiles_end_where_the_valid_rows_end(d, H, batch):
+    # Range-checked tile copies: scales of 1, 63, 64, 65, 127 and 129 tokens as current scale and as the last piece of a
+    # run (full budget, so every run ends with one of them), the last head's rows at the very end of every tensor; fused
+    # = separate bit for bit.
+    _bf16_case(1, H, ((1, 1), (7, 9), (8, 8), (5, 13), (1, 127), (3, 43)), 1, 1, batch, seed=33, fused=True, d=d)

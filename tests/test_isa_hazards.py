@@ -43,7 +43,7 @@ def scan(asm_text):
             continue
         toks = line.split()
         op, args = toks[0], toks[1:]
-        if op.startswith("global_load_lds"):
+        if op.startswith("global_load_lds") or (op.startswith("buffer_load") and "lds" in args):
             copies += 1
             base = set()
             for a in args:
@@ -92,6 +92,14 @@ def test_scanner_sees_a_planted_stale_address_and_a_planted_m0_hazard():
     n, hz = scan(m0)
     assert n == 1 and len(hz) == 1 and "M0" in hz[0]
     assert scan(m0.replace("global_load_lds", "s_mov_b64 s[6:7], s[4:5]\n    global_load_lds")) == (1, [])
+    checked = """
+    v_readlane_b32 s9, v255, 4
+    s_mov_b32 m0, s11
+    buffer_load_dwordx4 v2, s[8:11], s12 offen lds
+    """
+    n, hz = scan(checked)
+    assert n == 1 and len(hz) == 2 and "s9" in hz[0] and "M0" in hz[1]
+    assert scan(checked.replace("buffer_load", "s_nop 4\n    buffer_load")) == (1, [])
 
 
 def test_no_tile_copy_reads_a_stale_scalar_or_a_fresh_m0():
