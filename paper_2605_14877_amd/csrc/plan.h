@@ -3,8 +3,10 @@
 #pragma once
 
 #include <cstdint>
+#include <memory>
 #include <mutex>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "heatkv.h"
@@ -28,6 +30,21 @@ struct HeadWork {
   int32_t run_row;  // first arena row of the head's run (per batch entry)
   int32_t run_len;  // retained prior tokens
   int32_t pad;
+};
+
+// Vector storage that is not cleared on resize, for a table that is written in one go.
+template <class T>
+struct UnclearedAllocator : std::allocator<T> {
+  template <class U>
+  struct rebind {
+    using other = UnclearedAllocator<U>;
+  };
+  template <class U>
+  void construct(U*) {}
+  template <class U, class... Args>
+  void construct(U* p, Args&&... args) {
+    ::new (static_cast<void*>(p)) U(std::forward<Args>(args)...);
+  }
 };
 
 struct DeviceTables {
@@ -65,7 +82,7 @@ struct heatkv_plan {
   std::vector<int32_t> max_len;      // [K][L] longest run
   int64_t arena_tokens = 0;
 
-  std::vector<heatkv::CopyDesc> descs;
+  std::vector<heatkv::CopyDesc, heatkv::UnclearedAllocator<heatkv::CopyDesc>> descs;
   std::vector<int64_t> desc_begin;  // [K][L] index into descs
   std::vector<int32_t> desc_count;  // [K][L]
 
