@@ -71,10 +71,8 @@ __device__ __forceinline__ int scale_of_block(const CalibParams& p, int block) {
 // of the tile) and runs both against each K operand it has read from LDS, so a K
 // tile is copied and read once per 256 queries and the matrix-core work of one set
 // overlaps the exponentials of the other inside the wavefront; two workgroups per
-// compute unit.  On a full chip the two are equally fast (two wavefronts per SIMD
-// with twice the independent work against three); the launcher takes the second
-// when its workgroups fill their 512 slots at least once, which then needs fewer,
-// longer workgroups and ends with a shorter tail.
+// compute unit.  The launcher takes the second when its workgroups fill their 512
+// slots at least once.
 // ---------------------------------------------------------------------------
 constexpr int CBM1 = 128;  // queries per set of four wavefronts
 constexpr int CBN = tile::ROWS;
@@ -152,6 +150,46 @@ __global__ __launch_bounds__(256, CSETS == 1 ? 3 : 2) void calibrate_bf16_kernel
   }
   int k2 = 0, tile = 0;  // the tile being computed
 
+  // Adds a tile's probabilities (rs: four partial sums of this lane's 32, relative to m_run) to the block's sum.
+  // Probabilities are taken relative to the running reference m_run, which is only brought up to the true
+  // row maximum when it has fallen too far behind: as long as no score exceeds it by more than 8 in the
+  // base-2 exponent a lane's 32 probabilities of the tile sum to at most 2^13, so a larger sum, an infinity
+  // or a NaN (the first tile, where m_run is still -inf) sends the whole wavefront through the exact path,
+  // which finds the tile maximum, rescales what the block has summed so far and redoes the tile's
+  // exponentials.  The masses are ratios of such sums, so they do not depend on the reference; the max
+  // chain, one vector instruction per two scores, leaves the common path.
+  auto fold = [&](int qs, const f32x16 (&s)[2], float (&rs)[4], int block, bool last_of_block) {
+    float tile_sum = (rs[0] + rs[1]) + (rs[2] + rs[3]);
+    if (__any(!(tile_sum <= 8192.f))) {
+      float mx = s[0][0];
+#pragma unroll
+      for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[cb][r]);
+      mx = max_halves(mx);
+      const float m_new = fmaxf(m_run[qs], mx);
+      cur[qs] *= fast_exp2((m_run[qs] - m_new) * c);
+      m_run[qs] = m_new;
+      const float mc = m_new * c;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) rs[i] = 0.f;
+#pragma unroll
+      for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) rs[r & 3] += fast_exp2(fmaf(s[cb][r], c, -mc));
+      tile_sum = (rs[0] + rs[1]) + (rs[2] + rs[3]);
+    }
+    cur[qs] += tile_sum;
+    if (last_of_block) {
+      const float both = sum_halves(cur[qs]);
+      if (hl == 0) {
+        blk_sum[block * CBM + qs * 128 + wave * 32 + n] = both;
+        blk_max[block * CBM + qs * 128 + wave * 32 + n] = m_run[qs];
+      }
+      cur[qs] = 0.f;
+    }
+  };
+
   auto tile_step = [&](auto buf_tag) {
     constexpr int buf = decltype(buf_tag)::value;
     // successor of (k2, tile) in block-major order
@@ -195,60 +233,188 @@ __global__ __launch_bounds__(256, CSETS == 1 ? 3 : 2) void calibrate_bf16_kernel
           for (int r = 0; r < 16; ++r)
             if (32 * cb + 8 * (r >> 2) + 4 * hl + (r & 3) >= left) s[cb][r] = -INFINITY;
       }
-      // Probabilities are taken relative to the running reference m_run, which is only brought up to the true
-      // row maximum when it has fallen too far behind: as long as no score exceeds it by more than 8 in the
-      // base-2 exponent a lane's 32 probabilities of the tile sum to at most 2^13, so a larger sum, an infinity
-      // or a NaN (the first tile, where m_run is still -inf) sends the whole wavefront through the exact path,
-      // which finds the tile maximum, rescales what the block has summed so far and redoes the tile's
-      // exponentials.  The masses are ratios of such sums, so they do not depend on the reference; the max
-      // chain, one vector instruction per two scores, leaves the common path.
-      float mc = m_run[qs] * c;
+      const float mc = m_run[qs] * c;
       float rs[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int cb = 0; cb < 2; ++cb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) rs[r & 3] += fast_exp2(fmaf(s[cb][r], c, -mc));
-      float tile_sum = (rs[0] + rs[1]) + (rs[2] + rs[3]);
-      if (__any(!(tile_sum <= 8192.f))) {
-        float mx = s[0][0];
-#pragma unroll
-        for (int cb = 0; cb < 2; ++cb)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[cb][r]);
-        mx = max_halves(mx);
-        const float m_new = fmaxf(m_run[qs], mx);
-        cur[qs] *= fast_exp2((m_run[qs] - m_new) * c);
-        m_run[qs] = m_new;
-        mc = m_new * c;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) rs[i] = 0.f;
-#pragma unroll
-        for (int cb = 0; cb < 2; ++cb)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) rs[r & 3] += fast_exp2(fmaf(s[cb][r], c, -mc));
-        tile_sum = (rs[0] + rs[1]) + (rs[2] + rs[3]);
-      }
-      cur[qs] += tile_sum;
-
-      if (last_of_block) {
-        const float both = sum_halves(cur[qs]);
-        if (hl == 0) {
-          blk_sum[k2 * CBM + qs * 128 + wave * 32 + n] = both;
-          blk_max[k2 * CBM + qs * 128 + wave * 32 + n] = m_run[qs];
-        }
-        cur[qs] = 0.f;
-      }
+      fold(qs, s, rs, k2, last_of_block);
     }
     k2 = nk2;
     tile = ntile;
   };
 
-  issue_tile(0, 0, 0);
-  while (true) {
-    tile_step(std::integral_constant<int, 0>{});
-    if (k2 > k1) break;
-    tile_step(std::integral_constant<int, 1>{});
-    if (k2 > k1) break;
+  // The walk of the two-set instance, issue order fixed by hand.  Per tile two phases of 2 NK slots, one MFMA each:
+  //   A: scores of set 0; in its slots the exponentials of set 1 of the tile before
+  //   B: scores of set 1; in its slots the exponentials of set 0, the K operands of the next tile (each into the
+  //      registers that its MFMA has just read) and the copies of the tile after that
+  // The barrier stands between A and B: by then every wavefront has this tile's operands in registers, so its stage is
+  // free for the copies, and the next tile, copied during the phase B before, has landed.  No operand read stands
+  // between a barrier and the MFMAs that need it.
+  // Bound: the vector ALU (three instructions per score, busy 78 % of the time that wavefronts are resident) next to the
+  // matrix pipes (63 %), at the 1.8 GHz that this mix leaves.  All 13 scales of a 2B-like layer (16 heads, batch 2): 558
+  // -> 531 us, 1.06 PFLOP/s.  Exponent, exponential and sum of a probability in three successive slots: no faster.
+  auto two_set_walk = [&](auto two_tag) {
+    constexpr bool kTwo = decltype(two_tag)::value;  // a last tile of at most 128 rows has no set 1
+    struct Tile {
+      int k2, left;  // block, rows from the tile's first one to the block's end; left = 0: past the walk's end
+    };
+    const char* kb = kbase;  // first row of the tile that is fetched next
+    Tile next{0, p.t[0]};    // that tile
+    auto advance = [&] {     // sizes of blocks are read only when the walk enters one
+      if (next.left > CBN) {
+        kb += CTILE_BYTES;
+        next.left -= CBN;
+      } else {
+        kb += static_cast<long long>(next.left) * CROW_BYTES;
+        ++next.k2;
+        next.left = next.k2 <= k1 ? p.t[next.k2] : 0;
+      }
+    };
+    constexpr int CPT = CTILE_BYTES / 4096;  // copies of a tile per wavefront
+    auto copy = [&](const tile::Descriptor& src, int buf, int i) {
+      tile::copy_1k_checked(lds_base + buf * CTILE_BYTES + wave * 1024 + i * 4096, ld_off, src, i * 4096);
+    };
+    auto fence = [] { __builtin_amdgcn_sched_barrier(0); };
+    auto mask_tail = [&](int left, f32x16 (&s)[2]) {
+      if (left >= CBN) return;
+      int lim = left - 4 * hl;
+      asm volatile("; ragged tile mask" : "+v"(lim)::"memory");
+#pragma unroll
+      for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (32 * cb + 8 * (r >> 2) + (r & 3) >= lim) s[cb][r] = -INFINITY;
+    };
+    auto load_k = [&](bf16x8& dst, int buf, int cb, int ks) {
+      dst = *reinterpret_cast<const bf16x8*>(lds + buf * CTILE_BYTES + cb * 32 * CROW_BYTES + k_off[ks]);
+    };
+    bf16x8 ka[2][NK];
+    f32x16 s[2][2];  // [set][block of 32 keys]
+    float rs[4];
+    // Slot i's share of set qs's probabilities, summed in the order of the exact path.
+    constexpr int PER_SLOT = 16 / NK;
+    auto exps = [&](int qs, float mc, int i) {
+#pragma unroll
+      for (int u = 0; u < PER_SLOT; ++u) {
+        const int r = i * PER_SLOT + u;
+        rs[r & 3] += fast_exp2(fmaf(s[qs][r >> 4][r & 15], c, -mc));
+      }
+    };
+    auto settle = [&](int qs, const Tile& t) { fold(qs, s[qs], rs, t.k2, t.left <= CBN); };
+
+    Tile now = next;
+    const tile::Descriptor d0 = tile::tile_descriptor<CROW_BYTES>(kb, next.left);
+    advance();
+    const tile::Descriptor d1 = tile::tile_descriptor<CROW_BYTES>(kb, next.left);
+    Tile ahead = next;
+    advance();
+#pragma unroll
+    for (int i = 0; i < CPT; ++i) copy(d0, 0, i);
+#pragma unroll
+    for (int i = 0; i < CPT; ++i) copy(d1, 1, i);
+    wait_vmcnt<CPT>();
+    __syncthreads();
+#pragma unroll
+    for (int ks = 0; ks < NK; ++ks)
+#pragma unroll
+      for (int cb = 0; cb < 2; ++cb) load_k(ka[cb][ks], 0, cb, ks);
+    Tile before{0, 0};  // the tile whose set 1 is still to be summed
+    auto step = [&](auto buf_tag, auto first_tag) {
+      constexpr int buf = decltype(buf_tag)::value;
+#pragma unroll
+      for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s[0][cb][r] = 0.f;
+      const float mc1 = m_run[1] * c;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) rs[i] = 0.f;
+      fence();
+      if constexpr (kTwo && !decltype(first_tag)::value) {
+#pragma unroll
+        for (int i = 0; i < 2 * NK; ++i) {
+          s[0][i & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[i & 1][i >> 1], qreg[0][i >> 1], s[0][i & 1], 0, 0, 0);
+          fence();
+          exps(1, mc1, i);
+          fence();
+        }
+        settle(1, before);
+      } else {
+#pragma unroll
+        for (int i = 0; i < 2 * NK; ++i)
+          s[0][i & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[i & 1][i >> 1], qreg[0][i >> 1], s[0][i & 1], 0, 0, 0);
+      }
+      const tile::Descriptor src = tile::tile_descriptor<CROW_BYTES>(kb, next.left);
+      wait_vmcnt<0>();
+      __syncthreads();
+      mask_tail(now.left, s[0]);
+      const float mc0 = m_run[0] * c;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) rs[i] = 0.f;
+#pragma unroll
+      for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s[1][cb][r] = 0.f;
+      fence();
+      if constexpr (kTwo) {
+#pragma unroll
+        for (int i = 0; i < 2 * NK; ++i) {
+          s[1][i & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[i & 1][i >> 1], qreg[1][i >> 1], s[1][i & 1], 0, 0, 0);
+          fence();
+          load_k(ka[i & 1][i >> 1], buf ^ 1, i & 1, i >> 1);
+          if (i < CPT) copy(src, buf, i);
+          exps(0, mc0, i);
+          fence();
+        }
+        settle(0, now);
+        mask_tail(now.left, s[1]);
+      } else {
+#pragma unroll
+        for (int i = 0; i < 2 * NK; ++i) {
+          load_k(ka[i & 1][i >> 1], buf ^ 1, i & 1, i >> 1);
+          if (i < CPT) copy(src, buf, i);
+          exps(0, mc0, i);
+        }
+        settle(0, now);
+      }
+      before = now;
+      now = ahead;
+      ahead = next;
+      advance();
+    };
+    using Even = std::integral_constant<int, 0>;
+    using Odd = std::integral_constant<int, 1>;
+    step(Even{}, std::true_type{});
+    while (now.left > 0) {
+      step(Odd{}, std::false_type{});
+      if (now.left == 0) break;
+      step(Even{}, std::false_type{});
+    }
+    if constexpr (kTwo) {
+      const float mc1 = m_run[1] * c;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) rs[i] = 0.f;
+#pragma unroll
+      for (int i = 0; i < 2 * NK; ++i) exps(1, mc1, i);
+      settle(1, before);
+    }
+    wait_vmcnt<0>();  // the copies past the end (no rows: zeros) land before the workgroup ends
+  };
+
+  if constexpr (CSETS == 2) {
+    if (two_sets)
+      two_set_walk(std::true_type{});
+    else
+      two_set_walk(std::false_type{});
+  } else {
+    issue_tile(0, 0, 0);
+    while (true) {
+      tile_step(std::integral_constant<int, 0>{});
+      if (k2 > k1) break;
+      tile_step(std::integral_constant<int, 1>{});
+      if (k2 > k1) break;
+    }
   }
   if (hl == 0) {
 #pragma unroll

@@ -751,3 +751,38 @@ def test_bf16_tiles_end_where_the_valid_rows_end(d, H, batch):
     # run (full budget, so every run ends with one of them), the last head's rows at the very end of every tensor; fused
     # = separate bit for bit.
     _bf16_case(1, H, ((1, 1), (7, 9), (8, 8), (5, 13), (1, 127), (3, 43)), 1, 1, batch, seed=33, fused=True, d=d)
+
+
+@pytest.mark.parametrize("d,tokens", [
+    (128, (1, 64, 65, 128, 129, 257)),     # whole tiles, one row more, last query tiles with and without a second set
+    (64, (3, 63, 64, 127, 130, 200, 383)),
+])
+def test_bf16_calibration_with_two_query_sets_at_the_edges_of_its_tiles(d, tokens):
+    # One launch over all scales takes the instance with two query sets per wavefront (at least 512 workgroups), the
+    # calls per scale the one with a single set: same bits.  Keys grow by the row, so that references keep rising.
+    K, H, batch = len(tokens), 32, 4
+    c = hi.cumulative_tokens(tokens)
+    sm = 1.0 / np.sqrt(d)
+    assert sum((t + 255) // 256 for t in tokens) * H * batch >= 512 and H * batch < 512 // 2
+    g = torch.Generator().manual_seed(47)
+    q = torch.randn(batch, H, c[-1], d, generator=g).to(torch.bfloat16)
+    k = (torch.randn(batch, H, c[-1], d, generator=g) * torch.linspace(0.5, 6, c[-1])[:, None]).to(torch.bfloat16)
+    dq, dk = _dev(q, k)
+    shape = hk.Shape(1, H, d, tokens, batch, "bf16")
+    qs = [dq[:, :, c[i] - tokens[i]:c[i]].contiguous() for i in range(K)]
+    ks = [dk[:, :, :c[i]].contiguous() for i in range(K)]
+    mass_a, mass_b = ([torch.empty(batch, H, K, device="cuda") for _ in range(K)] for _ in range(2))
+    for i in range(K):
+        ws = torch.empty(max(hk.binding.calibrate_workspace_bytes(shape, i), 4), dtype=torch.uint8, device="cuda")
+        hk.heatkv_calibrate(shape, 0, i, qs[i], ks[i], sm, mass_a[i], ws)
+    ws = torch.empty(hk.binding.calibrate_scales_workspace_bytes(shape, list(range(K))), dtype=torch.uint8, device="cuda")
+    beta = torch.zeros(1, H, K, K, device="cuda")
+    hk.heatkv_calibrate_scales_accumulate(shape, 0, list(range(K)), qs, ks, sm, 0.25, beta, mass_b, ws)
+    torch.cuda.synchronize()
+    for i in range(K):
+        assert torch.equal(mass_a[i], mass_b[i]), i
+    t1 = orc.one_based(tokens)
+    for b, h, i in ((0, 0, K - 1), (3, 31, 4), (2, 7, 1)):
+        end = c[i]
+        want = orc.beta_row(q[b, h, :end].double().numpy(), k[b, h, :end].double().numpy(), t1, i + 1, sm)[1:]
+        assert np.abs(mass_b[i][b, h].cpu().double().numpy() - want).max() <= 1e-4
