@@ -753,6 +753,17 @@ def test_bf16_tiles_end_where_the_valid_rows_end(d, H, batch):
     _bf16_case(1, H, ((1, 1), (7, 9), (8, 8), (5, 13), (1, 127), (3, 43)), 1, 1, batch, seed=33, fused=True, d=d)
 
 
+@pytest.mark.parametrize("d,H,batch,tokens", [
+    # Runs of all earlier tokens (full budget): 3 + 1 and 60 + 4 keys in one tile, 70 + 64 (the run ends with a tile),
+    # 122 + 134 (58 + 6 rows share a tile, two tiles of the run remain), 129 + 256, 447 + 385 (63 + 1, two key streams)
+    (128, 3, 1, (1, 3, 60, 70, 122, 129, 447)),
+    # 33 + 30 keys: 63 of a tile; 65 + 63: 1 + 63; 129 + 128; 190 + 257: 62 + 2, 255 remain; 195 + 447: 3 + 63 do not fit
+    (64, 5, 2, (1, 5, 9, 15, 33, 65, 129, 190, 195)),
+])
+def test_bf16_ragged_ends_of_scale_and_run_share_a_tile(d, H, batch, tokens):
+    _bf16_case(1, H, tuple((1, n) for n in tokens), 1, 1, batch, seed=34, fused=True, d=d)
+
+
 @pytest.mark.parametrize("d,tokens", [
     (128, (1, 64, 65, 128, 129, 257)),     # whole tiles, one row more, last query tiles with and without a second set
     (64, (3, 63, 64, 127, 130, 200, 383)),
