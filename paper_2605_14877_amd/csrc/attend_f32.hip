@@ -102,9 +102,10 @@ __global__ __launch_bounds__(64 * NW) void attend_f32_kernel(AttendParams p) {
 #pragma unroll
   for (int i = 0; i < NB; ++i) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
   // Scores in base-2 exponents.  The reference m of a query is common to its four lanes and only raised when a score
-  // exceeds it by more than 8: probabilities stay at most 2^8 and the accumulators are rescaled a few times per row.
+  // exceeds it by more than 8: probabilities stay at most 2^8 and the accumulators are rescaled a few times per row.  It
+  // starts finite: a row whose first tiles hold scores of -inf only (keys masked by their values) is not NaN for that.
   const float c = p.sm_scale * kLog2e;
-  float m = -INFINITY, l = 0.f;
+  float m = kLowest, l = 0.f;
 
   for (int it = wave; it < tiles_all; it += NW) {
     const Tile t = tile_of(it);
@@ -146,7 +147,7 @@ __global__ __launch_bounds__(64 * NW) void attend_f32_kernel(AttendParams p) {
   }
 
   // Merge: every wavefront brings its accumulators to the common reference and divides by the common row sum; the
-  // parked tiles are then added in wavefront order.  A wavefront without a tile has reference -inf: factor 0.
+  // parked tiles are then added in wavefront order.  A wavefront without a tile has the lowest reference: factor 0.
   __syncthreads();  // every wavefront has taken its last tile
   l = f32m::sum_groups(l);
   if (g == 0) {

@@ -463,7 +463,6 @@ __global__ __launch_bounds__(256, CSETS == 1 ? 3 : 2) void calibrate_bf16_kernel
 // ---------------------------------------------------------------------------
 constexpr int FQ = f32m::TILE;
 constexpr int FW = 4;           // wavefronts of a workgroup
-constexpr float LOWEST = -3e38f;  // below any score; finite, so that differences of references are never NaN
 
 template <int D>
 __global__ __launch_bounds__(64 * FW) void calibrate_f32_kernel(CalibParams p) {
@@ -510,12 +509,12 @@ __global__ __launch_bounds__(64 * FW) void calibrate_f32_kernel(CalibParams p) {
   for (int j = 0; j <= k1; ++j)  // blocks without a tile of this wavefront
     if (g == 0) {
       blk_sum[j][wave][n] = 0.f;
-      blk_max[j][wave][n] = LOWEST;
+      blk_max[j][wave][n] = kLowest;
     }
   enter(wave);
   if (k2 <= k1) fetch();
   const float c = p.sm_scale * kLog2e;
-  float m = LOWEST, cur = 0.f;
+  float m = kLowest, cur = 0.f;
   while (k2 <= k1) {
     const int here = k2, rows = rows_left;
     Stage::take(k, stages[wave], lane);

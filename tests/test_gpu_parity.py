@@ -797,3 +797,24 @@ def test_bf16_calibration_with_two_query_sets_at_the_edges_of_its_tiles(d, token
         end = c[i]
         want = orc.beta_row(q[b, h, :end].double().numpy(), k[b, h, :end].double().numpy(), t1, i + 1, sm)[1:]
         assert np.abs(mass_b[i][b, h].cpu().double().numpy() - want).max() <= 1e-4
+
+
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 128), ("bf16", 64), ("bf16", 128)])
+@pytest.mark.parametrize("masked", ["first tiles", "shared ragged tile"])
+def test_keys_masked_by_their_values(dtype, d, masked):
+    # Keys of -inf in a component where the queries are 1: scores of -inf, probability 0.  Masked are all keys that the
+    # walk meets first (fp32: the first tile of each wavefront; bf16: the tile that the ragged ends share), never all.
+    t0, H, nb = [1, 3, 60, 70, 122], 3, 2
+    c, K, sm = hi.cumulative_tokens(t0), 5, 1.0 / np.sqrt(d)
+    cfg = dict(L=1, H=H, d=d, dtype=dtype, batch=nb, sides=[(1, n) for n in t0])
+    w = hi.head_weights(41, 1, H, K)
+    q, k, v = hi.make_qkv(41, 0, cfg, w=w)
+    plan = hk.heatkv_build_schedule(hk.Shape(1, H, d, t0, nb, dtype), hi.expected_beta_from_weights(w, t0).astype(np.float32),
+                                    H * c[-2] * 2 * d * hi.elem_bytes(dtype), 1)
+    q[..., 0] = 1.0
+    keys = range(c[3], c[3] + 64) if masked == "first tiles" else [*range(6), *range(c[3] + 64, c[4])]
+    k[:, :, list(keys), 0] = float("-inf")
+    got = device_generation(plan, 0, *_dev(q, k, v), t0, sm)[-1].double().cpu()
+    s = q[:, :, c[3]:].double() @ k.double().transpose(-1, -2) * sm
+    want = torch.softmax(s, -1) @ v.double()
+    assert (got - want).abs().max() <= TOL[dtype]
