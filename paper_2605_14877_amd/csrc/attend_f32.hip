@@ -126,7 +126,11 @@ __global__ __launch_bounds__(64 * NW) void attend_f32_kernel(AttendParams p) {
     if (t.rows < T) {
 #pragma unroll
       for (int r = 0; r < 4; ++r)
-        if (4 * g + r >= t.rows) s[r] = -INFINITY;
+        if (4 * g + r >= t.rows) {  // V too: these lanes hold the last valid row again, and 0 x inf is NaN
+          s[r] = -INFINITY;
+#pragma unroll
+          for (int j = 0; j < NB / 4; ++j) v[r][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
     }
     const float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
     if (__any(mx > m + 8.f)) {

@@ -818,3 +818,18 @@ def test_keys_masked_by_their_values(dtype, d, masked):
     s = q[:, :, c[3]:].double() @ k.double().transpose(-1, -2) * sm
     want = torch.softmax(s, -1) @ v.double()
     assert (got - want).abs().max() <= TOL[dtype]
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_fp32_infinite_value_in_the_last_row_of_a_ragged_tile(d):
+    # 122 keys end inside a tile of 16: the lanes past the end must not turn the infinity into NaN.
+    t0, H = [1, 4, 122], 2
+    cfg = dict(L=1, H=H, d=d, dtype="f32", batch=1, sides=[(1, n) for n in t0])
+    w = hi.head_weights(42, 1, H, 3)
+    q, k, v = hi.make_qkv(42, 0, cfg, w=w)
+    v[:, :, -1, 5] = float("inf")
+    plan = hk.heatkv_build_schedule(hk.Shape(1, H, d, t0, 1, "f32"), hi.expected_beta_from_weights(w, t0).astype(np.float32),
+                                    H * 5 * 2 * d * 4, 1)
+    got = device_generation(plan, 0, *_dev(q, k, v), t0, 1.0 / np.sqrt(d))[-1].cpu()
+    assert (got[..., 5] == float("inf")).all()
+    assert torch.isfinite(torch.cat([got[..., :5], got[..., 6:]], -1)).all()
