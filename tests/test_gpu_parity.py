@@ -833,3 +833,29 @@ def test_fp32_infinite_value_in_the_last_row_of_a_ragged_tile(d):
     got = device_generation(plan, 0, *_dev(q, k, v), t0, 1.0 / np.sqrt(d))[-1].cpu()
     assert (got[..., 5] == float("inf")).all()
     assert torch.isfinite(torch.cat([got[..., :5], got[..., 6:]], -1)).all()
+
+
+@pytest.mark.parametrize("dtype,fp8", [("bf16", False), ("bf16", True), ("f32", False)])
+def test_cache_update_with_several_workgroups_per_descriptor(dtype, fp8):
+    # The update's own launch puts four workgroups on a descriptor, the fused one does not; same arenas.
+    # Descriptors of 1, 3, 60, 65, 128 and 72 rows: no whole group of chunks, one and a remainder, whole groups only.
+    t0, H, nb, d = [1, 3, 60, 65, 200, 9], 4, 3, 128
+    c, K, sm = hi.cumulative_tokens(t0), 6, 1.0 / np.sqrt(d)
+    cfg = dict(L=1, H=H, d=d, dtype=dtype, batch=nb, sides=[(1, n) for n in t0])
+    w = hi.head_weights(43, 1, H, K)
+    plan = hk.heatkv_build_schedule(hk.Shape(1, H, d, t0, nb, dtype), hi.expected_beta_from_weights(w, t0).astype(np.float32),
+                                    H * c[-2] * 2 * d * (1 if fp8 else hi.elem_bytes(dtype)), 1, hk.VARIANT_HEATKV,
+                                    hk.KV_FP8_E4M3 if fp8 else hk.KV_NATIVE)
+    dq = hi.make_qkv_device(43, 0, cfg, w, torch.device("cuda:0"))
+    arenas = []
+    for fused in (False, True):
+        ka, va = (torch.zeros(plan.arena_bytes, dtype=torch.uint8, device="cuda") for _ in range(2))
+        for kk in range(K):
+            q, k, v = (x[:, :, c[kk] - t0[kk]:c[kk]].contiguous() for x in dq)
+            if fused:
+                hk.heatkv_attend_append_scale(plan, 0, kk, q, k, v, ka, va, sm, torch.empty_like(q))
+            else:
+                hk.heatkv_append_scale(plan, 0, kk, k, v, ka, va)
+        arenas.append((ka, va))
+    assert torch.equal(arenas[0][0], arenas[1][0]) and torch.equal(arenas[0][1], arenas[1][1])
+    assert arenas[0][0].any() and arenas[0][1].any()
