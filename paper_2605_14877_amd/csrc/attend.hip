@@ -26,8 +26,7 @@ namespace {
 // keys of a head are walked in 64-row tiles, first the current scale (dense
 // tensor), then the head's retained run in the arena (attention does not depend
 // on key order, and each segment is then one contiguous range, so a tile's
-// addresses are a wavefront-uniform base plus a fixed per-lane offset; the
-// segments' ragged ends may share the first tile).
+// addresses are a wavefront-uniform base plus a fixed per-lane offset).
 //
 // Tiles go from HBM straight into LDS (buffer_load .. lds, no registers, no LDS
 // store instructions), double-buffered with one barrier per tile; the descriptor's
@@ -155,27 +154,6 @@ __global__ __launch_bounds__(256 * KS * QS, (KS == 1 && QS == 1) ? 2 : 1) void a
 
   // Tile schedule: tiles [0, tiles_cur) cover the current scale, the rest the retained run.
   const int tiles_cur = (t_k + BN - 1) / BN;
-  // Where that saves a tile, the ragged ends of the two segments share one: tile 0 then holds the current scale's last
-  // t_k % 64 rows followed by the run's first ones (issue_shared), tiles 1 .. tiles_cur - 1 the full tiles of the current
-  // scale, the rest the run from there on.  A step of a short walk is latency (about 1 us, next to 4 of start-up), so
-  // this pays whenever a tile is saved: scales whose keys fit one tile 5.6 -> 4.6 us (d = 128, up to 36 + 21 keys,
-  // batch 2) and 4.8 -> 4.0 (d = 64), 100 + 91 keys at d = 64, 256 pairs 9.6 -> 9.2; longer ragged walks lose half a
-  // tile on average.  Not with 8-bit cache rows (tile 0 has to be a bf16 tile), nor with two query sets (walks of at
-  // least 16 tiles, and the compiler has few scalar registers left there).
-  int t_walk = t_k, shared_cur = 0, shared_run = 0;  // rows of the shared tile from either segment
-  if constexpr (!FP8 && QS == 1) {
-    const int rem = t_k & (BN - 1), rem_run = n_prior & (BN - 1);
-    if (rem > 0 && rem_run > 0 && rem + rem_run <= BN) {
-      shared_cur = rem;
-      shared_run = n_prior < BN - rem ? n_prior : BN - rem;
-      t_walk = tiles_cur * BN;  // as if the current scale's full tiles began at row 64
-      k_cur -= TILE_BYTES;
-      v_cur -= TILE_BYTES;
-      k_prior += shared_run * ROW_BYTES;
-      v_prior += shared_run * ROW_BYTES;
-      n_prior -= shared_run;
-    }
-  }
   const int tiles_all = tiles_cur + (n_prior + BN - 1) / BN;
   // Step j of stream g works on tile KS j + g; all streams make steps_all steps (the barriers are shared), a
   // stream whose last step has no tile sits it out.
@@ -224,7 +202,7 @@ __global__ __launch_bounds__(256 * KS * QS, (KS == 1 && QS == 1) ? 2 : 1) void a
     const int it = KS * j + g;
     const bool prior = it >= tiles_cur;
     const int local = prior ? it - tiles_cur : it;
-    return TileSpan{prior, local, (prior ? n_prior : t_walk) - local * BN};
+    return TileSpan{prior, local, (prior ? n_prior : t_k) - local * BN};
   };
   auto source = [&](int j, const char* cur, const char* prior) {
     const TileSpan t = span_of(j);
@@ -287,34 +265,6 @@ __global__ __launch_bounds__(256 * KS * QS, (KS == 1 && QS == 1) ? 2 : 1) void a
     for (int i = 0; i < CPT; ++i) copy_v(src, buf, i);
   };
 
-  // The shared tile 0 into stage 0: every lane copies its chunk of a row from the segment that the row belongs to.  `cur`
-  // and `prior` point where the walk's tile 1 and its first prior tile begin; rows past both segments land as zeros.
-  auto issue_shared = [&](const char* cur, const char* prior, unsigned stage, int ld_off) {
-    const tile::Descriptor c_src = tile::tile_descriptor<ROW_BYTES>(cur + static_cast<long long>(tiles_cur) * TILE_BYTES, shared_cur);
-    const tile::Descriptor p_src =
-        tile::tile_descriptor<ROW_BYTES>(prior - static_cast<long long>(shared_cur + shared_run) * ROW_BYTES, shared_cur + shared_run);
-#pragma unroll
-    for (int i = 0; i < CPT; ++i) {
-      const unsigned dst = stage + lw * 1024 + i * (1024 * NW);
-      if (ld_off + i * (1024 * NW) < shared_cur * ROW_BYTES)
-        tile::copy_1k_checked(dst, ld_off, c_src, i * (1024 * NW));
-      else
-        tile::copy_1k_checked(dst, ld_off, p_src, i * (1024 * NW));
-    }
-  };
-  auto issue_first_k = [&] {
-    if (shared_cur > 0 && g == 0)
-      issue_shared(k_cur, k_prior, lds_base, ld_off_k);
-    else
-      issue_k(0, 0);
-  };
-  auto issue_first_v = [&] {
-    if (shared_cur > 0 && g == 0)
-      issue_shared(v_cur, v_prior, lds_base + TILE_BYTES, ld_off_v);
-    else
-      issue_v(0, 0);
-  };
-
   // S^T = K Q^T for the 64 keys of the K tile in buffer `buf` x this wavefront's 32 queries.
   // s[cb][r] is key 32*cb + 8*(r/4) + 4*hl + r%4 of the tile, query column n.
   auto scores = [&](f32x16 (&s)[2], auto buf_tag) {
@@ -371,9 +321,9 @@ __global__ __launch_bounds__(256 * KS * QS, (KS == 1 && QS == 1) ? 2 : 1) void a
         if (32 * cb + 8 * (r >> 2) + (r & 3) >= lim) s[cb][r] = -INFINITY;
     return true;
   };
-  // Masks the tail of the first tile and folds its row maxima into the running reference.
-  auto settle_first = [&](f32x16 (&s)[2]) {
-    mask_tail(shared_cur > 0 && g == 0 ? shared_cur + shared_run : span_of(0).left, s);
+  // Masks the tail of tile j and folds its row maxima into the running reference.
+  auto settle = [&](int j, f32x16 (&s)[2]) {
+    mask_tail(span_of(j).left, s);
     raise(lane_max(s));
   };
   // P^T = 2^(S^T c - m c) in bf16, 16 keys at a time, each chunk feeding O^T += V^T P^T at once.  The row
@@ -588,11 +538,11 @@ __global__ __launch_bounds__(256 * KS * QS, (KS == 1 && QS == 1) ? 2 : 1) void a
   // Prologue: all four tile stages are free, so K(0), V(0), K(1) and V(1) all go out at once: one memory round
   // trip before the loop, and a walk of two tiles (every scale of up to 64 tokens) never waits for memory again.
   // Loads return in issue order, so waiting until only the copies younger than K(0) are outstanding means that
-  // K(0) has landed (CPT copies per wavefront and bf16 tile, two per 8-bit tile; up to 2 CPT for a shared tile 0, for
-  // which the wait is then longer than it has to be).
+  // K(0) has landed (CPT copies per wavefront and bf16 tile, two per 8-bit tile); tile 0 is a current-scale tile,
+  // whose address does not depend on the head's run.
   if (KS == 1) {
-    issue_first_k();
-    issue_first_v();
+    issue_k(0, 0);
+    issue_v(0, 0);
     if (tiles_all > 1) {
       issue_k(1, 1);
       issue_v(1, 1);
@@ -604,15 +554,15 @@ __global__ __launch_bounds__(256 * KS * QS, (KS == 1 && QS == 1) ? 2 : 1) void a
       wait_vmcnt<CPT>();
     }
   } else {
-    issue_first_k();
+    issue_k(0, 0);
     issue_k(1, 1);
-    issue_first_v();
+    issue_v(0, 0);
     wait_vmcnt<0>();
   }
   __syncthreads();
   if (active && has_tile(0)) {
     scores(s_cur, std::integral_constant<int, 0>{});
-    settle_first(s_cur);
+    settle(0, s_cur);
   }
   // Every path reaches the loop through a full wait that the compiler sees (a wavefront that skipped the scores
   // above never waited for its query rows): otherwise it waits for them inside every step, and with them for the

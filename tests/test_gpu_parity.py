@@ -754,14 +754,32 @@ def test_bf16_tiles_end_where_the_valid_rows_end(d, H, batch):
 
 
 @pytest.mark.parametrize("d,H,batch,tokens", [
-    # Runs of all earlier tokens (full budget): 3 + 1 and 60 + 4 keys in one tile, 70 + 64 (the run ends with a tile),
-    # 122 + 134 (58 + 6 rows share a tile, two tiles of the run remain), 129 + 256, 447 + 385 (63 + 1, two key streams)
+    # Runs of all earlier tokens (full budget): 3 + 1 and 60 + 4 keys, 70 + 64 (the run ends with a tile), 122 + 134 (58 and
+    # 6 rows in the ragged tiles), 129 + 256, 447 + 385 (63 and 1, two key streams)
     (128, 3, 1, (1, 3, 60, 70, 122, 129, 447)),
-    # 33 + 30 keys: 63 of a tile; 65 + 63: 1 + 63; 129 + 128; 190 + 257: 62 + 2, 255 remain; 195 + 447: 3 + 63 do not fit
+    # 33 + 30 keys; 65 + 63: ragged tiles of 1 and 63; 129 + 128; 190 + 257: 62 and 1; 195 + 447: 3 and 63
     (64, 5, 2, (1, 5, 9, 15, 33, 65, 129, 190, 195)),
 ])
-def test_bf16_ragged_ends_of_scale_and_run_share_a_tile(d, H, batch, tokens):
+def test_bf16_ragged_ends_of_scale_and_run(d, H, batch, tokens):
     _bf16_case(1, H, tuple((1, n) for n in tokens), 1, 1, batch, seed=34, fused=True, d=d)
+
+
+@pytest.mark.parametrize("d,tokens", [(64, (1, 31, 32)), (128, (1, 31, 32)), (128, (1, 31, 416))])
+def test_bf16_reference_comes_from_the_first_rows_of_the_current_scale(d, tokens):
+    # Probabilities are rounded to bf16 relative to the running reference, so which keys set it shows in the bits.  Current
+    # scale: scores 0, probabilities 1; run: exp(0.2109) = 1.2348, rounded to 1.234375.  32 rows of value 1.234375 against
+    # 32 of -1 then cancel exactly; relative to the run's score they would not (exp(-0.2109) = 0.8098 -> 0.8086).  416
+    # tokens: two key streams.
+    H, run = 2, 32
+    t_k = tokens[-1]
+    shape = hk.Shape(1, H, d, tokens, 1, "bf16")
+    plan = hk.heatkv_build_schedule(shape, harness.random_beta(5, 1, H, 3), H * run * 2 * d * 2, 1)
+    assert plan.runs(2, 0)[1].tolist() == [run] * H
+    q, k, v = (torch.zeros(1, H, sum(tokens), d, dtype=torch.bfloat16) for _ in range(3))
+    q[..., 0] = 1.0
+    k[:, :, :run, 0] = 0.2109375
+    v[:, :, :run], v[:, :, -32:] = -1.0, 1.234375
+    assert t_k >= 32 and not device_generation(plan, 0, *_dev(q, k, v), tokens, 1.0)[-1].any()
 
 
 @pytest.mark.parametrize("d,tokens", [
@@ -800,10 +818,10 @@ def test_bf16_calibration_with_two_query_sets_at_the_edges_of_its_tiles(d, token
 
 
 @pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 128), ("bf16", 64), ("bf16", 128)])
-@pytest.mark.parametrize("masked", ["first tiles", "shared ragged tile"])
+@pytest.mark.parametrize("masked", ["first tiles", "ragged ends"])
 def test_keys_masked_by_their_values(dtype, d, masked):
     # Keys of -inf in a component where the queries are 1: scores of -inf, probability 0.  Masked are all keys that the
-    # walk meets first (fp32: the first tile of each wavefront; bf16: the tile that the ragged ends share), never all.
+    # walk meets first (fp32: the first tile of each wavefront; bf16: the first tile), or those of the ragged ends, never all.
     t0, H, nb = [1, 3, 60, 70, 122], 3, 2
     c, K, sm = hi.cumulative_tokens(t0), 5, 1.0 / np.sqrt(d)
     cfg = dict(L=1, H=H, d=d, dtype=dtype, batch=nb, sides=[(1, n) for n in t0])
