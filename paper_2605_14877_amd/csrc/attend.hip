@@ -177,9 +177,8 @@ __global__ __launch_bounds__(256 * KS * QS, (KS == 1 && QS == 1) ? 2 : 1) void a
   for (int i = 0; i < NV; ++i)
 #pragma unroll
     for (int r = 0; r < 16; ++r) o[i][r] = 0.f;
-  // The reference starts finite: a row whose first tile holds scores of -inf only is not NaN for that.
-  float m_run = kLowest, l_run = 0.f;
   const float c = p.sm_scale * kLog2e;
+  float m_run = lowest_reference(c), l_run = 0.f;
   // The running reference m_run of a row is only raised when the tile maximum exceeds it by more than
   // kSlack in the exponent (base 2): probabilities are then at most 2^kSlack, far inside fp32/bf16 range,
   // the final division by the row sum makes the result independent of the reference, and the expensive
@@ -627,7 +626,7 @@ __global__ __launch_bounds__(256 * KS * QS, (KS == 1 && QS == 1) ? 2 : 1) void a
     if (g == 1 || !active) return;
     const float m_other = park[64 * 64 + lane], l_other = park[65 * 64 + lane];
     const float m_new = fmaxf(m_run, m_other);
-    const float a0 = fast_exp2((m_run - m_new) * c), a1 = fast_exp2((m_other - m_new) * c);  // kLowest: no tile, factor 0
+    const float a0 = fast_exp2((m_run - m_new) * c), a1 = fast_exp2((m_other - m_new) * c);  // no tile: lowest reference, factor 0
     l_run = l_run * a0 + l_other * a1;
 #pragma unroll
     for (int i = 0; i < 4; ++i)

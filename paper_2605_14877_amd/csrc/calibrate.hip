@@ -145,7 +145,7 @@ __global__ __launch_bounds__(256, CSETS == 1 ? 3 : 2) void calibrate_bf16_kernel
   float m_run[CSETS], cur[CSETS];
 #pragma unroll
   for (int qs = 0; qs < CSETS; ++qs) {
-    m_run[qs] = -INFINITY;
+    m_run[qs] = lowest_reference(c);
     cur[qs] = 0.f;
   }
   int k2 = 0, tile = 0;  // the tile being computed
@@ -153,9 +153,9 @@ __global__ __launch_bounds__(256, CSETS == 1 ? 3 : 2) void calibrate_bf16_kernel
   // Adds a tile's probabilities (rs: four partial sums of this lane's 32, relative to m_run) to the block's sum.
   // Probabilities are taken relative to the running reference m_run, which is only brought up to the true
   // row maximum when it has fallen too far behind: as long as no score exceeds it by more than 8 in the
-  // base-2 exponent a lane's 32 probabilities of the tile sum to at most 2^13, so a larger sum, an infinity
-  // or a NaN (the first tile, where m_run is still -inf) sends the whole wavefront through the exact path,
-  // which finds the tile maximum, rescales what the block has summed so far and redoes the tile's
+  // base-2 exponent a lane's 32 probabilities of the tile sum to at most 2^13, so a larger sum or an
+  // infinity (the first tile, where m_run still is the lowest reference) sends the whole wavefront through the
+  // exact path, which finds the tile maximum, rescales what the block has summed so far and redoes the tile's
   // exponentials.  The masses are ratios of such sums, so they do not depend on the reference; the max
   // chain, one vector instruction per two scores, leaves the common path.
   auto fold = [&](int qs, const f32x16 (&s)[2], float (&rs)[4], int block, bool last_of_block) {

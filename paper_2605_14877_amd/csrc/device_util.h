@@ -18,6 +18,11 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLowest = -3e38f;  // start of a running maximum: below any score, and finite, so that differences are never NaN
 
+// The same over scores that are multiplied by c afterwards, where the product has to be finite as well: exponents of 2 are
+// fma(score, c, -maximum * c), and a score of -inf would give NaN next to an infinity.  Above the types' lowest values on
+// purpose: a score masked to one of those gives 0, whereas a maximum of that size rounds by more than any exponent.
+__device__ __forceinline__ float lowest_reference(float c) { return kLowest / fmaxf(c, 1.f); }
+
 // 2^x on the transcendental unit; 2^-inf = 0.
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 

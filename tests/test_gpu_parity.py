@@ -819,9 +819,12 @@ def test_bf16_calibration_with_two_query_sets_at_the_edges_of_its_tiles(d, token
 
 @pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 128), ("bf16", 64), ("bf16", 128)])
 @pytest.mark.parametrize("masked", ["first tiles", "ragged ends"])
-def test_keys_masked_by_their_values(dtype, d, masked):
-    # Keys of -inf in a component where the queries are 1: scores of -inf, probability 0.  Masked are all keys that the
+@pytest.mark.parametrize("scaled", ["by the call", "beforehand"])
+@pytest.mark.parametrize("mask", ["inf", "lowest"])
+def test_keys_masked_by_their_values(dtype, d, masked, scaled, mask):
+    # Keys of -inf, or of the type's lowest value, in a component where the queries are 1: probability 0.  Masked are all keys that the
     # walk meets first (fp32: the first tile of each wavefront; bf16: the first tile), or those of the ragged ends, never all.
+    # Queries scaled beforehand: sm_scale = 1, whose product with a reference near the type's lowest value overflows.
     t0, H, nb = [1, 3, 60, 70, 122], 3, 2
     c, K, sm = hi.cumulative_tokens(t0), 5, 1.0 / np.sqrt(d)
     cfg = dict(L=1, H=H, d=d, dtype=dtype, batch=nb, sides=[(1, n) for n in t0])
@@ -829,13 +832,49 @@ def test_keys_masked_by_their_values(dtype, d, masked):
     q, k, v = hi.make_qkv(41, 0, cfg, w=w)
     plan = hk.heatkv_build_schedule(hk.Shape(1, H, d, t0, nb, dtype), hi.expected_beta_from_weights(w, t0).astype(np.float32),
                                     H * c[-2] * 2 * d * hi.elem_bytes(dtype), 1)
+    if scaled == "beforehand":
+        q, sm = (q.double() * sm).to(q.dtype), 1.0
     q[..., 0] = 1.0
     keys = range(c[3], c[3] + 64) if masked == "first tiles" else [*range(6), *range(c[3] + 64, c[4])]
-    k[:, :, list(keys), 0] = float("-inf")
+    k[:, :, list(keys), 0] = float("-inf") if mask == "inf" else torch.finfo(k.dtype).min
     got = device_generation(plan, 0, *_dev(q, k, v), t0, sm)[-1].double().cpu()
     s = q[:, :, c[3]:].double() @ k.double().transpose(-1, -2) * sm
     want = torch.softmax(s, -1) @ v.double()
     assert (got - want).abs().max() <= TOL[dtype]
+
+
+@pytest.mark.parametrize("one_launch", [False, True])
+@pytest.mark.parametrize("mask", ["inf", "lowest"])
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 128), ("bf16", 64), ("bf16", 128)])
+def test_calibration_keys_masked_by_their_values(dtype, d, mask, one_launch):
+    # The blocks that the walk meets first masked by -inf, or by the type's lowest value, in a component where the queries
+    # are 1: mass 0 there, the rest unmoved.  One launch over all scales: two query sets per wavefront (bf16).
+    t0, H, nb, K = [1, 63, 65, 200], 32, 8, 4
+    c = hi.cumulative_tokens(t0)
+    g = torch.Generator().manual_seed(44)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    q, k = (torch.randn(nb, H, c[-1], d, generator=g).to(dt) for _ in range(2))
+    q[..., 0] = 1.0
+    k[:, :, :c[1], 0] = float("-inf") if mask == "inf" else torch.finfo(dt).min
+    dq, dk = _dev(q, k)
+    shape, scales = hk.Shape(1, H, d, t0, nb, dtype), [2, 3]
+    qs = [dq[:, :, c[i - 1]:c[i]].contiguous() for i in scales]
+    ks = [dk[:, :, :c[i]].contiguous() for i in scales]
+    for sm in (1.0 / np.sqrt(d), 1.0):
+        mass = [torch.empty(nb, H, K, device="cuda") for _ in scales]
+        if one_launch:
+            ws = torch.empty(hk.binding.calibrate_scales_workspace_bytes(shape, scales), dtype=torch.uint8, device="cuda")
+            hk.heatkv_calibrate_scales_accumulate(shape, 0, scales, qs, ks, sm, 1.0, torch.zeros(1, H, K, K, device="cuda"),
+                                                  mass, ws)
+        else:
+            for m, i, a, b in zip(mass, scales, qs, ks):
+                ws = torch.empty(hk.binding.calibrate_workspace_bytes(shape, i), dtype=torch.uint8, device="cuda")
+                hk.heatkv_calibrate(shape, 0, i, a, b, sm, m, ws)
+        for m, i, a, b in zip(mass, scales, qs, ks):
+            p = torch.softmax(a[:1, :4].double() @ b[:1, :4].double().transpose(-1, -2) * sm, -1).mean(2).cpu()
+            want = torch.stack([x.sum(-1) for x in torch.split(p, t0[:i + 1], -1)], -1)
+            assert (m[:1, :4, :i + 1].double().cpu() - want).abs().max() <= 1e-4, (sm, i)  # what masses are held to
+            assert torch.isfinite(m).all()
 
 
 @pytest.mark.parametrize("d", [64, 128])
