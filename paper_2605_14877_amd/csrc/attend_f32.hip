@@ -101,11 +101,12 @@ __global__ __launch_bounds__(64 * NW) void attend_f32_kernel(AttendParams p) {
   f32x4 o[NB];
 #pragma unroll
   for (int i = 0; i < NB; ++i) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // Scores in base-2 exponents.  The reference m of a query is common to its four lanes and only raised when a score
-  // exceeds it by more than 8: probabilities stay at most 2^8 and the accumulators are rescaled a few times per row.  It
-  // starts finite: a row whose first tiles hold scores of -inf only (keys masked by their values) is not NaN for that.
-  const float c = p.sm_scale * kLog2e;
-  float m = kLowest, l = 0.f;
+  // The reference m of a query is common to its four lanes and only raised when a score's exponent exceeds it by more than
+  // 8: the accumulators are rescaled a few times per row.  Probabilities are taken 2^-8 times, at most 1, so that values
+  // up to the type's largest over the number of keys can be summed.
+  const f32m::Exponent prob(p.sm_scale);
+  const float slack = 8.f / prob.up;
+  float m = f32m::LOWEST, l = 0.f;
 
   for (int it = wave; it < tiles_all; it += NW) {
     const Tile t = tile_of(it);
@@ -122,7 +123,7 @@ __global__ __launch_bounds__(64 * NW) void attend_f32_kernel(AttendParams p) {
       for (int j = 0; j < NB / 4; ++j) v[r][j] = f32m::load16(vb, off + 256 * j);
     }
     f32x4 s = f32m::scores<D>(k, q);
-    s *= c;
+    s *= prob.c;
     if (t.rows < T) {
 #pragma unroll
       for (int r = 0; r < 4; ++r)
@@ -133,16 +134,16 @@ __global__ __launch_bounds__(64 * NW) void attend_f32_kernel(AttendParams p) {
         }
     }
     const float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
-    if (__any(mx > m + 8.f)) {
+    if (__any(mx > m + slack)) {
       const float m_new = fmaxf(m, f32m::max_groups(mx));
-      const float alpha = fast_exp2(m - m_new);
+      const float alpha = prob(m, m_new);
       m = m_new;
       l *= alpha;
 #pragma unroll
       for (int i = 0; i < NB; ++i) o[i] *= alpha;
     }
 #pragma unroll
-    for (int r = 0; r < 4; ++r) s[r] = fast_exp2(s[r] - m);
+    for (int r = 0; r < 4; ++r) s[r] = prob(s[r], m) * 0x1p-8f;
     l += (s[0] + s[1]) + (s[2] + s[3]);
 #pragma unroll
     for (int r = 0; r < 4; ++r)
@@ -163,8 +164,8 @@ __global__ __launch_bounds__(64 * NW) void attend_f32_kernel(AttendParams p) {
 #pragma unroll
   for (int w = 1; w < NW; ++w) m_all = fmaxf(m_all, part_m[w][n]);
 #pragma unroll
-  for (int w = 0; w < NW; ++w) l_all += part_l[w][n] * fast_exp2(part_m[w][n] - m_all);
-  const float f = fast_exp2(m - m_all) / l_all;
+  for (int w = 0; w < NW; ++w) l_all += part_l[w][n] * prob(part_m[w][n], m_all);
+  const float f = prob(m, m_all) / l_all;
 #pragma unroll
   for (int r = 0; r < 4; ++r)
 #pragma unroll

@@ -509,12 +509,12 @@ __global__ __launch_bounds__(64 * FW) void calibrate_f32_kernel(CalibParams p) {
   for (int j = 0; j <= k1; ++j)  // blocks without a tile of this wavefront
     if (g == 0) {
       blk_sum[j][wave][n] = 0.f;
-      blk_max[j][wave][n] = kLowest;
+      blk_max[j][wave][n] = f32m::LOWEST;
     }
   enter(wave);
   if (k2 <= k1) fetch();
-  const float c = p.sm_scale * kLog2e;
-  float m = kLowest, cur = 0.f;
+  const f32m::Exponent prob(p.sm_scale);
+  float m = f32m::LOWEST, cur = 0.f;
   while (k2 <= k1) {
     const int here = k2, rows = rows_left;
     Stage::take(k, stages[wave], lane);
@@ -528,19 +528,19 @@ __global__ __launch_bounds__(64 * FW) void calibrate_f32_kernel(CalibParams p) {
     }
     if (k2 <= k1) fetch();
     f32x4 s = f32m::scores<D>(k, q);
-    s *= c;
+    s *= prob.c;
     if (rows < FQ) {
 #pragma unroll
       for (int r = 0; r < 4; ++r)
         if (4 * g + r >= rows) s[r] = -INFINITY;
     }
     const float m_new = fmaxf(m, fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])));
-    cur *= fast_exp2(m - m_new);
+    cur *= prob(m, m_new);
     m = m_new;
-    cur += (fast_exp2(s[0] - m) + fast_exp2(s[1] - m)) + (fast_exp2(s[2] - m) + fast_exp2(s[3] - m));
+    cur += (prob(s[0], m) + prob(s[1], m)) + (prob(s[2], m) + prob(s[3], m));
     if (k2 != here) {  // the wavefront leaves the block
       const float mb = f32m::max_groups(m);
-      const float sb = f32m::sum_groups(cur * fast_exp2(m - mb));
+      const float sb = f32m::sum_groups(cur * prob(m, mb));
       if (g == 0) {
         blk_sum[here][wave][n] = sb;
         blk_max[here][wave][n] = mb;
@@ -561,7 +561,7 @@ __global__ __launch_bounds__(64 * FW) void calibrate_f32_kernel(CalibParams p) {
     for (int j = tid / FQ; j <= k1; j += 64 * FW / FQ) {
       float v = 0.f;
 #pragma unroll
-      for (int w = 0; w < FW; ++w) v += blk_sum[j][w][row] * fast_exp2(blk_max[j][w][row] - mf);
+      for (int w = 0; w < FW; ++w) v += blk_sum[j][w][row] * prob(blk_max[j][w][row], mf);
       blk_sum[j][0][row] = v;
     }
   }

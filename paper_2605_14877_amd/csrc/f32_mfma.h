@@ -106,6 +106,22 @@ __device__ __forceinline__ f32x4 scores(const Rows<D>& k, const Rows<D>& q) {
   return a + b;
 }
 
+// Scores are kept as s * c and turned into probabilities 2^((s * c - reference) * up): c * up = sm_scale * log2 e with |c| at
+// most 1 and `up` a power of two (1 for any ordinary scale), so that no finite score becomes infinite.  The running
+// references start at LOWEST, below which there is no finite number: rows masked throughout to the type's lowest value
+// have their maximum, and a score of -inf meets a finite reference.
+constexpr float LOWEST = -3.402823466e38f;
+struct Exponent {
+  float c, up;
+  __device__ __forceinline__ explicit Exponent(float sm_scale) : c(sm_scale * kLog2e), up(1.f) {
+    if (fabsf(c) > 1.f) {
+      up = ldexpf(1.f, __builtin_amdgcn_frexp_expf(c));
+      c = __builtin_amdgcn_frexp_mantf(c);
+    }
+  }
+  __device__ __forceinline__ float operator()(float s, float reference) const { return fast_exp2((s - reference) * up); }
+};
+
 // Reductions over the four lane groups (lanes n, n + 16, n + 32, n + 48), in a fixed order.
 __device__ __forceinline__ float max_groups(float v) {
   v = fmaxf(v, __shfl_xor(v, 16, 64));

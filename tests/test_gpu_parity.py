@@ -822,8 +822,9 @@ def test_bf16_calibration_with_two_query_sets_at_the_edges_of_its_tiles(d, token
 @pytest.mark.parametrize("scaled", ["by the call", "beforehand"])
 @pytest.mark.parametrize("mask", ["inf", "lowest"])
 def test_keys_masked_by_their_values(dtype, d, masked, scaled, mask):
-    # Keys of -inf, or of the type's lowest value, in a component where the queries are 1: probability 0.  Masked are all keys that the
-    # walk meets first (fp32: the first tile of each wavefront; bf16: the first tile), or those of the ragged ends, never all.
+    # Keys of -inf, or of the type's lowest value, in a component where the queries are 1: probability 0.  Masked are all
+    # keys that the walk meets first (fp32: the first tile of each wavefront; bf16: the first tile), or those of the ragged
+    # ends, never all.
     # Queries scaled beforehand: sm_scale = 1, whose product with a reference near the type's lowest value overflows.
     t0, H, nb = [1, 3, 60, 70, 122], 3, 2
     c, K, sm = hi.cumulative_tokens(t0), 5, 1.0 / np.sqrt(d)
@@ -875,6 +876,38 @@ def test_calibration_keys_masked_by_their_values(dtype, d, mask, one_launch):
             want = torch.stack([x.sum(-1) for x in torch.split(p, t0[:i + 1], -1)], -1)
             assert (m[:1, :4, :i + 1].double().cpu() - want).abs().max() <= 1e-4, (sm, i)  # what masses are held to
             assert torch.isfinite(m).all()
+
+
+@pytest.mark.parametrize("sm_scale", [None, 1.0])
+@pytest.mark.parametrize("d", [64, 128])
+def test_fp32_rows_masked_throughout_to_the_lowest_value_are_uniform(d, sm_scale):
+    # The type's lowest value on every key leaves all scores equal; sm_scale = 1: times log2 e it is past the type's range.
+    t0, H, K, sm = [1, 30, 70], 3, 3, sm_scale or 1.0 / np.sqrt(d)
+    c = hi.cumulative_tokens(t0)
+    shape = hk.Shape(1, H, d, t0, 1, "f32")
+    plan = hk.heatkv_build_schedule(shape, harness.random_beta(6, 1, H, K), H * c[-2] * 2 * d * 4, 1)
+    q, k = (torch.zeros(1, H, c[-1], d) for _ in range(2))
+    v = torch.randn(1, H, c[-1], d, generator=torch.Generator().manual_seed(45))
+    q[..., 0], k[..., 0] = 1.0, torch.finfo(torch.float32).min
+    dq, dk, dv = _dev(q, k, v)
+    got = device_generation(plan, 0, dq, dk, dv, t0, sm)[-1].double().cpu()
+    assert (got - v.double().mean(2, keepdim=True)).abs().max() <= TOL["f32"]
+    mass = torch.empty(1, H, K, device="cuda")
+    ws = torch.empty(hk.binding.calibrate_workspace_bytes(shape, 2), dtype=torch.uint8, device="cuda")
+    hk.heatkv_calibrate(shape, 0, 2, dq[:, :, c[1]:].contiguous(), dk, sm, mass, ws)
+    assert np.abs(mass.cpu().numpy() - np.array(t0) / c[-1]).max() <= TOL["f32"]
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_fp32_values_near_the_largest(d):
+    # One key per query ahead of its wavefront's first tile by an exponent of 7.5, not enough to move the reference: its
+    # probability relative to that is 181, and 181 x 1e37 is past the type's range.  The result is 1e37.
+    t0, H = [1, 2, 70], 2
+    q, k, v = (torch.zeros(1, H, 73, d) for _ in range(3))
+    q[..., 0], k[:, :, 3 + 64, 0], v[:] = 1.0, 7.5 * np.log(2.0), 1e37
+    plan = hk.heatkv_build_schedule(hk.Shape(1, H, d, t0, 1, "f32"), harness.random_beta(7, 1, H, 3), H * 3 * 2 * d * 4, 1)
+    got = device_generation(plan, 0, *_dev(q, k, v), t0, 1.0)[-1].double().cpu()
+    assert (got / 1e37 - 1.0).abs().max() <= TOL["f32"]
 
 
 @pytest.mark.parametrize("d", [64, 128])
