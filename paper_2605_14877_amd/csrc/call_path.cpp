@@ -4,7 +4,8 @@
 // shorter than the 10 us that operand checks, stream lookup and argument conversion took in Python and ctypes (2.1, 2.9
 // and 2.0 us, next to 3.7 us for the library call itself, 3.2 of them the launch).  The functions here do the same
 // checks on the tensors and call the library.  They return its error code, or None for anything that is not plainly
-// in order: the caller then takes the Python path, which names the mistake.
+// in order: the caller then takes the Python path, which names the mistake.  A tensor may answer a question about itself with
+// an exception (one without sizes, a subclass with a sizes policy of its own): that is not plainly in order either.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
@@ -12,6 +13,7 @@
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <cstdint>
+#include <new>
 #include <vector>
 
 #include "heatkv.h"
@@ -33,7 +35,7 @@ void free_plan_info(PyObject* capsule) {
 }
 
 // plan_info(handle, L, H, d, batch, dtype, t, arena_bytes) -> capsule
-PyObject* plan_info(PyObject*, PyObject* args) {
+PyObject* plan_info(PyObject*, PyObject* args) try {
   unsigned long long handle;
   long long L, H, d, batch, dtype, arena_bytes;
   PyObject* t;
@@ -49,6 +51,8 @@ PyObject* plan_info(PyObject*, PyObject* args) {
   PyObject* capsule = PyCapsule_New(info, kPlanName, free_plan_info);
   if (!capsule) delete info;
   return capsule;
+} catch (const std::bad_alloc&) {
+  return PyErr_NoMemory();
 }
 
 // Address and size of a contiguous device tensor; None is a null pointer.
@@ -60,11 +64,7 @@ bool device_tensor(PyObject* o, const at::Tensor** tensor, void** ptr) {
   const at::Tensor& x = THPVariable_Unpack(o);
   if (!x.is_cuda() || !x.is_contiguous()) return false;
   *tensor = &x;
-  try {
-    *ptr = x.data_ptr();
-  } catch (...) {  // no storage
-    return false;
-  }
+  *ptr = x.data_ptr();
   return true;
 }
 
@@ -94,11 +94,7 @@ bool number(PyObject* o, float* v) {
 
 bool stream_of(PyObject* o, void** stream) {
   if (o == Py_None) {
-    try {
-      *stream = c10::hip::getCurrentHIPStreamMasqueradingAsCUDA().stream();
-    } catch (...) {  // no device
-      return false;
-    }
+    *stream = c10::hip::getCurrentHIPStreamMasqueradingAsCUDA().stream();
     return true;
   }
   if (!PyLong_Check(o)) return false;
@@ -111,9 +107,25 @@ PyObject* not_plain() {
   Py_RETURN_NONE;
 }
 
+// The interpreter's lock is released for the library call.
+struct Unlocked {
+  PyThreadState* state = PyEval_SaveThread();
+  ~Unlocked() { PyEval_RestoreThread(state); }
+};
+
+// A C++ exception must not reach the interpreter's C frames.
+template <PyObject* (*F)(PyObject* const*, Py_ssize_t)>
+PyObject* guarded(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  try {
+    return F(a, n);
+  } catch (...) {
+  }
+  return not_plain();  // after the exception is gone: one that came from Python holds its error until then
+}
+
 // scale_call(plan_info, which, layer, k, q, k_cur, v_cur, k_arena, v_arena, sm_scale, out, ws, stream)
 // which: 0 append_scale (q, sm_scale, out and ws unused), 1 attend_scale, 2 attend_append_scale
-PyObject* scale_call(PyObject*, PyObject* const* a, Py_ssize_t n) {
+PyObject* scale_call(PyObject* const* a, Py_ssize_t n) {
   if (n != 13) return not_plain();
   auto* info = static_cast<PlanInfo*>(PyCapsule_GetPointer(a[0], kPlanName));
   long which, layer, k;
@@ -131,14 +143,15 @@ PyObject* scale_call(PyObject*, PyObject* const* a, Py_ssize_t n) {
                      !operand(a[10], shape, info->dtype, &out) || !buffer(a[11], 0, &ws, &ws_bytes)))
     return not_plain();
   int rc;
-  Py_BEGIN_ALLOW_THREADS
-  if (which == 0)
-    rc = heatkv_append_scale(info->plan, layer, k, kc, vc, ka, va, stream);
-  else if (which == 1)
-    rc = heatkv_attend_scale(info->plan, layer, k, q, kc, vc, ka, va, sm, out, ws, ws_bytes, stream);
-  else
-    rc = heatkv_attend_append_scale(info->plan, layer, k, q, kc, vc, ka, va, sm, out, ws, ws_bytes, stream);
-  Py_END_ALLOW_THREADS
+  {
+    const Unlocked unlocked;
+    if (which == 0)
+      rc = heatkv_append_scale(info->plan, layer, k, kc, vc, ka, va, stream);
+    else if (which == 1)
+      rc = heatkv_attend_scale(info->plan, layer, k, q, kc, vc, ka, va, sm, out, ws, ws_bytes, stream);
+    else
+      rc = heatkv_attend_append_scale(info->plan, layer, k, q, kc, vc, ka, va, sm, out, ws, ws_bytes, stream);
+  }
   return PyLong_FromLong(rc);
 }
 
@@ -165,7 +178,7 @@ bool beta_operand(const heatkv_shape* s, PyObject* beta, void** ptr) {
 
 // calibrate_call(address of the heatkv_shape, which, layer, k1, q, k_all, sm_scale, weight, beta, mass, ws, stream)
 // which: 0 calibrate, 1 calibrate_static (ws unused), 2 calibrate_accumulate
-PyObject* calibrate_call(PyObject*, PyObject* const* a, Py_ssize_t n) {
+PyObject* calibrate_call(PyObject* const* a, Py_ssize_t n) {
   if (n != 12) return not_plain();
   const heatkv_shape* s = shape_at(a[0]);
   long which, layer, k1;
@@ -177,21 +190,22 @@ PyObject* calibrate_call(PyObject*, PyObject* const* a, Py_ssize_t n) {
       !beta_operand(s, a[8], &beta) || !buffer(a[10], 0, &ws, &ws_bytes) || !stream_of(a[11], &stream))
     return not_plain();
   int rc;
-  Py_BEGIN_ALLOW_THREADS
-  if (which == 0)
-    rc = heatkv_calibrate(s, layer, k1, q, k_all, sm, static_cast<float*>(mass), ws, ws_bytes, stream);
-  else if (which == 1)
-    rc = heatkv_calibrate_static(s, layer, k1, q, k_all, sm, static_cast<float*>(mass), stream);
-  else
-    rc = heatkv_calibrate_accumulate(s, layer, k1, q, k_all, sm, weight, static_cast<float*>(beta),
-                                     static_cast<float*>(mass), ws, ws_bytes, stream);
-  Py_END_ALLOW_THREADS
+  {
+    const Unlocked unlocked;
+    if (which == 0)
+      rc = heatkv_calibrate(s, layer, k1, q, k_all, sm, static_cast<float*>(mass), ws, ws_bytes, stream);
+    else if (which == 1)
+      rc = heatkv_calibrate_static(s, layer, k1, q, k_all, sm, static_cast<float*>(mass), stream);
+    else
+      rc = heatkv_calibrate_accumulate(s, layer, k1, q, k_all, sm, weight, static_cast<float*>(beta),
+                                       static_cast<float*>(mass), ws, ws_bytes, stream);
+  }
   return PyLong_FromLong(rc);
 }
 
 // calibrate_scales_call(address of the heatkv_shape, layer, k1 list, q list, k_all list, sm_scale, weight, beta,
 //                       mass list or None, ws, stream); the lists have one length
-PyObject* calibrate_scales_call(PyObject*, PyObject* const* a, Py_ssize_t n) {
+PyObject* calibrate_scales_call(PyObject* const* a, Py_ssize_t n) {
   if (n != 11) return not_plain();
   const heatkv_shape* s = shape_at(a[0]);
   long layer;
@@ -217,22 +231,26 @@ PyObject* calibrate_scales_call(PyObject*, PyObject* const* a, Py_ssize_t n) {
     k1[i] = static_cast<int32_t>(k);
   }
   int rc;
-  Py_BEGIN_ALLOW_THREADS
-  rc = heatkv_calibrate_scales_accumulate(s, layer, static_cast<int>(scales), k1, q, k_all, sm, weight,
-                                          static_cast<float*>(beta),
-                                          a[8] == Py_None ? nullptr : reinterpret_cast<float* const*>(mass), ws, ws_bytes,
-                                          stream);
-  Py_END_ALLOW_THREADS
+  {
+    const Unlocked unlocked;
+    rc = heatkv_calibrate_scales_accumulate(s, layer, static_cast<int>(scales), k1, q, k_all, sm, weight,
+                                            static_cast<float*>(beta),
+                                            a[8] == Py_None ? nullptr : reinterpret_cast<float* const*>(mass), ws, ws_bytes,
+                                            stream);
+  }
   return PyLong_FromLong(rc);
 }
 
-PyMethodDef methods[] = {
-    {"plan_info", plan_info, METH_VARARGS, nullptr},
-    {"scale_call", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(scale_call)), METH_FASTCALL, nullptr},
-    {"calibrate_call", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(calibrate_call)), METH_FASTCALL, nullptr},
-    {"calibrate_scales_call", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(calibrate_scales_call)),
-     METH_FASTCALL, nullptr},
-    {nullptr, nullptr, 0, nullptr}};
+template <PyObject* (*F)(PyObject* const*, Py_ssize_t)>
+PyCFunction fastcall() {
+  return reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(guarded<F>));
+}
+
+PyMethodDef methods[] = {{"plan_info", plan_info, METH_VARARGS, nullptr},
+                         {"scale_call", fastcall<scale_call>(), METH_FASTCALL, nullptr},
+                         {"calibrate_call", fastcall<calibrate_call>(), METH_FASTCALL, nullptr},
+                         {"calibrate_scales_call", fastcall<calibrate_scales_call>(), METH_FASTCALL, nullptr},
+                         {nullptr, nullptr, 0, nullptr}};
 
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_heatkv_call", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 

@@ -6,6 +6,7 @@ import re
 
 import numpy as np
 import pytest
+import torch
 
 import heatkv_inputs as hi
 import paper_2605_14877_amd as hk
@@ -358,6 +359,32 @@ def test_binding_rejects_wrong_operands_before_any_gpu_call():
         hk.heatkv_attend_scale(plan, 0, 1, np.zeros(4), None, None, None, None, 0.125, None, stream=0)
     with pytest.raises(ValueError, match="device tensor"):
         hk.heatkv_calibrate(shape, 0, 1, good, good, 0.125, good, None, stream=0)
+
+
+def test_a_tensor_that_raises_ends_in_a_python_error():
+    # A subclass with a sizes policy of its own answers is_contiguous() and shape with an exception, in C++ as well.
+    class Odd(torch.Tensor):
+        @staticmethod
+        def __new__(cls, *size):
+            return torch.Tensor._make_wrapper_subclass(cls, size, dtype=torch.float32, device="cuda",
+                                                       dispatch_sizes_strides_policy="sizes")
+
+        @classmethod
+        def __torch_dispatch__(cls, func, types, args=(), kwargs=None):
+            raise RuntimeError("no answer")
+
+    shape = hk.Shape(1, 2, 64, [1, 4, 9], 1, "f32")
+    plan = hk.heatkv_build_schedule(shape, harness.random_beta(3, 1, 2, 3), 2 * 5 * 2 * 64 * 4, 1)
+    x = Odd(1, 2, 9, 64)
+    for call in (lambda: hk.heatkv_calibrate(shape, 0, 2, x, x, 1.0, x, None),
+                 lambda: hk.heatkv_calibrate_static(shape, 0, 2, x, x, 1.0, x),
+                 lambda: hk.heatkv_calibrate_accumulate(shape, 0, 2, x, x, 1.0, 1.0, x, None, x),
+                 lambda: hk.heatkv_calibrate_scales_accumulate(shape, 0, [2], [x], [x], 1.0, 1.0, x, None, x),
+                 lambda: hk.heatkv_append_scale(plan, 0, 1, x, x, x, x),
+                 lambda: hk.heatkv_attend_scale(plan, 0, 2, x, x, x, x, x, 1.0, x),
+                 lambda: hk.heatkv_attend_append_scale(plan, 0, 2, x, x, x, x, x, 1.0, x)):
+        with pytest.raises(RuntimeError, match="no answer"):
+            call()
 
 
 @pytest.mark.parametrize("variant", [binding.VARIANT_BINARY, binding.VARIANT_BINARY_NAIVE])
