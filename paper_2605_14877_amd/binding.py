@@ -143,11 +143,14 @@ class Shape:
         self.K = int(self.t.size)
         self.dtype = _DTYPES[dtype] if isinstance(dtype, str) else int(dtype)
         self.c_struct = _CShape(self.L, self.H, self.d, self.K, self.batch, self.dtype, _i32p(self.t))
-        self.address = C.addressof(self.c_struct)
 
     @property
     def ref(self):
         return C.byref(self.c_struct)
+
+    @property
+    def address(self):
+        return C.addressof(self.c_struct)
 
     @property
     def elem_size(self):
@@ -227,6 +230,7 @@ class Plan:
 
     def __del__(self):
         if getattr(self, "handle", None) and _lib is not None:
+            self.call_info = None  # knows the handle
             _lib.heatkv_plan_destroy(self.handle)
             self.handle = None
 

@@ -361,6 +361,17 @@ def test_binding_rejects_wrong_operands_before_any_gpu_call():
         hk.heatkv_calibrate(shape, 0, 1, good, good, 0.125, good, None, stream=0)
 
 
+def test_calls_see_a_destroyed_plan_and_a_replaced_shape():
+    # The native path must not go by addresses of what is gone.
+    shape = hk.Shape(1, 2, 64, [1, 4, 9], 1, "f32")
+    plan = hk.heatkv_build_schedule(shape, harness.random_beta(3, 1, 2, 3), 2 * 5 * 2 * 64 * 4, 1)
+    plan.__del__()
+    with pytest.raises(hk.HeatKVError, match="plan is null"):
+        hk.heatkv_append_scale(plan, 0, 1, None, None, None, None, stream=0)
+    shape.c_struct = hk.Shape(2, 2, 64, [1, 4, 9], 1, "f32").c_struct
+    assert shape.address == ctypes.addressof(shape.c_struct)
+
+
 def test_a_tensor_that_raises_ends_in_a_python_error():
     # A subclass with a sizes policy of its own answers is_contiguous() and shape with an exception, in C++ as well.
     class Odd(torch.Tensor):
