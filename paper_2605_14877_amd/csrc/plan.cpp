@@ -67,8 +67,9 @@ uint64_t order_bits(double x) {
 }
 
 // Stable ascending order of the heads by an fp64 score; ties keep the flat head id order.  From a few hundred heads on:
-// a radix sort on the upper 32 bits, stable, then insertion on the full value, which has ties of those 32 bits to put
-// right and nothing else (1280 heads: about 10 us against 60 with a comparison sort).
+// a radix sort on the upper 32 bits, stable, then a stable sort of every run of ties of those 32 bits on the full value
+// (1280 heads: 13 us with scores spread over 10 %, 34 with scores that agree to 1e-7, 63 with a comparison sort of all;
+// 10240 heads: 164, 745 and 811).
 std::vector<int32_t> rank_heads(const std::vector<double>& score) {
   const size_t n = score.size();
   std::vector<int32_t> order(n);
@@ -102,11 +103,18 @@ std::vector<int32_t> rank_heads(const std::vector<double>& score) {
     for (const Item& it : x) y[c[(it.key >> shift) & (DIGITS - 1)]++] = it;
     x.swap(y);
   }
-  for (size_t i = 1; i < n; ++i) {
-    const Item it = x[i];
-    size_t j = i;
-    for (; j > 0 && x[j - 1].key > it.key; --j) x[j] = x[j - 1];
-    x[j] = it;
+  for (size_t i = 0, end; i < n; i = end) {
+    for (end = i + 1; end < n && x[end].key >> 32 == x[i].key >> 32; ++end) {}
+    if (end - i > 16) {
+      std::stable_sort(x.begin() + i, x.begin() + end, [](const Item& a, const Item& b) { return a.key < b.key; });
+      continue;
+    }
+    for (size_t k = i + 1; k < end; ++k) {
+      const Item it = x[k];
+      size_t j = k;
+      for (; j > i && x[j - 1].key > it.key; --j) x[j] = x[j - 1];
+      x[j] = it;
+    }
   }
   for (size_t i = 0; i < n; ++i) order[i] = x[i].head;
   return order;

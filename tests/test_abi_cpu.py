@@ -3,6 +3,7 @@ error paths and the static memory layout.  No GPU needed."""
 import ctypes
 import os
 import re
+import time
 
 import numpy as np
 import pytest
@@ -359,6 +360,40 @@ def test_binding_rejects_wrong_operands_before_any_gpu_call():
         hk.heatkv_attend_scale(plan, 0, 1, np.zeros(4), None, None, None, None, 0.125, None, stream=0)
     with pytest.raises(ValueError, match="device tensor"):
         hk.heatkv_calibrate(shape, 0, 1, good, good, 0.125, good, None, stream=0)
+
+
+def _nearly_uniform_beta(seed, L, H, K, spread):
+    # masses in proportion to 1 + spread * noise: from about 1e-7 on scores agree to fp32 rounding
+    b = np.tril(np.ones((K, K))) * (1.0 + spread * np.random.default_rng(seed).standard_normal((L, H, K, K)))
+    return (b / b.sum(-1, keepdims=True)).astype(np.float32)
+
+
+@pytest.mark.parametrize("spread", [0.0, 1e-7, 1e-5, 1e-2])
+def test_orders_of_many_heads_with_nearly_equal_scores(spread):
+    L, H, t0, s = 40, 32, [1, 4, 9, 16, 25, 36], 1
+    beta = _nearly_uniform_beta(8, L, H, len(t0), spread)
+    shape = hk.Shape(L, H, 64, t0, 1, "bf16")
+    plan = hk.heatkv_build_schedule(shape, beta, L * H * 40 * 2 * 64 * 2, s)
+    scores = hk.heatkv_head_scores(shape, beta, s)
+    for i in range(s, len(t0) - 1):
+        assert plan.order(i).tolist() == np.argsort(scores[i], kind="stable").tolist(), i
+
+
+def test_ranking_nearly_equal_scores_takes_no_longer_than_others():
+    # 16384 heads; a sort that is quadratic in the number of nearly equal scores takes tens of times as long here
+    L, H, t0 = 128, 128, [1, 4, 9, 16, 25, 36]
+    shape = hk.Shape(L, H, 64, t0, 1, "bf16")
+    out = np.zeros(len(t0))
+    seconds = []
+    for spread in (1e-2, 1e-7):
+        beta = _nearly_uniform_beta(9, L, H, len(t0), spread)[None]
+        best = 1e9
+        for _ in range(5):
+            start = time.perf_counter()
+            out = hk.heatkv_rank_dispersion(shape, beta, 1)
+            best = min(best, time.perf_counter() - start)
+        seconds.append(best)
+    assert np.isfinite(out).all() and seconds[1] < 5 * seconds[0], seconds
 
 
 def test_calls_see_a_destroyed_plan_and_a_replaced_shape():
