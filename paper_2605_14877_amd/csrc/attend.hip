@@ -230,12 +230,12 @@ __global__ __launch_bounds__(256 * KS * QS, (KS == 1 && QS == 1) ? 2 : 1) void a
     }
   };
   // Copy i (0 .. CPT - 1) of a tile into K (V) stage `buf`.
+  const unsigned lds_wave = lds_base + lw * 1024;
   auto copy_k = [&](const tile::Descriptor& src, int buf, int i) {
-    tile::copy_1k_checked(lds_base + buf * (2 * TILE_BYTES) + lw * 1024 + i * (1024 * NW), ld_off_k, src, i * (1024 * NW));
+    tile::copy_1k_checked(lds_wave, buf * (2 * TILE_BYTES) + i * (1024 * NW), ld_off_k, src, i * (1024 * NW));
   };
   auto copy_v = [&](const tile::Descriptor& src, int buf, int i) {
-    tile::copy_1k_checked(lds_base + buf * (2 * TILE_BYTES) + TILE_BYTES + lw * 1024 + i * (1024 * NW), ld_off_v, src,
-                          i * (1024 * NW));
+    tile::copy_1k_checked(lds_wave, buf * (2 * TILE_BYTES) + TILE_BYTES + i * (1024 * NW), ld_off_v, src, i * (1024 * NW));
   };
   auto issue_k = [&](int j, int buf) {
     if constexpr (FP8) {  // codes land in the K landing buffer; the step that needs the tile converts it

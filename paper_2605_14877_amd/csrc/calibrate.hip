@@ -274,7 +274,7 @@ __global__ __launch_bounds__(256, CSETS == 1 ? 3 : 2) void calibrate_bf16_kernel
     };
     constexpr int CPT = CTILE_BYTES / 4096;  // copies of a tile per wavefront
     auto copy = [&](const tile::Descriptor& src, int buf, int i) {
-      tile::copy_1k_checked(lds_base + buf * CTILE_BYTES + wave * 1024 + i * 4096, ld_off, src, i * 4096);
+      tile::copy_1k_checked(lds_base + wave * 1024, buf * CTILE_BYTES + i * 4096, ld_off, src, i * 4096);
     };
     auto fence = [] { __builtin_amdgcn_sched_barrier(0); };
     auto mask_tail = [&](int left, f32x16 (&s)[2]) {

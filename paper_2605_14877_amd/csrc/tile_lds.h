@@ -114,22 +114,32 @@ __device__ __forceinline__ void issue_ragged(unsigned lds_tile, int wave, int la
 // Range-checked form of the copy: buffer_load .. lds with a descriptor that ends where the tile's valid rows end.  Lanes
 // past the end write zeros and touch no memory, so a ragged tile (or one that does not exist: no valid rows) takes the
 // same instructions as a full one, with no per-lane address arithmetic.  The check covers lane offset + soffset.
-typedef int Descriptor __attribute__((ext_vector_type(4)));
+struct Descriptor {
+  unsigned long long base;   // words 0 and 1: address, stride 0
+  unsigned long long bound;  // words 2 and 3: valid bytes, format
+};
 template <int RB = ROW_BYTES>
 __device__ __forceinline__ Descriptor tile_descriptor(const char* src, int left) {
   static_assert(RB == 256 || RB == 128, "row of 256 or 128 bytes");
   // max(0, min(left, ROWS)) rows; as text, because the compiler takes the vector ALU's three-operand form for it.
-  int bytes;
+  unsigned bytes;
   asm("s_min_i32 %0, %1, 64\n\ts_max_i32 %0, %0, 0\n\ts_lshl_b32 %0, %0, %2" : "=s"(bytes) : "s"(left), "n"(RB == 256 ? 8 : 7) : "scc");
-  const unsigned long long a = reinterpret_cast<unsigned long long>(src);
-  return Descriptor{static_cast<int>(a), static_cast<int>((a >> 32) & 0xffff), bytes, 0x00020000};
+  return Descriptor{reinterpret_cast<unsigned long long>(src) & 0xffffffffffffull, bytes | 0x00020000ull << 32};
 }
-// The leading s_nop is the wait state between the write of M0 and the copy (copy_1k has a move there).
-__device__ __forceinline__ void copy_1k_checked(unsigned lds_dst, int lane_off, const Descriptor& tile, int soffset) {
-  asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
-               :
-               : "v"(lane_off), "s"(tile), "s"(soffset), "{m0}"(lds_dst)
-               : "memory");
+// One 1 KB copy to LDS byte address lds_base + lds_off (a constant) + 16 * lane, from byte lane_off + soffset (a constant)
+// of the descriptor's range.  No scalar that the instruction reads may come from the vector ALU (see copy_1k), whatever
+// the compiler does with the operands in front of the statement: M0, descriptor and scalar offset are all written inside
+// it by scalar instructions, into registers of its own (fixed ones, since text cannot name the halves of a quad that the
+// compiler picks; M0 is an output that nobody reads, so that the compiler knows of the write).  One base and constants
+// instead of a destination per copy also spare the scalar registers.
+__device__ __forceinline__ void copy_1k_checked(unsigned lds_base, int lds_off, int lane_off, const Descriptor& tile,
+                                                int soffset) {
+  unsigned m0;
+  asm volatile("s_add_u32 m0, %1, %2\n\ts_mov_b64 s[92:93], %4\n\ts_mov_b64 s[94:95], %5\n\ts_movk_i32 s91, %6\n\t"
+               "buffer_load_dwordx4 %3, s[92:95], s91 offen lds"
+               : "=&{m0}"(m0)
+               : "s"(lds_base), "i"(lds_off), "v"(lane_off), "s"(tile.base), "s"(tile.bound), "i"(soffset)
+               : "memory", "scc", "s91", "s92", "s93", "s94", "s95");
 }
 
 // 8-bit cache rows (FP8 E4M3 codes, 128 bytes per row): a 64-row tile is 8 KB and lands in LDS as it lies in
@@ -141,7 +151,7 @@ __device__ __forceinline__ void issue_raw8(unsigned lds_tile, int wave, int lane
   const Descriptor tile = tile_descriptor<RAW8_ROW_BYTES>(src, left);
 #pragma unroll
   for (int j = 0; j < RAW8_BYTES / (1024 * NW); ++j)
-    copy_1k_checked(lds_tile + (NW * j + wave) * 1024, wave * 1024 + lane * 16, tile, j * (1024 * NW));
+    copy_1k_checked(lds_tile + wave * 1024, NW * j * 1024, wave * 1024 + lane * 16, tile, j * (1024 * NW));
 }
 // Turns a landed 8-bit tile (`raw`, LDS) into the bf16 tile format at `stage` (LDS): NT lanes, 1024 / NT groups of
 // eight codes each; every E4M3 value is a bf16 value, so the conversion is exact.  SWZ_V selects the V swizzle.
