@@ -12,6 +12,7 @@ import numpy as np
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libheatkv.so")
+_CALL_PATH = os.path.join(os.path.dirname(_LIB_PATH), "_heatkv_call.so")
 
 F32, BF16 = 0, 1
 VARIANT_HEATKV, VARIANT_BINARY, VARIANT_NAIVE, VARIANT_BINARY_NAIVE = 0, 1, 2, 3
@@ -41,12 +42,13 @@ def library_path():
 
 
 def lib():
-    """Loads libheatkv.so; there is no fallback when it is missing."""
+    """Loads libheatkv.so and the module _heatkv_call; there is no fallback when one is missing."""
     global _lib
     if _lib is not None:
         return _lib
-    if not os.path.exists(_LIB_PATH):
-        raise ImportError(f"{_LIB_PATH} is not built; run `python -m paper_2605_14877_amd.build`")
+    for path in (_LIB_PATH, _CALL_PATH):
+        if not os.path.exists(path):
+            raise ImportError(f"{path} is not built; run `python -m paper_2605_14877_amd.build`")
     # The library must share PyTorch's HIP runtime (streams and device pointers cross the boundary):
     # importing torch first makes its libamdhip64.so.7 the one the dynamic linker binds us to.
     import torch

@@ -407,6 +407,14 @@ def test_calls_see_a_destroyed_plan_and_a_replaced_shape():
     assert shape.address == ctypes.addressof(shape.c_struct)
 
 
+@pytest.mark.parametrize("path", ["_LIB_PATH", "_CALL_PATH"])
+def test_a_missing_library_or_module_names_the_build(monkeypatch, path):
+    monkeypatch.setattr(hk.binding, "_lib", None)
+    monkeypatch.setattr(hk.binding, path, "/nonexistent.so")
+    with pytest.raises(ImportError, match="is not built; run"):
+        hk.binding.lib()
+
+
 def test_a_tensor_that_raises_ends_in_a_python_error():
     # A subclass with a sizes policy of its own answers is_contiguous() and shape with an exception, in C++ as well.
     class Odd(torch.Tensor):
