@@ -782,6 +782,34 @@ def test_bf16_reference_comes_from_the_first_rows_of_the_current_scale(d, tokens
     assert t_k >= 32 and not device_generation(plan, 0, *_dev(q, k, v), tokens, 1.0)[-1].any()
 
 
+@pytest.mark.parametrize("dtype,fp8,d,H,batch,tokens,den", [
+    ("bf16", False, 128, 4, 1, (1, 63, 65, 127, 390), 1),      # one valid row in a tile, 63, 6; the last with two key streams
+    ("bf16", False, 128, 4, 3, (1, 33, 65, 97, 161), 2),       # runs of different lengths
+    ("bf16", False, 64, 6, 2, (1, 2, 63, 65, 129, 200), 2),
+    ("bf16", False, 128, 16, 7, (1, 70, 1271), 1),             # two query sets
+    ("bf16", True, 128, 4, 3, (1, 33, 65, 97, 161), 2),
+    ("bf16", True, 128, 16, 7, (1, 70, 1271), 1),
+    ("f32", False, 64, 4, 2, (1, 15, 17, 33, 70), 2),
+    ("f32", False, 128, 4, 2, (1, 15, 17, 33, 70), 1),
+])
+def test_values_behind_a_heads_rows_do_not_reach_its_outputs(dtype, fp8, d, H, batch, tokens, den):
+    # NaN in all values of every other head, which lie right behind the rows of the head before, in the scale's tensors and
+    # in the arena: fetched with a ragged tile they would meet probability 0 and come out as NaN.
+    t0, c, K, sm = list(tokens), hi.cumulative_tokens(tokens), len(tokens), 1.0 / np.sqrt(d)
+    cfg = dict(L=1, H=H, d=d, dtype=dtype, batch=batch, sides=[(1, n) for n in t0])
+    w = hi.head_weights(51, 1, H, K)
+    q, k, v = hi.make_qkv_device(51, 0, cfg, w, torch.device("cuda:0"))
+    esz = 1 if fp8 else hi.elem_bytes(dtype)
+    plan = hk.heatkv_build_schedule(hk.Shape(1, H, d, t0, batch, dtype), hi.expected_beta_from_weights(w, t0).astype(np.float32),
+                                    (H * c[-2] // den + H * c[0]) * 2 * d * esz, 1, hk.VARIANT_HEATKV,
+                                    hk.KV_FP8_E4M3 if fp8 else hk.KV_NATIVE)
+    want = device_generation(plan, 0, q, k, v, t0, sm)
+    v[:, 1::2] = float("nan")
+    got = device_generation(plan, 0, q, k, v, t0, sm)
+    for a, b in zip(got, want):
+        assert torch.equal(a[:, ::2], b[:, ::2]) and torch.isfinite(b).all() and torch.isnan(a[:, 1::2]).all()
+
+
 @pytest.mark.parametrize("d,tokens", [
     (128, (1, 64, 65, 128, 129, 257)),     # whole tiles, one row more, last query tiles with and without a second set
     (64, (3, 63, 64, 127, 130, 200, 383)),
