@@ -286,6 +286,7 @@ int heatkv_append_scale(heatkv_plan* plan, int layer, int k, const void* k_new, 
   a.arena_tokens = plan->arena_tokens;
   a.descs = plan->dev.descs + plan->desc_begin[plan->idx(k, layer)];
   a.ndesc = ndesc;
+  a.rows = plan->region_size[plan->idx(k + 1, layer)];
   a.k_new = k_new;
   a.v_new = v_new;
   a.k_arena = k_arena;

@@ -18,7 +18,7 @@ struct AttendArgs {
   const HeadWork* work;      // device [H]: the layer's heads by descending run length, each with its run
   int max_len;               // longest run among the H heads (host copy)
   int uniform_len = -1;      // >= 0: all H runs have this length and lie back to back from row uniform_row0 in
-  int uniform_row0 = 0;      //       head order; the bf16 kernel then needs no table read (the fp32 one ignores it)
+  int uniform_row0 = 0;      //       head order; the kernels then need no table read
   const void *q, *k_cur, *v_cur, *k_arena, *v_arena;
   void* out;
   float sm_scale;
@@ -42,6 +42,7 @@ struct AppendArgs {
   int64_t arena_tokens;
   const CopyDesc* descs;     // device
   int ndesc;
+  int64_t rows;              // that the descriptors move, per batch entry
   const void *k_new, *v_new;
   void *k_arena, *v_arena;
 };

@@ -953,11 +953,13 @@ def test_fp32_infinite_value_in_the_last_row_of_a_ragged_tile(d):
     assert torch.isfinite(torch.cat([got[..., :5], got[..., 6:]], -1)).all()
 
 
-@pytest.mark.parametrize("dtype,fp8", [("bf16", False), ("bf16", True), ("f32", False)])
-def test_cache_update_with_several_workgroups_per_descriptor(dtype, fp8):
-    # The update's own launch puts four workgroups on a descriptor, the fused one does not; same arenas.
+@pytest.mark.parametrize("dtype,fp8,H,nb", [("bf16", False, 4, 3), ("bf16", True, 4, 3), ("f32", False, 4, 3),
+                                            # up to 9216 descriptors: one workgroup each where they are more than 2304 (4608)
+                                            ("bf16", False, 48, 48), ("bf16", True, 48, 48)])
+def test_cache_update_with_several_workgroups_per_descriptor(dtype, fp8, H, nb):
+    # The update's own launch puts four workgroups on a descriptor unless they are many, the fused one does not; same arenas.
     # Descriptors of 1, 3, 60, 65, 128 and 72 rows: no whole group of chunks, one and a remainder, whole groups only.
-    t0, H, nb, d = [1, 3, 60, 65, 200, 9], 4, 3, 128
+    t0, d = [1, 3, 60, 65, 200, 9], 128
     c, K, sm = hi.cumulative_tokens(t0), 6, 1.0 / np.sqrt(d)
     cfg = dict(L=1, H=H, d=d, dtype=dtype, batch=nb, sides=[(1, n) for n in t0])
     w = hi.head_weights(43, 1, H, K)
