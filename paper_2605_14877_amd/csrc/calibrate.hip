@@ -190,6 +190,7 @@ __global__ __launch_bounds__(256, CSETS == 1 ? 3 : 2) void calibrate_bf16_kernel
     }
   };
 
+  // A step of the one-set instance, in the compiler's order.
   auto tile_step = [&](auto buf_tag) {
     constexpr int buf = decltype(buf_tag)::value;
     // successor of (k2, tile) in block-major order
@@ -208,39 +209,33 @@ __global__ __launch_bounds__(256, CSETS == 1 ? 3 : 2) void calibrate_bf16_kernel
       for (int cb = 0; cb < 2; ++cb)
         ka[cb][ks] = *reinterpret_cast<const bf16x8*>(kt + cb * 32 * CROW_BYTES + k_off[ks]);
     const int left = p.t[k2] - tile * CBN;
+    f32x16 s[2];
 #pragma unroll
-    for (int qs = 0; qs < CSETS; ++qs) {
-      if (qs == 1 && !two_sets) break;
-      f32x16 s[2];
+    for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[cb][r] = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < NK; ++ks)
+#pragma unroll
+      for (int cb = 0; cb < 2; ++cb)
+        s[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[cb][ks], qreg[0][ks], s[cb], 0, 0, 0);
+    // all sixteen operand reads go out before the first MFMA instead of two at a time
+    __builtin_amdgcn_sched_group_barrier(0x100, 2 * NK, 0);
+    __builtin_amdgcn_sched_group_barrier(0x008, 2 * NK, 0);
+    if (left < CBN) {
 #pragma unroll
       for (int cb = 0; cb < 2; ++cb)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) s[cb][r] = 0.f;
-#pragma unroll
-      for (int ks = 0; ks < NK; ++ks)
-#pragma unroll
-        for (int cb = 0; cb < 2; ++cb)
-          s[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[cb][ks], qreg[qs][ks], s[cb], 0, 0, 0);
-      if (qs == 0) {  // all sixteen operand reads go out before the first MFMA instead of two at a time
-        __builtin_amdgcn_sched_group_barrier(0x100, 2 * NK, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 2 * NK, 0);
-      }
-
-      if (left < CBN) {
-#pragma unroll
-        for (int cb = 0; cb < 2; ++cb)
-#pragma unroll
-          for (int r = 0; r < 16; ++r)
-            if (32 * cb + 8 * (r >> 2) + 4 * hl + (r & 3) >= left) s[cb][r] = -INFINITY;
-      }
-      const float mc = m_run[qs] * c;
-      float rs[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int cb = 0; cb < 2; ++cb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) rs[r & 3] += fast_exp2(fmaf(s[cb][r], c, -mc));
-      fold(qs, s, rs, k2, last_of_block);
+        for (int r = 0; r < 16; ++r)
+          if (32 * cb + 8 * (r >> 2) + 4 * hl + (r & 3) >= left) s[cb][r] = -INFINITY;
     }
+    const float mc = m_run[0] * c;
+    float rs[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) rs[r & 3] += fast_exp2(fmaf(s[cb][r], c, -mc));
+    fold(0, s, rs, k2, last_of_block);
     k2 = nk2;
     tile = ntile;
   };
