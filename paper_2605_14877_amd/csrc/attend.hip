@@ -30,8 +30,8 @@ namespace {
 //
 // Tiles go from HBM straight into LDS (buffer_load .. lds, no registers, no LDS
 // store instructions), double-buffered with one barrier per tile; the descriptor's
-// range check takes care of ragged tiles.  A tile is stored row-major, 256 bytes per row, unpadded; the 16-byte chunks of a row are
-// XOR-swizzled with the row number (the lane that fills an LDS slot simply
+// range check takes care of ragged tiles.  A tile is stored row-major, 256 bytes
+// per row, unpadded; the 16-byte chunks of a row are XOR-swizzled with the row number (the lane that fills an LDS slot simply
 // fetches the matching global chunk), K tiles and V tiles each with the pattern
 // that keeps their read instruction free of bank conflicts (tile_lds.h holds the
 // format; the calibration kernel and the measurement probes share it).
@@ -374,8 +374,8 @@ __global__ __launch_bounds__(256 * KS * QS, (KS == 1 && QS == 1) ? 2 : 1) void a
   //   slots of S(g), the V operands of A(g+1) in those of A(g): every operand a whole phase before its MFMA (those
   //   of S(0) and A(0), which only exist after the barrier, in preload() and in the slots of S(0)).
   // The step's tile copies go out one per slot, from the second slot on.  The path into LDS takes 64 bytes per clock
-  // and compute unit, 512 cycles for a K and a V tile; issued together behind the barrier (550 cycles of every step for a
-  // lone wavefront, 740 with two workgroups on the unit) they held back the step's arithmetic.  Spread out: t_k = 4096 of
+  // and compute unit, 512 cycles for a K and a V tile; issued together behind the barrier (by in-kernel clock stamps 550
+  // cycles of every step for a lone wavefront, 740 with two workgroups on the unit) they held back the step's arithmetic.  Spread out: t_k = 4096 of
   // the serving shape 4211 -> 4052 us, 1600: 782 -> 751; two key streams at 1024 tokens (batch 2): 56.5 -> 50.6 us.
   // Where they start (slot 0, 1, 2 or 4) and whether every slot or every second one has a copy makes no difference.
   // Returns this lane's maximum over the new scores (before any tail mask).

@@ -247,8 +247,8 @@ __global__ __launch_bounds__(256, CSETS == 1 ? 3 : 2) void calibrate_bf16_kernel
   // The barrier stands between A and B: by then every wavefront has this tile's operands in registers, so its stage is
   // free for the copies, and the next tile, copied during the phase B before, has landed.  No operand read stands
   // between a barrier and the MFMAs that need it.
-  // Bound: the vector ALU (three instructions per score, busy 78 % of the time that wavefronts are resident) next to the
-  // matrix pipes (63 %), at the 1.8 GHz that this mix leaves.  All 13 scales of a 2B-like layer (16 heads, batch 2): 558
+  // Bound: the vector ALU (three instructions per score, busy 77 % of the time that wavefronts are resident) next to the
+  // matrix pipes (62 %), at the 1.85 GHz that this mix leaves.  All 13 scales of a 2B-like layer (16 heads, batch 2): 558
   // -> 531 us, 1.06 PFLOP/s.  Exponent, exponential and sum of a probability in three successive slots: no faster.
   auto two_set_walk = [&](auto two_tag) {
     constexpr bool kTwo = decltype(two_tag)::value;  // a last tile of at most 128 rows has no set 1

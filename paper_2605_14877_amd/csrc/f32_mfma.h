@@ -8,8 +8,8 @@
 // lane then takes its row in pieces of 16 bytes.
 //
 // Two things about this chip shape the kernels.  (1) fp32 matrix instructions do not overlap with vector-ALU
-// instructions, not even those of another wavefront (32 MFMAs 1.75 ms, 128 FMAs 1.10 ms, both side by side 2.85 ms; with
-// bf16 MFMAs 1.89, 1.13 and 1.94): every vector instruction of a tile step adds to its 1024 (scores, d = 128) or 2048
+// instructions, not even those of another wavefront (loops of 32 MFMAs 1.85 ms, of 128 FMAs 0.63 ms, of both 2.84 ms; with
+// bf16 MFMAs 1.75, 0.57 and 1.90; profiles/f32_kernel_traces_and_overlap.txt): every vector instruction of a tile step adds to its 1024 (scores, d = 128) or 2048
 // cycles, hence the care with addresses below.  (2) The vector L1 coalesces neighbouring lanes only, and in the operand
 // layout those are in different rows: a fetch of keys straight into it costs 64 accesses per instruction, 2048 cycles
 // of the L1 for the tiles of four wavefronts, twice their score MFMAs.  So a wavefront fetches its key tiles into an LDS

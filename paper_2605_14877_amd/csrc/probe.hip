@@ -85,11 +85,14 @@ __global__ __launch_bounds__(256, 2) void probe_tile_step_kernel(const char* kv,
   const int ld_off_v = tile::loader_off_v(wave, lane);
   const unsigned lds_base = __builtin_amdgcn_readfirstlane(static_cast<unsigned>(
       reinterpret_cast<unsigned long long>((__attribute__((address_space(3))) char*)(&lds[0][0][0]))));
-  // Copy of model tile `tile` (K: which = 0, V: which = 1) into buffer `buf`; all addresses stay inside the
-  // 2 * kModelTiles tiles of `kv` and inside the 64 KB of LDS.
-  auto issue = [&](int tile_i, int buf, int which) {
-    const char* src = kv + (which * kModelTiles + (tile_i & (kModelTiles - 1))) * kTileBytes;
-    tile::issue_full(lds_base + buf * (2 * kTileBytes) + which * kTileBytes, wave, which ? ld_off_v : ld_off_k, src);
+  // Model tile `tile_i` (K: which = 0, V: which = 1), and copy i (0..3) of it into buffer `buf`; all addresses stay
+  // inside the 2 * kModelTiles tiles of `kv` and inside the 64 KB of LDS.
+  auto source = [&](int tile_i, int which) {
+    return tile::tile_descriptor(kv + (which * kModelTiles + (tile_i & (kModelTiles - 1))) * kTileBytes, tile::ROWS);
+  };
+  auto copy = [&](const tile::Descriptor& src, int buf, int which, int i) {
+    tile::copy_1k_checked(lds_base + wave * 1024, buf * (2 * kTileBytes) + which * kTileBytes + i * 4096,
+                          which ? ld_off_v : ld_off_k, src, i * 4096);
   };
   f32x16 o[4], s_cur[2], s_nxt[2];
 #pragma unroll
@@ -120,10 +123,12 @@ __global__ __launch_bounds__(256, 2) void probe_tile_step_kernel(const char* kv,
   // the vector and LDS work, scheduling fences between them.  Phases S(g) (the two K-steps of the score product that
   // go with 16-key chunk g, both 32-key blocks) and A(g) (P V of chunk g) alternate; the probabilities of chunk 0
   // are computed in the slots of S(0), those of chunk g+1 in the slots of A(g) and S(g+1), the maxima of the new
-  // scores in the slots of A(3); every LDS operand is read a phase before its MFMA, the first ones right after
-  // the barrier.
+  // scores in the slots of A(3); every LDS operand is read a phase before its MFMA, those of the first two MFMAs right
+  // after the barrier and the others of S(0) and A(0) in the slots of S(0); the tile copies go out one per slot from the
+  // second slot on.
   auto step = [&](int it, auto buf_tag, f32x16 (&s_in)[2], f32x16 (&s_out)[2]) {
     constexpr int buf = decltype(buf_tag)::value;
+    const tile::Descriptor k_src = source(it + 2, 0), v_src = source(it + 1, 1);
     wait_vmcnt<0>();
     __syncthreads();
     const char* kt = lds[buf ^ 1][0];
@@ -142,13 +147,7 @@ __global__ __launch_bounds__(256, 2) void probe_tile_step_kernel(const char* kv,
       vop[chunk][d] = t.v;
     };
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int cb = 0; cb < 2; ++cb) load_k(i, cb);
-#pragma unroll
-    for (int d = 0; d < 4; ++d) load_v(0, d);
-    issue(it + 2, buf, 0);
-    issue(it + 1, buf ^ 1, 1);
+    for (int cb = 0; cb < 2; ++cb) load_k(0, cb);
     const float mc = m_run * c;
     auto p_half = [&](int chunk, int u) {
       const int cb = chunk >> 1, r = 8 * (chunk & 1) + u;
@@ -165,11 +164,21 @@ __global__ __launch_bounds__(256, 2) void probe_tile_step_kernel(const char* kv,
       for (int r = 0; r < 16; ++r) s_out[cb][r] = 0.f;
     fence();
     float mx = -INFINITY;
+    int slot_no = 0;
+    auto copy_slot = [&] {
+      const int i = slot_no++ - 1;
+      if (i >= 0 && i < 8) i < 4 ? copy(k_src, buf, 0, i) : copy(v_src, buf ^ 1, 1, i - 4);
+    };
     auto s_slot = [&](int gch, int i, int& half) {
       const int ks = 2 * gch + (i >> 1), cb = i & 1;
       s_out[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kop[ks][cb], qreg[ks], s_out[cb], 0, 0, 0);
       fence();
+      if (gch == 0) {
+        if (i < 2) load_k(1, cb);
+        load_v(0, i);
+      }
       if (gch < 3) load_k(ks + 2, cb);
+      copy_slot();
       const int n = gch == 0 ? 2 : 1;
       for (int u = 0; u < n; ++u) p_half(gch, half++);
       fence();
@@ -186,6 +195,7 @@ __global__ __launch_bounds__(256, 2) void probe_tile_step_kernel(const char* kv,
         fence();
         if (gch < 3) {
           load_v(gch + 1, d);
+          copy_slot();
           p_half(gch + 1, half++);
         } else {
 #pragma unroll
