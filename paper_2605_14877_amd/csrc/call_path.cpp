@@ -6,8 +6,7 @@
 // checks on the tensors and call the library.  They return its error code, or None for anything that is not plainly
 // in order: the caller then takes the Python path, which names the mistake.  A tensor may answer a question about itself with
 // an exception (one without sizes, a subclass with a sizes policy of its own): that is not plainly in order either.
-#define PY_SSIZE_T_CLEAN
-#include <Python.h>
+#include "python_calls.h"
 
 #include <ATen/hip/impl/HIPStreamMasqueradingAsCUDA.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -107,22 +106,6 @@ PyObject* not_plain() {
   Py_RETURN_NONE;
 }
 
-// The interpreter's lock is released for the library call.
-struct Unlocked {
-  PyThreadState* state = PyEval_SaveThread();
-  ~Unlocked() { PyEval_RestoreThread(state); }
-};
-
-// A C++ exception must not reach the interpreter's C frames.
-template <PyObject* (*F)(PyObject* const*, Py_ssize_t)>
-PyObject* guarded(PyObject*, PyObject* const* a, Py_ssize_t n) {
-  try {
-    return F(a, n);
-  } catch (...) {
-  }
-  return not_plain();  // after the exception is gone: one that came from Python holds its error until then
-}
-
 // scale_call(plan_info, which, layer, k, q, k_cur, v_cur, k_arena, v_arena, sm_scale, out, ws, stream)
 // which: 0 append_scale (q, sm_scale, out and ws unused), 1 attend_scale, 2 attend_append_scale
 PyObject* scale_call(PyObject* const* a, Py_ssize_t n) {
@@ -142,17 +125,11 @@ PyObject* scale_call(PyObject* const* a, Py_ssize_t n) {
   if (which != 0 && (!operand(a[4], shape, info->dtype, &q) || !number(a[9], &sm) ||
                      !operand(a[10], shape, info->dtype, &out) || !buffer(a[11], 0, &ws, &ws_bytes)))
     return not_plain();
-  int rc;
-  {
-    const Unlocked unlocked;
-    if (which == 0)
-      rc = heatkv_append_scale(info->plan, layer, k, kc, vc, ka, va, stream);
-    else if (which == 1)
-      rc = heatkv_attend_scale(info->plan, layer, k, q, kc, vc, ka, va, sm, out, ws, ws_bytes, stream);
-    else
-      rc = heatkv_attend_append_scale(info->plan, layer, k, q, kc, vc, ka, va, sm, out, ws, ws_bytes, stream);
-  }
-  return PyLong_FromLong(rc);
+  return PyLong_FromLong(heatkv::without_lock([&] {
+    if (which == 0) return heatkv_append_scale(info->plan, layer, k, kc, vc, ka, va, stream);
+    if (which == 1) return heatkv_attend_scale(info->plan, layer, k, q, kc, vc, ka, va, sm, out, ws, ws_bytes, stream);
+    return heatkv_attend_append_scale(info->plan, layer, k, q, kc, vc, ka, va, sm, out, ws, ws_bytes, stream);
+  }));
 }
 
 const heatkv_shape* shape_at(PyObject* o) {
@@ -189,18 +166,13 @@ PyObject* calibrate_call(PyObject* const* a, Py_ssize_t n) {
       !number(a[7], &weight) || !calibrate_operands(s, k1, a[4], a[5], a[9], &q, &k_all, &mass) ||
       !beta_operand(s, a[8], &beta) || !buffer(a[10], 0, &ws, &ws_bytes) || !stream_of(a[11], &stream))
     return not_plain();
-  int rc;
-  {
-    const Unlocked unlocked;
-    if (which == 0)
-      rc = heatkv_calibrate(s, layer, k1, q, k_all, sm, static_cast<float*>(mass), ws, ws_bytes, stream);
-    else if (which == 1)
-      rc = heatkv_calibrate_static(s, layer, k1, q, k_all, sm, static_cast<float*>(mass), stream);
-    else
-      rc = heatkv_calibrate_accumulate(s, layer, k1, q, k_all, sm, weight, static_cast<float*>(beta),
-                                       static_cast<float*>(mass), ws, ws_bytes, stream);
-  }
-  return PyLong_FromLong(rc);
+  return PyLong_FromLong(heatkv::without_lock([&] {
+    float* const m = static_cast<float*>(mass);
+    if (which == 0) return heatkv_calibrate(s, layer, k1, q, k_all, sm, m, ws, ws_bytes, stream);
+    if (which == 1) return heatkv_calibrate_static(s, layer, k1, q, k_all, sm, m, stream);
+    return heatkv_calibrate_accumulate(s, layer, k1, q, k_all, sm, weight, static_cast<float*>(beta), m, ws, ws_bytes,
+                                       stream);
+  }));
 }
 
 // calibrate_scales_call(address of the heatkv_shape, layer, k1 list, q list, k_all list, sm_scale, weight, beta,
@@ -230,26 +202,18 @@ PyObject* calibrate_scales_call(PyObject* const* a, Py_ssize_t n) {
       return not_plain();
     k1[i] = static_cast<int32_t>(k);
   }
-  int rc;
-  {
-    const Unlocked unlocked;
-    rc = heatkv_calibrate_scales_accumulate(s, layer, static_cast<int>(scales), k1, q, k_all, sm, weight,
-                                            static_cast<float*>(beta),
-                                            a[8] == Py_None ? nullptr : reinterpret_cast<float* const*>(mass), ws, ws_bytes,
-                                            stream);
-  }
-  return PyLong_FromLong(rc);
-}
-
-template <PyObject* (*F)(PyObject* const*, Py_ssize_t)>
-PyCFunction fastcall() {
-  return reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(guarded<F>));
+  return PyLong_FromLong(heatkv::without_lock([&] {
+    return heatkv_calibrate_scales_accumulate(s, layer, static_cast<int>(scales), k1, q, k_all, sm, weight,
+                                              static_cast<float*>(beta),
+                                              a[8] == Py_None ? nullptr : reinterpret_cast<float* const*>(mass), ws, ws_bytes,
+                                              stream);
+  }));
 }
 
 PyMethodDef methods[] = {{"plan_info", plan_info, METH_VARARGS, nullptr},
-                         {"scale_call", fastcall<scale_call>(), METH_FASTCALL, nullptr},
-                         {"calibrate_call", fastcall<calibrate_call>(), METH_FASTCALL, nullptr},
-                         {"calibrate_scales_call", fastcall<calibrate_scales_call>(), METH_FASTCALL, nullptr},
+                         {"scale_call", heatkv::fastcall<scale_call>(), METH_FASTCALL, nullptr},
+                         {"calibrate_call", heatkv::fastcall<calibrate_call>(), METH_FASTCALL, nullptr},
+                         {"calibrate_scales_call", heatkv::fastcall<calibrate_scales_call>(), METH_FASTCALL, nullptr},
                          {nullptr, nullptr, 0, nullptr}};
 
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_heatkv_call", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};

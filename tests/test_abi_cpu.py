@@ -3,6 +3,9 @@ error paths and the static memory layout.  No GPU needed."""
 import ctypes
 import os
 import re
+import subprocess
+import sys
+import sysconfig
 import time
 
 import numpy as np
@@ -439,6 +442,26 @@ def test_a_tensor_that_raises_ends_in_a_python_error():
                  lambda: hk.heatkv_attend_append_scale(plan, 0, 2, x, x, x, x, x, 1.0, x)):
         with pytest.raises(RuntimeError, match="no answer"):
             call()
+
+
+def test_a_thread_in_a_call_does_not_end_the_process_with_the_interpreter(tmp_path):
+    # A daemon thread that comes back from the library while the interpreter ends is unwound when it takes the lock.
+    subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Werror", "-I", sysconfig.get_paths()["include"],
+                    "-I", os.path.join(ROOT, "paper_2605_14877_amd", "csrc"), os.path.join(ROOT, "tests", "native", "call_lock.cpp"),
+                    "-o", str(tmp_path / "call_lock.so")], check=True)
+    (tmp_path / "run.py").write_text("""
+import call_lock, sys, threading, time
+assert call_lock.fail() is None and call_lock.fail() is None and call_lock.wait(1) == 0
+class Late:
+    def __del__(self):
+        time.sleep(1)  # a module's last reference goes while the interpreter ends
+sys.modules["late"] = Late()
+threading.Thread(target=call_lock.wait, args=(400000,), daemon=True).start()
+time.sleep(0.1)
+print("end")
+""")
+    r = subprocess.run([sys.executable, str(tmp_path / "run.py")], capture_output=True, text=True, timeout=60)
+    assert (r.returncode, r.stdout) == (0, "end\n"), r.stderr[-2000:]
 
 
 @pytest.mark.parametrize("variant", [binding.VARIANT_BINARY, binding.VARIANT_BINARY_NAIVE])
