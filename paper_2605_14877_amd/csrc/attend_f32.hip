@@ -10,13 +10,14 @@
 // stands for column 64 j + 4 n + i, so that 16 lanes read 64 consecutive floats of a V row, 16 bytes each.
 //
 // Bound: the matrix pipe plus the vector instructions that do not overlap with it (f32_mfma.h) where a launch fills the
-// chip (128 pairs x 400 queries x 800 keys, d = 128: 200 us = 105 TFLOP/s of the 151 a large fp32 matrix product reaches
-// here; d = 64, 784 x 1384: 320 us = 111), the distribution of a few workgroups per compute unit below that (16 pairs,
-// 625 + 500 keys: 72 us = 80 TFLOP/s).  The vector-ALU kernel that this one replaced fed its FMAs from LDS and reached 7
-// TFLOP/s (the 625-query layer of a pruned image: 334 -> 58 us).  Keys straight into registers instead of through the
-// stage: 221 us with the compiler's 64-bit vector addresses, 208 us with scalar ones, on the first shape.  Eight
-// wavefronts per workgroup, or 32 queries per workgroup (half the loads per MFMA): 0-15 % slower at every size, the
-// first for the longer merge, the second for the coarser distribution and one wavefront less per SIMD.
+// chip (128 pairs x 400 queries x 800 keys, d = 128: 204 us = 103 TFLOP/s of the 151 a large fp32 matrix product reaches
+// here; d = 64, 784 x 1384: 315 us = 113), the distribution of a few workgroups per compute unit below that (16 pairs,
+// 625 + 500 keys: 70 us = 82 TFLOP/s).  The vector-ALU kernel that this one replaced fed its FMAs from LDS and reached 7
+// TFLOP/s (the 625-query layer of a pruned image: 334 -> 62 us).  On the first shape, before scores and values had their
+// full range (200 us then): keys straight into registers instead of through the stage 221 us with the compiler's 64-bit
+// vector addresses, 208 us with scalar ones.  Eight wavefronts per workgroup, or 32 queries per workgroup (half the loads
+// per MFMA): 0-15 % slower at every size, the first for the longer merge, the second for the coarser distribution and one
+// wavefront less per SIMD.
 #include "attend_params.h"
 #include "device_util.h"
 #include "f32_mfma.h"
