@@ -308,16 +308,7 @@ __global__ __launch_bounds__(256 * KS * QS, (KS == 1 && QS == 1) ? 2 : 1) void a
   // get -inf); returns whether there was one.
   auto mask_tail = [&](int left, f32x16 (&s)[2]) {
     if (left >= BN) return false;  // workgroup-uniform and rare: kept a branch
-    // Register r of block cb holds key 32 cb + 8 (r / 4) + r % 4 + 4 hl: compared as a compile-time constant
-    // against one per-lane limit, formed here and hidden from the optimiser so that it is not turned back into
-    // 32 per-lane key numbers that would live in registers across the whole tile loop (nor into 32 selects).
-    int lim = left - 4 * hl;
-    asm volatile("; ragged tile mask" : "+v"(lim)::"memory");
-#pragma unroll
-    for (int cb = 0; cb < 2; ++cb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r)
-        if (32 * cb + 8 * (r >> 2) + (r & 3) >= lim) s[cb][r] = -INFINITY;
+    tile::mask_rows(left, hl, s);
     return true;
   };
   // Masks the tail of tile j and folds its row maxima into the running reference.

@@ -222,13 +222,7 @@ __global__ __launch_bounds__(256, CSETS == 1 ? 3 : 2) void calibrate_bf16_kernel
     // all sixteen operand reads go out before the first MFMA instead of two at a time
     __builtin_amdgcn_sched_group_barrier(0x100, 2 * NK, 0);
     __builtin_amdgcn_sched_group_barrier(0x008, 2 * NK, 0);
-    if (left < CBN) {
-#pragma unroll
-      for (int cb = 0; cb < 2; ++cb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          if (32 * cb + 8 * (r >> 2) + 4 * hl + (r & 3) >= left) s[cb][r] = -INFINITY;
-    }
+    if (left < CBN) tile::mask_rows(left, hl, s);
     const float mc = m_run[0] * c;
     float rs[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -273,14 +267,7 @@ __global__ __launch_bounds__(256, CSETS == 1 ? 3 : 2) void calibrate_bf16_kernel
     };
     auto fence = [] { __builtin_amdgcn_sched_barrier(0); };
     auto mask_tail = [&](int left, f32x16 (&s)[2]) {
-      if (left >= CBN) return;
-      int lim = left - 4 * hl;
-      asm volatile("; ragged tile mask" : "+v"(lim)::"memory");
-#pragma unroll
-      for (int cb = 0; cb < 2; ++cb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          if (32 * cb + 8 * (r >> 2) + (r & 3) >= lim) s[cb][r] = -INFINITY;
+      if (left < CBN) tile::mask_rows(left, hl, s);
     };
     auto load_k = [&](bf16x8& dst, int buf, int cb, int ks) {
       dst = *reinterpret_cast<const bf16x8*>(lds + buf * CTILE_BYTES + cb * 32 * CROW_BYTES + k_off[ks]);
