@@ -7,7 +7,6 @@
 // running row maxima and row sums in fp32 (online softmax) and normalises once at
 // the end.  This file holds the bf16 kernel and the launcher; fp32: attend_f32.hip.
 #include <atomic>
-#include <cstdlib>
 #include <type_traits>
 
 #include "attend_params.h"
@@ -108,28 +107,9 @@ __global__ __launch_bounds__(256 * KS * QS, (KS == 1 && QS == 1) ? 2 : 1) void a
   const int lw = QS == 1 ? wave : wave_all;                       // its place among the NW that copy a tile
   const int n = lane & 31, hl = lane >> 5;
 
-  // Workgroup ids are dealt round-robin to the 8 XCDs, each with its own L2.  All query tiles of one
-  // (batch row, head) pair read the same K/V, so they are given ids that land on one XCD; pairs are dealt
-  // to XCDs in order of decreasing run length, alternating direction, which balances the work between XCDs.
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  const int turn = fast_div(slot, p.n_qtiles, p.div_qtiles);  // pairs are dealt to the XCDs back and forth (0..7, 7..0, 0..7, ...)
-  const int pair = turn * 8 + ((turn & 1) ? 7 - xcd : xcd);
-  if (pair >= p.H * p.batch) return;
-  const int qt = slot - turn * p.n_qtiles;
-  const int rank = fast_div(pair, p.batch, p.div_batch), b = pair - rank * p.batch;
-  int h, n_prior, run_row;
-  if (p.uniform_len >= 0) {
-    h = rank;
-    n_prior = p.uniform_len;
-    run_row = p.uniform_row0 + h * p.uniform_len;
-  } else {
-    // One 16-byte record: head, first row and length of its run.  Read as constant memory, i.e. by a scalar load: what
-    // follows from it (tile addresses, descriptors) is then known to be wavefront-uniform.
-    const auto* hw = (const __attribute__((address_space(4))) HeadWork*)(p.work) + rank;
-    h = hw->head;
-    n_prior = hw->run_len;
-    run_row = hw->run_row;
-  }
+  Task task;
+  if (!find_task(p, task)) return;
+  const int h = task.h, b = task.b, qt = task.qt, n_prior = task.run_len, run_row = task.run_row;
 
   const int t_k = p.t_k;
   const long long cur_off = (static_cast<long long>(b) * p.H + h) * t_k * D;
@@ -667,15 +647,14 @@ namespace {
 constexpr int TWO_STREAM_LDS_BYTES = 2 * 2 * 2 * TILE_BYTES_D128;  // two streams x two stages x (K, V)
 constexpr int FP8_LDS_BYTES = 2 * 2 * TILE_BYTES_D128 + 2 * tile::RAW8_BYTES;  // two stages x (K, V) + two landing buffers
 constexpr int TWO_STREAM_MAX_BLOCKS = 256;                    // compute units of the chip
-constexpr int TWO_STREAM_MIN_TOKENS = 384;                    // shorter walks gain nothing (measured at 256)
 // Two query sets per workgroup: from this scale size on, when the launch still gives every compute unit two rounds
 // of such workgroups (measured: a single round of 256 is slower than 512 workgroups of 128 queries), and when the
 // last 256-query tile is not mostly empty (1600 tokens: 7 tiles, the last one a quarter full, measured slower).
 constexpr int TWO_SET_MIN_TOKENS = 1024;
 constexpr int TWO_SET_MIN_BLOCKS = 512;
 
-// 128 KB of dynamic LDS need the function attribute raised, once per device.
-hipError_t allow_two_stream_lds() {
+// More than 64 KB of dynamic LDS needs the function attribute raised, once per device.
+hipError_t allow_lds() {
   static std::atomic<unsigned long long> done{0};  // one bit per device ordinal below 64
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
@@ -689,13 +668,14 @@ hipError_t allow_two_stream_lds() {
   if (e == hipSuccess)
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attend_bf16_kernel<1, true, 128, 2>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, FP8_LDS_BYTES);
+  if (e == hipSuccess) e = attend_short_prepare();
   if (e == hipSuccess && dev >= 0 && dev < 64) done.fetch_or(1ull << dev, std::memory_order_release);
   return e;
 }
 
 }  // namespace
 
-hipError_t attend_prepare_device() { return allow_two_stream_lds(); }
+hipError_t attend_prepare_device() { return allow_lds(); }
 
 hipError_t launch_attend(const AttendArgs& a, hipStream_t stream) {
   AttendParams p{};
@@ -746,10 +726,14 @@ hipError_t launch_attend(const AttendArgs& a, hipStream_t stream) {
     set_split((a.t_k + BM - 1) / BM);
     p.div_batch = reciprocal(pairs8, a.batch);
     const dim3 grid(unsigned(p.attend_blocks) + copy_blocks);
+    if (!a.kv_fp8 && attend_short_fits(p, a.d, a.max_len, copy_blocks)) {
+      const hipError_t e = allow_lds();
+      return e == hipSuccess ? launch_attend_short(p, a.d, a.max_len, copy_blocks, stream) : e;
+    }
     if (a.d == 64) {  // rows of 128 bytes: the single-stream instance
       hipLaunchKernelGGL((attend_bf16_kernel<1, false, 64>), grid, dim3(256), 0, stream, p);
     } else if (a.kv_fp8) {  // 8-bit cache rows: the single-stream instances with landing buffers
-      const hipError_t e = allow_two_stream_lds();
+      const hipError_t e = allow_lds();
       if (e != hipSuccess) return e;
       if (two_sets) {
         set_split(wide);
@@ -760,7 +744,7 @@ hipError_t launch_attend(const AttendArgs& a, hipStream_t stream) {
       }
     } else if (p.attend_blocks <= TWO_STREAM_MAX_BLOCKS && a.t_k >= TWO_STREAM_MIN_TOKENS) {
       // At most one workgroup per compute unit: two key streams per workgroup put two wavefronts on every SIMD.
-      const hipError_t e = allow_two_stream_lds();
+      const hipError_t e = allow_lds();
       if (e != hipSuccess) return e;
       hipLaunchKernelGGL((attend_bf16_kernel<2, false, 128>), grid, dim3(512), TWO_STREAM_LDS_BYTES, stream, p);
     } else if (two_sets) {

@@ -47,25 +47,9 @@ __global__ __launch_bounds__(64 * NW) void attend_f32_kernel(AttendParams p) {
   }
   const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // All query tiles of a (batch row, head) pair get ids on one XCD (id % 8): they read the same keys.  Pairs come by
-  // decreasing run length and are dealt back and forth.
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  const int turn = fast_div(slot, p.n_qtiles, p.div_qtiles);
-  const int pair = turn * 8 + ((turn & 1) ? 7 - xcd : xcd);
-  if (pair >= p.H * p.batch) return;
-  const int qt = slot - turn * p.n_qtiles;
-  const int rank = fast_div(pair, p.batch, p.div_batch), b = pair - rank * p.batch;
-  int h, n_prior, run_row;
-  if (p.uniform_len >= 0) {
-    h = rank;
-    n_prior = p.uniform_len;
-    run_row = p.uniform_row0 + h * p.uniform_len;
-  } else {
-    const auto* hw = (const __attribute__((address_space(4))) HeadWork*)(p.work) + rank;  // a scalar load
-    h = hw->head;
-    n_prior = hw->run_len;
-    run_row = hw->run_row;
-  }
+  Task task;
+  if (!find_task(p, task)) return;
+  const int h = task.h, b = task.b, qt = task.qt, n_prior = task.run_len, run_row = task.run_row;
   const int t_k = p.t_k;
   const long long cur_off = (static_cast<long long>(b) * p.H + h) * t_k * D;
   const long long run_off = (static_cast<long long>(b) * p.arena_tokens + run_row) * D;

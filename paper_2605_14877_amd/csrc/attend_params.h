@@ -45,7 +45,43 @@ __device__ __forceinline__ void touch_params(const AttendParams& p) {
                "s"(p.v_cur), "s"(p.k_arena), "s"(p.v_arena), "s"(p.out), "s"(p.sm_scale), "s"(p.attend_blocks));
 }
 
-// attend_f32.hip; `p` filled in except for the split into workgroups, copy_blocks = workgroups of the fused update.
+// What an attention workgroup works on: query tile qt of a (batch row, head) pair, and the head's run in the arena.
+struct Task {
+  int h, b, qt, run_row, run_len;
+};
+// Workgroup ids are dealt round-robin to the 8 XCDs, each with its own L2.  All query tiles of a pair read the same K/V, so
+// they have ids on one XCD; pairs come by decreasing run length and are dealt to the XCDs back and forth (0..7, 7..0, ...),
+// which balances them.  False: a pair past the end (pairs are padded to a multiple of 8).
+__device__ __forceinline__ bool find_task(const AttendParams& p, Task& t) {
+  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+  const int turn = fast_div(slot, p.n_qtiles, p.div_qtiles);
+  const int pair = turn * 8 + ((turn & 1) ? 7 - xcd : xcd);
+  if (pair >= p.H * p.batch) return false;
+  t.qt = slot - turn * p.n_qtiles;
+  const int rank = fast_div(pair, p.batch, p.div_batch);
+  t.b = pair - rank * p.batch;
+  if (p.uniform_len >= 0) {
+    t.h = rank;
+    t.run_len = p.uniform_len;
+    t.run_row = p.uniform_row0 + t.h * p.uniform_len;
+  } else {
+    // One 16-byte record: head, first row and length of its run.  Read as constant memory, i.e. by a scalar load: what
+    // follows from it (tile addresses, descriptors) is then known to be wavefront-uniform.
+    const auto* hw = (const __attribute__((address_space(4))) HeadWork*)(p.work) + rank;
+    t.h = hw->head;
+    t.run_len = hw->run_len;
+    t.run_row = hw->run_row;
+  }
+  return true;
+}
+
+constexpr int TWO_STREAM_MIN_TOKENS = 384;  // two key streams per workgroup (attend.hip): shorter walks gain nothing
+
+// attend_f32.hip and attend_short.hip (bf16, native cache rows); `p` filled in except for the split into workgroups,
+// max_len = longest run, copy_blocks = workgroups of the fused update.
 hipError_t launch_attend_f32(AttendParams p, int d, unsigned copy_blocks, hipStream_t stream);
+bool attend_short_fits(const AttendParams& p, int d, int max_len, unsigned copy_blocks);
+hipError_t launch_attend_short(AttendParams p, int d, int max_len, unsigned copy_blocks, hipStream_t stream);
+hipError_t attend_short_prepare();  // once per device
 
 }  // namespace heatkv

@@ -39,6 +39,7 @@ __device__ __forceinline__ uint4 bf16x16_to_e4m3(const uint4& lo, const uint4& h
 // they take turns over its groups of chunks.
 __device__ __forceinline__ void copy_rows_block(const CopyParams& p, int desc, int b, int part = 0, int parts = 1) {
   const CopyDesc d = p.descs[desc];
+  const int lane = threadIdx.x & 255;
   const long long cpr = p.kv_fp8 ? p.chunks_per_row / 2 : p.chunks_per_row;  // chunks of an arena row
   const long long arena_base = static_cast<long long>(b) * p.arena_tokens * cpr;
   if (p.kv_fp8 && d.src_kind != 0) {  // rows of the new scale enter the 8-bit cache: one output chunk per lane and turn
@@ -47,7 +48,7 @@ __device__ __forceinline__ void copy_rows_block(const CopyParams& p, int desc, i
     uint4* kd = p.k_arena + arena_base + static_cast<long long>(d.dst_row) * cpr;
     uint4* vd = p.v_arena + arena_base + static_cast<long long>(d.dst_row) * cpr;
     const int total = d.nrows * static_cast<int>(cpr);
-    for (int i = part * 256 + threadIdx.x; i < total; i += 256 * parts) {
+    for (int i = part * 256 + lane; i < total; i += 256 * parts) {
       const uint4 k0 = ks[2 * i], k1 = ks[2 * i + 1], v0 = vs[2 * i], v1 = vs[2 * i + 1];
       kd[i] = bf16x16_to_e4m3(k0, k1);
       vd[i] = bf16x16_to_e4m3(v0, v1);
@@ -71,7 +72,7 @@ __device__ __forceinline__ void copy_rows_block(const CopyParams& p, int desc, i
   // Whole groups of 4 x 256 chunks take the unconditional path (eight loads in flight per lane, all values
   // in registers); the remainder goes one chunk per lane at a time.
   const int whole = total & ~1023;
-  for (int i = part * 1024 + threadIdx.x; i < whole; i += 1024 * parts) {
+  for (int i = part * 1024 + lane; i < whole; i += 1024 * parts) {
     const uint4 k0 = ks[i], k1 = ks[i + 256], k2 = ks[i + 512], k3 = ks[i + 768];
     const uint4 v0 = vs[i], v1 = vs[i + 256], v2 = vs[i + 512], v3 = vs[i + 768];
     kd[i] = k0;
@@ -83,7 +84,7 @@ __device__ __forceinline__ void copy_rows_block(const CopyParams& p, int desc, i
     vd[i + 512] = v2;
     vd[i + 768] = v3;
   }
-  for (int i = whole + part * 256 + threadIdx.x; i < total; i += 256 * parts) {
+  for (int i = whole + part * 256 + lane; i < total; i += 256 * parts) {
     const uint4 k0 = ks[i], v0 = vs[i];
     kd[i] = k0;
     vd[i] = v0;

@@ -200,19 +200,22 @@ __device__ __forceinline__ void reader_off_v(int lane, int (&v_off)[RB / 64]) {
   }
 }
 
-// Scores of a tile with only `left` valid rows: keys past the end get -inf.  s[cb][r] of lane (n, hl) is key 32 cb +
+// Scores of 32 keys of which only `left` (possibly none) are valid: the others get -inf.  s[r] of lane (n, hl) is key
 // 8 (r / 4) + r % 4 + 4 hl, compared as a constant against one per-lane limit.  The limit is hidden from the optimiser anew
-// for every register: otherwise it keeps 32 key numbers in registers across the caller's loop, or sees that one comparison
-// implies the next and joins them by a chain of 31 scalar ORs of vector results (830 cycles a tile instead of 300).
-__device__ __forceinline__ void mask_rows(int left, int hl, f32x16 (&s)[2]) {
+// for every register: otherwise it keeps the key numbers in registers across the caller's loop, or sees that one comparison
+// implies the next and joins them by a chain of scalar ORs of vector results (830 cycles a tile instead of 300).
+__device__ __forceinline__ void mask_block(int left, int hl, f32x16& s) {
   int lim = left - 4 * hl;
 #pragma unroll
-  for (int cb = 0; cb < 2; ++cb)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      asm("; ragged tile mask" : "+v"(lim));
-      s[cb][r] = 32 * cb + 8 * (r >> 2) + (r & 3) < lim ? s[cb][r] : -INFINITY;
-    }
+  for (int r = 0; r < 16; ++r) {
+    asm("; ragged tile mask" : "+v"(lim));
+    s[r] = 8 * (r >> 2) + (r & 3) < lim ? s[r] : -INFINITY;
+  }
+}
+// The same for a tile with `left` valid rows.
+__device__ __forceinline__ void mask_rows(int left, int hl, f32x16 (&s)[2]) {
+  mask_block(left, hl, s[0]);
+  mask_block(left - 32, hl, s[1]);
 }
 
 }  // namespace tile
