@@ -218,11 +218,13 @@ int heatkv_plan_sets(const heatkv_plan* plan, int k, int which, uint8_t* bitmap)
   if (!plan->from_schedule) return fail(HEATKV_EINVAL, "plan was loaded from an explicit pattern");
   const int kmax = which == HEATKV_SET_A ? plan->K : plan->K - 1;
   if (k < 0 || k >= kmax) return fail(HEATKV_EINVAL, "scale index out of range");
-  const std::vector<uint8_t>* src = which == HEATKV_SET_G ? &plan->G : which == HEATKV_SET_E ? &plan->E
+  const std::vector<uint32_t>* src = which == HEATKV_SET_G ? &plan->G : which == HEATKV_SET_E ? &plan->E
                                     : which == HEATKV_SET_A ? &plan->A : nullptr;
   if (!src) return fail(HEATKV_EINVAL, "unknown set");
-  const size_t KT = size_t(plan->K) * plan->T;
-  std::memcpy(bitmap, src->data() + size_t(k) * KT, KT);
+  const size_t T = size_t(plan->T);
+  const uint32_t* masks = src->data() + size_t(k) * T;
+  for (int i = 0; i < plan->K; ++i)
+    for (size_t head = 0; head < T; ++head) bitmap[size_t(i) * T + head] = uint8_t(masks[head] >> i & 1u);
   return HEATKV_OK;
 }
 

@@ -66,10 +66,9 @@ uint64_t order_bits(double x) {
   return u ^ (u >> 63 ? ~uint64_t(0) : uint64_t(1) << 63);
 }
 
-// Stable ascending order of the heads by an fp64 score; ties keep the flat head id order.  From a few hundred heads on:
-// a radix sort on the upper 32 bits, stable, then a stable sort of every run of ties of those 32 bits on the full value
-// (1280 heads: 13 us with scores spread over 10 %, 34 with scores that agree to 1e-7, 63 with a comparison sort of all;
-// 10240 heads: 164, 745 and 811).
+// Stable ascending order of the heads by an fp64 score; ties keep the flat head id order.  From a few hundred heads on: a
+// radix sort, stable, on the upper 22 bits of the range that the scores span, then a stable sort of every run of ties of
+// those bits on the full value.  No branch depends on the scores but for the ties.
 std::vector<int32_t> rank_heads(const std::vector<double>& score) {
   const size_t n = score.size();
   std::vector<int32_t> order(n);
@@ -79,44 +78,46 @@ std::vector<int32_t> rank_heads(const std::vector<double>& score) {
     return order;
   }
   constexpr int BITS = 11, DIGITS = 1 << BITS;
-  struct Item {
-    uint64_t key;
-    int32_t head;
-  };
-  std::vector<Item> x(n), y(n);
-  std::vector<uint32_t> count(3 * DIGITS, 0);
+  std::vector<uint64_t, UnclearedAllocator<uint64_t>> key(n), x(n), y(n);  // x, y: digits above bit 32, head below
+  uint64_t least = ~uint64_t(0), most = 0;
   for (size_t i = 0; i < n; ++i) {
-    const uint64_t key = order_bits(score[i]);
-    x[i] = Item{key, int32_t(i)};
-    for (int d = 0; d < 3; ++d) ++count[d * DIGITS + ((key >> (32 + BITS * d)) & (DIGITS - 1))];
+    key[i] = order_bits(score[i]);
+    least = std::min(least, key[i]);
+    most = std::max(most, key[i]);
   }
-  for (int d = 0; d < 3; ++d) {
-    uint32_t* c = &count[d * DIGITS];
-    const int shift = 32 + BITS * d;
-    if (c[(x[0].key >> shift) & (DIGITS - 1)] == n) continue;  // the digit is the same everywhere
-    uint32_t first = 0;
-    for (int v = 0; v < DIGITS; ++v) {
-      const uint32_t here = c[v];
-      c[v] = first;
-      first += here;
-    }
-    for (const Item& it : x) y[c[(it.key >> shift) & (DIGITS - 1)]++] = it;
-    x.swap(y);
+  if (least == most) return order;
+  const int shift = std::max(0, 64 - 2 * BITS - __builtin_clzll(most - least));
+  uint32_t low[DIGITS] = {}, high[DIGITS] = {};
+  for (size_t i = 0; i < n; ++i) {
+    const uint64_t q = (key[i] - least) >> shift;
+    x[i] = q << 32 | i;
+    ++low[q & (DIGITS - 1)];
+    ++high[q >> BITS];
   }
+  uint32_t a = 0, b = 0;
+  for (int v = 0; v < DIGITS; ++v) {
+    const uint32_t la = low[v], hb = high[v];
+    low[v] = a;
+    high[v] = b;
+    a += la;
+    b += hb;
+  }
+  for (const uint64_t it : x) y[low[it >> 32 & (DIGITS - 1)]++] = it;
+  for (const uint64_t it : y) x[high[it >> (32 + BITS)]++] = it;
+  for (size_t i = 0; i < n; ++i) order[i] = int32_t(x[i]);
   for (size_t i = 0, end; i < n; i = end) {
-    for (end = i + 1; end < n && x[end].key >> 32 == x[i].key >> 32; ++end) {}
+    for (end = i + 1; end < n && x[end] >> 32 == x[i] >> 32; ++end) {}
     if (end - i > 16) {
-      std::stable_sort(x.begin() + i, x.begin() + end, [](const Item& a, const Item& b) { return a.key < b.key; });
+      std::stable_sort(order.begin() + i, order.begin() + end, [&](int32_t a, int32_t b) { return key[a] < key[b]; });
       continue;
     }
     for (size_t k = i + 1; k < end; ++k) {
-      const Item it = x[k];
+      const int32_t it = order[k];
       size_t j = k;
-      for (; j > i && x[j - 1].key > it.key; --j) x[j] = x[j - 1];
-      x[j] = it;
+      for (; j > i && key[order[j - 1]] > key[it]; --j) order[j] = order[j - 1];
+      order[j] = it;
     }
   }
-  for (size_t i = 0; i < n; ++i) order[i] = x[i].head;
   return order;
 }
 
@@ -152,7 +153,6 @@ void head_scores(int K, int T, int s, bool binary, const float* beta, std::vecto
 
 struct Candidate {
   int32_t layer, scale, head;
-  int64_t weight;  // tokens its early removal takes out of a not-yet-run layer
 };
 
 }  // namespace
@@ -182,11 +182,12 @@ int build_sets(heatkv_plan* p, const float* beta) {
     else p->orders[i] = rank_heads(score[i]);
   }
 
-  const size_t KT = size_t(K) * T;
-  p->G.assign(size_t(K) * KT, 0);
-  p->E.assign(size_t(K) * KT, 0);
-  p->A.assign(size_t(K) * KT, 0);
-  auto row = [&](std::vector<uint8_t>& S, int k, int i) { return S.data() + size_t(k) * KT + size_t(i) * T; };
+  p->G.assign(size_t(K) * T, 0);
+  p->E.assign(size_t(K) * T, 0);
+  p->A.assign(size_t(K) * T, 0);
+  const uint32_t all = K - 1 > s ? (1u << (K - 1)) - (1u << s) : 0u;  // source scales that can be pruned
+  std::vector<int32_t> layer_of(T);
+  for (int head = 0; head < T; ++head) layer_of[head] = head / H;
 
   // Cache size per layer: `done` with G_k applied (layers that have run), `todo` with only G_{k-1} applied (layers still
   // to run; early removals lower it).  Both follow from the step before: scale k enters, the newly pruned leave.
@@ -199,31 +200,29 @@ int build_sets(heatkv_plan* p, const float* beta) {
     // G_{k-1}, a shorter prefix, can be removed early.
     const int32_t n = p->N[k], n_before = k > s ? p->N[k - 1] : 0;
     unsorted.clear();
+    uint32_t* g = &p->G[size_t(k) * T];
+    if (k > 0) std::memcpy(g, g - T, T * sizeof(uint32_t));
+    // Tokens that an early removal takes out of a layer that has not run.
+    auto weight = [&](const Candidate& c) { return binary ? int64_t(p->c[k]) - cs : int64_t(p->t[c.scale]); };
     if (k >= s && binary) {
-      uint8_t* g = row(p->G, k, s);
-      if (k > 0) std::memcpy(g, row(p->G, k - 1, s), T);
       for (int r = n_before; r < n; ++r) {
         const int head = p->orders[s][r];
-        g[head] = 1;
-        unsorted.push_back({head / H, 0, head, int64_t(p->c[k]) - cs});
+        g[head] = all;
+        unsorted.push_back({layer_of[head], 0, head});
       }
-      for (int i = s + 1; i < K - 1; ++i) std::memcpy(row(p->G, k, i), g, T);
     } else if (k >= s) {
-      for (int i = k; i >= s; --i) {
-        uint8_t* g = row(p->G, k, i);
-        if (i < k) std::memcpy(g, row(p->G, k - 1, i), T);
+      for (int i = k; i >= s; --i)
         for (int r = i < k ? n_before : 0; r < n; ++r) {
           const int head = p->orders[i][r];
-          g[head] = 1;
-          unsorted.push_back({head / H, i, head, int64_t(p->t[i])});
+          g[head] |= 1u << i;
+          unsorted.push_back({layer_of[head], i, head});
         }
-      }
     }
     for (int l = 0; l < L; ++l) {
       todo[l] = done[l] + (k < s ? 0 : int64_t(binary ? whole[l] : H) * p->t[k]);
       done[l] = todo[l];
     }
-    for (const Candidate& c : unsorted) done[c.layer] -= c.weight;
+    for (const Candidate& c : unsorted) done[c.layer] -= weight(c);
     if (binary)
       for (const Candidate& c : unsorted) --whole[c.layer];
 
@@ -241,12 +240,8 @@ int build_sets(heatkv_plan* p, const float* beta) {
     size_t next = 0;
     auto pop = [&]() {
       const Candidate& cd = cand[next++];
-      if (binary) {
-        for (int i = s; i < K - 1; ++i) row(p->E, k, i)[cd.head] = 1;
-      } else {
-        row(p->E, k, cd.scale)[cd.head] = 1;
-      }
-      todo[cd.layer] -= cd.weight;
+      p->E[size_t(k) * T + cd.head] |= binary ? all : 1u << cd.scale;
+      todo[cd.layer] -= weight(cd);
       return cd.layer;
     };
     if (naive) {
@@ -258,40 +253,22 @@ int build_sets(heatkv_plan* p, const float* beta) {
       M += done[l] - todo[l];
       while (M > B) {
         if (next >= cand.size()) return fail(HEATKV_EBUDGET, "early pruning cannot reach the budget");
-        const int64_t w = cand[next].weight;
+        const int64_t w = weight(cand[next]);
         if (pop() > l) M -= w;
       }
     }
     // A_k = G_{k-1} u E_k
-    for (int i = s; i < K - 1; ++i) {
-      uint8_t* a = row(p->A, k, i);
-      if (next == 0) {  // nothing was removed early
-        if (k > 0) std::memcpy(a, row(p->G, k - 1, i), T);
-        continue;
-      }
-      const uint8_t* e = row(p->E, k, i);
-      std::memcpy(a, e, T);
-      if (k > 0) {
-        const uint8_t* g = row(p->G, k - 1, i);
-        for (int head = 0; head < T; ++head) a[head] |= g[head];
-      }
-    }
+    uint32_t* a = &p->A[size_t(k) * T];
+    const uint32_t* e = &p->E[size_t(k) * T];
+    for (int head = 0; head < T; ++head) a[head] = k > 0 ? g[head - T] | e[head] : e[head];
   }
   // Last scale: nothing is appended any more, so only the removals already decided apply.
-  if (K >= 2) std::memcpy(&p->A[size_t(K - 1) * KT], &p->G[size_t(K - 2) * KT], KT);
+  if (K >= 2) std::memcpy(&p->A[size_t(K - 1) * T], &p->G[size_t(K - 2) * T], T * sizeof(uint32_t));
 
-  p->retained.assign(size_t(K) * T, 0);
-  for (int k = 0; k < K; ++k) {
-    uint32_t* m = &p->retained[size_t(k) * T];
-    for (int i = 0; i < k; ++i) {
-      const uint8_t* a = row(p->A, k, i);
-      const uint32_t bit = 1u << i;
-      if (i < s)
-        for (int head = 0; head < T; ++head) m[head] |= bit;
-      else
-        for (int head = 0; head < T; ++head) m[head] |= a[head] ? 0u : bit;
-    }
-  }
+  p->retained.resize(size_t(K) * T);
+  for (int k = 0; k < K; ++k)
+    for (int head = 0; head < T; ++head)
+      p->retained[size_t(k) * T + head] = ((1u << k) - 1u) & ~p->A[size_t(k) * T + head];
   return HEATKV_OK;
 }
 
@@ -425,18 +402,25 @@ bool place_regions(heatkv_plan* p, int64_t cap) {
 }
 
 // Heads of a layer by descending run length, equal ones in index order.  Up to 64 heads: the place of each is the number
-// of heads in front of it, counted without branches.
+// of heads in front of it, counted without branches over keys that hold length and index.
 void order_by_length(const int32_t* len, int H, int32_t* ord) {
-  if (H > 64) {
+  bool equal = true;
+  int64_t longest = len[0];
+  for (int h = 1; h < H; ++h) {
+    equal = equal && len[h] == len[0];
+    longest = std::max<int64_t>(longest, len[h]);
+  }
+  if (equal || H > 64 || longest >= 1 << 24) {
     std::iota(ord, ord + H, 0);
-    std::stable_sort(ord, ord + H, [&](int32_t a, int32_t b) { return len[a] > len[b]; });
+    if (!equal) std::stable_sort(ord, ord + H, [&](int32_t a, int32_t b) { return len[a] > len[b]; });
     return;
   }
+  int32_t key[64];
+  for (int h = 0; h < H; ++h) key[h] = len[h] * 64 + (63 - h);
   for (int h = 0; h < H; ++h) {
-    const int32_t n = len[h];
+    const int32_t mine = key[h];
     int32_t before = 0;
-    for (int j = 0; j < h; ++j) before += len[j] >= n;
-    for (int j = h + 1; j < H; ++j) before += len[j] > n;
+    for (int j = 0; j < H; ++j) before += key[j] > mine;
     ord[before] = h;
   }
 }
@@ -456,9 +440,11 @@ int derive_layout(heatkv_plan* p) {
   for (int k = 0; k < K; ++k) {
     const uint32_t* m = &p->retained[size_t(k) * T];
     int32_t* len = &p->run_len[p->idx(k, 0, 0)];
-    for (int i = 0; i < k; ++i) {
-      const int32_t t = p->t[i];
-      for (int head = 0; head < T; ++head) len[head] += (m[head] >> i & 1u) ? t : 0;
+    for (int head = 0; k > 0 && head < T; ++head) {  // what the scale before had, less what has left, plus that scale itself
+      const uint32_t before = m[head - T];
+      int32_t n = len[head - T] + ((m[head] >> (k - 1) & 1u) ? p->t[k - 1] : 0);
+      for (uint32_t gone = before & ~m[head]; gone; gone &= gone - 1) n -= p->t[__builtin_ctz(gone)];
+      len[head] = n;
     }
     for (int l = 0; l < L; ++l) {
       int64_t sum = 0;

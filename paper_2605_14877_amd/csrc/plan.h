@@ -68,7 +68,7 @@ struct heatkv_plan {
   // schedule (only when from_schedule)
   std::vector<int32_t> N;                    // [K-1]
   std::vector<std::vector<int32_t>> orders;  // [K] (valid for i in [sinks,K-1)), each [T]
-  std::vector<uint8_t> G, E, A;              // [K][K][T]: set of scale k, source scale i, head
+  std::vector<uint32_t> G, E, A;             // [K][T]: bit i of an entry: source scale i of the head is in the set of scale k
 
   // retained[k*T + head]: bit i set iff prior scale i (< k) is attended at scale k
   std::vector<uint32_t> retained;
