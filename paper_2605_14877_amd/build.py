@@ -13,7 +13,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libheatkv.so")
 PROBE_LIB = os.path.join(HERE, "libheatkv_probe.so")
-LIBRARIES = {LIB: ["plan.cpp", "abi.cpp", "attend.hip", "attend_short.hip", "attend_f32.hip", "append.hip", "calibrate.hip"], PROBE_LIB: ["probe.hip"]}
+LIBRARIES = {LIB: ["plan.cpp", "abi.cpp", "attend.hip", "attend_short.hip", "attend_f32.hip", "attend_f32_split.hip", "append.hip", "calibrate.hip"], PROBE_LIB: ["probe.hip"]}
 CALL_MODULE = os.path.join(HERE, "_heatkv_call.so")
 SOURCES = [src for srcs in LIBRARIES.values() for src in srcs]
 

@@ -675,7 +675,7 @@ hipError_t allow_lds() {
 
 }  // namespace
 
-hipError_t attend_prepare_device() { return allow_lds(); }
+hipError_t attend_prepare_device(int dtype) { return dtype == HEATKV_BF16 ? allow_lds() : attend_f32_split_prepare(); }
 
 hipError_t launch_attend(const AttendArgs& a, hipStream_t stream) {
   AttendParams p{};

@@ -83,5 +83,8 @@ hipError_t launch_attend_f32(AttendParams p, int d, unsigned copy_blocks, hipStr
 bool attend_short_fits(const AttendParams& p, int d, int max_len, unsigned copy_blocks);
 hipError_t launch_attend_short(AttendParams p, int d, int max_len, unsigned copy_blocks, hipStream_t stream);
 hipError_t attend_short_prepare();  // once per device
+// attend_f32_split.hip: the same for fp32 launches of many queries and keys.
+hipError_t launch_attend_f32_split(AttendParams p, int d, unsigned copy_blocks, hipStream_t stream);
+hipError_t attend_f32_split_prepare();  // once per device
 
 }  // namespace heatkv

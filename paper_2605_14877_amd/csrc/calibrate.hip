@@ -18,6 +18,7 @@
 
 #include "device_util.h"
 #include "f32_mfma.h"
+#include "f32_split.h"
 #include "kernels.h"
 #include "tile_lds.h"
 
@@ -562,6 +563,248 @@ __global__ __launch_bounds__(64 * FW) void calibrate_f32_kernel(CalibParams p) {
   }
 }
 
+// ---------------------------------------------------------------------------
+// fp32 scales of many query rows: S^T = K Q^T on the bf16 matrix instructions, operands in three bf16 parts (f32_split.h).
+// 32 queries per workgroup, whose parts every wavefront keeps in registers; key tiles of 32 rows dealt round robin to
+// eight wavefronts.  Otherwise as above.  Bound: vector instructions, 48 for the six products of a step, as in the
+// attention kernel (attend_f32_split.hip).  16 heads, 400 x 937, d = 128: 27.0 -> 21.3 us; 256 pairs, 625 x 2667: 1048 -> 869.
+// ---------------------------------------------------------------------------
+constexpr int SQ = 32;  // queries of a workgroup, keys of a tile
+constexpr int SW = 8;   // wavefronts
+constexpr int kMaxLds = 160 * 1024;
+
+template <int D>
+struct SplitLds {
+  static constexpr int ROW = 4 * D, STAGE = SQ * ROW;
+  static constexpr int BLOCKS = SW * STAGE;            // block sums and references; at first the parts of the query rows
+  static constexpr int PARTS = 3 * (D / 16) * 1024;
+  static constexpr int PER_BLOCK = 2 * SW * SQ * 4;    // [sum, maximum][wavefront][query]
+  static constexpr int REST = SW * SQ * 4 + SQ * 4 + SW * 4;  // final maxima, inverse row sums, flags
+  __host__ __device__ static constexpr size_t bytes(int k1) {
+    return BLOCKS + (PARTS > (k1 + 1) * PER_BLOCK ? PARTS : (k1 + 1) * PER_BLOCK) + REST;
+  }
+};
+
+template <int D>
+__global__ __launch_bounds__(64 * SW) void calibrate_f32_split_kernel(CalibParams p) {
+  using Lds = SplitLds<D>;
+  constexpr int NK = D / 16, ROW = Lds::ROW, CPR = D / 4;
+  constexpr int COPIES = Lds::STAGE / 1024, ROWS = 64 / CPR;  // copies of a tile, rows of one
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
+
+  const int tid = threadIdx.x, lane = tid & 63, n = lane & 31, hl = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  touch_params(p);
+  const ScaleJob& job = p.job[scale_of_block(p, blockIdx.x)];
+  const int k1 = job.k1, t_k1 = p.t[k1];
+  const int n_qtiles = (t_k1 + SQ - 1) / SQ;
+  const int block = blockIdx.x - job.block_begin;
+  const int xcd = block & 7, slot = block >> 3;  // all query tiles of a (batch row, head) on one XCD
+  const int bh = (slot / n_qtiles) * 8 + xcd;
+  if (bh >= p.batch * p.H) return;
+  const int qt = slot % n_qtiles;
+  const int q_rows = min(t_k1 - qt * SQ, SQ);
+  const float* kbase = static_cast<const float*>(job.k_all) + static_cast<long long>(bh) * p.c[k1] * D;
+  const int at_rest = Lds::BLOCKS + (Lds::PARTS > (k1 + 1) * Lds::PER_BLOCK ? Lds::PARTS : (k1 + 1) * Lds::PER_BLOCK);
+  float* const blk = reinterpret_cast<float*>(lds + Lds::BLOCKS);
+  auto blk_sum = [&](int j, int w, int row) -> float& { return blk[(2 * j * SW + w) * SQ + row]; };
+  auto blk_max = [&](int j, int w, int row) -> float& { return blk[((2 * j + 1) * SW + w) * SQ + row]; };
+  float* const fin_max = reinterpret_cast<float*>(lds + at_rest);
+  float* const row_inv = fin_max + SW * SQ;
+  int* const big = reinterpret_cast<int*>(row_inv + SQ);
+
+  // The wavefront's tile: first row, rows from it to the end of its block k2.
+  int k2 = 0, first = 0, rows_left = 0;
+  auto enter = [&](int tile) {  // tile number counted from the start of block k2; carries it over to the block that has it
+    while (k2 <= k1) {
+      const int rows = p.t[k2], here = (rows + SQ - 1) / SQ;
+      if (tile < here) {
+        first = p.c[k2] - rows + tile * SQ;
+        rows_left = rows - tile * SQ;
+        return;
+      }
+      tile -= here;
+      ++k2;
+    }
+  };
+  // Rows past the tile's end are zeros; the 16-byte chunks of a row are XORed with the row number.
+  const unsigned stage = static_cast<unsigned>(
+      reinterpret_cast<unsigned long long>((__attribute__((address_space(3))) char*)(&lds[0]))) + wave * Lds::STAGE;
+  auto fetch = [&] {
+    const tile::Descriptor src =
+        tile::tile_descriptor<ROW>(reinterpret_cast<const char*>(kbase + static_cast<long long>(first) * D), rows_left);
+    const int b = lane / CPR;
+    const int off = b * ROW + (((lane & (CPR - 1)) ^ b) << 4);  // row ROWS i + b, chunk c ^ row = (c ^ b) ^ ROWS i
+#pragma unroll
+    for (int i = 0; i < COPIES; ++i) tile::copy_1k_checked(stage, i * 1024, off ^ ((ROWS * i & 15) << 4), src, i * 1024);
+  };
+  enter(wave);
+  if (k2 <= k1) fetch();
+
+  // Query rows: wavefront `step` splits the elements 16 step + 8 hl .. + 7 of row n, all take the parts of all.
+  const float* const q_row = static_cast<const float*>(job.q) +
+                             (static_cast<long long>(bh) * t_k1 + qt * SQ + min(n, q_rows - 1)) * D + 8 * hl;
+  auto load_q = [&](int step, float (&x)[8]) {
+    const f32x4 a = *reinterpret_cast<const f32x4*>(q_row + 16 * step), b = *reinterpret_cast<const f32x4*>(q_row + 16 * step + 4);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      x[j] = a[j];
+      x[4 + j] = b[j];
+    }
+  };
+  float q_most = 0.f;
+  if (wave < NK) {
+    float x[8];
+    load_q(wave, x);
+    q_most = f32s::magnitude(0.f, x);
+    f32s::Parts parts;
+    f32s::split(parts, x);
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+      *reinterpret_cast<bf16x8*>(lds + Lds::BLOCKS + (i * NK + wave) * 1024 + lane * 16) = parts.part(i);
+  }
+  const bool mine_big = __any(q_most > f32s::LARGEST);
+  if (lane == 0) big[wave] = mine_big;
+  __syncthreads();
+  f32s::Parts qp[NK];
+#pragma unroll
+  for (int step = 0; step < NK; ++step)
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+      qp[step].set(i, *reinterpret_cast<const bf16x8*>(lds + Lds::BLOCKS + (i * NK + step) * 1024 + lane * 16));
+  int q_big = 0;
+#pragma unroll
+  for (int w = 0; w < SW; ++w) q_big |= big[w];
+  q_big = __builtin_amdgcn_readfirstlane(q_big);
+  __syncthreads();  // the parts' place is free
+  for (int j = 0; j <= k1; ++j)  // blocks without a tile of this wavefront
+    if (hl == 0) {
+      blk_sum(j, wave, n) = 0.f;
+      blk_max(j, wave, n) = f32m::LOWEST;
+    }
+  const f32m::Exponent prob(p.sm_scale);
+  auto fence = [] { __builtin_amdgcn_sched_barrier(0); };
+  float m = f32m::LOWEST, cur = 0.f;
+  while (k2 <= k1) {
+    const int here = k2, rows = rows_left;
+    wait_vmcnt<0>();
+    asm volatile("" ::: "memory");
+    // Chunks 4 step + 2 hl and the next one of row n, XORed with the row: address bits in which the row's own has no ones.
+    unsigned k_at = stage + n * ROW + (((2 * hl) ^ (n & 15)) << 4);
+    asm volatile("" : "+v"(k_at));
+    auto load_k = [&](int step, float (&x)[8]) {
+      typedef const __attribute__((address_space(3))) f32x4* LdsChunk;
+      const f32x4 a = *(LdsChunk)(k_at ^ (step << 6)), b = *(LdsChunk)(k_at ^ (step << 6) ^ 16);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        x[j] = a[j];
+        x[4 + j] = b[j];
+      }
+    };
+    f32x16 s, small;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = small[r] = 0.f;
+    // Between the products of a step: the split of the next one's keys, the keys after that.
+    float x[2][8], k_most = 0.f;
+    f32s::Parts kp[2];
+    load_k(0, x[0]);
+    load_k(1, x[1]);
+    k_most = f32s::magnitude(k_most, x[0]);
+    f32s::split(kp[0], x[0]);
+#pragma unroll
+    for (int step = 0; step < NK; ++step)
+#pragma unroll
+      for (int i = 0; i < f32s::PRODUCTS; ++i) {
+        fence();
+        f32s::add_product(i, small, s, kp[step & 1], qp[step]);
+        fence();
+        if (i == 0 && step + 2 < NK) load_k(step + 2, x[step & 1]);
+        if (step + 1 < NK) {
+          if (i == 0) k_most = f32s::magnitude(k_most, x[(step + 1) & 1]);
+          f32s::split_piece(kp[(step + 1) & 1], x[(step + 1) & 1], i);
+        }
+      }
+    fence();
+    if (q_big || __any(k_most > f32s::LARGEST)) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[r] = small[r] = 0.f;
+#pragma unroll 1
+      for (int step = 0; step < NK; ++step) {
+        float y[8], z[8];
+        load_k(step, y);
+        load_q(step, z);
+        f32s::add_f32(s, y, z);
+      }
+      wait_vmcnt<0>();
+    }
+    wait_lgkmcnt0();
+    fence();
+    if (rows_left > SW * SQ) {
+      first += SW * SQ;
+      rows_left -= SW * SQ;
+    } else {
+      const int tiles_left = (rows_left + SQ - 1) / SQ;  // of this block, from the tile on: at most SW
+      ++k2;
+      enter(SW - tiles_left);
+    }
+    if (k2 <= k1) fetch();
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = (s[r] + small[r]) * prob.c;
+    if (rows < SQ) tile::mask_block(rows, hl, s);
+    float m_new = m;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) m_new = fmaxf(m_new, s[r]);
+    cur *= prob(m, m_new);
+    m = m_new;
+    float sum[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int r = 0; r < 16; ++r) sum[r & 3] += prob(s[r], m);
+    cur += (sum[0] + sum[1]) + (sum[2] + sum[3]);
+    if (k2 != here) {  // the wavefront leaves the block
+      const float mb = max_halves(m);
+      const float sb = sum_halves(cur * prob(m, mb));
+      if (hl == 0) {
+        blk_sum(here, wave, n) = sb;
+        blk_max(here, wave, n) = mb;
+      }
+      cur = 0.f;
+    }
+  }
+  m = max_halves(m);
+  if (hl == 0) fin_max[wave * SQ + n] = m;
+  __syncthreads();
+
+  // Row masses relative to the final maximum, normalised; rows past t_k1 contribute nothing.
+  {
+    const int row = tid & (SQ - 1);
+    float mf = fin_max[row];
+#pragma unroll
+    for (int w = 1; w < SW; ++w) mf = fmaxf(mf, fin_max[w * SQ + row]);
+    for (int j = tid / SQ; j <= k1; j += 64 * SW / SQ) {
+      float v = 0.f;
+#pragma unroll
+      for (int w = 0; w < SW; ++w) v += blk_sum(j, w, row) * prob(blk_max(j, w, row), mf);
+      blk_sum(j, 0, row) = v;
+    }
+  }
+  __syncthreads();
+  if (tid < SQ) {
+    float l = 0.f;
+    for (int j = 0; j <= k1; ++j) l += blk_sum(j, 0, tid);
+    row_inv[tid] = tid < q_rows ? 1.f / l : 0.f;
+  }
+  __syncthreads();
+  // One partial per FQ query rows, as the other kernel leaves them.
+  const int n_parts = (t_k1 + FQ - 1) / FQ, half = tid / 32, j = tid % 32;  // MAXK is at most 32
+  const int part = qt * (SQ / FQ) + half;
+  if (half < SQ / FQ && j <= k1 && part < n_parts) {
+    float v = 0.f;
+#pragma unroll
+    for (int rr = 0; rr < FQ; ++rr) v += blk_sum(j, 0, half * FQ + rr) * row_inv[half * FQ + rr];
+    job.partial[(static_cast<long long>(bh) * n_parts + part) * p.K + j] = v;
+  }
+}
+
 // Sum of one (batch row, head, key block) entry over the query tiles, in tile order, divided by the number of
 // query rows.  The loads of a group of eight go out together (the kernel is a chain of dependent additions fed
 // by L2 latency otherwise); the additions keep the order.
@@ -668,6 +911,19 @@ hipError_t launch_calibrate(const CalibrateArgs& a, hipStream_t stream) {
       wide_blocks += (unsigned long long)((a.t[a.k1[i]] + 2 * CBM1 - 1) / (2 * CBM1)) * a.H * a.batch;
     if (wide_blocks >= 512) rows_per_block = 2 * CBM1;
   }
+  int k1_last = 0, t_most = 0;
+  unsigned long long blocks16 = 0, blocks32 = 0;
+  for (int i = 0; i < a.n_scales; ++i) {
+    const unsigned long long pairs8 = (unsigned(a.H) * a.batch + 7) / 8 * 8;
+    k1_last = std::max(k1_last, a.k1[i]);
+    t_most = std::max(t_most, a.t[a.k1[i]]);
+    blocks16 += (a.t[a.k1[i]] + FQ - 1) / FQ * pairs8;
+    blocks32 += (a.t[a.k1[i]] + SQ - 1) / SQ * pairs8;
+  }
+  // The block sums of many scales (d = 128: more than 15) do not fit next to the key stages.
+  const size_t split_bytes = a.d == 64 ? SplitLds<64>::bytes(k1_last) : SplitLds<128>::bytes(k1_last);
+  const bool split = !bf16 && split_bytes <= kMaxLds && f32s::pays(a.d, t_most, blocks16, blocks32);
+  if (split) rows_per_block = SQ;
   if (bf16 && a.d != 128 && a.d != 64) return hipErrorInvalidValue;
   if (!bf16 && a.d != 64 && a.d != 128) return hipErrorInvalidValue;
   // Largest scale first: its workgroups are the long ones, the short ones then fill the gaps they leave.
@@ -717,6 +973,25 @@ hipError_t launch_calibrate(const CalibrateArgs& a, hipStream_t stream) {
       hipLaunchKernelGGL((calibrate_bf16_kernel<1, 64>), dim3(blocks), dim3(256), lds_bytes, stream, p);
     else
       hipLaunchKernelGGL((calibrate_bf16_kernel<2, 64>), dim3(blocks), dim3(256), lds_bytes, stream, p);
+  }
+  else if (split) {
+    static std::atomic<unsigned long long> raised{0};  // one bit per device ordinal below 64
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    if (dev < 0 || dev >= 64 || !(raised.load(std::memory_order_acquire) >> dev & 1)) {
+      e = hipFuncSetAttribute(reinterpret_cast<const void*>(&calibrate_f32_split_kernel<64>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds);
+      if (e == hipSuccess)
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&calibrate_f32_split_kernel<128>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds);
+      if (e != hipSuccess) return e;
+      if (dev >= 0 && dev < 64) raised.fetch_or(1ull << dev, std::memory_order_release);
+    }
+    if (a.d == 64)
+      hipLaunchKernelGGL(calibrate_f32_split_kernel<64>, dim3(blocks), dim3(64 * SW), split_bytes, stream, p);
+    else
+      hipLaunchKernelGGL(calibrate_f32_split_kernel<128>, dim3(blocks), dim3(64 * SW), split_bytes, stream, p);
   }
   else if (a.d == 64)
     hipLaunchKernelGGL(calibrate_f32_kernel<64>, dim3(blocks), dim3(256), 0, stream, p);

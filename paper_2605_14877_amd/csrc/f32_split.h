@@ -1,0 +1,119 @@
+// fp32 contractions on the bf16 matrix instructions, shared by the fp32 kernels (attention, calibration).
+//
+// A float is the exact sum of three bf16 numbers: x1 = bf16(x), x2 = bf16(x - x1), x3 = x - x1 - x2 (8 significant bits each;
+// the differences are exact).  Of the nine products of two such sums six are taken; the others are below 2^-26 of x * y,
+// less than half a unit in the last place of a float.  Six bf16 instructions do the work of sixteen fp32 ones of the same
+// duration, and unlike those they overlap with vector instructions.  The sum of the five small products has an accumulator
+// of its own where there is room for one.
+//
+// Valid for operands up to LARGEST in magnitude (products and their sums stay finite, no part rounds to infinity, infinities
+// and the difference of two of them do not occur); the caller checks (`magnitude`) and takes the fp32 instructions on the
+// same operand layout (32x32x2) otherwise.  NaN stays NaN.
+#pragma once
+
+#include "device_util.h"
+
+namespace heatkv {
+namespace f32s {
+
+// Whether a launch of fp32 scales takes a kernel on these parts (32 queries per workgroup, one workgroup per compute unit) or
+// one on the fp32 instructions (16, up to four): the former where it needs fewer turns of 256 workgroups.  A turn of it takes
+// 1.1 times one of the latter, whose second and third take 0.55 and 0.95 more (d = 128, 400 queries x 1513 keys: 37 us and 41,
+// at twice the heads 58 and 42, at three times 92 and 71; at 264 against 504 workgroups 47 and 64).  Short scales have
+// more of its longer start, merge and, where the cache update rides along, of the turns that update takes: 100 queries x 193
+// keys 14.1 -> 12.6 us, with the update 1.08 times as long; full chip, d = 128: 196 x 533 153 -> 141 us, 625 x 2407 1067 ->
+// 880; d = 64: 75 -> 81 and 522 -> 492.  Calibration alike (625 x 2667 1048 -> 869, d = 64 585 -> 503).
+// blocks16, blocks32: workgroups of either; t: queries of the largest scale.
+inline bool pays(int d, int t, unsigned long long blocks16, unsigned long long blocks32) {
+  const unsigned long long turns16 = (blocks16 + 255) / 256, turns32 = (blocks32 + 255) / 256;
+  return t >= 128 && turns32 < turns16 && (turns32 == 1 || t >= (d == 64 ? 320 : 196));
+}
+
+constexpr float LARGEST = 0x1p60f;
+// Values whose largest is below this go to the fp32 instructions as well: their third parts would become subnormal bf16.
+constexpr float SMALLEST = 0x1p-60f;
+
+// Eight numbers in three parts: elements 2 i, 2 i + 1 of part k are the halves of w[k][i].
+struct Parts {
+  unsigned w[3][4];
+  __device__ __forceinline__ bf16x8 part(int k) const {
+    return __builtin_bit_cast(bf16x8, make_uint4(w[k][0], w[k][1], w[k][2], w[k][3]));
+  }
+  __device__ __forceinline__ void set(int k, bf16x8 x) {
+    const uint4 u = __builtin_bit_cast(uint4, x);
+    w[k][0] = u.x;
+    w[k][1] = u.y;
+    w[k][2] = u.z;
+    w[k][3] = u.w;
+  }
+};
+
+// Two numbers rounded to a packed pair.  Opaque: the compiler otherwise rounds the low one once more by itself where only it
+// is needed.
+__device__ __forceinline__ unsigned round_pair(float lo, float hi) {
+  unsigned u = __builtin_bit_cast(unsigned, bf16x2{static_cast<bf16_t>(lo), static_cast<bf16_t>(hi)});
+  asm("" : "+v"(u));
+  return u;
+}
+// x - (the low or high half of a pair), exact.  Not as a two-element dot product with (-1, 0) or (0, -1), which would spare
+// the shift: that instruction does not overlap with matrix instructions (next to a 32x32x16 of 36 cycles one of them takes
+// it to 62, four additions to 42).
+__device__ __forceinline__ float minus_low(float x, unsigned h) { return x - __uint_as_float(h << 16); }
+__device__ __forceinline__ float minus_high(float x, unsigned h) { return x - __uint_as_float(h & 0xffff0000u); }
+
+// The split in six pieces, to go between the six products of another step.  x is used up.
+__device__ __forceinline__ void split_piece(Parts& p, float (&x)[8], int piece) {
+  auto round = [&](int k, int i) { p.w[k][i] = round_pair(x[2 * i], x[2 * i + 1]); };
+  auto rest = [&](int k, int i) {
+    x[2 * i] = minus_low(x[2 * i], p.w[k][i]);
+    x[2 * i + 1] = minus_high(x[2 * i + 1], p.w[k][i]);
+  };
+  if (piece == 0) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) round(0, i);
+  } else if (piece == 1) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i) rest(0, i);
+  } else if (piece == 2) {
+    rest(0, 3);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) round(1, i);
+  } else if (piece == 3) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i) rest(1, i);
+  } else if (piece == 4) {
+    rest(1, 3);
+    round(2, 0);
+    round(2, 1);
+  } else {
+    round(2, 2);
+    round(2, 3);
+  }
+}
+__device__ __forceinline__ void split(Parts& p, float (&x)[8]) {
+#pragma unroll
+  for (int i = 0; i < 6; ++i) split_piece(p, x, i);
+}
+
+// Product m = 0..5 of a 32 x 16 by 16 x 32 product, the large one last, which is added to `large`, the others to `small`
+// (which may be the same).  b's part 2 is free after product 0, part 1 after 2, part 0 after 5.
+constexpr int PRODUCTS = 6;
+__device__ __forceinline__ void add_product(int m, f32x16& small, f32x16& large, const Parts& a, const Parts& b) {
+  constexpr int A[PRODUCTS] = {0, 1, 0, 2, 1, 0}, B[PRODUCTS] = {2, 1, 1, 0, 0, 0};
+  f32x16& acc = m == PRODUCTS - 1 ? large : small;
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.part(A[m]), b.part(B[m]), acc, 0, 0, 0);
+}
+// The same product on the fp32 instructions: step j takes element j of both operands.
+__device__ __forceinline__ void add_f32(f32x16& acc, const float (&a)[8], const float (&b)[8]) {
+#pragma unroll
+  for (int j = 0; j < 8; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[j], b[j], acc, 0, 0, 0);
+}
+
+__device__ __forceinline__ float magnitude(float m, const float (&x)[8]) {
+#pragma unroll
+  for (int j = 0; j < 8; j += 2) m = fmaxf(m, fmaxf(fabsf(x[j]), fabsf(x[j + 1])));
+  return m;
+}
+
+}  // namespace f32s
+}  // namespace heatkv

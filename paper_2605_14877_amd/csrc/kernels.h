@@ -77,8 +77,8 @@ hipError_t calibrate_static_workspace(void** ptr);
 hipError_t launch_accumulate_beta(int H, int batch, int K, int layer, int k1, const float* mass, float weight,
                                   float* beta, hipStream_t stream);
 
-// One-time set-up of the attention kernels on the current device (the LDS limit of the two-stream instance);
+// One-time set-up of a dtype's attention kernels on the current device (the LDS limit of those that need more than 64 KB);
 // called at plan upload, repeated calls are cheap.
-hipError_t attend_prepare_device();
+hipError_t attend_prepare_device(int dtype);
 
 }  // namespace heatkv

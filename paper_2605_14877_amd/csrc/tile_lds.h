@@ -120,10 +120,10 @@ struct Descriptor {
 };
 template <int RB = ROW_BYTES>
 __device__ __forceinline__ Descriptor tile_descriptor(const char* src, int left) {
-  static_assert(RB == 256 || RB == 128, "row of 256 or 128 bytes");
+  static_assert(RB == 512 || RB == 256 || RB == 128, "row of 512, 256 or 128 bytes");
   // max(0, min(left, ROWS)) rows; as text, because the compiler takes the vector ALU's three-operand form for it.
   unsigned bytes;
-  asm("s_min_i32 %0, %1, 64\n\ts_max_i32 %0, %0, 0\n\ts_lshl_b32 %0, %0, %2" : "=s"(bytes) : "s"(left), "n"(RB == 256 ? 8 : 7) : "scc");
+  asm("s_min_i32 %0, %1, 64\n\ts_max_i32 %0, %0, 0\n\ts_lshl_b32 %0, %0, %2" : "=s"(bytes) : "s"(left), "n"(RB == 512 ? 9 : RB == 256 ? 8 : 7) : "scc");
   return Descriptor{reinterpret_cast<unsigned long long>(src) & 0xffffffffffffull, bytes | 0x00020000ull << 32};
 }
 // One 1 KB copy to LDS byte address lds_base + lds_off (a constant) + 16 * lane, from byte lane_off + soffset (a constant)

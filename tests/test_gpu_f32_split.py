@@ -1,0 +1,116 @@
+"""fp32 attention and calibration on three bf16 parts (csrc/f32_split.h): every row against the oracle at the edges of its
+tiles, and operands outside the range of the parts against the kernels on the fp32 instructions, which the same heads take
+in a launch of few workgroups."""
+import numpy as np
+import pytest
+import torch
+
+import heatkv_inputs as hi
+import paper_2605_14877_amd as hk
+from oracle import heatkv_oracle as orc
+from tests import harness
+from tests.gpu_driver import device_generation
+from tests.test_gpu_parity import TOL, _check_all, _dev
+
+pytestmark = pytest.mark.gpu
+
+
+# From the third scale on more than 256 workgroups of 16 queries, at most 256 of 32; the last one takes more than one turn of
+# either.  Blocks of 32 keys and queries: one row over, whole, one short; runs that end next to and at a block's end.
+@pytest.mark.parametrize("d,H,batch,tokens", [
+    (128, 6, 5, (1, 31, 129, 160, 191)),
+    (64, 5, 6, (2, 30, 143, 224)),
+    (128, 5, 13, (1, 64, 257)),
+])
+def test_attention_at_the_edges(d, H, batch, tokens):
+    t0, K, sm = list(tokens), len(tokens), 1.0 / np.sqrt(d)
+    cfg = dict(L=1, H=H, d=d, dtype="f32", batch=batch, sides=[(1, n) for n in t0])
+    c = hi.cumulative_tokens(t0)
+    B = H * c[-2] * 2 // 3 + H * c[0]
+    w = hi.head_weights(71, 1, H, K)
+    beta = hi.expected_beta_from_weights(w, t0).astype(np.float32)
+    plan = hk.heatkv_build_schedule(hk.Shape(1, H, d, t0, batch, "f32"), beta, B * 2 * d * 4, 1)
+    q, k, v = hi.make_qkv(71, 0, cfg, w=w)
+    outs = device_generation(plan, 0, *_dev(q, k, v), t0, sm, fused=True)
+    for a, b in zip(outs, device_generation(plan, 0, *_dev(q, k, v), t0, sm)):
+        assert torch.equal(a, b)
+    _check_all(outs, q, k, v, t0, harness.oracle_schedule(beta, 1, H, t0, 1, B)["present"], 0, sm, TOL["f32"])
+
+
+@pytest.mark.parametrize("d,H,batch,tokens", [(128, 6, 5, (1, 31, 129, 160)), (64, 5, 6, (2, 30, 143, 224))])
+def test_calibration_at_the_edges(d, H, batch, tokens):
+    t0, c, K, sm = list(tokens), hi.cumulative_tokens(tokens), len(tokens), 1.0 / np.sqrt(d)
+    cfg = dict(L=1, H=H, d=d, dtype="f32", batch=batch, sides=[(1, n) for n in t0])
+    q, k, _ = hi.make_qkv(72, 0, cfg, w=hi.head_weights(72, 1, H, K))
+    shape = hk.Shape(1, H, d, t0, batch, "f32")
+    mass = torch.empty(batch, H, K, device="cuda")
+    ws = torch.empty(hk.binding.calibrate_workspace_bytes(shape, K - 1), dtype=torch.uint8, device="cuda")
+    hk.heatkv_calibrate(shape, 0, K - 1, *_dev(q[:, :, c[-1] - t0[-1]:].contiguous(), k), sm, mass, ws)
+    got = mass.cpu().double().numpy()
+    for b in range(batch):
+        for h in range(H):
+            want = orc.beta_row(q[b, h].double().numpy(), k[b, h].double().numpy(), orc.one_based(t0), K, sm)
+            assert np.abs(got[b, h] - want[1:]).max() <= 1e-5, (b, h)  # as the kernel on the fp32 instructions
+
+
+KINDS = ["plain", "keys of -inf", "keys of the lowest value", "an infinite key", "large keys", "large queries, small keys",
+         "large values", "tiny values", "an infinite value", "a NaN value", "a NaN query"]
+
+
+def _operands(kind, d, n):
+    g = torch.Generator().manual_seed(73)
+    q, k, v = (torch.randn(1, 1, n, d, generator=g) for _ in range(3))
+    if kind.startswith("keys of"):
+        q[..., 0], k[:, :, 3::5, 0] = 1.0, -float("inf") if "inf" in kind else torch.finfo(torch.float32).min
+    elif kind == "an infinite key":
+        k[:, :, n - 7, 5] = float("inf")
+    elif kind == "large keys":
+        k[:, :, 2::7] *= 2.0 ** 70
+    elif kind == "large queries, small keys":
+        q, k = q * 2.0 ** 65, k * 2.0 ** -65
+    elif kind == "large values":
+        v = v * 2.0 ** 110
+    elif kind == "tiny values":
+        v = v * 2.0 ** -112
+    elif kind == "an infinite value":
+        v[:, :, n - 9, 3] = float("inf")
+    elif kind == "a NaN value":
+        v[:, :, n - 9, 3] = float("nan")
+    elif kind == "a NaN query":
+        q[:, :, n - 3, 7] = float("nan")
+    return q, k, v
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("d", [64, 128])
+def test_attention_beyond_the_range_of_the_parts(d, kind):
+    tokens, many = [1, 33, 147], 32
+    q, k, v = _dev(*_operands(kind, d, sum(tokens)))
+    outs = []
+    for batch in (1, many):
+        plan = hk.heatkv_build_schedule(hk.Shape(1, 1, d, tokens, batch, "f32"), harness.random_beta(5, 1, 1, 3),
+                                        34 * 2 * d * 4, 1)
+        rep = lambda x: x.repeat(batch, 1, 1, 1).contiguous()
+        outs.append(device_generation(plan, 0, rep(q), rep(k), rep(v), tokens, 1.0 / np.sqrt(d))[-1])
+    a, b = outs[0].double(), outs[1].double()
+    assert torch.equal(b, b[:1].expand_as(b)) or torch.isnan(b).any()
+    # Two fp32 evaluations: scores of up to 2^3 in the exponent with errors of 1e-6, and sums of 181 products.  One-hot
+    # softmax rows (large keys) are decided by scores far apart.
+    scale = v[torch.isfinite(v)].abs().max().item()
+    torch.testing.assert_close(b[:1], a, rtol=1e-5, atol=1e-5 * scale, equal_nan=True)
+
+
+@pytest.mark.parametrize("kind", [x for x in KINDS if "value" not in x or "lowest" in x])
+@pytest.mark.parametrize("d", [64, 128])
+def test_calibration_beyond_the_range_of_the_parts(d, kind):
+    tokens, many = [1, 33, 147], 32
+    q, k, _ = _dev(*_operands(kind, d, sum(tokens)))
+    got = []
+    for batch in (1, many):
+        shape = hk.Shape(1, 1, d, tokens, batch, "f32")
+        mass = torch.empty(batch, 1, 3, device="cuda")
+        ws = torch.empty(hk.binding.calibrate_workspace_bytes(shape, 2), dtype=torch.uint8, device="cuda")
+        hk.heatkv_calibrate(shape, 0, 2, q[:, :, 34:].repeat(batch, 1, 1, 1).contiguous(), k.repeat(batch, 1, 1, 1).contiguous(),
+                            1.0 / np.sqrt(d), mass, ws)
+        got.append(mass.double())
+    torch.testing.assert_close(got[1], got[0].expand_as(got[1]), rtol=0, atol=1e-6, equal_nan=True)

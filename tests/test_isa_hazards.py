@@ -17,7 +17,7 @@ import pytest
 
 from paper_2605_14877_amd import build as hb
 
-SOURCES_WITH_COPIES = ["attend.hip", "attend_short.hip", "attend_f32.hip", "calibrate.hip", "probe.hip"]
+SOURCES_WITH_COPIES = ["attend.hip", "attend_short.hip", "attend_f32.hip", "attend_f32_split.hip", "calibrate.hip", "probe.hip"]
 NO_SCALAR_RESULT = ("s_cmp", "s_cbranch", "s_branch", "s_waitcnt", "s_nop", "s_barrier", "s_endpgm", "s_setprio",
                     "s_sleep", "s_bitcmp", "s_setpc", "s_inst_prefetch", "s_sethalt")
 
