@@ -1,0 +1,47 @@
+"""The reductions behind the calibration kernels against the sums they stand for, bit for bit: the partial sums that a call
+leaves in its workspace added in tile order, divided by the number of query rows, and the batch rows added in order."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2605_14877_amd as hk
+
+pytestmark = pytest.mark.gpu
+
+
+# Query tiles (of 16 rows, bf16: 128): one, one group of sixteen less one, whole, one over, two over; batch rows: one turn of
+# eight less seven, whole, one over, two turns and one; 5 * 7 entries of beta are a block of 32 and three.
+@pytest.mark.parametrize("with_mass", [True, False])
+@pytest.mark.parametrize("dtype,t,batch", [
+    ("f32", 16, 8), ("f32", 239, 1), ("f32", 256, 9), ("f32", 257, 2), ("f32", 520, 17), ("bf16", 128, 9), ("bf16", 2100, 3),
+])
+def test_partial_sums_in_order(dtype, t, batch, with_mass):
+    H, K, d, k1, L = 5, 7, 64, 4, 2
+    tokens = [1, 2, 5, 9, t, 11, 13]
+    tile = 16 if dtype == "f32" else 128
+    tiles = -(-t // tile)
+    torch.manual_seed(91)
+    kind = torch.float32 if dtype == "f32" else torch.bfloat16
+    q = torch.randn(batch, H, t, d).to("cuda", kind)
+    k = torch.randn(batch, H, sum(tokens[:k1 + 1]), d).to("cuda", kind)
+    shape = hk.Shape(L, H, d, tokens, batch, dtype)
+    ws = torch.empty(hk.binding.calibrate_workspace_bytes(shape, k1), dtype=torch.uint8, device="cuda")
+    mass = torch.full((batch, H, K), -1.0, device="cuda")
+    beta = torch.rand(L, H, K, K).cuda()
+    before = beta.cpu().numpy()
+    hk.heatkv_calibrate_accumulate(shape, 1, k1, q, k, d ** -0.5, 0.25, beta, mass if with_mass else None, ws)
+    parts = ws.cpu().numpy().view(np.float32)[:batch * H * tiles * K].reshape(batch, H, tiles, K)
+    want = np.zeros((batch, H, K), np.float32)
+    for i in range(tiles):
+        want[..., :k1 + 1] += parts[:, :, i, :k1 + 1]
+    want /= np.float32(t)
+    if with_mass:
+        assert np.array_equal(mass.cpu().numpy(), want)
+    total = np.zeros((H, K), np.float32)
+    for b in range(batch):
+        total += want[b]
+    after = before.copy()
+    after[1, :, k1] += np.float32(0.25) * total  # a power of two: one rounding, with or without a fused multiply-add
+    assert np.array_equal(beta.cpu().numpy(), after)
+    hk.heatkv_calibrate(shape, 1, k1, q, k, d ** -0.5, mass, ws)
+    assert np.array_equal(mass.cpu().numpy(), want)
