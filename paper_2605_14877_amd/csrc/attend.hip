@@ -5,7 +5,8 @@
 // followed by the t_k rows of the current scale; queries are the t_k rows of
 // the current scale.  The kernel walks this virtual key sequence in tiles, keeps
 // running row maxima and row sums in fp32 (online softmax) and normalises once at
-// the end.  This file holds the bf16 kernel and the launcher; fp32: attend_f32.hip.
+// the end.  This file holds the bf16 kernel and the launcher; bf16 launches of short walks or few workgroups:
+// attend_short.hip; fp32: attend_f32.hip and, for many queries, attend_f32_split.hip.
 #include <atomic>
 #include <type_traits>
 

@@ -1,4 +1,4 @@
-// Kernel arguments of the attention kernels (attend.hip: bf16, attend_f32.hip: fp32).
+// Kernel arguments of the attention kernels (bf16: attend.hip, attend_short.hip; fp32: attend_f32.hip, attend_f32_split.hip).
 #pragma once
 
 #include "copy_rows.h"

@@ -563,7 +563,7 @@ __global__ __launch_bounds__(64 * FW) void calibrate_f32_kernel(CalibParams p) {
 // fp32 scales of many query rows: S^T = K Q^T on the bf16 matrix instructions, operands in three bf16 parts (f32_split.h).
 // 32 queries per workgroup, whose parts every wavefront keeps in registers; key tiles of 32 rows dealt round robin to
 // eight wavefronts.  Otherwise as above.  Bound: vector instructions, 48 for the six products of a step, as in the
-// attention kernel (attend_f32_split.hip).  16 heads, 400 x 937, d = 128: 27.0 -> 21.3 us; 256 pairs, 625 x 2667: 1048 -> 869.
+// attention kernel (attend_f32_split.hip).  d = 128: 256 pairs, 625 x 2667 keys 1048 -> 869 us.
 // ---------------------------------------------------------------------------
 constexpr int SQ = 32;  // queries of a workgroup, keys of a tile
 constexpr int SW = 8;   // wavefronts
@@ -940,41 +940,50 @@ hipError_t launch_calibrate(const CalibrateArgs& a, hipStream_t stream) {
       wide_blocks += (unsigned long long)((a.t[a.k1[i]] + 2 * CBM1 - 1) / (2 * CBM1)) * a.H * a.batch;
     if (wide_blocks >= 512) rows_per_block = 2 * CBM1;
   }
-  int k1_last = 0, t_most = 0;
-  unsigned long long blocks16 = 0, blocks32 = 0;
-  for (int i = 0; i < a.n_scales; ++i) {
-    const unsigned long long pairs8 = (unsigned(a.H) * a.batch + 7) / 8 * 8;
-    k1_last = std::max(k1_last, a.k1[i]);
-    t_most = std::max(t_most, a.t[a.k1[i]]);
-    blocks16 += (a.t[a.k1[i]] + FQ - 1) / FQ * pairs8;
-    blocks32 += (a.t[a.k1[i]] + SQ - 1) / SQ * pairs8;
-  }
-  // The block sums of many scales (d = 128: more than 15) do not fit next to the key stages.
-  const size_t split_bytes = a.d == 64 ? SplitLds<64>::bytes(k1_last) : SplitLds<128>::bytes(k1_last);
-  const bool split = !bf16 && split_bytes <= kMaxLds && f32s::pays(a.d, t_most, blocks16, blocks32);
-  if (split) rows_per_block = SQ;
+  // The (batch row, head) pairs are padded to a multiple of 8 so that id % 8 is the XCD.
+  const unsigned pairs = (unsigned(a.H) * a.batch + 7) / 8 * 8;
+  // fp32: the kernel of a scale follows from that scale alone, so that a launch of several has the bits of one each; the scales
+  // of either kernel are a launch, and the second one no longer fills the gaps of the first.  Hence only large scales on three
+  // bf16 parts (all scales up to the largest in one call, fp32 instructions alone -> both, d = 128): 16 pairs, 400 rows 37 -> 39 us,
+  // 48 x 256 40 -> 42, 72 x 256 39 -> 41, 64 x 400 107 -> 109, 64 x 484 140 -> 124, 128 x 256 93 -> 83, 256 x 400 314 -> 291; d = 64, where
+  // parts cost as much for half the work: 64 x 400 63 -> 68.  The block sums of many scales (d = 128: more than 15) do not fit next to the key stages.
+  auto split_bytes = [&](int k1) { return a.d == 64 ? SplitLds<64>::bytes(k1) : SplitLds<128>::bytes(k1); };
+  auto takes_split = [&](int i) {
+    const int t = a.t[a.k1[i]];
+    const unsigned long long blocks16 = (unsigned long long)((t + FQ - 1) / FQ) * pairs;
+    return !bf16 && split_bytes(a.k1[i]) <= kMaxLds && blocks16 >= (a.d == 64 ? 8192 : 1920) &&
+           f32s::pays(a.d, t, blocks16, (unsigned long long)((t + SQ - 1) / SQ) * pairs);
+  };
   if (bf16 && a.d != 128 && a.d != 64) return hipErrorInvalidValue;
   if (!bf16 && a.d != 64 && a.d != 128) return hipErrorInvalidValue;
   // Largest scale first: its workgroups are the long ones, the short ones then fill the gaps they leave.
   int order[MAXK];
   for (int i = 0; i < a.n_scales; ++i) order[i] = i;
   std::stable_sort(order, order + a.n_scales, [&](int x, int y) { return a.t[a.k1[x]] > a.t[a.k1[y]]; });
-  // The (batch row, head) pairs are padded to a multiple of 8 so that id % 8 is the XCD.
-  const unsigned pairs = (unsigned(a.H) * a.batch + 7) / 8 * 8;
-  unsigned blocks = 0;
+  const int n_split = int(std::stable_partition(order, order + a.n_scales, takes_split) - order);
+  CalibParams split_p = p;
+  split_p.n_scales = n_split;
+  p.n_scales = a.n_scales - n_split;
+  FinishParams fin{};
+  unsigned blocks = 0, split_blocks = 0;
   size_t ws_off = 0;
-  int k1_max = 0;
+  int k1_max = 0, split_k1_max = 0;
   for (int i = 0; i < a.n_scales; ++i) {
     const int src = order[i];
-    ScaleJob& job = p.job[i];
+    const bool split = i < n_split;
+    ScaleJob& job = split ? split_p.job[i] : p.job[i - n_split];
+    unsigned& begin = split ? split_blocks : blocks;
     job.k1 = a.k1[src];
-    job.block_begin = int(blocks);
+    job.block_begin = int(begin);
     job.q = a.q[src];
     job.k_all = a.k_all[src];
     job.partial = reinterpret_cast<float*>(static_cast<char*>(a.ws) + ws_off);
-    blocks += unsigned((a.t[job.k1] + rows_per_block - 1) / rows_per_block) * pairs;
+    fin.job[i] = FinishJob{job.partial, a.mass[src], job.k1, a.t[job.k1]};
+    const int rows = split ? SQ : rows_per_block;
+    begin += unsigned((a.t[job.k1] + rows - 1) / rows) * pairs;
     ws_off += (calibrate_workspace_bytes(a.dtype, a.d, a.H, a.batch, a.K, a.t[job.k1]) + 255) / 256 * 256;
-    k1_max = job.k1 > k1_max ? job.k1 : k1_max;
+    int& last = split ? split_k1_max : k1_max;
+    last = std::max(last, job.k1);
   }
   if (bf16) {
     // Many scales need more than the default 64 KB of dynamic LDS for the parked block sums: raise the limit to
@@ -1002,7 +1011,7 @@ hipError_t launch_calibrate(const CalibrateArgs& a, hipStream_t stream) {
     else
       hipLaunchKernelGGL((calibrate_bf16_kernel<2, 64>), dim3(blocks), dim3(256), lds_bytes, stream, p);
   }
-  else if (split) {
+  if (n_split > 0) {
     static std::atomic<unsigned long long> raised{0};  // one bit per device ordinal below 64
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -1017,17 +1026,20 @@ hipError_t launch_calibrate(const CalibrateArgs& a, hipStream_t stream) {
       if (dev >= 0 && dev < 64) raised.fetch_or(1ull << dev, std::memory_order_release);
     }
     if (a.d == 64)
-      hipLaunchKernelGGL(calibrate_f32_split_kernel<64>, dim3(blocks), dim3(64 * SW), split_bytes, stream, p);
+      hipLaunchKernelGGL(calibrate_f32_split_kernel<64>, dim3(split_blocks), dim3(64 * SW), split_bytes(split_k1_max), stream,
+                         split_p);
     else
-      hipLaunchKernelGGL(calibrate_f32_split_kernel<128>, dim3(blocks), dim3(64 * SW), split_bytes, stream, p);
+      hipLaunchKernelGGL(calibrate_f32_split_kernel<128>, dim3(split_blocks), dim3(64 * SW), split_bytes(split_k1_max), stream,
+                         split_p);
   }
-  else if (a.d == 64)
-    hipLaunchKernelGGL(calibrate_f32_kernel<64>, dim3(blocks), dim3(256), 0, stream, p);
-  else
-    hipLaunchKernelGGL(calibrate_f32_kernel<128>, dim3(blocks), dim3(256), 0, stream, p);
-  hipError_t e = hipGetLastError();
+  if (!bf16 && p.n_scales > 0) {
+    if (a.d == 64)
+      hipLaunchKernelGGL(calibrate_f32_kernel<64>, dim3(blocks), dim3(256), 0, stream, p);
+    else
+      hipLaunchKernelGGL(calibrate_f32_kernel<128>, dim3(blocks), dim3(256), 0, stream, p);
+  }
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  FinishParams fin{};
   fin.H = a.H;
   fin.batch = a.batch;
   fin.K = a.K;
@@ -1035,10 +1047,6 @@ hipError_t launch_calibrate(const CalibrateArgs& a, hipStream_t stream) {
   fin.beta = a.beta;
   fin.weight = a.weight;
   fin.layer = a.layer;
-  for (int i = 0; i < a.n_scales; ++i) {
-    const ScaleJob& job = p.job[i];
-    fin.job[i] = FinishJob{job.partial, a.mass[order[i]], job.k1, a.t[job.k1]};
-  }
   if (a.beta) {
     hipLaunchKernelGGL(calibrate_finish_accumulate_kernel,
                        dim3((a.H * a.K + FINISH_ENTRIES - 1) / FINISH_ENTRIES, a.n_scales),

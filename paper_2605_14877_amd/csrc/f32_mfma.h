@@ -1,4 +1,5 @@
-// Operand layouts shared by the fp32 matrix-core kernels (attention, calibration).
+// Operand layouts of the kernels on the fp32 matrix instructions (attention, calibration), and the softmax arithmetic that
+// those on three bf16 parts (f32_split.h) share with them.
 //
 // v_mfma_f32_16x16x4_f32: D[16][16] += A[16][4] B[4][16].  Lane L = n + 16 g (n = L % 16, g = L / 16) supplies
 // A[n][g] and B[g][n] and holds D[4 g + r][n] in register r = 0..3.

@@ -22,7 +22,8 @@ namespace f32s {
 // at twice the heads 58 and 42, at three times 92 and 71; at 264 against 504 workgroups 47 and 64).  Short scales have
 // more of its longer start, merge and, where the cache update rides along, of the turns that update takes: 100 queries x 193
 // keys 14.1 -> 12.6 us, with the update 1.08 times as long; full chip, d = 128: 196 x 533 153 -> 141 us, 625 x 2407 1067 ->
-// 880; d = 64: 75 -> 81 and 522 -> 492.  Calibration alike (625 x 2667 1048 -> 869, d = 64 585 -> 503).
+// 880; d = 64: 75 -> 81 and 522 -> 492.  Calibration alike (625 x 2667 1048 -> 869, d = 64 585 -> 503),
+// and from a number of workgroups on (calibrate.hip).
 // blocks16, blocks32: workgroups of either; t: queries of the largest scale.
 inline bool pays(int d, int t, unsigned long long blocks16, unsigned long long blocks32) {
   const unsigned long long turns16 = (blocks16 + 255) / 256, turns32 = (blocks32 + 255) / 256;

@@ -37,7 +37,9 @@ def test_attention_at_the_edges(d, H, batch, tokens):
     _check_all(outs, q, k, v, t0, harness.oracle_schedule(beta, 1, H, t0, 1, B)["present"], 0, sm, TOL["f32"])
 
 
-@pytest.mark.parametrize("d,H,batch,tokens", [(128, 6, 5, (1, 31, 129, 160)), (64, 5, 6, (2, 30, 143, 224))])
+# Calibration takes it from 1920 workgroups of 16 queries on (d = 64: 8192).
+@pytest.mark.parametrize("d,H,batch,tokens", [(128, 6, 5, (1, 31, 129, 961)), (128, 6, 23, (2, 30, 143, 224)),
+                                              (64, 8, 31, (2, 30, 143, 544))])
 def test_calibration_at_the_edges(d, H, batch, tokens):
     t0, c, K, sm = list(tokens), hi.cumulative_tokens(tokens), len(tokens), 1.0 / np.sqrt(d)
     cfg = dict(L=1, H=H, d=d, dtype="f32", batch=batch, sides=[(1, n) for n in t0])
@@ -103,7 +105,7 @@ def test_attention_beyond_the_range_of_the_parts(d, kind):
 @pytest.mark.parametrize("kind", [x for x in KINDS if "value" not in x or "lowest" in x])
 @pytest.mark.parametrize("d", [64, 128])
 def test_calibration_beyond_the_range_of_the_parts(d, kind):
-    tokens, many = [1, 33, 147], 32
+    tokens, many = ([1, 33, 197], 152) if d == 128 else ([1, 33, 321], 392)
     q, k, _ = _dev(*_operands(kind, d, sum(tokens)))
     got = []
     for batch in (1, many):
@@ -114,3 +116,24 @@ def test_calibration_beyond_the_range_of_the_parts(d, kind):
                             1.0 / np.sqrt(d), mass, ws)
         got.append(mass.double())
     torch.testing.assert_close(got[1], got[0].expand_as(got[1]), rtol=0, atol=1e-6, equal_nan=True)
+
+
+# Scales of enough 16-query workgroups among shorter ones: a launch over all of them has the bits of one each.
+@pytest.mark.parametrize("d,tokens", [(128, (1, 250, 40, 190, 230)), (64, (1030, 9, 150, 260))])
+def test_calibration_of_several_scales_has_the_bits_of_one_each(d, tokens):
+    t0, c, K, H, batch, sm = list(tokens), hi.cumulative_tokens(tokens), len(tokens), 8, 16, 1.0 / np.sqrt(d)
+    g = torch.Generator().manual_seed(74)
+    q, k = _dev(*(torch.randn(batch, H, c[-1], d, generator=g) for _ in range(2)))
+    shape = hk.Shape(1, H, d, t0, batch, "f32")
+    qs = [q[:, :, c[i] - t0[i]:c[i]].contiguous() for i in range(K)]
+    ks = [k[:, :, :c[i]].contiguous() for i in range(K)]
+    one, several = (torch.zeros(1, H, K, K, device="cuda") for _ in range(2))
+    for i in range(K):
+        ws = torch.empty(hk.binding.calibrate_workspace_bytes(shape, i), dtype=torch.uint8, device="cuda")
+        hk.heatkv_calibrate_accumulate(shape, 0, i, qs[i], ks[i], sm, 0.25, one, None, ws)
+    for scales in (list(range(K)), [K - 1, 1]):
+        several.zero_()
+        ws = torch.empty(hk.binding.calibrate_scales_workspace_bytes(shape, scales), dtype=torch.uint8, device="cuda")
+        hk.heatkv_calibrate_scales_accumulate(shape, 0, scales, [qs[i] for i in scales], [ks[i] for i in scales], sm, 0.25,
+                                              several, None, ws)
+        assert torch.equal(several[:, :, scales], one[:, :, scales])
