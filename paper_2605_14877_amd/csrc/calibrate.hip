@@ -803,7 +803,7 @@ __global__ __launch_bounds__(64 * SW) void calibrate_f32_split_kernel(CalibParam
 
 // The reductions of a launch's partial sums.  Their bound is the latency of a few dependent reads, so these arguments are a
 // short record of their own (a launch reads it cold), in which all that a thread needs is one read away; reads of tiles and
-// batch rows go out together.  fp32, 8 heads, batch 2, eight calls of up to 25 tiles each with its reduction: 86 -> 83 us.
+// batch rows go out together.  fp32, 8 heads, batch 2, eight calls of up to 25 tiles each with its reduction: 93 -> 89 us.
 struct FinishJob {
   const float* partial;  // [batch*H][n_qtiles][K]
   float* mass;           // [batch*H][K], may be null in the accumulating variant
