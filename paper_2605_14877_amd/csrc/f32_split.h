@@ -31,8 +31,12 @@ inline bool pays(int d, int t, unsigned long long blocks16, unsigned long long b
 }
 
 constexpr float LARGEST = 0x1p60f;
-// Values whose largest is below this go to the fp32 instructions as well: their third parts would become subnormal bf16.
-constexpr float SMALLEST = 0x1p-60f;
+// Below 2^-110 the third part of a number is no longer exact: bf16 has no bits below 2^-133.  Where such a number can decide
+// an output on its own (a column of tiny values next to ordinary ones, a value that only a tiny probability meets) the
+// caller takes the fp32 instructions from this magnitude down; zero has parts.
+constexpr float SMALLEST = 0x1p-100f;
+// Orders like the magnitude, but for zero, which comes last.
+__device__ __forceinline__ unsigned above_zero(float x) { return 2 * __float_as_uint(x) - 1; }
 
 // Eight numbers in three parts: elements 2 i, 2 i + 1 of part k are the halves of w[k][i].
 struct Parts {

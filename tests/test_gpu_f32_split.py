@@ -102,6 +102,38 @@ def test_attention_beyond_the_range_of_the_parts(d, kind):
     torch.testing.assert_close(b[:1], a, rtol=1e-5, atol=1e-5 * scale, equal_nan=True)
 
 
+def _exact(q, k, v, idx, rows, sm):
+    """Attention of the last `rows` queries over the keys idx, in 64 bits."""
+    q, k, v = (x[0, 0].double().cpu() for x in (q, k, v))
+    return torch.softmax(q[-rows:] @ k[idx].T * sm, -1) @ v[idx]
+
+
+# What decides an output need not be large: a column of tiny values next to ordinary ones, values that are zero but where the
+# probabilities are tiny.  The third bf16 part of a number below 2^-110 is inexact, in the worst column by 4e-6 (values of
+# 2^-117) and 2e-4 (probabilities of 2^-117, taken 2^-8 times).  Bounds: sums of fp32 products that are subnormal, each off
+# by 2^-150 where the result is about 2^-125: 6e-7, three times that; scores of 113 in the exponent of 2, off by 2^-24 of that
+# and as much again in the sum of the products: 1e-5, twice that.
+@pytest.mark.parametrize("kind,bound", [("a column of tiny values", 2e-6), ("values under tiny probabilities", 2e-5)])
+@pytest.mark.parametrize("d", [64, 128])
+def test_attention_decided_by_tiny_numbers(d, kind, bound):
+    tokens, many, column, sm = [1, 33, 147], 32, 3, 1.0 / np.sqrt(d)
+    q, k, v = _operands("plain", d, sum(tokens))
+    if kind == "a column of tiny values":
+        v[..., column] *= 2.0 ** -117
+    else:
+        q[..., 0], k[..., 0] = 8.0, 0.0
+        weak = torch.arange(sum(tokens)) % 5 == 3
+        k[:, :, weak, 0] = -78.0 * np.sqrt(d) / 8.0
+        v[:, :, :, column] = torch.where(weak, v[..., column] * 2.0 ** 40, 0.0)
+    plan = hk.heatkv_build_schedule(hk.Shape(1, 1, d, tokens, many, "f32"), harness.random_beta(5, 1, 1, 3), 34 * 2 * d * 4, 1)
+    idx = list(plan.retained(2, 0, 0)) + list(range(34, 181))
+    out = device_generation(plan, 0, *_dev(*(x.repeat(many, 1, 1, 1).contiguous() for x in (q, k, v))), tokens, sm)[-1]
+    want, got = _exact(q, k, v, idx, tokens[-1], sm), out[many - 1, 0].double().cpu()
+    error = (got - want).norm(dim=0) / want.norm(dim=0)
+    assert error[column] <= bound
+    assert error.max() <= (bound if kind == "a column of tiny values" else 2e-5)
+
+
 @pytest.mark.parametrize("kind", [x for x in KINDS if "value" not in x or "lowest" in x])
 @pytest.mark.parametrize("d", [64, 128])
 def test_calibration_beyond_the_range_of_the_parts(d, kind):
