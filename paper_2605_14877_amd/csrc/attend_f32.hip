@@ -174,7 +174,7 @@ __global__ __launch_bounds__(64 * NW) void attend_f32_kernel(AttendParams p) {
 
 hipError_t launch_attend_f32(AttendParams p, int d, unsigned copy_blocks, hipStream_t stream) {
   const unsigned long long all = (unsigned long long)((p.H * p.batch + 7) / 8 * 8);
-  if ((d == 64 || d == 128) && f32s::pays(d, p.t_k, (p.t_k + 15) / 16 * all, (p.t_k + 31) / 32 * all))
+  if ((d == 64 || d == 128) && f32s::pays(d, p.t_k, (p.t_k + 15) / 16 * all, (p.t_k + 31) / 32 * all, p.sm_scale))
     return launch_attend_f32_split(p, d, copy_blocks, stream);
   p.n_qtiles = (p.t_k + f32m::TILE - 1) / f32m::TILE;
   const unsigned pairs8 = (unsigned(p.H) * p.batch + 7) / 8 * 8;  // padded so that id % 8 is the XCD

@@ -952,7 +952,7 @@ hipError_t launch_calibrate(const CalibrateArgs& a, hipStream_t stream) {
     const int t = a.t[a.k1[i]];
     const unsigned long long blocks16 = (unsigned long long)((t + FQ - 1) / FQ) * pairs;
     return !bf16 && split_bytes(a.k1[i]) <= kMaxLds && blocks16 >= (a.d == 64 ? 8192 : 1920) &&
-           f32s::pays(a.d, t, blocks16, (unsigned long long)((t + SQ - 1) / SQ) * pairs);
+           f32s::pays(a.d, t, blocks16, (unsigned long long)((t + SQ - 1) / SQ) * pairs, a.sm_scale);
   };
   if (bf16 && a.d != 128 && a.d != 64) return hipErrorInvalidValue;
   if (!bf16 && a.d != 64 && a.d != 128) return hipErrorInvalidValue;

@@ -25,7 +25,10 @@ namespace f32s {
 // 880; d = 64: 75 -> 81 and 522 -> 492.  Calibration alike (625 x 2667 1048 -> 869, d = 64 585 -> 503),
 // and from a number of workgroups on (calibrate.hip).
 // blocks16, blocks32: workgroups of either; t: queries of the largest scale.
-inline bool pays(int d, int t, unsigned long long blocks16, unsigned long long blocks32) {
+// Not for a softmax scale above 2^20 (or NaN), which makes scores of keys or queries whose parts are inexact (SMALLEST): below
+// it they are off by less than 128 x 2^60 x 2^-134 x 2^20, nothing in an exponent.
+inline bool pays(int d, int t, unsigned long long blocks16, unsigned long long blocks32, float sm_scale) {
+  if (!(fabsf(sm_scale) <= 0x1p20f)) return false;
   const unsigned long long turns16 = (blocks16 + 255) / 256, turns32 = (blocks32 + 255) / 256;
   return t >= 128 && turns32 < turns16 && (turns32 == 1 || t >= (d == 64 ? 320 : 196));
 }

@@ -108,6 +108,48 @@ def _exact(q, k, v, idx, rows, sm):
     return torch.softmax(q[-rows:] @ k[idx].T * sm, -1) @ v[idx]
 
 
+# Errors against 64 bits.  The fp32 instructions have up to 3.3e-7 (norm) here, the parts 1.9e-7, and without one of the
+# six products, in the scores or in P V, 1.7e-6 or more.  Bound: twice that of the fp32 instructions.  Keys of 2^-117 whose softmax scale makes ordinary
+# scores of them have an inexact third part (4e-6): such a scale takes the fp32 instructions.
+SCALED = [("plain", 0), ("tiny keys, large softmax scale", 117)]
+
+
+@pytest.mark.parametrize("kind,up", SCALED)
+@pytest.mark.parametrize("d", [64, 128])
+def test_attention_error_against_64_bits(d, kind, up):
+    tokens, many = [1, 33, 147], 32
+    g = torch.Generator().manual_seed(75)
+    q, k, v = (torch.randn(many, 1, sum(tokens), d, generator=g) for _ in range(3))
+    sm = 2.0 ** up / np.sqrt(d)
+    k *= 2.0 ** -up
+    plan = hk.heatkv_build_schedule(hk.Shape(1, 1, d, tokens, many, "f32"), harness.random_beta(5, 1, 1, 3), 34 * 2 * d * 4, 1)
+    idx = list(plan.retained(2, 0, 0)) + list(range(34, 181))
+    out = device_generation(plan, 0, *_dev(q, k, v), tokens, sm)[-1]
+    for b in (0, 9, many - 1):
+        want = _exact(q[b:], k[b:], v[b:], idx, tokens[-1], sm)
+        assert (out[b, 0].double().cpu() - want).norm() <= 6.6e-7 * want.norm()
+
+
+# Masses of blocks of one key, the query rows of a head all the same, so that no error averages out: rms of the relative error.
+# The fp32 instructions have 2.4e-7, the parts 2.2e-7, and without one of the products 2e-6.  Bound: twice the former.
+@pytest.mark.parametrize("kind,up", SCALED)
+@pytest.mark.parametrize("d,rows,many", [(128, 197, 152), (64, 321, 392)])
+def test_calibration_error_against_64_bits(d, rows, many, kind, up):
+    ones = 12  # with more scales the block sums do not fit next to the stages of the parts (d = 128)
+    tokens = [1] * ones + [rows]
+    g = torch.Generator().manual_seed(76)
+    q = torch.randn(many, 1, 1, d, generator=g).expand(many, 1, rows, d).contiguous()
+    k = torch.randn(many, 1, sum(tokens), d, generator=g) * 2.0 ** -up
+    sm = 2.0 ** up / np.sqrt(d)
+    shape = hk.Shape(1, 1, d, tokens, many, "f32")
+    mass = torch.empty(many, 1, ones + 1, device="cuda")
+    ws = torch.empty(hk.binding.calibrate_workspace_bytes(shape, ones), dtype=torch.uint8, device="cuda")
+    hk.heatkv_calibrate(shape, 0, ones, *_dev(q, k), sm, mass, ws)
+    want = torch.softmax((q[:, 0, :1].double() @ k[:, 0].double().transpose(1, 2)) * sm, -1)[:, 0, :ones]
+    error = mass[:, 0, :ones].double().cpu() / want - 1
+    assert error.square().mean().sqrt() <= 5e-7
+
+
 # What decides an output need not be large: a column of tiny values next to ordinary ones, values that are zero but where the
 # probabilities are tiny.  The third bf16 part of a number below 2^-110 is inexact, in the worst column by 4e-6 (values of
 # 2^-117) and 2e-4 (probabilities of 2^-117, taken 2^-8 times).  Bounds: sums of fp32 products that are subnormal, each off
