@@ -14,6 +14,8 @@
 // keys, of which only chunks of 16 with a valid one are copied and multiplied), 900 in the output, and 1.2 us outside the
 // kernel; a wavefront that does all of it alone takes 2100 + 3300 + 1150 for the same.  A further round adds 3000 to 4000
 // cycles, of which 1700 go to issuing its 64 copies of 1 KB, under the work of the round before.
+#include <algorithm>
+
 #include "attend_params.h"
 #include "device_util.h"
 #include "tile_lds.h"
@@ -327,8 +329,10 @@ hipError_t attend_short_prepare() {
 //   One round, d = 64: 4.2 -> 3.5 us up to 256 workgroups; with the cache update 4.6 -> 3.9, for 512 of them 5.4 -> 6.1.
 //   More rounds, d = 128: two stages leave room for one workgroup per compute unit.  Up to 256 of them 7.2 -> 5.4 us (64 + 140
 //   keys), 13.2 -> 10.0 (144 + 385), 20.5 -> 17.6 (324 + 807); 25.2 -> 24.2 for 27 tiles, 33.3 -> 34.1 for 40.  288
-//   take a second turn: 9.4 -> 12.4.  So do the workgroups of the cache update behind them, two turns of which are hidden
-//   by the long walks: 256 + 224 workgroups 16.8 -> 14.0, 192 + 288 8.6 -> 8.2, 256 + 256 11.6 -> 11.6, 256 + 384 9.2 -> 10.4.
+//   take a second turn: 9.4 -> 12.4.  The workgroups of the cache update take as much room and wait for a unit; how many of them
+//   the walks hide depends on their length (inputs in cache; inputs from memory).  256 + 160 of 9 tiles 14.4 -> 14.5; 16.4 -> 16.8,
+//   240 + 111 of 5 tiles 10.6 -> 10.8; 11.9 -> 12.4, 256 + 192 of 5 tiles 11.6 -> 12.3; 13.9 -> 14.1; but 192 + 160 of 8 tiles
+//   13.4 -> 11.3; 15.1 -> 13.4, 224 + 160 of 10 tiles 15.5 -> 13.4; 17.3 -> 16.1, 256 + 170 of 13 tiles 19.6 -> 19.1; 23.6 -> 21.0.
 //   More rounds, d = 64: 0.94 to 1.09 times the other kernel's time.
 // Never where two key streams may be taken (attend.hip): their outputs have other last bits, and whether a launch carries
 // the cache update must not show in its outputs.
@@ -339,7 +343,8 @@ bool attend_short_fits(const AttendParams& p, int d, int max_len, unsigned copy_
   const unsigned long long blocks = (unsigned long long)((p.t_k + queries - 1) / queries) * pairs8;
   if (tiles <= 2 && d == 64) return blocks <= 256;
   if (tiles <= 2) return p.t_k <= queries || blocks <= (copy_blocks ? 384 : 512);
-  return d == 128 && p.t_k < TWO_STREAM_MIN_TOKENS && tiles <= 24 && blocks <= 256 && blocks + copy_blocks <= 480;
+  return d == 128 && p.t_k < TWO_STREAM_MIN_TOKENS && tiles <= 24 && blocks <= 256 &&
+         blocks + copy_blocks <= unsigned(std::min(272 + 12 * tiles, 480));
 }
 
 hipError_t launch_attend_short(AttendParams p, int d, int max_len, unsigned copy_blocks, hipStream_t stream) {
