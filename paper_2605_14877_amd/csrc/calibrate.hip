@@ -946,13 +946,16 @@ hipError_t launch_calibrate(const CalibrateArgs& a, hipStream_t stream) {
   // of either kernel are a launch, and the second one no longer fills the gaps of the first.  Hence only large scales on three
   // bf16 parts (all scales up to the largest in one call, fp32 instructions alone -> both, d = 128): 16 pairs, 400 rows 37 -> 39 us,
   // 48 x 256 40 -> 42, 72 x 256 39 -> 41, 64 x 400 107 -> 109, 64 x 484 140 -> 124, 128 x 256 93 -> 83, 256 x 400 314 -> 291; d = 64, where
-  // parts cost as much for half the work: 64 x 400 63 -> 68.  The block sums of many scales (d = 128: more than 15) do not fit next to the key stages.
+  // parts cost as much for half the work: 64 x 400 63 -> 68.  One scale alone, below 256 rows only in few turns (128 pairs, 225 x 633
+  // keys, 4 turns 74 -> 64; 384 pairs, 196 x 408, 11 turns 120 -> 124; 625 pairs, 225 x 633, 20 turns 280 -> 289, 324 x 957 540 -> 535).
+  // The block sums of many scales (d = 128: more than 15) do not fit next to the key stages.
   auto split_bytes = [&](int k1) { return a.d == 64 ? SplitLds<64>::bytes(k1) : SplitLds<128>::bytes(k1); };
   auto takes_split = [&](int i) {
     const int t = a.t[a.k1[i]];
     const unsigned long long blocks16 = (unsigned long long)((t + FQ - 1) / FQ) * pairs;
-    return !bf16 && split_bytes(a.k1[i]) <= kMaxLds && blocks16 >= (a.d == 64 ? 8192 : 1920) &&
-           f32s::pays(a.d, t, blocks16, (unsigned long long)((t + SQ - 1) / SQ) * pairs, a.sm_scale);
+    const unsigned long long blocks32 = (unsigned long long)((t + SQ - 1) / SQ) * pairs;
+    return !bf16 && split_bytes(a.k1[i]) <= kMaxLds && blocks16 >= (a.d == 64 ? 8192 : 1920) && (t >= 256 || blocks32 <= 7 * 256) &&
+           f32s::pays(a.d, t, blocks16, blocks32, a.sm_scale);
   };
   if (bf16 && a.d != 128 && a.d != 64) return hipErrorInvalidValue;
   if (!bf16 && a.d != 64 && a.d != 128) return hipErrorInvalidValue;

@@ -17,20 +17,25 @@ namespace heatkv {
 namespace f32s {
 
 // Whether a launch of fp32 scales takes a kernel on these parts (32 queries per workgroup, one workgroup per compute unit) or
-// one on the fp32 instructions (16, up to four): the former where it needs fewer turns of 256 workgroups.  A turn of it takes
-// 1.1 times one of the latter, whose second and third take 0.55 and 0.95 more (d = 128, 400 queries x 1513 keys: 37 us and 41,
-// at twice the heads 58 and 42, at three times 92 and 71; at 264 against 504 workgroups 47 and 64).  Short scales have
-// more of its longer start, merge and, where the cache update rides along, of the turns that update takes: 100 queries x 193
-// keys 14.1 -> 12.6 us, with the update 1.08 times as long; full chip, d = 128: 196 x 533 153 -> 141 us, 625 x 2407 1067 ->
-// 880; d = 64: 75 -> 81 and 522 -> 492.  Calibration alike (625 x 2667 1048 -> 869, d = 64 585 -> 503),
-// and from a number of workgroups on (calibrate.hip).
-// blocks16, blocks32: workgroups of either; t: queries of the largest scale.
+// one on the fp32 instructions (16, up to four): the former where it needs fewer turns of 256 workgroups (blocks16, blocks32:
+// workgroups of either; t: queries).  Attention, fp32 instructions -> parts:
+//   d = 128: 1 turn, 16 pairs 400 x 1939 keys 66 -> 55 us; 2 turns, 529 x 2160 112 -> 103, 784 x 2194 129 -> 102; 264
+//   against 504 workgroups 47 -> 64; full chip, 196 x 855 keys 267 -> 216, 625 x 2525 1253 -> 1048.
+//   d = 64, where the parts cost as much for half the products: 1 turn, 16 pairs 400 x 1939 38 -> 34; more turns only where they
+//   are at most 0.6 times as many (3 against 2: 529 x 2160 59 -> 61, 40 pairs 4 against 3: 400 x 2060 67 -> 72; 4 against 2: 784 x
+//   2194 72 -> 60, 7 against 4: 64 pairs, 400 x 1996 102 -> 98) and from 400 queries on (full chip: 324 x 1660 299 -> 296, 317 ->
+//   319 with the cache update; 529 x 2525 511 -> 483).
+//   Below 196 queries start and merge, which are longer, show, and the update's workgroups, which take a unit each: 40 pairs,
+//   169 x 659 (240 + 240 workgroups) 32.7 -> 27.8 without it, 35.4 -> 36.4 with it; 36 pairs, 144 x 490 (200 + 144) 26.1 -> 21.5.
+// Calibration alike, and from a number of workgroups on (calibrate.hip).
 // Not for a softmax scale above 2^20 (or NaN), which makes scores of keys or queries whose parts are inexact (SMALLEST): below
 // it they are off by less than 128 x 2^60 x 2^-134 x 2^20, nothing in an exponent.
 inline bool pays(int d, int t, unsigned long long blocks16, unsigned long long blocks32, float sm_scale) {
   if (!(fabsf(sm_scale) <= 0x1p20f)) return false;
   const unsigned long long turns16 = (blocks16 + 255) / 256, turns32 = (blocks32 + 255) / 256;
-  return t >= 128 && turns32 < turns16 && (turns32 == 1 || t >= (d == 64 ? 320 : 196));
+  if (turns32 >= turns16) return false;
+  if (t < 196) return t >= 128 && blocks32 <= 224;
+  return d == 128 || turns32 == 1 || (t >= 400 && 5 * turns32 <= 3 * turns16);
 }
 
 constexpr float LARGEST = 0x1p60f;
