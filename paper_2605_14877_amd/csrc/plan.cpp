@@ -66,58 +66,85 @@ uint64_t order_bits(double x) {
   return u ^ (u >> 63 ? ~uint64_t(0) : uint64_t(1) << 63);
 }
 
-// Stable ascending order of the heads by an fp64 score; ties keep the flat head id order.  From a few hundred heads on: a
-// radix sort, stable, on the upper 22 bits of the range that the scores span, then a stable sort of every run of ties of
-// those bits on the full value.  No branch depends on the scores but for the ties.
+// Sorts `n` heads, given in the order of their ids (ALL: all of them), by key, then id; x, y: scratch of n each.  From a few
+// hundred on a radix sort on the upper 22 bits of the range that the keys span, then the same for every run of ties of those
+// bits; 8 bits where there are fewer.  No branch depends on the keys but for the ties, of which there are many where one score
+// lies far from the others (a head without mass on a scale).  Scores spread over 0.1 %: 1280 heads 9.8 us, with one head at
+// zero 19.5 (runs of ties sorted by comparison: 20.2), 10240 heads 136 and 215 (539).
+constexpr size_t RADIX_MIN = 256;
+template <bool ALL>
+void sort_heads(int32_t* order, size_t n, const uint64_t* key, uint64_t* x, uint64_t* y) {
+  if (n <= 16) {
+    for (size_t k = 1; k < n; ++k) {
+      const int32_t it = order[k];
+      size_t j = k;
+      for (; j > 0 && key[order[j - 1]] > key[it]; --j) order[j] = order[j - 1];
+      order[j] = it;
+    }
+    return;
+  }
+  auto head = [&](size_t i) { return ALL ? uint32_t(i) : uint32_t(order[i]); };
+  uint64_t least = ~uint64_t(0), most = 0;
+  for (size_t i = 0; i < n; ++i) {
+    least = std::min(least, key[head(i)]);
+    most = std::max(most, key[head(i)]);
+  }
+  if (least == most) return;
+  const int range = 64 - __builtin_clzll(most - least);
+  int shift;
+  if (n < RADIX_MIN) {
+    constexpr int BITS = 8, DIGITS = 1 << BITS;
+    shift = std::max(0, range - BITS);
+    uint32_t first[DIGITS + 1] = {};
+    for (size_t i = 0; i < n; ++i) {
+      const uint64_t q = (key[head(i)] - least) >> shift;
+      y[i] = q << 32 | head(i);  // digits above bit 32, head below
+      ++first[q + 1];
+    }
+    for (int v = 0; v < DIGITS; ++v) first[v + 1] += first[v];
+    for (size_t i = 0; i < n; ++i) x[first[y[i] >> 32]++] = y[i];
+  } else {
+    constexpr int BITS = 11, DIGITS = 1 << BITS;
+    shift = std::max(0, range - 2 * BITS);
+    uint32_t low[DIGITS] = {}, high[DIGITS] = {};
+    for (size_t i = 0; i < n; ++i) {
+      const uint64_t q = (key[head(i)] - least) >> shift;
+      x[i] = q << 32 | head(i);
+      ++low[q & (DIGITS - 1)];
+      ++high[q >> BITS];
+    }
+    uint32_t a = 0, b = 0;
+    for (int v = 0; v < DIGITS; ++v) {
+      const uint32_t la = low[v], hb = high[v];
+      low[v] = a;
+      high[v] = b;
+      a += la;
+      b += hb;
+    }
+    for (size_t i = 0; i < n; ++i) y[low[x[i] >> 32 & (DIGITS - 1)]++] = x[i];
+    for (size_t i = 0; i < n; ++i) x[high[y[i] >> (32 + BITS)]++] = y[i];
+  }
+  for (size_t i = 0; i < n; ++i) order[i] = int32_t(uint32_t(x[i]));
+  if (shift == 0) return;
+  for (size_t i = 0, end; i < n; i = end) {
+    for (end = i + 1; end < n && x[end] >> 32 == x[i] >> 32; ++end) {}
+    if (end - i > 1) sort_heads<false>(order + i, end - i, key, x + i, y + i);
+  }
+}
+
+// Stable ascending order of the heads by an fp64 score; ties keep the flat head id order.
 std::vector<int32_t> rank_heads(const std::vector<double>& score) {
   const size_t n = score.size();
   std::vector<int32_t> order(n);
-  std::iota(order.begin(), order.end(), 0);
-  if (n < 256) {
+  if (n < RADIX_MIN) {
+    std::iota(order.begin(), order.end(), 0);
     std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return score[a] < score[b]; });
     return order;
   }
-  constexpr int BITS = 11, DIGITS = 1 << BITS;
-  std::vector<uint64_t, UnclearedAllocator<uint64_t>> key(n), x(n), y(n);  // x, y: digits above bit 32, head below
-  uint64_t least = ~uint64_t(0), most = 0;
-  for (size_t i = 0; i < n; ++i) {
-    key[i] = order_bits(score[i]);
-    least = std::min(least, key[i]);
-    most = std::max(most, key[i]);
-  }
-  if (least == most) return order;
-  const int shift = std::max(0, 64 - 2 * BITS - __builtin_clzll(most - least));
-  uint32_t low[DIGITS] = {}, high[DIGITS] = {};
-  for (size_t i = 0; i < n; ++i) {
-    const uint64_t q = (key[i] - least) >> shift;
-    x[i] = q << 32 | i;
-    ++low[q & (DIGITS - 1)];
-    ++high[q >> BITS];
-  }
-  uint32_t a = 0, b = 0;
-  for (int v = 0; v < DIGITS; ++v) {
-    const uint32_t la = low[v], hb = high[v];
-    low[v] = a;
-    high[v] = b;
-    a += la;
-    b += hb;
-  }
-  for (const uint64_t it : x) y[low[it >> 32 & (DIGITS - 1)]++] = it;
-  for (const uint64_t it : y) x[high[it >> (32 + BITS)]++] = it;
-  for (size_t i = 0; i < n; ++i) order[i] = int32_t(x[i]);
-  for (size_t i = 0, end; i < n; i = end) {
-    for (end = i + 1; end < n && x[end] >> 32 == x[i] >> 32; ++end) {}
-    if (end - i > 16) {
-      std::stable_sort(order.begin() + i, order.begin() + end, [&](int32_t a, int32_t b) { return key[a] < key[b]; });
-      continue;
-    }
-    for (size_t k = i + 1; k < end; ++k) {
-      const int32_t it = order[k];
-      size_t j = k;
-      for (; j > i && key[order[j - 1]] > key[it]; --j) order[j] = order[j - 1];
-      order[j] = it;
-    }
-  }
+  std::vector<uint64_t, UnclearedAllocator<uint64_t>> key(n), x(n), y(n);
+  for (size_t i = 0; i < n; ++i) key[i] = order_bits(score[i]);
+  std::iota(order.begin(), order.end(), 0);
+  sort_heads<true>(order.data(), n, key.data(), x.data(), y.data());
   return order;
 }
 

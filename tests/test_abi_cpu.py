@@ -382,6 +382,45 @@ def test_orders_of_many_heads_with_nearly_equal_scores(spread):
         assert plan.order(i).tolist() == np.argsort(scores[i], kind="stable").tolist(), i
 
 
+# One head without mass, one with ten times the others', every ninth without: the other scores lie in a small part of the range.
+def _with_outliers(beta, which):
+    heads = beta.reshape((-1,) + beta.shape[2:])
+    if which == "every ninth at zero":
+        heads[::9] = 0.0
+    elif which != "none":
+        heads[len(heads) // 3] *= 0.0 if which == "one at zero" else 10.0
+    return beta
+
+
+@pytest.mark.parametrize("spread", [0.0, 1e-7, 1e-3, 1e-1])
+@pytest.mark.parametrize("which", ["one at zero", "one at ten times", "every ninth at zero"])
+@pytest.mark.parametrize("L,H", [(8, 32), (40, 32), (80, 64)])
+def test_orders_of_many_heads_with_outliers(L, H, which, spread):
+    t0, s = [1, 4, 9, 16, 25, 36], 1
+    beta = _with_outliers(_nearly_uniform_beta(10, L, H, len(t0), spread), which)
+    shape = hk.Shape(L, H, 64, t0, 1, "bf16")
+    plan = hk.heatkv_build_schedule(shape, beta, L * H * 40 * 2 * 64 * 2, s)
+    scores = hk.heatkv_head_scores(shape, beta, s)
+    for i in range(s, len(t0) - 1):
+        assert plan.order(i).tolist() == np.argsort(scores[i], kind="stable").tolist(), i
+
+
+def test_ranking_with_one_outlier_takes_little_longer():
+    # 16384 heads; where the digits of a radix sort span the range up to the outlier, the rest is left to comparisons
+    L, H, t0 = 128, 128, [1, 4, 9, 16, 25, 36]
+    shape = hk.Shape(L, H, 64, t0, 1, "bf16")
+    seconds = []
+    for which in ("none", "one at zero"):
+        beta = _with_outliers(_nearly_uniform_beta(9, L, H, len(t0), 1e-3), which)[None]
+        best = 1e9
+        for _ in range(15):
+            start = time.perf_counter()
+            hk.heatkv_rank_dispersion(shape, beta, 1)
+            best = min(best, time.perf_counter() - start)
+        seconds.append(best)
+    assert seconds[1] < 2.7 * seconds[0], seconds  # 1.5; 3.9 by comparisons
+
+
 def test_ranking_nearly_equal_scores_takes_no_longer_than_others():
     # 16384 heads; a sort that is quadratic in the number of nearly equal scores takes tens of times as long here
     L, H, t0 = 128, 128, [1, 4, 9, 16, 25, 36]
