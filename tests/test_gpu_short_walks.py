@@ -38,21 +38,53 @@ def test_short_walks_against_the_oracle(d, H, tokens):
     _bf16_case(1, H, tuple((1, n) for n in tokens), 1, 2, 3, seed=62, fused=True, d=d)
 
 
+def _rising(q, k):
+    """Scores that raise the reference from tile to tile: logits climb by far more than 8 in the exponent of 2 along the walk."""
+    n = k.shape[2]
+    q[..., 0], k[..., 0] = 8.0, -torch.arange(n, device=k.device).to(k.dtype) * (400.0 / n)
+    k[:, :, :n // 2, 0] += 300.0  # the run's scores lie above the current scale's
+
+
 @pytest.mark.parametrize("rising", [False, True])
 @pytest.mark.parametrize("d,H,tokens", EDGES)
 def test_short_walks_have_the_bits_of_the_long_ones(d, H, tokens, rising):
     # 512 / H + 1 batch rows: more workgroups than the compute units take at once, so that all scales beyond a workgroup's
-    # queries go to the other kernels.  Rising scores: the reference is raised from tile to tile (logits climb by far more
-    # than 8 in the exponent of 2 along the walk).
+    # queries go to the other kernels (at d = 128 those of up to 32 queries and two tiles do not; next test).
     cfg = dict(L=1, H=H, d=d, dtype="bf16", batch=1, sides=[(1, n) for n in tokens])
     q, k, v = _dev(*hi.make_qkv(63, 0, cfg))
     if rising:
-        n = k.shape[2]
-        q[..., 0], k[..., 0] = 8.0, -torch.arange(n, device="cuda").to(k.dtype) * (400.0 / n)
-        k[:, :, :n // 2, 0] += 300.0  # the run's scores lie above the current scale's
+        _rising(q, k)
     few = _outputs(d, H, tokens, (q, k, v), 1, False)
     fused = _outputs(d, H, tokens, (q, k, v), 1, True)
     many = _outputs(d, H, tokens, (q, k, v), 512 // H + 1, False)
     for a, b, m in zip(few, fused, many):
         assert torch.isfinite(a).all() and torch.equal(a, b)
         assert torch.equal(m, a.expand_as(m))
+
+
+# One round of up to 32 queries, d = 128, goes to the short-walk kernel whatever the number of workgroups, but not in a launch
+# with a longer walk: the same heads next to one that keeps the 100 rows of the first scale, in more workgroups than there
+# are compute units.
+@pytest.mark.parametrize("rising", [False, True])
+@pytest.mark.parametrize("tokens", [(100, 1, 15, 16, 17, 31), (100, 30, 32, 2, 1), (100, 31, 33, 32)])
+def test_one_round_walks_have_the_bits_of_the_long_ones(tokens, rising):
+    H, K, d, batch, tokens = 5, len(tokens), 128, 47, list(tokens)
+    cfg = dict(L=1, H=H + 1, d=d, dtype="bf16", batch=1, sides=[(1, n) for n in tokens])
+    q, k, v = _dev(*hi.make_qkv(64, 0, cfg))
+    if rising:
+        _rising(q, k)
+    outs = []
+    for heads, rows in ((H, 1), (H + 1, batch)):
+        present = np.zeros((K, 1, heads, K), np.uint8)
+        for kk in range(1, K):
+            present[kk, 0, :, 1:kk] = 1
+            present[kk, 0, H:, 0] = 1
+        plan = hk.heatkv_load_schedule(hk.Shape(1, heads, d, tokens, rows, "bf16"), present)
+        qkv = (x[:, :heads].repeat(rows, 1, 1, 1).contiguous() for x in (q, k, v))
+        outs.append(device_generation(plan, 0, *qkv, tokens, 1.0 / np.sqrt(d)))
+    tiles = lambda *rows: sum(-(-n // 64) for n in rows)
+    for kk in range(1, K):
+        run = sum(tokens[1:kk])
+        assert tiles(tokens[kk], run) <= 2 < tiles(tokens[kk], 100 + run) and (H + 1) * batch > 256
+        assert torch.isfinite(outs[0][kk]).all()
+        assert torch.equal(outs[1][kk][:, :H], outs[0][kk].expand(batch, -1, -1, -1)), kk
