@@ -334,9 +334,11 @@ hipError_t attend_short_prepare() {
 //   240 + 111 of 5 tiles 10.6 -> 10.8; 11.9 -> 12.4, 256 + 192 of 5 tiles 11.6 -> 12.3; 13.9 -> 14.1; but 192 + 160 of 8 tiles
 //   13.4 -> 11.3; 15.1 -> 13.4, 224 + 160 of 10 tiles 15.5 -> 13.4; 17.3 -> 16.1, 256 + 170 of 13 tiles 19.6 -> 19.1; 23.6 -> 21.0.
 //   More rounds, d = 64: 0.94 to 1.09 times the other kernel's time.
+// Never for queries off the 4-byte grid: they come by the copies into LDS here, in the other kernels by ordinary loads.
 // Never where two key streams may be taken (attend.hip): their outputs have other last bits, and whether a launch carries
 // the cache update must not show in its outputs.
 bool attend_short_fits(const AttendParams& p, int d, int max_len, unsigned copy_blocks) {
+  if (reinterpret_cast<unsigned long long>(p.q) % 4 != 0) return false;
   const int tiles = (p.t_k + tile::ROWS - 1) / tile::ROWS + (max_len + tile::ROWS - 1) / tile::ROWS;
   const int queries = 32 * (128 / d);  // per workgroup
   const unsigned pairs8 = (unsigned(p.H) * p.batch + 7) / 8 * 8;

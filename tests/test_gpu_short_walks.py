@@ -88,3 +88,36 @@ def test_one_round_walks_have_the_bits_of_the_long_ones(tokens, rising):
         assert tiles(tokens[kk], run) <= 2 < tiles(tokens[kk], 100 + run) and (H + 1) * batch > 256
         assert torch.isfinite(outs[0][kk]).all()
         assert torch.equal(outs[1][kk][:, :H], outs[0][kk].expand(batch, -1, -1, -1)), kk
+
+
+# Tensors need not start on a 16-byte boundary: views of a longer one at 4, 8 and 12 bytes, and queries at 2 (another kernel).
+@pytest.mark.parametrize("d,dtype,tokens,batch", [(128, "bf16", [1, 17, 31, 70, 129], 2), (64, "bf16", [1, 17, 31], 2),
+                                                  (128, "f32", [1, 33, 147], 32), (64, "f32", [1, 33, 147], 32)])
+def test_operands_off_the_16_byte_grid(d, dtype, tokens, batch):
+    kind = torch.bfloat16 if dtype == "bf16" else torch.float32
+    K, c, sm = len(tokens), hi.cumulative_tokens(tokens), 1.0 / np.sqrt(d)
+    plan = hk.heatkv_load_schedule(hk.Shape(1, 2, d, tokens, batch, dtype),
+                                   np.tril(np.ones((K, K), np.uint8), -1)[:, None, None].repeat(2, 2))
+    g = torch.Generator(device="cuda").manual_seed(65)
+    q, k, v = (torch.randn(batch, 2, c[-1], d, generator=g, device="cuda").to(kind) for _ in range(3))
+
+    def moved(x, n_bytes):
+        skip = n_bytes // x.element_size()
+        y = torch.empty(x.numel() + skip, dtype=x.dtype, device="cuda")[skip:].view(x.shape)
+        return y.copy_(x)
+
+    def outputs(q_at, at):
+        ka, va = (moved(torch.zeros(plan.arena_bytes, dtype=torch.uint8, device="cuda"), at) for _ in range(2))
+        outs = []
+        for i in range(K):
+            cut = slice(c[i] - tokens[i], c[i])
+            out = moved(torch.zeros(batch, 2, tokens[i], d, dtype=kind, device="cuda"), at)
+            hk.heatkv_attend_append_scale(plan, 0, i, moved(q[:, :, cut], q_at), moved(k[:, :, cut], at),
+                                          moved(v[:, :, cut], at), ka, va, sm, out)
+            outs.append(out)
+        return outs
+
+    want = outputs(0, 0)
+    for q_at, at in [(4, 4), (8, 8), (12, 12)] + ([(2, 0)] if dtype == "bf16" else []):
+        for a, b in zip(outputs(q_at, at), want):
+            assert torch.equal(a, b), (q_at, at)
