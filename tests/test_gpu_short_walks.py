@@ -90,6 +90,40 @@ def test_one_round_walks_have_the_bits_of_the_long_ones(tokens, rising):
         assert torch.equal(outs[1][kk][:, :H], outs[0][kk].expand(batch, -1, -1, -1)), kk
 
 
+# The same in both kernels where operands are not finite, masked to the lowest value or scaled to one-hot rows.
+@pytest.mark.parametrize("kind", ["keys of -inf", "keys of the lowest value", "all keys of -inf", "an infinite key", "large keys",
+                                  "an infinite value", "a NaN value", "a NaN query", "large scale"])
+@pytest.mark.parametrize("d", [64, 128])
+def test_special_operands_as_in_the_long_walks(d, kind):
+    H, batch, tokens = 5, 47, [100, 31, 33, 32, 70]
+    K, n = len(tokens), sum(tokens)
+    sm = 1e30 if kind == "large scale" else 1.0 / np.sqrt(d)
+    g = torch.Generator(device="cuda").manual_seed(66)
+    q, k, v = (torch.randn(1, H + 1, n, d, generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+    if "keys of" in kind:
+        q[..., 0] = 1.0
+        k[:, :, ::1 if kind.startswith("all") else 3, 0] = -float("inf") if "inf" in kind else torch.finfo(k.dtype).min
+    elif kind == "an infinite key":
+        k[:, :, 120::40, 5] = float("inf")
+    elif kind == "large keys":
+        k[:, :, 2::7] *= 2.0 ** 100
+    elif "value" in kind:
+        v[:, :, 110::31, 3] = float("inf") if "inf" in kind else float("nan")
+    elif kind == "a NaN query":
+        q[:, :, 3::17, 7] = float("nan")
+    outs = []
+    for heads, rows in ((H, 1), (H + 1, batch)):
+        present = np.zeros((K, 1, heads, K), np.uint8)
+        for kk in range(1, K):
+            present[kk, 0, :, 1:kk] = 1
+            present[kk, 0, H:, 0] = 1
+        plan = hk.heatkv_load_schedule(hk.Shape(1, heads, d, tokens, rows, "bf16"), present)
+        qkv = (x[:, :heads].repeat(rows, 1, 1, 1).contiguous() for x in (q, k, v))
+        outs.append(device_generation(plan, 0, *qkv, tokens, sm))
+    for a, m in zip(*outs):
+        torch.testing.assert_close(m[:, :H], a.expand(batch, -1, -1, -1), rtol=0, atol=0, equal_nan=True)
+
+
 # Tensors need not start on a 16-byte boundary: views of a longer one at 4, 8 and 12 bytes, and queries at 2 (another kernel).
 @pytest.mark.parametrize("d,dtype,tokens,batch", [(128, "bf16", [1, 17, 31, 70, 129], 2), (64, "bf16", [1, 17, 31], 2),
                                                   (128, "f32", [1, 33, 147], 32), (64, "f32", [1, 33, 147], 32)])
