@@ -1,14 +1,14 @@
 // fp32 contractions on the bf16 matrix instructions, shared by the fp32 kernels (attention, calibration).
 //
 // A float is the exact sum of three bf16 numbers: x1 = bf16(x), x2 = bf16(x - x1), x3 = x - x1 - x2 (8 significant bits each;
-// the differences are exact).  Of the nine products of two such sums six are taken; the others are below 2^-26 of x * y,
-// less than half a unit in the last place of a float.  Six bf16 instructions do the work of sixteen fp32 ones of the same
-// duration, and unlike those they overlap with vector instructions.  The sum of the five small products has an accumulator
-// of its own where there is room for one.
+// the differences are exact).  Of the nine products of two such sums six are taken; the others are together at most 2^-24 of
+// x * y, half a unit in the last place of a float (6e-9 of a dot product of 128 ordinary numbers, whose fp32 sum is off by 2e-7).
+// Six bf16 instructions do the work of sixteen fp32 ones of the same duration, and unlike those they overlap with vector
+// instructions.  The sum of the five small products has an accumulator of its own where there is room for one.
 //
 // Valid for operands up to LARGEST in magnitude (products and their sums stay finite, no part rounds to infinity, infinities
-// and the difference of two of them do not occur); the caller checks (`magnitude`) and takes the fp32 instructions on the
-// same operand layout (32x32x2) otherwise.  NaN stays NaN.
+// and the difference of two of them do not occur) and, where tiny ones count, from SMALLEST on; the caller checks and takes the
+// fp32 instructions on the same operand layout (32x32x2) otherwise.  NaN stays NaN.
 #pragma once
 
 #include "device_util.h"
@@ -19,14 +19,14 @@ namespace f32s {
 // Whether a launch of fp32 scales takes a kernel on these parts (32 queries per workgroup, one workgroup per compute unit) or
 // one on the fp32 instructions (16, up to four): the former where it needs fewer turns of 256 workgroups (blocks16, blocks32:
 // workgroups of either; t: queries).  Attention, fp32 instructions -> parts:
-//   d = 128: 1 turn, 16 pairs 400 x 1939 keys 66 -> 55 us; 2 turns, 529 x 2160 112 -> 103, 784 x 2194 129 -> 102; 264
-//   against 504 workgroups 47 -> 64; full chip, 196 x 855 keys 267 -> 216, 625 x 2525 1253 -> 1048.
-//   d = 64, where the parts cost as much for half the products: 1 turn, 16 pairs 400 x 1939 38 -> 34; more turns only where they
+//   d = 128: 1 turn, 16 pairs 400 x 1939 keys 66 -> 57 us; 2 turns, 529 x 2160 111 -> 106, 784 x 2194 129 -> 105; as many turns
+//   of either, 264 against 504 workgroups 47 -> 64; full chip, 196 x 855 keys 261 -> 226, 625 x 2525 1221 -> 1039.
+//   d = 64, where the parts cost as much for half the products: 1 turn, 16 pairs 400 x 1939 38 -> 35; more turns only where they
 //   are at most 0.6 times as many (3 against 2: 529 x 2160 59 -> 61, 40 pairs 4 against 3: 400 x 2060 67 -> 72; 4 against 2: 784 x
-//   2194 72 -> 60, 7 against 4: 64 pairs, 400 x 1996 102 -> 98) and from 400 queries on (full chip: 324 x 1660 299 -> 296, 317 ->
-//   319 with the cache update; 529 x 2525 511 -> 483).
+//   2194 72 -> 61) and from 400 queries on, 500 on a full chip (64 pairs, 4 turns, 400 x 1996 109 -> 107; 128 pairs, 7 turns 200 ->
+//   203; 256 pairs, 324 x 1660 317 -> 319, 529 x 2525 526 -> 504).
 //   Below 196 queries start and merge, which are longer, show, and the update's workgroups, which take a unit each: 40 pairs,
-//   169 x 659 (240 + 240 workgroups) 32.7 -> 27.8 without it, 35.4 -> 36.4 with it; 36 pairs, 144 x 490 (200 + 144) 26.1 -> 21.5.
+//   169 x 659 (240 + 240 workgroups) 32.7 -> 27.8 without it, 35.4 -> 36.4 with it; 36 pairs, 144 x 490 (200 + 144) 26.1 -> 22.1.
 // Calibration alike, and from a number of workgroups on (calibrate.hip).
 // Not for a softmax scale above 2^20 (or NaN), which makes scores of keys or queries whose parts are inexact (SMALLEST): below
 // it they are off by less than 128 x 2^60 x 2^-134 x 2^20, nothing in an exponent.
@@ -35,7 +35,7 @@ inline bool pays(int d, int t, unsigned long long blocks16, unsigned long long b
   const unsigned long long turns16 = (blocks16 + 255) / 256, turns32 = (blocks32 + 255) / 256;
   if (turns32 >= turns16) return false;
   if (t < 196) return t >= 128 && blocks32 <= 224;
-  return d == 128 || turns32 == 1 || (t >= 400 && 5 * turns32 <= 3 * turns16);
+  return d == 128 || turns32 == 1 || (t >= (turns32 <= 4 ? 400 : 500) && 5 * turns32 <= 3 * turns16);
 }
 
 constexpr float LARGEST = 0x1p60f;
