@@ -96,7 +96,8 @@ const char* heatkv_last_error(void);
  * k_all  device [batch][H][c[k1]][d], c[k1] = t[0]+..+t[k1], scale blocks in order
  * mass   device fp32 [batch][H][K], fully overwritten
  * ws     device scratch of at least heatkv_calibrate_workspace_bytes(shape,k1) bytes
- * The result is deterministic (fixed reduction order, no floating-point atomics).
+ * The result is deterministic (fixed reduction order, no floating-point atomics); of fp32 shapes it may differ in the
+ * last bits between batch sizes or numbers of heads, from which the kernel of a scale follows (bf16: the same bits).
  * `layer` is not used by the arithmetic (every layer has the same shape); it is
  * range-checked only.
  */
@@ -246,7 +247,11 @@ int heatkv_append_scale(heatkv_plan* plan, int layer, int k, const void* k_new, 
  *     (may be null when that is 0).
  * Softmax statistics and accumulation are fp32; bf16 inputs are multiplied on
  * the matrix cores with fp32 accumulation, probabilities are rounded to bf16
- * before the second product.
+ * before the second product.  sm_scale of bf16 shapes must be positive.
+ * Which kernel a launch takes follows from its sizes (t[k], H, batch, run lengths)
+ * and, for fp32, sm_scale: a head's outputs are the same bits from call to call and
+ * with heatkv_attend_append_scale, but may differ in the last bits between batch
+ * sizes or numbers of heads.
  */
 size_t heatkv_attend_workspace_bytes(const heatkv_plan* plan, int layer, int k);
 int heatkv_attend_scale(heatkv_plan* plan, int layer, int k, const void* q, const void* k_cur,

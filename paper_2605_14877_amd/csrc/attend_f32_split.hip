@@ -9,9 +9,10 @@
 // wavefront issues in order.
 //
 // Bound: vector instructions, 44 of them for the six products of a step (48 with the magnitudes), which take 75 to 80 clocks a
-// product when a wavefront has the SIMD to itself and about half of that per product when two share it.  16 pairs, 625 queries
-// x up to 1847 keys: 92 -> 83 us; 256 pairs 1067 -> 880 us.  Error against 64 bits over listed and drawn cases 1.1-1.8e-7 (norm)
-// where the fp32 instructions have 1.4-2.6e-7.
+// product when a wavefront has the SIMD to itself and about half of that per product when two share it.  fp32 instructions ->
+// this kernel, d = 128: 16 pairs, 784 queries x up to 2194 keys 129 -> 105 us, 8 pairs 529 x 2160 83 -> 60, 256 pairs 625 x 2525
+// 1221 -> 1039.  Error against 64 bits (norm) on the same inputs, 18 kinds of them: 0.65 to 0.72 times that of the fp32
+// instructions, 1.8-2.2e-7 for 2.5-3.3e-7 on N(0,1) operands, 3.7-4.9e-7 for 5.2-7.1e-7 on scores four times as large.
 #include <atomic>
 
 #include "attend_params.h"
@@ -261,7 +262,7 @@ __global__ __launch_bounds__(64 * NW) void attend_f32_split_kernel(AttendParams 
     f32s::Parts pp[2], vp[2];
     auto accumulate = [&](int c, const float (&v)[8][NV]) {
       // Operands that have exact parts, neither too large nor too small (f32_split.h).  Zeros are told from tiny numbers only
-      // where there is one of either (16 pairs, 625 queries x 1338 keys: 52.8 us without the lower limit, 54.0 with it, 55.8
+      // where there is one of either (16 pairs, 625 queries x up to 1139 keys: 52.8 us without the lower limit, 54.0 with it, 55.8
       // with a column of zeros).
       float most = 0.f, least = pr[c][0];
 #pragma unroll

@@ -562,8 +562,9 @@ __global__ __launch_bounds__(64 * FW) void calibrate_f32_kernel(CalibParams p) {
 // ---------------------------------------------------------------------------
 // fp32 scales of many query rows: S^T = K Q^T on the bf16 matrix instructions, operands in three bf16 parts (f32_split.h).
 // 32 queries per workgroup, whose parts every wavefront keeps in registers; key tiles of 32 rows dealt round robin to
-// eight wavefronts.  Otherwise as above.  Bound: vector instructions, 48 for the six products of a step, as in the
-// attention kernel (attend_f32_split.hip).  d = 128: 256 pairs, 625 x 2667 keys 1048 -> 869 us.
+// eight wavefronts.  Otherwise as above.  Error of the masses against 64 bits on the same inputs (16 kinds, 40 seeds each): 1.002
+// +- 0.005 times that of the kernel above, 7e-8 to 1.1e-7.  Bound: vector instructions, 48 for the six products of a step, as in
+// the attention kernel (attend_f32_split.hip).  d = 128: 256 pairs, 625 x 2511 keys 976 -> 834 us.
 // ---------------------------------------------------------------------------
 constexpr int SQ = 32;  // queries of a workgroup, keys of a tile
 constexpr int SW = 8;   // wavefronts

@@ -33,10 +33,10 @@ __device__ __forceinline__ uint4 bf16x16_to_e4m3(const uint4& lo, const uint4& h
                     bf16x4_to_e4m3(hi.z, hi.w));
 }
 
-// One workgroup (256 lanes) moves descriptor `desc` of batch entry `b`: up to 128 contiguous rows, 16 bytes per
-// lane, four independent loads in flight per lane and arena, K and V together.  Source and destination never
-// overlap (the planner places the new region of a layer in free space).  `parts` workgroups may share a descriptor:
-// they take turns over its groups of chunks.
+// 256 lanes move descriptor `desc` of batch entry `b`: up to 128 contiguous rows, 16 bytes per lane, four independent loads
+// in flight per lane and arena, K and V together.  Source and destination never overlap (the planner places the new region
+// of a layer in free space).  `parts` workgroups, or halves of a workgroup of 512 lanes, may share a descriptor: they take
+// turns over its groups of chunks.
 __device__ __forceinline__ void copy_rows_block(const CopyParams& p, int desc, int b, int part = 0, int parts = 1) {
   const CopyDesc d = p.descs[desc];
   const int lane = threadIdx.x & 255;
