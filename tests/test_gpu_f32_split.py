@@ -109,8 +109,8 @@ def _exact(q, k, v, idx, rows, sm):
 
 
 # Errors against 64 bits.  The fp32 instructions have up to 3.3e-7 (norm) here, the parts 1.9e-7, and without one of the
-# six products, in the scores or in P V, 1.7e-6 or more.  Bound: twice that of the fp32 instructions.  Keys of 2^-117 whose softmax scale makes ordinary
-# scores of them have an inexact third part (4e-6): such a scale takes the fp32 instructions.
+# six products, in the scores or in P V, 1.7e-6 or more.  Bound: twice that of the fp32 instructions.  Keys of 2^-117 whose
+# softmax scale makes ordinary scores of them have an inexact third part (4e-6): such a scale takes the fp32 instructions.
 SCALED = [("plain", 0), ("tiny keys, large softmax scale", 117)]
 
 
