@@ -153,6 +153,19 @@ def test_8_bit_cache_with_two_query_sets_per_workgroup():
     print(f"fp8 cache, two query sets: worst |err| {worst:.4f}")
 
 
+@pytest.mark.parametrize("side", [13, 14, 16, 17, 20, 21, 24])
+def test_8_bit_cache_walks_of_few_current_tiles(side):
+    # 3 to 9 tiles of the current scale in front of ragged retained runs: the steps that touch tiles of the current
+    # scale only are a loop of their own, of none, two, four or six steps
+    t0, c, K, d, shape, plan, ref, qkv = _case(1, 3, (1, 2, 5, 11, side), 2, 2, 1, seed=77)
+    sm = 1.0 / np.sqrt(d)
+    sep = _run(plan, qkv, t0, c, sm)
+    fused = _run(plan, qkv, t0, c, sm, fused_layers=(0,))
+    for a, b in zip(sep[0], fused[0]):
+        assert torch.equal(a, b)
+    _check_attention(sep, qkv, t0, ref["present"], sm)
+
+
 def test_layer2b_full_size_with_8_bit_cache():
     # one 2B-like layer at its real shape; the same byte budget as the bf16 case now holds twice the tokens
     cfg = hi.CONFIGS["layer2b"]
