@@ -53,7 +53,7 @@ extern __shared__ __attribute__((aligned(1024))) char attend_dynamic_lds[];
 // KS = number of key streams.  KS = 1: the workgroup described above.  KS = 2, for launches that give every
 // compute unit at most one workgroup (few heads, small batch): 8 wavefronts, one workgroup per unit; wavefronts
 // 4-7 take the same 128 queries as 0-3 but every other key tile (stream g walks tiles g, g + 2, ...), each
-// stream with its own pair of tile stages (128 KB of dynamic LDS), and at the end stream 1 hands its partial
+// stream with its own pair of tile stages (128 KB of dynamic LDS; d = 64: 64 KB), and at the end stream 1 hands its partial
 // output, row sums and references to stream 0 through LDS.  The unit then runs two wavefronts per SIMD, as it
 // does when two workgroups share it, without a second pass over HBM.
 //
@@ -64,7 +64,7 @@ extern __shared__ __attribute__((aligned(1024))) char attend_dynamic_lds[];
 // straight to their stage.  80 KB of LDS per workgroup: two workgroups still share a compute unit.
 //
 // D: head dimension, 128 or 64 (rows of 256 or 128 bytes, tiles of 16 or 8 KB, 8 or 4 MFMA steps per score block and
-// 4 or 2 accumulator blocks; the single-stream, bf16-cache instance only).
+// 4 or 2 accumulator blocks; one query set and bf16 cache rows only).
 //
 // QS = 2, for launches that keep every compute unit busy for rounds of long walks: 8 wavefronts, one workgroup
 // per unit, 256 queries per workgroup; wavefronts 4-7 take the next 128 queries against the SAME key tiles, which
@@ -79,7 +79,7 @@ __global__ __launch_bounds__(256 * KS * QS, (KS == 1 && QS == 1) ? 2 : 1) void a
   static_assert(KS == 1 || KS == 2, "one or two key streams");
   static_assert(QS == 1 || QS == 2, "one or two query sets");
   static_assert(!(FP8 && KS == 2), "the 8-bit cache path has one key stream");
-  static_assert(D == 128 || (D == 64 && KS == 1 && !FP8), "d = 64: single stream, bf16 cache rows");
+  static_assert(D == 128 || (D == 64 && !FP8), "d = 64: bf16 cache rows");
   static_assert(QS == 1 || (KS == 1 && D == 128), "two query sets: single stream, d = 128");
   constexpr int NW = 4 * QS;  // wavefronts that share the copying of a tile
   constexpr int ROW_BYTES = 2 * D;            // one bf16 row
@@ -594,25 +594,25 @@ __global__ __launch_bounds__(256 * KS * QS, (KS == 1 && QS == 1) ? 2 : 1) void a
   if constexpr (KS == 2) {
     // Stream 1 parks its accumulators (64 registers, one 256-byte row of LDS per register), row-sum partials and
     // references in the idle tile stages (66 KB from byte 48 K on: clear of the 16 KB at 0 and at 32 K where
-    // stream 0 stages its output); stream 0 brings both halves to the larger reference and adds.
+    // stream 0 stages its output; d = 64: 32 registers, 34 KB from byte 24 K on); stream 0 brings both halves to the larger reference and adds.
     __syncthreads();  // every wavefront has finished reading the tile stages
-    float* park = reinterpret_cast<float*>(lds[1][1]) + wave * (66 * 64);
+    float* park = reinterpret_cast<float*>(lds[1][1]) + wave * ((16 * NV + 2) * 64);
     if (g == 1 && active) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < NV; ++i)
 #pragma unroll
         for (int r = 0; r < 16; ++r) park[(16 * i + r) * 64 + lane] = o[i][r];
-      park[64 * 64 + lane] = m_run;
-      park[65 * 64 + lane] = l_run;
+      park[16 * NV * 64 + lane] = m_run;
+      park[(16 * NV + 1) * 64 + lane] = l_run;
     }
     __syncthreads();
     if (g == 1 || !active) return;
-    const float m_other = park[64 * 64 + lane], l_other = park[65 * 64 + lane];
+    const float m_other = park[16 * NV * 64 + lane], l_other = park[(16 * NV + 1) * 64 + lane];
     const float m_new = fmaxf(m_run, m_other);
     const float a0 = fast_exp2((m_run - m_new) * c), a1 = fast_exp2((m_other - m_new) * c);  // no tile: lowest reference, factor 0
     l_run = l_run * a0 + l_other * a1;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < NV; ++i)
 #pragma unroll
       for (int r = 0; r < 16; ++r) o[i][r] = o[i][r] * a0 + park[(16 * i + r) * 64 + lane] * a1;
   }
@@ -680,6 +680,9 @@ hipError_t allow_lds() {
   if (e == hipSuccess)
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attend_bf16_kernel<1, true, 128, 2>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, FP8_LDS_BYTES);
+  if (e == hipSuccess)
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attend_bf16_kernel<2, false, 64>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, TWO_STREAM_LDS_BYTES / 2);
   if (e == hipSuccess) e = attend_short_prepare();
   if (e == hipSuccess && dev >= 0 && dev < 64) done.fetch_or(1ull << dev, std::memory_order_release);
   return e;
@@ -742,7 +745,15 @@ hipError_t launch_attend(const AttendArgs& a, hipStream_t stream) {
       const hipError_t e = allow_lds();
       return e == hipSuccess ? launch_attend_short(p, a.d, a.max_len, copy_blocks, stream) : e;
     }
-    if (a.d == 64) {  // rows of 128 bytes: the single-stream instance
+    // At most one workgroup per compute unit: two key streams per workgroup put two wavefronts on every SIMD.  d = 64, one
+    // launch, one stream -> two: 16 heads, 576 tokens 15.0 -> 13.4 us, 1024 24.6 -> 21.1, 1600 36.5 -> 30.6, 32 pairs 1024 tokens
+    // 26.1 -> 22.9; 100 tokens 6.8 -> 7.4, 169 and 256 the same; 320 workgroups (64 pairs, 576 tokens) 18.2 -> 20.0.
+    const bool two_streams = !a.kv_fp8 && p.attend_blocks <= TWO_STREAM_MAX_BLOCKS && a.t_k >= TWO_STREAM_MIN_TOKENS;
+    if (a.d == 64 && two_streams) {
+      const hipError_t e = allow_lds();
+      if (e != hipSuccess) return e;
+      hipLaunchKernelGGL((attend_bf16_kernel<2, false, 64>), grid, dim3(512), TWO_STREAM_LDS_BYTES / 2, stream, p);
+    } else if (a.d == 64) {  // rows of 128 bytes
       hipLaunchKernelGGL((attend_bf16_kernel<1, false, 64>), grid, dim3(256), 0, stream, p);
     } else if (a.kv_fp8) {  // 8-bit cache rows: the single-stream instances with landing buffers
       const hipError_t e = allow_lds();
@@ -754,8 +765,7 @@ hipError_t launch_attend(const AttendArgs& a, hipStream_t stream) {
       } else {
         hipLaunchKernelGGL((attend_bf16_kernel<1, true, 128>), grid, dim3(256), FP8_LDS_BYTES, stream, p);
       }
-    } else if (p.attend_blocks <= TWO_STREAM_MAX_BLOCKS && a.t_k >= TWO_STREAM_MIN_TOKENS) {
-      // At most one workgroup per compute unit: two key streams per workgroup put two wavefronts on every SIMD.
+    } else if (two_streams) {
       const hipError_t e = allow_lds();
       if (e != hipSuccess) return e;
       hipLaunchKernelGGL((attend_bf16_kernel<2, false, 128>), grid, dim3(512), TWO_STREAM_LDS_BYTES, stream, p);

@@ -256,6 +256,18 @@ def test_bf16_head_dimension_64():
     _bf16_case(1, 2, (1, 2, 4, 9, 20, 22), 2, 1, 1, seed=84, d=64)  # full budget: the longest runs
 
 
+@pytest.mark.parametrize("H,batch,tokens,den", [
+    (3, 1, (1, 63, 383), 1),        # 383 tokens: still one stream
+    (3, 1, (1, 63, 384), 1),        # 6 + 1 tiles: the second stream lacks the last one; three query tiles without a rest
+    (5, 2, (1, 64, 129, 447), 1),   # 7 + 4 tiles, 63 and 2 rows in the ragged ones; idle wavefronts in the last query tile
+    (7, 1, (1, 30, 65, 400, 385), 2),  # runs of different lengths, a fused update of rows longer than the scale
+    (16, 2, (1, 4, 200, 1024), 2),  # 256 workgroups
+    (16, 2, (1, 4, 200, 1025), 2),  # one query tile more: one stream
+])
+def test_bf16_two_key_streams_head_dimension_64(H, batch, tokens, den):
+    _bf16_case(1, H, tuple((1, n) for n in tokens), 1, den, batch, seed=85, fused=True, d=64)
+
+
 def test_bf16_budget_extremes():
     # Full budget: nothing is pruned, every head walks all prior scales (the longest runs the layout can hold).
     # Smallest legal budget (the sink scales only): every head keeps just the sinks.  Both at sizes that use the
