@@ -45,6 +45,13 @@ struct CalibParams {
   float sm_scale;
 };
 
+// Where the masses of a launch of one query tile go, and the table that they are added to.
+struct CalibDirect {
+  float *mass, *beta;  // mass may be null
+  float weight;
+  int layer;
+};
+
 // The kernel arguments take more than a kilobyte, and which of them a workgroup needs follows from others: read one
 // after the other they are a chain of scalar-cache misses.  This asks for their lines together.
 __device__ __forceinline__ void touch_params(const CalibParams& p) {
@@ -441,16 +448,27 @@ __global__ __launch_bounds__(256, CSETS == 1 ? 3 : 2) void calibrate_bf16_kernel
 // 34 us; sizes of blocks looked up in every step: 33 us; kernel arguments read one after the other: +0.8 us per launch.
 // ---------------------------------------------------------------------------
 constexpr int FQ = f32m::TILE;
-constexpr int FW = 4;           // wavefronts of a workgroup
+constexpr int FW = 4;           // wavefronts that share a query tile
 
+// Dynamic LDS of a query tile: key stages [FW], final maxima [FW][FQ] and inverse row sums [FQ], then block sums and references
+// [k1+1][2][FW][FQ], rounded up to whole kilobytes.
 template <int D>
-__global__ __launch_bounds__(64 * FW) void calibrate_f32_kernel(CalibParams p) {
-  using Stage = f32m::KeyStage<D>;
-  __shared__ __attribute__((aligned(1024))) char stages[FW][Stage::BYTES];
-  __shared__ float blk_sum[MAXK][FW][FQ], blk_max[MAXK][FW][FQ];
-  __shared__ float fin_max[FW][FQ], row_inv[FQ];
+__host__ __device__ constexpr size_t f32_lds_bytes(int k1) {
+  const size_t b = FW * f32m::KeyStage<D>::BYTES + ((2 * size_t(k1 + 1) + 1) * FW + 1) * FQ * sizeof(float);
+  return (b + 1023) / 1024 * 1024;
+}
 
-  const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, g = lane >> 4;
+// G > 0: one query scale of at most FQ rows, G batch rows.  A workgroup takes a head, G times four wavefronts its batch rows,
+// and the row masses of the one query tile are all there is to average: the workgroup divides them by the number of rows and
+// adds them up as the reduction below does, bit for bit, and there is no second launch.  In a captured graph: 8 heads, batch 2,
+// d = 128, 1 x 1 and 16 x 21 keys 5.7 -> 4.7 and 6.3 -> 5.8 us; 4 heads, batch 1, d = 64, 1 x 1 and 16 x 21 5.0 -> 3.5 and 5.4 -> 3.8.
+template <int D, int G>
+__global__ __launch_bounds__(64 * FW * (G > 0 ? G : 1)) void calibrate_f32_kernel(CalibParams p, CalibDirect direct) {
+  using Stage = f32m::KeyStage<D>;
+  extern __shared__ __attribute__((aligned(1024))) char calib_f32_lds[];
+
+  const int group = G > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / (64 * FW)) : 0;
+  const int tid = G > 1 ? threadIdx.x % (64 * FW) : threadIdx.x, lane = tid & 63, n = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   touch_params(p);
   const ScaleJob& job = p.job[scale_of_block(p, blockIdx.x)];
@@ -458,13 +476,19 @@ __global__ __launch_bounds__(64 * FW) void calibrate_f32_kernel(CalibParams p) {
   const int n_qtiles = (t_k1 + FQ - 1) / FQ;
   const int block = blockIdx.x - job.block_begin;
   const int xcd = block & 7, slot = block >> 3;  // all query tiles of a (batch row, head) on one XCD
-  const int bh = (slot / n_qtiles) * 8 + xcd;
+  const int bh = G > 0 ? group * p.H + block : (slot / n_qtiles) * 8 + xcd;
   if (bh >= p.batch * p.H) return;
-  const int qt = slot % n_qtiles;
+  const int qt = G > 0 ? 0 : slot % n_qtiles;
   const int q_rows = min(t_k1 - qt * FQ, FQ);
   const float* kbase = static_cast<const float*>(job.k_all) + static_cast<long long>(bh) * p.c[k1] * D;
 
-  const Stage keys(stages[wave], lane);
+  char* const lds = calib_f32_lds + group * f32_lds_bytes<D>(k1);
+  float(*const fin_max)[FQ] = reinterpret_cast<float(*)[FQ]>(lds + FW * Stage::BYTES);
+  float* const row_inv = fin_max[FW];
+  constexpr int BLOCKS = FW * Stage::BYTES + (FW + 1) * FQ * 4;
+  float(*const blk)[2][FW][FQ] = reinterpret_cast<float(*)[2][FW][FQ]>(lds + BLOCKS);  // [.][0] sums, [.][1] references
+  char* const stage = lds + wave * Stage::BYTES;
+  const Stage keys(stage, lane);
   f32m::Rows<D> q, k;
   q.load(static_cast<const float*>(job.q) + (static_cast<long long>(bh) * t_k1 + qt * FQ) * D, q_rows, lane);
 
@@ -487,8 +511,8 @@ __global__ __launch_bounds__(64 * FW) void calibrate_f32_kernel(CalibParams p) {
   auto fetch = [&] { keys.fill(kbase + static_cast<long long>(first) * D, min(rows_left, FQ), lane); };
   for (int j = 0; j <= k1; ++j)  // blocks without a tile of this wavefront
     if (g == 0) {
-      blk_sum[j][wave][n] = 0.f;
-      blk_max[j][wave][n] = f32m::LOWEST;
+      blk[j][0][wave][n] = 0.f;
+      blk[j][1][wave][n] = f32m::LOWEST;
     }
   enter(wave);
   if (k2 <= k1) fetch();
@@ -496,7 +520,7 @@ __global__ __launch_bounds__(64 * FW) void calibrate_f32_kernel(CalibParams p) {
   float m = f32m::LOWEST, cur = 0.f;
   while (k2 <= k1) {
     const int here = k2, rows = rows_left;
-    Stage::take(k, stages[wave], lane);
+    Stage::take(k, stage, lane);
     if (rows_left > FW * FQ) {
       first += FW * FQ;
       rows_left -= FW * FQ;
@@ -521,8 +545,8 @@ __global__ __launch_bounds__(64 * FW) void calibrate_f32_kernel(CalibParams p) {
       const float mb = f32m::max_groups(m);
       const float sb = f32m::sum_groups(cur * prob(m, mb));
       if (g == 0) {
-        blk_sum[here][wave][n] = sb;
-        blk_max[here][wave][n] = mb;
+        blk[here][0][wave][n] = sb;
+        blk[here][1][wave][n] = mb;
       }
       cur = 0.f;
     }
@@ -540,22 +564,39 @@ __global__ __launch_bounds__(64 * FW) void calibrate_f32_kernel(CalibParams p) {
     for (int j = tid / FQ; j <= k1; j += 64 * FW / FQ) {
       float v = 0.f;
 #pragma unroll
-      for (int w = 0; w < FW; ++w) v += blk_sum[j][w][row] * prob(blk_max[j][w][row], mf);
-      blk_sum[j][0][row] = v;
+      for (int w = 0; w < FW; ++w) v += blk[j][0][w][row] * prob(blk[j][1][w][row], mf);
+      blk[j][0][0][row] = v;
     }
   }
   __syncthreads();
   if (tid < FQ) {
     float l = 0.f;
-    for (int j = 0; j <= k1; ++j) l += blk_sum[j][0][tid];
+    for (int j = 0; j <= k1; ++j) l += blk[j][0][0][tid];
     row_inv[tid] = tid < q_rows ? 1.f / l : 0.f;
   }
   __syncthreads();
   if (tid <= k1) {
     float v = 0.f;
 #pragma unroll
-    for (int rr = 0; rr < FQ; ++rr) v += blk_sum[tid][0][rr] * row_inv[rr];
-    job.partial[(static_cast<long long>(bh) * n_qtiles + qt) * p.K + tid] = v;
+    for (int rr = 0; rr < FQ; ++rr) v += blk[tid][0][0][rr] * row_inv[rr];
+    if constexpr (G > 0)
+      blk[tid][0][1][0] = v / static_cast<float>(t_k1);
+    else
+      job.partial[(static_cast<long long>(bh) * n_qtiles + qt) * p.K + tid] = v;
+  }
+  if constexpr (G > 0) {
+    __syncthreads();
+    const int j = tid;
+    if (j >= p.K) return;
+    if (direct.mass) direct.mass[static_cast<long long>(bh) * p.K + j] = j <= k1 ? blk[j][0][1][0] : 0.f;
+    if (group > 0) return;
+    float acc = 0.f;
+    for (int b = 0; b < G; ++b) {
+      const auto* sums = reinterpret_cast<const float(*)[2][FW][FQ]>(calib_f32_lds + b * f32_lds_bytes<D>(k1) + BLOCKS);
+      acc += j <= k1 ? sums[j][0][1][0] : 0.f;
+    }
+    float* const out = direct.beta + ((static_cast<long long>(direct.layer) * p.H + block) * p.K + k1) * p.K + j;
+    *out = *out + direct.weight * acc;
   }
 }
 
@@ -901,6 +942,37 @@ int queries_per_tile(int dtype) { return dtype == HEATKV_BF16 ? CBM1 : FQ; }
 
 }  // namespace
 
+namespace {
+
+hipError_t launch_calibrate_one_tile(const CalibParams& p, const CalibDirect& direct, int d, size_t lds, hipStream_t stream) {
+  const dim3 grid(p.H), block(64 * FW * p.batch);
+  if (p.batch == 1) {
+    if (d == 64)
+      hipLaunchKernelGGL((calibrate_f32_kernel<64, 1>), grid, block, lds, stream, p, direct);
+    else
+      hipLaunchKernelGGL((calibrate_f32_kernel<128, 1>), grid, block, lds, stream, p, direct);
+    return hipGetLastError();
+  }
+  // d = 128: more than 64 KB of dynamic LDS needs the function attribute raised, once per device.
+  static std::atomic<unsigned long long> raised{0};  // one bit per device ordinal below 64
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  if (dev < 0 || dev >= 64 || !(raised.load(std::memory_order_acquire) >> dev & 1)) {
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&calibrate_f32_kernel<128, 2>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, int(2 * f32_lds_bytes<128>(MAXK - 1)));
+    if (e != hipSuccess) return e;
+    if (dev >= 0 && dev < 64) raised.fetch_or(1ull << dev, std::memory_order_release);
+  }
+  if (d == 64)
+    hipLaunchKernelGGL((calibrate_f32_kernel<64, 2>), grid, block, 2 * lds, stream, p, direct);
+  else
+    hipLaunchKernelGGL((calibrate_f32_kernel<128, 2>), grid, block, 2 * lds, stream, p, direct);
+  return hipGetLastError();
+}
+
+}  // namespace
+
 size_t calibrate_workspace_bytes(int dtype, int, int H, int batch, int K, int t_k1) {
   const int qpt = queries_per_tile(dtype);
   const size_t n_qtiles = size_t((t_k1 + qpt - 1) / qpt);
@@ -1037,10 +1109,20 @@ hipError_t launch_calibrate(const CalibrateArgs& a, hipStream_t stream) {
                          split_p);
   }
   if (!bf16 && p.n_scales > 0) {
+    const CalibDirect direct{a.mass[0], a.beta, a.weight, a.layer};
+    size_t lds = a.d == 64 ? f32_lds_bytes<64>(k1_max) : f32_lds_bytes<128>(k1_max);
+    // One query tile and the average asked for: no second launch.  Several scales in one call keep it, the launch reduces all.
+    if (a.beta && a.n_scales == 1 && a.t[a.k1[0]] <= FQ && a.batch <= 2)
+      return launch_calibrate_one_tile(p, direct, a.d, lds, stream);
+    // d = 128: three or four workgroups per compute unit (the registers allow four, the LDS as well up to 15 scales), whichever
+    // needs fewer turns times workgroups side by side; three where neither does.  Three -> four: 32 pairs, 400 x 921 keys (800
+    // workgroups) 50 -> 45 us, 64 pairs 256 x 521 (1024) 41 -> 32 and 400 x 921 (1600) 80 -> 74, 256 pairs 64 x 121 (1024) 23 -> 17;
+    // but 256 pairs 144 x 265 (2304) 46.5 -> 49, 32 and 64 pairs 144 x 265 (288, 576) 14.2 -> 14.6 and 18.1 -> 18.6.
+    if (a.d == 128 && (blocks + 767) / 768 * 3 <= (blocks + 1023) / 1024 * 4) lds = std::max(lds, size_t(kMaxLds / 4 + 1024));
     if (a.d == 64)
-      hipLaunchKernelGGL(calibrate_f32_kernel<64>, dim3(blocks), dim3(256), 0, stream, p);
+      hipLaunchKernelGGL((calibrate_f32_kernel<64, 0>), dim3(blocks), dim3(64 * FW), lds, stream, p, direct);
     else
-      hipLaunchKernelGGL(calibrate_f32_kernel<128>, dim3(blocks), dim3(256), 0, stream, p);
+      hipLaunchKernelGGL((calibrate_f32_kernel<128, 0>), dim3(blocks), dim3(64 * FW), lds, stream, p, direct);
   }
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

@@ -45,3 +45,30 @@ def test_partial_sums_in_order(dtype, t, batch, with_mass):
     assert np.array_equal(beta.cpu().numpy(), after)
     hk.heatkv_calibrate(shape, 1, k1, q, k, d ** -0.5, mass, ws)
     assert np.array_equal(mass.cpu().numpy(), want)
+
+
+# A call for one scale of at most 16 rows with one or two batch rows reduces in its own launch; a call for several scales has
+# the second launch: same bits, in all of mass and beta, with a weight that rounds.
+@pytest.mark.parametrize("with_mass", [True, False])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("H,batch,tokens", [
+    (5, 1, (1, 15, 16, 17)), (5, 2, (1, 15, 16, 17)), (5, 3, (2, 16)), (9, 2, (3, 16) + (1, 4) * 14 + (16,)),
+])
+def test_scales_of_one_query_tile_have_the_bits_of_a_call_for_all_scales(H, batch, tokens, d, with_mass):
+    K, L = len(tokens), 2
+    torch.manual_seed(92)
+    q = [torch.randn(batch, H, t, d).cuda() for t in tokens]
+    k = torch.randn(batch, H, sum(tokens), d)
+    k_all = [k[:, :, :sum(tokens[:i + 1])].contiguous().cuda() for i in range(K)]
+    shape = hk.Shape(L, H, d, tokens, batch, "f32")
+    start = torch.rand(L, H, K, K).cuda()
+    one, each = start.clone(), start.clone()
+    masses = [[torch.full((batch, H, K), -1.0, device="cuda") if with_mass else None for _ in tokens] for _ in range(2)]
+    scales = list(range(K))
+    ws = torch.empty(hk.binding.calibrate_scales_workspace_bytes(shape, scales), dtype=torch.uint8, device="cuda")
+    hk.heatkv_calibrate_scales_accumulate(shape, 1, scales, q, k_all, d ** -0.5, 0.3, one, masses[0] if with_mass else None, ws)
+    for i in scales:
+        hk.heatkv_calibrate_accumulate(shape, 1, i, q[i], k_all[i], d ** -0.5, 0.3, each, masses[1][i], ws)
+    assert torch.equal(one, each) and not torch.equal(one[1], start[1]) and torch.equal(one[0], start[0])
+    for a, b in zip(*masses):
+        assert a is b is None or torch.equal(a, b)
