@@ -74,13 +74,18 @@ extern __shared__ __attribute__((aligned(1024))) char attend_dynamic_lds[];
 // now pass the same barriers and so run the same part of the step at the same time; that costs nothing because
 // every slot of the hand-ordered step below mixes matrix and vector work (with the compiler's own order, score
 // MFMAs clustered apart from the exponentials, the same instance gained 1 % instead of 4-6 %).
-template <int KS, bool FP8, int D, int QS = 1>
-__global__ __launch_bounds__(256 * KS * QS, (KS == 1 && QS == 1) ? 2 : 1) void attend_bf16_kernel(AttendParams p) {
+//
+// COPIERS, for launches that give every compute unit at most one workgroup of walks too short for two key streams: four more
+// wavefronts copy the tiles and do nothing else.  A wavefront that issues copies is held about 100 cycles by each, and here it
+// has its SIMD to itself, with nobody to compute meanwhile.  Same steps, same bits as without.
+template <int KS, bool FP8, int D, int QS = 1, bool COPIERS = false>
+__global__ __launch_bounds__(256 * KS * QS * (COPIERS ? 2 : 1), (KS == 1 && QS == 1) ? 2 : 1) void attend_bf16_kernel(AttendParams p) {
   static_assert(KS == 1 || KS == 2, "one or two key streams");
   static_assert(QS == 1 || QS == 2, "one or two query sets");
   static_assert(!(FP8 && KS == 2), "the 8-bit cache path has one key stream");
   static_assert(D == 128 || (D == 64 && !FP8), "d = 64: bf16 cache rows");
   static_assert(QS == 1 || (KS == 1 && D == 128), "two query sets: single stream, d = 128");
+  static_assert(!COPIERS || (KS == 1 && QS == 1 && !FP8), "copying wavefronts: one stream, one query set, bf16 cache rows");
   constexpr int NW = 4 * QS;  // wavefronts that share the copying of a tile
   constexpr int ROW_BYTES = 2 * D;            // one bf16 row
   constexpr int TILE_BYTES = BN * ROW_BYTES;  // 16 KB (d = 128) or 8 KB (d = 64)
@@ -97,7 +102,10 @@ __global__ __launch_bounds__(256 * KS * QS, (KS == 1 && QS == 1) ? 2 : 1) void a
   touch_params(p);
   if (static_cast<int>(blockIdx.x) >= p.attend_blocks) {  // fused append: a plain row copy by 256 lanes
     const int j = blockIdx.x - p.attend_blocks;
-    if ((KS == 1 && QS == 1) || threadIdx.x < 256) copy_rows_block(p.copy, j % p.ndesc, j / p.ndesc);
+    if constexpr (COPIERS)  // both halves of the workgroup
+      copy_rows_block(p.copy, j % p.ndesc, j / p.ndesc, threadIdx.x >> 8, 2);
+    else if ((KS == 1 && QS == 1) || threadIdx.x < 256)
+      copy_rows_block(p.copy, j % p.ndesc, j / p.ndesc);
     return;
   }
   const int tid = threadIdx.x, lane = tid & 63;
@@ -107,6 +115,7 @@ __global__ __launch_bounds__(256 * KS * QS, (KS == 1 && QS == 1) ? 2 : 1) void a
   const int wave = wave_all & 3;                                  // its place among the four of the stream / set
   const int lw = QS == 1 ? wave : wave_all;                       // its place among the NW that copy a tile
   const int n = lane & 31, hl = lane >> 5;
+  const bool computes = !COPIERS || wave_all < 4, copies_tiles = !COPIERS || wave_all >= 4;
 
   Task task;
   if (!find_task(p, task)) return;
@@ -125,8 +134,8 @@ __global__ __launch_bounds__(256 * KS * QS, (KS == 1 && QS == 1) ? 2 : 1) void a
   // Q as B operand: lane (n, hl) holds Q[row][16*ks + 8*hl .. +7] for ks = 0..7.
   const int q_row0 = qt * (BM * QS) + qs * BM + wave * 32;  // first query row of this wavefront
   const int q_row = q_row0 + n;
-  bf16x8 qreg[NK];
-  {
+  bf16x8 qreg[NK] = {};
+  if (computes) {
     const int ld = q_row < t_k ? q_row : t_k - 1;
     const bf16_t* qp = static_cast<const bf16_t*>(p.q) + cur_off + static_cast<long long>(ld) * D + 8 * hl;
 #pragma unroll
@@ -463,7 +472,7 @@ __global__ __launch_bounds__(256 * KS * QS, (KS == 1 && QS == 1) ? 2 : 1) void a
   f32x16 s_cur[2], s_nxt[2];
   // A wavefront whose 32 query rows all lie past t_k (ragged last query tile) keeps loading its share of
   // every tile and keeps the barriers, but leaves the matrix cores to the other workgroup on the unit.
-  const bool active = q_row0 < t_k;
+  const bool active = computes && q_row0 < t_k;
   // Steady-state step j (j + 1 < steps_all): K of the stream's tile j+1 sits in K stage kb1, V of its tile j in
   // V stage vb0.  s_in holds the scores of tile j, s_out receives those of tile j+1: the two register sets swap
   // roles from step to step instead of being copied.  With two streams the second may lack the last successor tile: it
@@ -498,12 +507,13 @@ __global__ __launch_bounds__(256 * KS * QS, (KS == 1 && QS == 1) ? 2 : 1) void a
       if (COPIES > 1) issue_v(j + 1, decltype(kb1)::value);
       if (!active) return;
     } else if (!active) {
+      if (!copies_tiles) return;
 #pragma unroll
       for (int i = 0; i < COPIES * CPT; ++i)
         i < CPT ? copy_k(k_src, decltype(vb0)::value, i) : copy_v(v_src, decltype(kb1)::value, i - CPT);
       return;
     }
-    const float mx = step_math(s_in, s_out, k0, kb1, vb0, std::integral_constant<int, CODES ? 0 : COPIES>{}, k_src, v_src);
+    const float mx = step_math(s_in, s_out, k0, kb1, vb0, std::integral_constant<int, CODES || COPIERS ? 0 : COPIES>{}, k_src, v_src);
     raise(mask_tail(left1, s_out) ? lane_max(s_out) : mx);
   };
 
@@ -512,7 +522,9 @@ __global__ __launch_bounds__(256 * KS * QS, (KS == 1 && QS == 1) ? 2 : 1) void a
   // Loads return in issue order, so waiting until only the copies younger than K(0) are outstanding means that
   // K(0) has landed (CPT copies per wavefront and bf16 tile, two per 8-bit tile); tile 0 is a current-scale tile,
   // whose address does not depend on the head's run.
-  if (KS == 1) {
+  if (!copies_tiles) {
+    // the copying wavefronts wait for K(0) before the barrier
+  } else if (KS == 1) {
     issue_k(0, 0);
     issue_v(0, 0);
     if (tiles_all > 1) {
@@ -749,10 +761,25 @@ hipError_t launch_attend(const AttendArgs& a, hipStream_t stream) {
     // launch, one stream -> two: 16 heads, 576 tokens 15.0 -> 13.4 us, 1024 24.6 -> 21.1, 1600 36.5 -> 30.6, 32 pairs 1024 tokens
     // 26.1 -> 22.9; 100 tokens 6.8 -> 7.4, 169 and 256 the same; 320 workgroups (64 pairs, 576 tokens) 18.2 -> 20.0.
     const bool two_streams = !a.kv_fp8 && p.attend_blocks <= TWO_STREAM_MAX_BLOCKS && a.t_k >= TWO_STREAM_MIN_TOKENS;
+    // For shorter walks wavefronts that only copy, on the SIMDs of those that compute.  One launch, without -> with them: d =
+    // 128, 48 pairs, 196 tokens 13.9 -> 13.1 us, 324 19.2 -> 17.8; 64 pairs, 144 10.2 -> 9.7; 128 pairs, 256 (256 workgroups)
+    // 15.8 -> 14.8; d = 64, 64 pairs, 196 10.9 -> 10.3, 324 14.7 -> 13.9.  From 384 tokens on two streams: d = 128, 112
+    // workgroups of 784 tokens 23.9 us, copiers 24.1; d = 64, 17.0 and 18.6.  One workgroup takes a compute unit, also one that
+    // copies rows of the cache update: these have to find units enough while the walks last (d = 128, workgroups of attention +
+    // update, tiles of the longest walk: 96 + 192, 4 9.4 -> 9.0; 128 + 256, 4 10.2 -> 10.4; 192 + 270, 10 15.8 -> 15.1; 256 + 360,
+    // 10 17.1 -> 19.4; 256 + 512, 4 15.7 -> 19.2).
+    const int tiles = (a.t_k + BN - 1) / BN + (a.max_len + BN - 1) / BN;
+    const bool copiers = !a.kv_fp8 && !two_streams && p.attend_blocks <= TWO_STREAM_MAX_BLOCKS &&
+                         p.attend_blocks + copy_blocks <= 190u + 28u * tiles;
     if (a.d == 64 && two_streams) {
       const hipError_t e = allow_lds();
       if (e != hipSuccess) return e;
       hipLaunchKernelGGL((attend_bf16_kernel<2, false, 64>), grid, dim3(512), TWO_STREAM_LDS_BYTES / 2, stream, p);
+    } else if (copiers) {
+      if (a.d == 64)
+        hipLaunchKernelGGL((attend_bf16_kernel<1, false, 64, 1, true>), grid, dim3(512), 0, stream, p);
+      else
+        hipLaunchKernelGGL((attend_bf16_kernel<1, false, 128, 1, true>), grid, dim3(512), 0, stream, p);
     } else if (a.d == 64) {  // rows of 128 bytes
       hipLaunchKernelGGL((attend_bf16_kernel<1, false, 64>), grid, dim3(256), 0, stream, p);
     } else if (a.kv_fp8) {  // 8-bit cache rows: the single-stream instances with landing buffers

@@ -62,6 +62,34 @@ def test_short_walks_have_the_bits_of_the_long_ones(d, H, tokens, rising):
         assert torch.equal(m, a.expand_as(m))
 
 
+# At most 256 workgroups of 128 queries that the short-walk kernel does not take: wavefronts of their own copy the tiles.  Query
+# tiles of one row and of 127, idle wavefronts, walks of two tiles and more, and the cache update by workgroups of 512 lanes.
+@pytest.mark.parametrize("rising", [False, True])
+@pytest.mark.parametrize("d,H,few,tokens", [
+    (128, 4, 16, (1, 63, 129, 200, 255)),   # 64, 128, 128, 128 workgroups
+    (128, 4, 16, (2, 64, 65, 257, 383)),    # 192 workgroups
+    (128, 4, 64, (1, 64, 66, 97, 128)),     # 256 workgroups: with the cache update by the other form, at four tiles by either
+    (64, 3, 5, (1, 65, 130, 256, 300)),
+    (64, 4, 64, (3, 64, 100, 33, 128)),     # 256 workgroups, likewise
+])
+def test_copying_wavefronts_change_no_bits(d, H, few, tokens, rising):
+    cfg = dict(L=1, H=H, d=d, dtype="bf16", batch=1, sides=[(1, n) for n in tokens])
+    q, k, v = _dev(*hi.make_qkv(65, 0, cfg))
+    if rising:
+        _rising(q, k)
+    alone = _outputs(d, H, tokens, (q, k, v), few, False)
+    fused = _outputs(d, H, tokens, (q, k, v), few, True)
+    many = _outputs(d, H, tokens, (q, k, v), 256 // H + 1, False)
+    for a, b, m in zip(alone, fused, many):
+        assert torch.isfinite(a).all() and torch.equal(a, b)
+        assert torch.equal(m, a[:1].expand_as(m)) and torch.equal(a, a[:1].expand_as(a))
+
+
+@pytest.mark.parametrize("d,batch,tokens", [(128, 16, (1, 64, 130, 200)), (64, 4, (2, 65, 130, 300))])
+def test_copying_wavefronts_against_the_oracle(d, batch, tokens):
+    _bf16_case(1, 4, tuple((1, n) for n in tokens), 1, 2, batch, seed=66, fused=True, d=d)
+
+
 # One round of up to 32 queries, d = 128, goes to the short-walk kernel whatever the number of workgroups, but not in a launch
 # with a longer walk: the same heads next to one that keeps the 100 rows of the first scale, in more workgroups than there
 # are compute units.
