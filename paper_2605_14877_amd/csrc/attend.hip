@@ -75,7 +75,7 @@ extern __shared__ __attribute__((aligned(1024))) char attend_dynamic_lds[];
 // every slot of the hand-ordered step below mixes matrix and vector work (with the compiler's own order, score
 // MFMAs clustered apart from the exponentials, the same instance gained 1 % instead of 4-6 %).
 //
-// COPIERS, for launches that give every compute unit at most one workgroup of walks too short for two key streams: four more
+// COPIERS, for launches that give every compute unit at most one workgroup, where two key streams do not pay: four more
 // wavefronts copy the tiles and do nothing else.  A wavefront that issues copies is held about 100 cycles by each, and here it
 // has its SIMD to itself, with nobody to compute meanwhile.  Same steps, same bits as without.
 template <int KS, bool FP8, int D, int QS = 1, bool COPIERS = false>
@@ -85,7 +85,8 @@ __global__ __launch_bounds__(256 * KS * QS * (COPIERS ? 2 : 1), (KS == 1 && QS =
   static_assert(!(FP8 && KS == 2), "the 8-bit cache path has one key stream");
   static_assert(D == 128 || (D == 64 && !FP8), "d = 64: bf16 cache rows");
   static_assert(QS == 1 || (KS == 1 && D == 128), "two query sets: single stream, d = 128");
-  static_assert(!COPIERS || (KS == 1 && QS == 1 && !FP8), "copying wavefronts: one stream, one query set, bf16 cache rows");
+  static_assert(!COPIERS || (KS == 1 && QS == 1), "copying wavefronts: one stream, one query set");
+  constexpr int LANES = 256 * KS * QS * (COPIERS ? 2 : 1);  // of the workgroup
   constexpr int NW = 4 * QS;  // wavefronts that share the copying of a tile
   constexpr int ROW_BYTES = 2 * D;            // one bf16 row
   constexpr int TILE_BYTES = BN * ROW_BYTES;  // 16 KB (d = 128) or 8 KB (d = 64)
@@ -496,15 +497,15 @@ __global__ __launch_bounds__(256 * KS * QS * (COPIERS ? 2 : 1), (KS == 1 && QS =
       // V(j) likewise.  Their stages are free (last read in step j-2), the landing buffers are free again after
       // the barrier, before this step's copies go out.
       const bool ck = j + 1 < tiles_all && j + 1 >= tiles_cur, cv = j >= tiles_cur;
-      if (ck) tile::convert_raw8<false, 64 * NW>(raw_k, lds[decltype(kb1)::value][0], tid);
-      if (cv) tile::convert_raw8<true, 64 * NW>(raw_v, lds[decltype(vb0)::value][1], tid);
+      if (ck) tile::convert_raw8<false, LANES>(raw_k, lds[decltype(kb1)::value][0], tid);
+      if (cv) tile::convert_raw8<true, LANES>(raw_v, lds[decltype(vb0)::value][1], tid);
       if (ck || cv) __syncthreads();
     }
     bf16x8 k0[2];
     if (active) preload(k0, kb1);
     if constexpr (CODES) {
-      if (j + 2 < steps_all) issue_k(j + 2, decltype(vb0)::value);
-      if (COPIES > 1) issue_v(j + 1, decltype(kb1)::value);
+      if (copies_tiles && j + 2 < steps_all) issue_k(j + 2, decltype(vb0)::value);
+      if (copies_tiles && COPIES > 1) issue_v(j + 1, decltype(kb1)::value);
       if (!active) return;
     } else if (!active) {
       if (!copies_tiles) return;
@@ -586,9 +587,9 @@ __global__ __launch_bounds__(256 * KS * QS * (COPIERS ? 2 : 1), (KS == 1 && QS =
   if constexpr (FP8) {
     if (it >= tiles_cur) {  // V of the last tile is still in its landing buffer
       if (it & 1)
-        tile::convert_raw8<true, 64 * NW>(raw_v, lds[1][1], tid);
+        tile::convert_raw8<true, LANES>(raw_v, lds[1][1], tid);
       else
-        tile::convert_raw8<true, 64 * NW>(raw_v, lds[0][1], tid);
+        tile::convert_raw8<true, LANES>(raw_v, lds[0][1], tid);
       __syncthreads();
     }
   }
@@ -690,6 +691,9 @@ hipError_t allow_lds() {
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attend_bf16_kernel<1, true, 128>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, FP8_LDS_BYTES);
   if (e == hipSuccess)
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attend_bf16_kernel<1, true, 128, 1, true>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, FP8_LDS_BYTES);
+  if (e == hipSuccess)
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attend_bf16_kernel<1, true, 128, 2>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, FP8_LDS_BYTES);
   if (e == hipSuccess)
@@ -767,15 +771,17 @@ hipError_t launch_attend(const AttendArgs& a, hipStream_t stream) {
     // workgroups of 784 tokens 23.9 us, copiers 24.1; d = 64, 17.0 and 18.6.  One workgroup takes a compute unit, also one that
     // copies rows of the cache update: these have to find units enough while the walks last (d = 128, workgroups of attention +
     // update, tiles of the longest walk: 96 + 192, 4 9.4 -> 9.0; 128 + 256, 4 10.2 -> 10.4; 192 + 270, 10 15.8 -> 15.1; 256 + 360,
-    // 10 17.1 -> 19.4; 256 + 512, 4 15.7 -> 19.2).
+    // 10 17.1 -> 19.4; 256 + 512, 4 15.7 -> 19.2).  8-bit cache rows have one stream, hence copiers for walks of any length, and
+    // all eight wavefronts convert: a 2B-like layer, 13 scales, batch 1 611 -> 574 us, batch 2 828 -> 802; 12 heads, batch 3,
+    // up to 361 tokens 264 -> 241.
     const int tiles = (a.t_k + BN - 1) / BN + (a.max_len + BN - 1) / BN;
-    const bool copiers = !a.kv_fp8 && !two_streams && p.attend_blocks <= TWO_STREAM_MAX_BLOCKS &&
+    const bool copiers = !two_streams && p.attend_blocks <= TWO_STREAM_MAX_BLOCKS &&
                          p.attend_blocks + copy_blocks <= 190u + 28u * tiles;
     if (a.d == 64 && two_streams) {
       const hipError_t e = allow_lds();
       if (e != hipSuccess) return e;
       hipLaunchKernelGGL((attend_bf16_kernel<2, false, 64>), grid, dim3(512), TWO_STREAM_LDS_BYTES / 2, stream, p);
-    } else if (copiers) {
+    } else if (copiers && !a.kv_fp8) {
       if (a.d == 64)
         hipLaunchKernelGGL((attend_bf16_kernel<1, false, 64, 1, true>), grid, dim3(512), 0, stream, p);
       else
@@ -790,7 +796,10 @@ hipError_t launch_attend(const AttendArgs& a, hipStream_t stream) {
         hipLaunchKernelGGL((attend_bf16_kernel<1, true, 128, 2>), dim3(wide_blocks + copy_blocks), dim3(512),
                            FP8_LDS_BYTES, stream, p);
       } else {
-        hipLaunchKernelGGL((attend_bf16_kernel<1, true, 128>), grid, dim3(256), FP8_LDS_BYTES, stream, p);
+        if (copiers)
+          hipLaunchKernelGGL((attend_bf16_kernel<1, true, 128, 1, true>), grid, dim3(512), FP8_LDS_BYTES, stream, p);
+        else
+          hipLaunchKernelGGL((attend_bf16_kernel<1, true, 128>), grid, dim3(256), FP8_LDS_BYTES, stream, p);
       }
     } else if (two_streams) {
       const hipError_t e = allow_lds();

@@ -166,6 +166,20 @@ def test_8_bit_cache_walks_of_few_current_tiles(side):
     _check_attention(sep, qkv, t0, ref["present"], sm)
 
 
+@pytest.mark.parametrize("sides", [(1, 2, 5, 8, 11), (1, 2, 8, 13, 18), (1, 2, 7, 19, 22)])
+def test_8_bit_cache_with_copying_wavefronts_has_the_bits_of_a_launch_of_many_workgroups(sides):
+    # 3 heads: one batch row takes at most 12 workgroups, next to which four wavefronts only copy and all eight convert; 257
+    # workgroups and more go without.  Walks of a current-scale tile and codes, of several of both, with and without the update.
+    few = _case(1, 3, sides, 2, 2, 1, seed=78)
+    many = _case(1, 3, sides, 2, 2, 86, seed=78)
+    t0, c, d, qkv = few[0], few[1], few[3], few[7]
+    rep = [tuple(x.repeat(86, 1, 1, 1) for x in xs) for xs in qkv]
+    sm = 1.0 / np.sqrt(d)
+    outs = [_run(few[5], qkv, t0, c, sm)[0], _run(few[5], qkv, t0, c, sm, fused_layers=(0,))[0], _run(many[5], rep, t0, c, sm)[0]]
+    for a, b, m in zip(*outs):
+        assert torch.equal(a, b) and torch.equal(m, a.expand_as(m))
+
+
 def test_layer2b_full_size_with_8_bit_cache():
     # one 2B-like layer at its real shape; the same byte budget as the bf16 case now holds twice the tokens
     cfg = hi.CONFIGS["layer2b"]
