@@ -543,7 +543,7 @@ __global__ __launch_bounds__(64 * FW * (G > 0 ? G : 1)) void calibrate_f32_kerne
     cur += (prob(s[0], m) + prob(s[1], m)) + (prob(s[2], m) + prob(s[3], m));
     if (k2 != here) {  // the wavefront leaves the block
       const float mb = f32m::max_groups(m);
-      const float sb = f32m::sum_groups(cur * prob(m, mb));
+      const float sb = f32m::sum_groups_product(cur, prob(m, mb));
       if (g == 0) {
         blk[here][0][wave][n] = sb;
         blk[here][1][wave][n] = mb;

@@ -41,6 +41,14 @@ __device__ __forceinline__ void split_halves(float v, float& lower, float& upper
   lower = a;
   upper = b;
 }
+// The same for the four rows of 16 lanes, with one v_permlane16_swap (odd rows of the first register for even rows of the
+// second): the value of the even row of each pair of rows, and that of the odd row, on the lanes of both.
+__device__ __forceinline__ void split_rows(float v, float& even, float& odd) {
+  float a = v, b = v;
+  asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+  even = a;
+  odd = b;
+}
 __device__ __forceinline__ float max_halves(float v) {
   float a, b;
   split_halves(v, a, b);

@@ -139,3 +139,17 @@ def test_no_tile_copy_depends_on_scalars_from_the_vector_alu():
             assert not hazards, (src, hazards[:8])
             total += copies
         print(f"{total} copy instructions checked")
+
+
+def test_fp32_kernels_reduce_over_lane_groups_in_registers():
+    # At the end of every block of keys: an exchange through LDS takes a round trip, and lane numbers to go with it.
+    with tempfile.TemporaryDirectory() as tmp:
+        for src, kernel in (("calibrate.hip", "calibrate_f32_kernel"), ("attend_f32.hip", "attend_f32_kernel")):
+            out = os.path.join(tmp, src + ".s")
+            subprocess.run(["hipcc", *hb.HIP_FLAGS, "-S", "--cuda-device-only", os.path.join(hb.CSRC, src), "-o", out],
+                           check=True, capture_output=True)
+            with open(out) as f:
+                bodies = re.findall(r"^(_ZN\S*%s\S*):[^\n]*\n(.*?)^\.Lfunc_end" % kernel, f.read(), re.M | re.S)
+            assert bodies, src
+            for name, body in bodies:
+                assert "v_permlane16_swap_b32" in body and "ds_bpermute" not in body, name
