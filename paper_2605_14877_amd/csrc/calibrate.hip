@@ -1112,7 +1112,15 @@ hipError_t launch_calibrate(const CalibrateArgs& a, hipStream_t stream) {
     const CalibDirect direct{a.mass[0], a.beta, a.weight, a.layer};
     size_t lds = a.d == 64 ? f32_lds_bytes<64>(k1_max) : f32_lds_bytes<128>(k1_max);
     // One query tile and the average asked for: no second launch.  Several scales in one call keep it, the launch reduces all.
-    if (a.beta && a.n_scales == 1 && a.t[a.k1[0]] <= FQ && a.batch <= 2)
+    // Two batch rows share a workgroup, two wavefronts per SIMD whose matrix instructions take turns, where the other form has
+    // a unit for each (up to 128 heads): every key tile costs more, until the launch is not worth it.  Two -> one launch, 4 to
+    // 128 heads, d = 64: 272 keys (17 tiles) 7.5 -> 7.3 us, 384 8.2 -> 8.2, 512 8.9 -> 9.3, 1000 12.5 -> 14.6; d = 128: 64 keys 6.4 ->
+    // 6.1, 31 scales of 16 up to 8 tiles 7.8 -> 7.4 and up to 12 8.7 -> 8.8, but 112 + 16 keys 7.4 -> 7.5, 272 9.4 -> 10.7, 1000 17.4 ->
+    // 23.3.  129 to 256 heads share units in either form: 160 heads, d = 128, 64 keys 8.0 -> 6.3, 1000 23.5 -> 20.6.
+    int key_tiles = 0;
+    for (int k = 0; k <= a.k1[0]; ++k) key_tiles += (a.t[k] + FQ - 1) / FQ;
+    const bool rows_share = a.batch == 1 || (a.batch == 2 && (key_tiles <= (a.d == 64 ? 20 : 8) || (a.H > 128 && a.H <= 256)));
+    if (a.beta && a.n_scales == 1 && a.t[a.k1[0]] <= FQ && rows_share)
       return launch_calibrate_one_tile(p, direct, a.d, lds, stream);
     // d = 128: three or four workgroups per compute unit (the registers allow four, the LDS as well up to 15 scales), whichever
     // needs fewer turns times workgroups side by side; three where neither does.  Three -> four: 32 pairs, 400 x 921 keys (800

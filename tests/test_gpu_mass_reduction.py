@@ -72,3 +72,29 @@ def test_scales_of_one_query_tile_have_the_bits_of_a_call_for_all_scales(H, batc
     assert torch.equal(one, each) and not torch.equal(one[1], start[1]) and torch.equal(one[0], start[0])
     for a, b in zip(*masses):
         assert a is b is None or torch.equal(a, b)
+
+
+# Two batch rows of one query tile share a workgroup while the walk over the keys is short, or where there are units for half of
+# the workgroups only; one row has its own at any length.  The form with a second launch leaves its partial sums in the workspace.
+@pytest.mark.parametrize("d,H,batch,tokens,one_launch", [
+    (64, 3, 2, (304, 16), True), (64, 3, 2, (305, 16), False),   # 20 and 21 key tiles
+    (128, 3, 2, (112, 16), True), (128, 3, 2, (113, 16), False),  # 8 and 9
+    (128, 3, 2, (1,) * 7 + (16,), True), (128, 3, 2, (1,) * 8 + (16,), False),
+    (128, 128, 2, (500, 16), False), (128, 129, 2, (500, 16), True), (128, 256, 2, (500, 16), True), (64, 257, 2, (500, 16), False),
+    (128, 3, 1, (900, 16), True), (64, 3, 1, (900, 16), True), (64, 3, 3, (1, 16), False),
+])
+def test_two_batch_rows_share_a_workgroup_for_short_walks(d, H, batch, tokens, one_launch):
+    K = len(tokens)
+    torch.manual_seed(93)
+    q = torch.randn(batch, H, tokens[-1], d, device="cuda")
+    k = torch.randn(batch, H, sum(tokens), d, device="cuda")
+    shape = hk.Shape(1, H, d, tokens, batch, "f32")
+    ws = torch.full((hk.binding.calibrate_scales_workspace_bytes(shape, [K - 1]),), 255, dtype=torch.uint8, device="cuda")
+    one, each = torch.zeros(1, H, K, K, device="cuda"), torch.zeros(1, H, K, K, device="cuda")
+    hk.heatkv_calibrate_accumulate(shape, 0, K - 1, q, k, d ** -0.5, 0.5, one, None, ws)
+    assert bool((ws == 255).all()) == one_launch
+    mass = torch.empty(batch, H, K, device="cuda")
+    hk.heatkv_calibrate(shape, 0, K - 1, q, k, d ** -0.5, mass, ws)
+    each[0, :, K - 1] = 0.5 * sum(mass[b] for b in range(batch))
+    assert torch.equal(one, each)
+    assert torch.allclose(mass.sum(-1), torch.ones(batch, H, device="cuda"), atol=1e-5)
