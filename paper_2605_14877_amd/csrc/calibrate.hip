@@ -20,6 +20,7 @@
 #include "f32_mfma.h"
 #include "f32_split.h"
 #include "kernels.h"
+#include "launch_rules.h"
 #include "tile_lds.h"
 
 namespace heatkv {
@@ -1122,11 +1123,10 @@ hipError_t launch_calibrate(const CalibrateArgs& a, hipStream_t stream) {
     const bool rows_share = a.batch == 1 || (a.batch == 2 && (key_tiles <= (a.d == 64 ? 20 : 8) || (a.H > 128 && a.H <= 256)));
     if (a.beta && a.n_scales == 1 && a.t[a.k1[0]] <= FQ && rows_share)
       return launch_calibrate_one_tile(p, direct, a.d, lds, stream);
-    // d = 128: three or four workgroups per compute unit (the registers allow four, the LDS as well up to 15 scales), whichever
-    // needs fewer turns times workgroups side by side; three where neither does.  Three -> four: 32 pairs, 400 x 921 keys (800
-    // workgroups) 50 -> 45 us, 64 pairs 256 x 521 (1024) 41 -> 32 and 400 x 921 (1600) 80 -> 74, 256 pairs 64 x 121 (1024) 23 -> 17;
-    // but 256 pairs 144 x 265 (2304) 46.5 -> 49, 32 and 64 pairs 144 x 265 (288, 576) 14.2 -> 14.6 and 18.1 -> 18.6.
-    if (a.d == 128 && (blocks + 767) / 768 * 3 <= (blocks + 1023) / 1024 * 4) lds = std::max(lds, size_t(kMaxLds / 4 + 1024));
+    const int fit = std::min(int(kMaxLds / lds), a.d == 64 ? 7 : 4);
+    const int per_unit = rules::calibration_f32_per_unit(a.d, p.n_scales, blocks, fit);
+    if (per_unit < fit)  // more LDS than it needs keeps further workgroups off the unit
+      lds = std::max(lds, size_t(kMaxLds / (per_unit + 1) + 1024) & ~size_t(1023));
     if (a.d == 64)
       hipLaunchKernelGGL((calibrate_f32_kernel<64, 0>), dim3(blocks), dim3(64 * FW), lds, stream, p, direct);
     else

@@ -1,0 +1,8 @@
+// The launchers' rules as C functions, for tests without a GPU.
+#include "launch_rules.h"
+
+using namespace heatkv;
+
+extern "C" int calibration_f32_per_unit(int d, int n_scales, unsigned blocks, int fit) {
+  return rules::calibration_f32_per_unit(d, n_scales, blocks, fit);
+}

@@ -1,0 +1,35 @@
+"""Rules of the launchers that change no bits, or that kernels of other last bits hang on: shapes that were timed on both
+sides stay on the one that was faster."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    lib = str(tmp_path_factory.mktemp("rules") / "rules.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC",
+                    "-I", os.path.join(ROOT, "paper_2605_14877_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "native", "launch_rules.cpp"), "-o", lib], check=True)
+    return ctypes.CDLL(lib)
+
+
+@pytest.mark.parametrize("d,n_scales,blocks,fit,per_unit", [
+    # one scale: 32 pairs x 400 rows, 64 x 256, 256 x 144, 32 x 144
+    (128, 1, 800, 4, 4), (128, 1, 1024, 4, 4), (128, 1, 2304, 4, 3), (128, 1, 288, 4, 3),
+    # the same behind so many scales that four do not fit: 64 pairs x 225 rows, 80 x 169, 104 x 144; 48 x 225, 80 x 196
+    (128, 1, 960, 3, 2), (128, 1, 880, 3, 2), (128, 1, 936, 3, 2), (128, 1, 720, 3, 3), (128, 1, 1040, 3, 3), (128, 1, 800, 3, 3),
+    (128, 1, 801, 3, 2), (128, 1, 1025, 3, 3),
+    # all scales in one call: 16 pairs up to 400 rows, 40 pairs up to 276 and up to 300; many short workgroups behind the long ones
+    (128, 8, 960, 4, 3), (128, 7, 1720, 4, 3), (128, 6, 1760, 4, 3), (128, 7, 2000, 4, 4), (128, 7, 4472, 4, 4), (128, 5, 13312, 4, 4),
+    (128, 20, 4472, 3, 3), (128, 2, 7 * 256, 4, 3), (128, 2, 7 * 256 + 1, 4, 4), (128, 20, 960, 3, 3),
+    # d = 64: 48 pairs x 603 rows, 48 x 635, 64 x 491, 64 x 507, 48 x 683; all scales of 40 pairs up to 276, of 48 up to 625
+    (64, 1, 1824, 7, 7), (64, 1, 1920, 7, 6), (64, 1, 1984, 7, 6), (64, 1, 2048, 7, 6), (64, 1, 2064, 7, 7), (64, 1, 1984, 6, 6),
+    (64, 1, 1984, 4, 4), (64, 7, 1720, 7, 7), (64, 8, 1984, 7, 7),
+])
+def test_workgroups_of_the_fp32_calibration_per_compute_unit(rules, d, n_scales, blocks, fit, per_unit):
+    assert rules.calibration_f32_per_unit(d, n_scales, blocks, fit) == per_unit
