@@ -13,6 +13,7 @@
 #include "attend_params.h"
 #include "device_util.h"
 #include "kernels.h"
+#include "launch_rules.h"
 #include "tile_lds.h"
 
 namespace heatkv {
@@ -765,18 +766,11 @@ hipError_t launch_attend(const AttendArgs& a, hipStream_t stream) {
     // launch, one stream -> two: 16 heads, 576 tokens 15.0 -> 13.4 us, 1024 24.6 -> 21.1, 1600 36.5 -> 30.6, 32 pairs 1024 tokens
     // 26.1 -> 22.9; 100 tokens 6.8 -> 7.4, 169 and 256 the same; 320 workgroups (64 pairs, 576 tokens) 18.2 -> 20.0.
     const bool two_streams = !a.kv_fp8 && p.attend_blocks <= TWO_STREAM_MAX_BLOCKS && a.t_k >= TWO_STREAM_MIN_TOKENS;
-    // For shorter walks wavefronts that only copy, on the SIMDs of those that compute.  One launch, without -> with them: d =
-    // 128, 48 pairs, 196 tokens 13.9 -> 13.1 us, 324 19.2 -> 17.8; 64 pairs, 144 10.2 -> 9.7; 128 pairs, 256 (256 workgroups)
-    // 15.8 -> 14.8; d = 64, 64 pairs, 196 10.9 -> 10.3, 324 14.7 -> 13.9.  From 384 tokens on two streams: d = 128, 112
-    // workgroups of 784 tokens 23.9 us, copiers 24.1; d = 64, 17.0 and 18.6.  One workgroup takes a compute unit, also one that
-    // copies rows of the cache update: these have to find units enough while the walks last (d = 128, workgroups of attention +
-    // update, tiles of the longest walk: 96 + 192, 4 9.4 -> 9.0; 128 + 256, 4 10.2 -> 10.4; 192 + 270, 10 15.8 -> 15.1; 256 + 360,
-    // 10 17.1 -> 19.4; 256 + 512, 4 15.7 -> 19.2).  8-bit cache rows have one stream, hence copiers for walks of any length, and
-    // all eight wavefronts convert: a 2B-like layer, 13 scales, batch 1 611 -> 574 us, batch 2 828 -> 802; 12 heads, batch 3,
-    // up to 361 tokens 264 -> 241.
-    const int tiles = (a.t_k + BN - 1) / BN + (a.max_len + BN - 1) / BN;
+    // Otherwise wavefronts that only copy.  From 384 tokens on, two streams -> copiers: d = 128, 112 workgroups of 784 tokens 23.9
+    // us -> 24.1; d = 64, 17.0 -> 18.6.  8-bit cache rows have one stream, hence copiers for walks of any length.
+    const unsigned tiles = (a.t_k + BN - 1) / BN + (a.max_len + BN - 1) / BN;
     const bool copiers = !two_streams && p.attend_blocks <= TWO_STREAM_MAX_BLOCKS &&
-                         p.attend_blocks + copy_blocks <= 190u + 28u * tiles;
+                         rules::copying_wavefronts(a.d, p.attend_blocks, copy_blocks, tiles);
     if (a.d == 64 && two_streams) {
       const hipError_t e = allow_lds();
       if (e != hipSuccess) return e;

@@ -28,5 +28,26 @@ inline int calibration_f32_per_unit(int d, int n_scales, unsigned blocks, int fi
   return n_scales == 1 && blocks > 800 && blocks <= 1024 ? 2 : 3;
 }
 
+// bf16 attention, launches of at most 256 workgroups that take a compute unit each, also those that copy rows of the cache
+// update: do these find free units, or units that short walks leave, before the longest walk (`tiles` of 64 keys) is over?
+// Fitted, like the lines below, to 2600 launches of 150 schedules each at d = 64, at d = 128 and with 8-bit rows.
+inline bool update_finds_units(int d, unsigned attend_blocks, unsigned update_blocks, unsigned tiles) {
+  return update_blocks <= 4 * (256 - attend_blocks) + (d == 64 ? 14 : 22) * tiles;
+}
+
+// Wavefronts that only copy tiles, on the SIMDs of those that compute, where a workgroup has one key stream.  One launch,
+// without -> with them: d = 128, 48 pairs, 196 tokens 13.9 -> 13.1 us, 324 19.2 -> 17.8; 64 pairs, 144 10.2 -> 9.7; 128 pairs, 256
+// (256 workgroups) 15.8 -> 14.8; d = 64, 64 pairs, 196 10.9 -> 10.3, 324 14.7 -> 13.9.  8-bit cache rows, where all eight
+// wavefronts convert: a 2B-like layer, 13 scales, batch 1 611 -> 574, batch 2 828 -> 802; 12 heads, batch 3, up to 361 tokens 264
+// -> 241.  Not for walks of one tile, which have nothing to copy ahead (8-bit rows 4.27 -> 4.37), nor where the update's
+// workgroups would wait for units.  Two lines, workgroups of attention + update, tiles of the longest walk: for short walks d =
+// 128, 96 + 192, 4 9.4 -> 9.0; 128 + 256, 4 10.2 -> 10.4; 192 + 270, 10 15.8 -> 15.1; 256 + 360, 10 17.1 -> 19.4; 256 + 512, 4 15.7 ->
+// 19.2; for long ones the line above, 8-bit rows, 256 + 208, 10 19.4 -> 17.4; 256 + 378, 20 32.3 -> 28.0; 200 + 480, 23 36.2 -> 31.7;
+// but 256 + 320, 14 23.2 -> 24.7; 256 + 333, 15 25.4 -> 26.9; 256 + 480, 20 32.5 -> 33.0; d = 64, 256 + 336, 15 15.0 -> 16.1; 240 + 678,
+// 31 27.2 -> 29.2.
+inline bool copying_wavefronts(int d, unsigned attend_blocks, unsigned copy_blocks, unsigned tiles) {
+  return tiles > 1 && attend_blocks + copy_blocks <= 190 + 28 * tiles && update_finds_units(d, attend_blocks, copy_blocks, tiles);
+}
+
 }  // namespace rules
 }  // namespace heatkv

@@ -33,3 +33,19 @@ def rules(tmp_path_factory):
 ])
 def test_workgroups_of_the_fp32_calibration_per_compute_unit(rules, d, n_scales, blocks, fit, per_unit):
     assert rules.calibration_f32_per_unit(d, n_scales, blocks, fit) == per_unit
+
+
+@pytest.mark.parametrize("d,attend,copies,tiles,copiers", [
+    # short walks, bf16 rows
+    (128, 96, 192, 4, True), (128, 128, 256, 4, False), (128, 192, 270, 10, True), (128, 256, 360, 10, False), (128, 256, 512, 4, False),
+    # long walks, 8-bit rows
+    (128, 256, 208, 10, True), (128, 256, 378, 20, True), (128, 200, 480, 23, True), (128, 240, 456, 23, True), (128, 224, 304, 15, True),
+    (128, 256, 320, 14, False), (128, 256, 333, 15, False), (128, 256, 480, 20, False), (128, 240, 960, 23, False),
+    # long walks, d = 64
+    (64, 160, 200, 8, True), (64, 240, 188, 16, True), (64, 256, 288, 14, False), (64, 256, 336, 15, False), (64, 240, 678, 31, False),
+    (64, 256, 640, 39, False),
+    # no update; one tile
+    (128, 256, 0, 14, True), (64, 192, 0, 7, True), (128, 32, 0, 1, False), (128, 16, 15, 1, False), (128, 32, 0, 2, True),
+])
+def test_wavefronts_that_only_copy(rules, d, attend, copies, tiles, copiers):
+    assert rules.copying_wavefronts(d, attend, copies, tiles) == copiers
