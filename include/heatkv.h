@@ -248,10 +248,10 @@ int heatkv_append_scale(heatkv_plan* plan, int layer, int k, const void* k_new, 
  * Softmax statistics and accumulation are fp32; bf16 inputs are multiplied on
  * the matrix cores with fp32 accumulation, probabilities are rounded to bf16
  * before the second product.  sm_scale of bf16 shapes must be positive.
- * Which kernel a launch takes follows from its sizes (t[k], H, batch, run lengths)
- * and, for fp32, sm_scale: a head's outputs are the same bits from call to call and
- * with heatkv_attend_append_scale, but may differ in the last bits between batch
- * sizes or numbers of heads.
+ * Which kernel a launch takes follows from its sizes (t[k], H, batch, run lengths
+ * before and after the scale's update) and, for fp32, sm_scale: a head's outputs are
+ * the same bits from call to call and with heatkv_attend_append_scale, but may differ
+ * in the last bits between batch sizes, numbers of heads or plans.
  */
 size_t heatkv_attend_workspace_bytes(const heatkv_plan* plan, int layer, int k);
 int heatkv_attend_scale(heatkv_plan* plan, int layer, int k, const void* q, const void* k_cur,

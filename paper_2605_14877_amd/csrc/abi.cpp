@@ -315,7 +315,8 @@ int attend_impl(heatkv_plan* plan, int layer, int k, const void* q, const void* 
   if (max_len > 0 && (!k_arena || !v_arena)) return fail(HEATKV_EINVAL, "null arena pointer");
   const size_t need = heatkv::attend_workspace_bytes(plan->dtype, plan->d, plan->H, plan->batch, plan->t[k], max_len);
   if (need > 0 && (!ws || ws_bytes < need)) return fail(HEATKV_EINVAL, "attend workspace too small");
-  const int ndesc = (with_append && k < plan->K - 1) ? plan->desc_count[plan->idx(k, layer)] : 0;
+  const int update_descs = k < plan->K - 1 ? plan->desc_count[plan->idx(k, layer)] : 0;
+  const int ndesc = with_append ? update_descs : 0;
   if (ndesc > 0 && (!k_arena_rw || !v_arena_rw)) return fail(HEATKV_EINVAL, "null arena pointer");
   if ((rc = ensure_uploaded(plan))) return rc;
   heatkv::AttendArgs a{};
@@ -329,6 +330,7 @@ int attend_impl(heatkv_plan* plan, int layer, int k, const void* q, const void* 
   const size_t off = plan->idx(k, layer, 0);
   a.work = plan->dev.work + off;
   a.max_len = max_len;
+  a.update_descs = update_descs;
   {  // runs of equal length (no head of the layer has lost a scale yet): addresses follow from the head index
     const int32_t* len = &plan->run_len[off];
     bool uniform = true;

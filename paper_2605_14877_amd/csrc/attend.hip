@@ -762,15 +762,14 @@ hipError_t launch_attend(const AttendArgs& a, hipStream_t stream) {
       const hipError_t e = allow_lds();
       return e == hipSuccess ? launch_attend_short(p, a.d, a.max_len, copy_blocks, stream) : e;
     }
-    // At most one workgroup per compute unit: two key streams per workgroup put two wavefronts on every SIMD.  d = 64, one
-    // launch, one stream -> two: 16 heads, 576 tokens 15.0 -> 13.4 us, 1024 24.6 -> 21.1, 1600 36.5 -> 30.6, 32 pairs 1024 tokens
-    // 26.1 -> 22.9; 100 tokens 6.8 -> 7.4, 169 and 256 the same; 320 workgroups (64 pairs, 576 tokens) 18.2 -> 20.0.
-    const bool two_streams = !a.kv_fp8 && p.attend_blocks <= TWO_STREAM_MAX_BLOCKS && a.t_k >= TWO_STREAM_MIN_TOKENS;
-    // Otherwise wavefronts that only copy.  From 384 tokens on, two streams -> copiers: d = 128, 112 workgroups of 784 tokens 23.9
-    // us -> 24.1; d = 64, 17.0 -> 18.6.  8-bit cache rows have one stream, hence copiers for walks of any length.
-    const unsigned tiles = (a.t_k + BN - 1) / BN + (a.max_len + BN - 1) / BN;
+    // At most one workgroup per compute unit: two key streams per workgroup put two wavefronts on every SIMD.
+    const unsigned tiles = (a.t_k + BN - 1) / BN + (a.max_len + BN - 1) / BN, with_queries = unsigned(p.n_qtiles) * a.H * a.batch;
+    const bool two_streams = !a.kv_fp8 && p.attend_blocks <= TWO_STREAM_MAX_BLOCKS && a.t_k >= TWO_STREAM_MIN_TOKENS &&
+                             rules::two_key_streams(a.d, with_queries, unsigned(a.update_descs) * a.batch, tiles);
+    // Otherwise wavefronts that only copy (112 workgroups of 784 tokens, two streams -> copiers: d = 128 23.9 us -> 24.1, d = 64 17.0
+    // -> 18.6).  8-bit cache rows have one stream, hence copiers for walks of any length.
     const bool copiers = !two_streams && p.attend_blocks <= TWO_STREAM_MAX_BLOCKS &&
-                         rules::copying_wavefronts(a.d, p.attend_blocks, copy_blocks, tiles);
+                         rules::copying_wavefronts(a.d, with_queries, copy_blocks, tiles);
     if (a.d == 64 && two_streams) {
       const hipError_t e = allow_lds();
       if (e != hipSuccess) return e;

@@ -24,6 +24,7 @@ struct AttendArgs {
   float sm_scale;
   void* ws;
   size_t ws_bytes;
+  int update_descs = 0;      // copy descriptors of the cache update behind this layer and scale, in this launch or not
   // Optional fused cache update (append_scale of the same layer and scale): extra workgroups of the same
   // launch run these copy descriptors.  ndesc == 0: attention only.
   const CopyDesc* descs = nullptr;

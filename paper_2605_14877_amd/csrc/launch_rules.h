@@ -30,9 +30,10 @@ inline int calibration_f32_per_unit(int d, int n_scales, unsigned blocks, int fi
 
 // bf16 attention, launches of at most 256 workgroups that take a compute unit each, also those that copy rows of the cache
 // update: do these find free units, or units that short walks leave, before the longest walk (`tiles` of 64 keys) is over?
-// Fitted, like the lines below, to 2600 launches of 150 schedules each at d = 64, at d = 128 and with 8-bit rows.
+// `attend_blocks`: workgroups that have queries (the grid is padded to a multiple of 8 pairs, those without end at once).
+// Fitted, like the lines below, to 1200 launches of two-stream shapes at d = 64 and 2600 each of others, with bf16 and 8-bit rows.
 inline bool update_finds_units(int d, unsigned attend_blocks, unsigned update_blocks, unsigned tiles) {
-  return update_blocks <= 4 * (256 - attend_blocks) + (d == 64 ? 14 : 22) * tiles;
+  return update_blocks <= 9 * (256 - attend_blocks) / 2 + (d == 64 ? 14 : 22) * tiles;
 }
 
 // Wavefronts that only copy tiles, on the SIMDs of those that compute, where a workgroup has one key stream.  One launch,
@@ -47,6 +48,18 @@ inline bool update_finds_units(int d, unsigned attend_blocks, unsigned update_bl
 // 31 27.2 -> 29.2.
 inline bool copying_wavefronts(int d, unsigned attend_blocks, unsigned copy_blocks, unsigned tiles) {
   return tiles > 1 && attend_blocks + copy_blocks <= 190 + 28 * tiles && update_finds_units(d, attend_blocks, copy_blocks, tiles);
+}
+
+// Two key streams per workgroup from 384 tokens on.  d = 128: always.  d = 64: workgroups of two streams have a unit to themselves,
+// also those that copy rows of the update, which one-stream workgroups have room for: not where these would wait, and below 12
+// tiles one stream next to copying wavefronts is the faster one.  `update_blocks` counts the plan's update also for a launch
+// without it, whose outputs have to be the same bits (such launches lose 6 to 10 % by that where the update is what decides).  One
+// launch, one stream (the better of its forms) -> two, workgroups of attention + update, tiles: 256 + 0, 39 30.4 -> 27.2 us; 256 +
+// 284, 39 29.9 -> 27.4; 256 + 256, 20 17.4 -> 16.2; 240 + 324, 31 24.2 -> 22.3; 192 + 576, 23 19.2 -> 18.2; 180 + 810, 36 31.5 -> 24.5;
+// 192 + 384, 12 12.2 -> 12.0; but 256 + 288, 14 14.0 -> 15.4; 256 + 768, 23 22.7 -> 24.9; 240 + 640, 16 16.9 -> 20.5; 240 + 248, 12 12.5
+// -> 13.6; 256 + 128, 8 9.7 -> 10.6; 192 + 0, 7 8.2 -> 8.8; 160 + 0, 8 8.8 -> 8.9.
+inline bool two_key_streams(int d, unsigned attend_blocks, unsigned update_blocks, unsigned tiles) {
+  return d == 128 || (tiles >= 12 && update_finds_units(d, attend_blocks, update_blocks, tiles));
 }
 
 }  // namespace rules

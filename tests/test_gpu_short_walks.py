@@ -90,6 +90,27 @@ def test_copying_wavefronts_against_the_oracle(d, batch, tokens):
     _bf16_case(1, 4, tuple((1, n) for n in tokens), 1, 2, batch, seed=66, fused=True, d=d)
 
 
+# 256 workgroups of 400 queries.  The first two have walks of 8 and 14 tiles and updates of 256 and 512 workgroups behind them,
+# which would wait for units: one stream, the bits of a launch of more workgroups, with the update in the launch or not.  The last
+# scale, without an update and of 21 tiles, has two streams, whose last bits are others.
+def test_updates_of_many_workgroups_keep_one_stream_at_head_dimension_64():
+    d, H, tokens = 64, 4, [1, 400, 400, 401]
+    K = len(tokens)
+    cfg = dict(L=1, H=H, d=d, dtype="bf16", batch=1, sides=[(1, n) for n in tokens])
+    q, k, v = _dev(*hi.make_qkv(67, 0, cfg))
+    present = np.zeros((K, 1, H, K), np.uint8)
+    for kk in range(1, K):
+        present[kk, 0, :, :kk] = 1
+    outs = []
+    for rows, fused in ((16, False), (16, True), (17, False)):
+        plan = hk.heatkv_load_schedule(hk.Shape(1, H, d, tokens, rows, "bf16"), present)
+        qkv = (x.repeat(rows, 1, 1, 1).contiguous() for x in (q, k, v))
+        outs.append(device_generation(plan, 0, *qkv, tokens, 1.0 / np.sqrt(d), fused=fused))
+    for kk, (a, b, m) in enumerate(zip(*outs)):
+        assert torch.equal(a, b) and torch.equal(a, a[:1].expand_as(a)) and torch.equal(m, m[:1].expand_as(m))
+        assert torch.equal(m[0], a[0]) == (kk < 3), kk
+
+
 # One round of up to 32 queries, d = 128, goes to the short-walk kernel whatever the number of workgroups, but not in a launch
 # with a longer walk: the same heads next to one that keeps the 100 rows of the first scale, in more workgroups than there
 # are compute units.

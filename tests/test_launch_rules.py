@@ -49,3 +49,14 @@ def test_workgroups_of_the_fp32_calibration_per_compute_unit(rules, d, n_scales,
 ])
 def test_wavefronts_that_only_copy(rules, d, attend, copies, tiles, copiers):
     assert rules.copying_wavefronts(d, attend, copies, tiles) == copiers
+
+
+@pytest.mark.parametrize("attend,update,tiles,two", [
+    (256, 0, 39, True), (256, 284, 39, True), (256, 256, 20, True), (256, 148, 14, True), (256, 196, 15, True), (240, 324, 31, True),
+    (240, 192, 18, True), (180, 675, 29, True), (180, 810, 36, True), (224, 328, 23, True), (192, 576, 23, True), (192, 384, 12, True), (160, 512, 31, True),
+    (256, 288, 14, False), (256, 336, 15, False), (256, 768, 23, False), (240, 640, 16, False), (240, 480, 18, False),
+    (240, 248, 12, False), (224, 448, 14, False), (256, 128, 8, False), (192, 0, 7, False), (240, 0, 7, False), (160, 0, 8, False),
+])
+def test_two_key_streams_at_head_dimension_64(rules, attend, update, tiles, two):
+    assert rules.two_key_streams(64, attend, update, tiles) == two
+    assert rules.two_key_streams(128, attend, update, tiles)
