@@ -954,6 +954,8 @@ hipError_t launch_calibrate_one_tile(const CalibParams& p, const CalibDirect& di
       hipLaunchKernelGGL((calibrate_f32_kernel<128, 1>), grid, block, lds, stream, p, direct);
     return hipGetLastError();
   }
+  static_assert(2 * f32_lds_bytes<64>(MAXK - 1) <= 64 * 1024 && f32_lds_bytes<128>(MAXK - 1) <= 64 * 1024,
+                "launched without a raised limit");
   // d = 128: more than 64 KB of dynamic LDS needs the function attribute raised, once per device.
   static std::atomic<unsigned long long> raised{0};  // one bit per device ordinal below 64
   int dev = 0;

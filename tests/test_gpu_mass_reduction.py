@@ -82,6 +82,7 @@ def test_scales_of_one_query_tile_have_the_bits_of_a_call_for_all_scales(H, batc
     (128, 3, 2, (1,) * 7 + (16,), True), (128, 3, 2, (1,) * 8 + (16,), False),
     (128, 128, 2, (500, 16), False), (128, 129, 2, (500, 16), True), (128, 256, 2, (500, 16), True), (64, 257, 2, (500, 16), False),
     (128, 3, 1, (900, 16), True), (64, 3, 1, (900, 16), True), (64, 3, 3, (1, 16), False),
+    (64, 129, 2, (1,) * 30 + (16,), True), (128, 129, 2, (1,) * 30 + (16,), True),  # 31 scales: the most LDS, 64 and 98 KB
 ])
 def test_two_batch_rows_share_a_workgroup_for_short_walks(d, H, batch, tokens, one_launch):
     K = len(tokens)
