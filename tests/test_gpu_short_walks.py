@@ -173,6 +173,55 @@ def test_special_operands_as_in_the_long_walks(d, kind):
         torch.testing.assert_close(m[:, :H], a.expand(batch, -1, -1, -1), rtol=0, atol=0, equal_nan=True)
 
 
+# Two key streams at d = 64 (385 and more tokens, 12 tiles and more), whose merge brings two references together: operands that
+# raise them far apart, tiles of one stream masked throughout, and the special ones above, against 64 bits.  Probabilities and
+# outputs are rounded to bf16, 2^-9 each, the row sum is taken over the rounded ones, and scores of up to 750 in fp32 move
+# a probability by 1e-4.
+@pytest.mark.parametrize("kind", ["ordinary", "rising", "falling", "one stream of -inf", "one stream of the lowest value",
+                                  "other stream of -inf", "keys of -inf", "all keys of -inf", "an infinite key", "large keys",
+                                  "an infinite value", "a NaN value", "a NaN query"])
+def test_two_key_streams_of_head_dimension_64_on_special_operands(kind):
+    d, H, tokens = 64, 3, [100, 300, 385, 450]
+    K, n, sm = len(tokens), sum(tokens), 1.0 / np.sqrt(64)
+    g = torch.Generator(device="cuda").manual_seed(68)
+    q, k, v = (torch.randn(1, H, n, d, generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+    if kind in ("rising", "falling"):
+        _rising(q, k)
+        if kind == "falling":
+            k[..., 0] = k[..., 0].flip(2)
+    elif "stream" in kind:  # of the last scale: current tiles 0..7, then those of the run
+        q[..., 0] = 1.0
+        first = 1 if kind.startswith("one") else 0
+        for tile in range(first, 8 + 13, 2):
+            lo, end = (785 + 64 * tile, n) if tile < 8 else (64 * (tile - 8), 785)
+            k[:, :, lo:min(lo + 64, end), 0] = -float("inf") if "inf" in kind else torch.finfo(k.dtype).min
+    elif "keys of" in kind:
+        q[..., 0] = 1.0
+        k[:, :, ::1 if kind.startswith("all") else 3, 0] = -float("inf")
+    elif kind == "an infinite key":
+        k[:, :, 120::40, 5] = float("inf")
+    elif kind == "large keys":
+        k[:, :, 2::7] *= 2.0 ** 7
+    elif "value" in kind:
+        v[:, :, 110::31, 3] = float("inf") if "inf" in kind else float("nan")
+    elif kind == "a NaN query":
+        q[:, :, 3::17, 7] = float("nan")
+    plan = hk.heatkv_load_schedule(hk.Shape(1, H, d, tokens, 1, "bf16"),
+                                   np.tril(np.ones((K, K), np.uint8), -1)[:, None, None].repeat(H, 2))
+    outs = device_generation(plan, 0, q, k, v, tokens, sm)
+    for kk in (2, 3):
+        end = sum(tokens[:kk + 1])
+        qs = q[0, :, end - tokens[kk]:end].double().cpu()
+        ks, vs = k[0, :, :end].double().cpu(), v[0, :, :end].double().cpu()
+        p = torch.softmax(torch.matmul(qs, ks.transpose(1, 2)) * sm, -1)
+        want, got = torch.matmul(p, vs), outs[kk][0].double().cpu()
+        finite = torch.isfinite(want)
+        assert torch.equal(torch.isfinite(got), finite) and torch.equal(torch.isnan(got), torch.isnan(want)), kind
+        size = torch.matmul(p, vs.abs())
+        bound = (2.0 ** -8 + 2e-4) * size + 2.0 ** -9 * want.abs() + 1e-30
+        assert ((got - want).abs() <= bound)[finite].all(), (kind, kk, ((got - want).abs() / bound)[finite].max())
+
+
 # Tensors need not start on a 16-byte boundary: views of a longer one at 4, 8 and 12 bytes, and queries at 2 (another kernel).
 @pytest.mark.parametrize("d,dtype,tokens,batch", [(128, "bf16", [1, 17, 31, 70, 129], 2), (64, "bf16", [1, 17, 31], 2),
                                                   (128, "f32", [1, 33, 147], 32), (64, "f32", [1, 33, 147], 32)])
