@@ -52,7 +52,7 @@ constexpr int TILE_BYTES_D128 = tile::BYTES;  // 64 rows x 256 bytes
 extern __shared__ __attribute__((aligned(1024))) char attend_dynamic_lds[];
 
 // KS = number of key streams.  KS = 1: the workgroup described above.  KS = 2, for launches that give every
-// compute unit at most one workgroup (few heads, small batch): 8 wavefronts, one workgroup per unit; wavefronts
+// compute unit at most one workgroup (few heads, small batch; launch_rules.h): 8 wavefronts, one workgroup per unit; wavefronts
 // 4-7 take the same 128 queries as 0-3 but every other key tile (stream g walks tiles g, g + 2, ...), each
 // stream with its own pair of tile stages (128 KB of dynamic LDS; d = 64: 64 KB), and at the end stream 1 hands its partial
 // output, row sums and references to stream 0 through LDS.  The unit then runs two wavefronts per SIMD, as it
@@ -76,8 +76,8 @@ extern __shared__ __attribute__((aligned(1024))) char attend_dynamic_lds[];
 // every slot of the hand-ordered step below mixes matrix and vector work (with the compiler's own order, score
 // MFMAs clustered apart from the exponentials, the same instance gained 1 % instead of 4-6 %).
 //
-// COPIERS, for launches that give every compute unit at most one workgroup, where two key streams do not pay: four more
-// wavefronts copy the tiles and do nothing else.  A wavefront that issues copies is held about 100 cycles by each, and here it
+// COPIERS, for launches that give every compute unit at most one workgroup, where two key streams do not pay (launch_rules.h):
+// four more wavefronts copy the tiles and do nothing else.  A wavefront that issues copies is held about 100 cycles by each, and here it
 // has its SIMD to itself, with nobody to compute meanwhile.  Same steps, same bits as without.
 template <int KS, bool FP8, int D, int QS = 1, bool COPIERS = false>
 __global__ __launch_bounds__(256 * KS * QS * (COPIERS ? 2 : 1), (KS == 1 && QS == 1) ? 2 : 1) void attend_bf16_kernel(AttendParams p) {
@@ -566,7 +566,7 @@ __global__ __launch_bounds__(256 * KS * QS * (COPIERS ? 2 : 1), (KS == 1 && QS =
     if constexpr (FP8) {
       // Steps that touch tiles of the current scale only (K(it+3) at most): the bf16 cache's step, one copy per slot and no
       // test for codes.  At 20x these are nine in ten steps of a large scale, and with their copies in one burst they held
-      // the instance back: two layers of 16 heads, batch 32, 13 scales 14780 -> 14405 us (bf16 cache: 14140).
+      // the instance back: two layers of 16 heads, batch 32, 13 scales 14378 -> 13998 us (bf16 cache: 13640).
       w = walk_at(2);
       for (; it + 3 < tiles_cur; it += 2) {
         pipe_step(it, Zero{}, One{}, s_nxt, s_cur, Both{}, std::false_type{});
@@ -608,7 +608,8 @@ __global__ __launch_bounds__(256 * KS * QS * (COPIERS ? 2 : 1), (KS == 1 && QS =
   if constexpr (KS == 2) {
     // Stream 1 parks its accumulators (64 registers, one 256-byte row of LDS per register), row-sum partials and
     // references in the idle tile stages (66 KB from byte 48 K on: clear of the 16 KB at 0 and at 32 K where
-    // stream 0 stages its output; d = 64: 32 registers, 34 KB from byte 24 K on); stream 0 brings both halves to the larger reference and adds.
+    // stream 0 stages its output; d = 64: 32 registers, 34 KB from byte 24 K on, clear of 8 KB at 0 and at 16 K);
+    // stream 0 brings both halves to the larger reference and adds.
     __syncthreads();  // every wavefront has finished reading the tile stages
     float* park = reinterpret_cast<float*>(lds[1][1]) + wave * ((16 * NV + 2) * 64);
     if (g == 1 && active) {
